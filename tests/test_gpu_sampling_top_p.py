@@ -137,3 +137,41 @@ def test_full_size_rows_rerun_identical_and_sampled_check():
     tok_s, out_s = run(sub, u[sample], 1.0, 0.9)
     assert np.array_equal(tok_s, tok1[sample])                 # a row's result does not depend on the batch
     check(sub, u[sample], 1.0, 0.9)
+
+
+def _route_rows(kind, V, rng):
+    """Rows that send the threshold search down one of its routes."""
+    x = (rng.standard_normal((3, V)) * 3).astype(np.float32)
+    if kind == "negative":           # every logit negative: the list's cut has to be positive
+        x = -np.abs(x) - 0.5
+    elif kind == "shifted":          # all positive, within a few octaves
+        x = x + 40.0
+    elif kind == "one_wave":         # the likely tokens lie in every eighth group of 2048: one wave's list overflows
+        x = x * 0.3
+        pos = np.arange(V)
+        x[:, (pos // 2048) % 8 == 2] += 9.0
+    elif kind == "unsampled":        # the unlikely half of the mass lies where the estimate does not look
+        x = np.full((3, V), -20.0, dtype=np.float32)
+        pos = np.arange(V)
+        x[:, (pos % 512) % 8 >= 4] = 4.0
+        x[:, 7::1024] = 11.0
+    elif kind == "near_zero":        # a flat row: the threshold value is a tiny number of either sign
+        x = x * 0.05
+    return torch.from_numpy(x).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("kind", ["normal", "negative", "shifted", "one_wave", "unsampled", "near_zero"])
+@pytest.mark.parametrize("V,T,top_p", [(2047, 1.0, 0.9), (2049, 0.7, 0.6), (20481, 1.0, 0.9), (65536, 1.3, 0.8), (152064, 1.0, 0.95)])
+def test_threshold_search_routes(kind, V, T, top_p):
+    """Short list (found, too long, cut not positive, threshold missed by the estimate) and the count of
+    whole rows by windows of values give the same nucleus as the reference."""
+    print("case: top-p routes", kind, V, T, top_p, flush=True)
+    rng = np.random.default_rng(V + len(kind))
+    check(_route_rows(kind, V, rng), np.array([0.0, rng.random(), 0.999999]), T, top_p)
+
+
+@pytest.mark.parametrize("V", [327680, 327681])
+def test_longest_row_with_a_list(V):
+    print("case: top-p list limit", V, flush=True)
+    rng = np.random.default_rng(V)
+    check(_route_rows("normal", V, rng)[:2], np.array([0.3, 0.8]), 0.7, 0.9)
