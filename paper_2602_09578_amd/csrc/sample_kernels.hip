@@ -25,26 +25,9 @@ typedef u32x4 u32x4_any __attribute__((aligned(2)));   // 16-byte access at any 
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float ex2_diff(float a, float b) { return ex2(a - (b == -INFINITY ? 0.f : b)); }
 
-// y values of the 8 logits at x[pos .. pos+8) that exist (pos + e < end); missing ones are -inf.
-// Uses one 16-byte load when all 8 exist (at any alignment: rows of an odd vocabulary start anywhere).
-__device__ __forceinline__ void load8(const uint16_t* x, long pos, long end, float c, float (&y)[8]) {
-  const uint16_t* p = x + pos;
-  if (pos + 8 <= end) {
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p));
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      y[2 * d] = __uint_as_float(v[d] << 16) * c;
-      y[2 * d + 1] = __uint_as_float(v[d] & 0xffff0000u) * c;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      y[e] = pos + e < end ? __uint_as_float((uint32_t)p[e] << 16) * c : -INFINITY;
-  }
-}
-
 // the 8 logits at x[pos .. pos+8) as four packed words (token 2d in the low half of word d);
-// positions past the end read as -inf
+// positions past the end read as -inf.  One 16-byte load when all 8 exist, at any alignment (rows of
+// an odd vocabulary start anywhere).
 __device__ __forceinline__ u32x4 load8_words(const uint16_t* x, long pos, long end) {
   const uint16_t* p = x + pos;
   if (pos + 8 <= end) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p));
@@ -119,23 +102,31 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
     if (chunk >= a.num_chunks) break;
     const bool more = k + 1 < a.chunks_per_wave && chunk + 4 < a.num_chunks;   // wave-uniform
     if (more) fetch(chunk + 4, nxt);
-    float m = -INFINITY;
+    // per lane a running (largest raw logit, sum relative to it), 16 logits at a time as they arrive: with
+    // the wave's maximum first, all of a batch's waves waited for whole chunks and then summed together
+    float xr = -INFINITY, sr = 0.f;
 #pragma unroll
-    for (int it = 0; it < kIters; ++it)
+    for (int it = 0; it < kIters; it += 2) {
+      float xn = xr;
 #pragma unroll
-      for (int d = 0; d < 4; ++d)
-        m = fmaxf(m, fmaxf(__uint_as_float(cur[it][d] << 16), __uint_as_float(cur[it][d] & 0xffff0000u)));
-    m = wave_max(m) * c;                 // c > 0: the scaled maximum is the maximum of the scaled values
-    const float ms = m == -INFINITY ? 0.f : m;
-    float s = 0.f;
+      for (int i = it; i < it + 2; ++i)
 #pragma unroll
-    for (int it = 0; it < kIters; ++it)
+        for (int d = 0; d < 4; ++d)
+          xn = fmaxf(xn, fmaxf(__uint_as_float(cur[i][d] << 16), __uint_as_float(cur[i][d] & 0xffff0000u)));
+      const float ms = xn == -INFINITY ? 0.f : xn * c;   // c > 0: the scaled maximum is the maximum of the scaled values
+      float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        s += ex2(__builtin_fmaf(__uint_as_float(cur[it][d] << 16), c, -ms));
-        s += ex2(__builtin_fmaf(__uint_as_float(cur[it][d] & 0xffff0000u), c, -ms));
-      }
-    s = wave_sum(s);
+      for (int i = it; i < it + 2; ++i)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          s0 += ex2(__builtin_fmaf(__uint_as_float(cur[i][d] << 16), c, -ms));
+          s1 += ex2(__builtin_fmaf(__uint_as_float(cur[i][d] & 0xffff0000u), c, -ms));
+        }
+      sr = sr * ex2(xr * c - ms) + (s0 + s1);
+      xr = xn;
+    }
+    const float m = wave_max(xr) * c;
+    const float s = wave_sum(sr * ex2_diff(xr * c, m));
     if (lane == 0) a.partials[(size_t)row * a.num_chunks + chunk] = make_float2(m, s);
     if (more) {
 #pragma unroll
@@ -144,32 +135,44 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
   }
 }
 
+// One wave per row.  It is a chain of dependent reads (chunk sums, then the chosen chunk), so each of
+// them is one round trip: the sums of the first 64 chunks (all of them up to a vocabulary of 262144)
+// are read once and stay in a register, and the chunk's 4096 logits are requested together
+// (256 rows x 152064: 10.5 us with the sums re-read for every use and the chunk in eight dependent
+// pieces, 4.8 us now).
 __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   const int lane = threadIdx.x;
   const int row = blockIdx.x;
   const float2* part = a.partials + (size_t)row * a.num_chunks;
   const uint16_t* x = a.logits + (size_t)row * a.vocab;
   const float c = a.inv_temp_log2e;
+  const float u = a.uniforms[row];
+  const float2 first = lane < a.num_chunks ? part[lane] : make_float2(-INFINITY, 0.f);
+  auto chunk_sum = [&](int base) {   // (max, sum) of chunk base + lane
+    if (base == 0) return first;
+    return base + lane < a.num_chunks ? part[base + lane] : make_float2(-INFINITY, 0.f);
+  };
   // global max and total, chunk sums rescaled to the global max.  The few dozen chunk sums are
   // accumulated in double precision: they decide in which chunk the uniform number falls, and a
   // float32 running sum over the whole vocabulary would move a CDF step by up to ~1e-5.
   float M = -INFINITY;
-  for (int k = lane; k < a.num_chunks; k += 64) M = fmaxf(M, part[k].x);
+  for (int base = 0; base < a.num_chunks; base += 64) M = fmaxf(M, chunk_sum(base).x);
   M = wave_max(M);
-  auto chunk_mass = [&](int k) -> double {
-    return k < a.num_chunks ? (double)(part[k].y * ex2_diff(part[k].x, M)) : 0.0;
+  auto chunk_mass = [&](int base) -> double {
+    const float2 p = chunk_sum(base);
+    return base + lane < a.num_chunks ? (double)(p.y * ex2_diff(p.x, M)) : 0.0;
   };
   double total = 0.0;
   for (int base = 0; base < a.num_chunks; base += 64)   // fixed order: tiles of 64 chunks
-    total += from_lane(wave_inclusive_scan(chunk_mass(base + lane)), 63);
-  const double target = (double)a.uniforms[row] * total;
+    total += from_lane(wave_inclusive_scan(chunk_mass(base)), 63);
+  const double target = (double)u * total;
   // the chunk in which the running sum passes the target
   double before = 0.0;
   bool take_last = false;
   int chunk = -1, last_nonzero = -1;
   for (int base = 0; base < a.num_chunks && chunk < 0; base += 64) {
     const int k = base + lane;
-    const double v = chunk_mass(k);
+    const double v = chunk_mass(base);
     const double cum = before + wave_inclusive_scan(v);
     const unsigned long long hit = __builtin_amdgcn_ballot_w64(k < a.num_chunks && cum > target);
     const unsigned long long nz = __builtin_amdgcn_ballot_w64(v > 0.0);
@@ -186,53 +189,68 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
     chunk = max(last_nonzero, 0);
     take_last = true;   // any non-zero element of the chunk passes; the last one is taken below
   }
-  // remaining mass to pass inside the chunk (-inf: nothing passes, the last non-zero token is taken)
+  // remaining mass to pass inside the chunk (inf: nothing passes, the last non-zero token is taken)
   const float want = take_last ? INFINITY : (float)(target - before);
-  const long cbase = (long)chunk * kChunk;
-  float run = 0.f;
-  int tok = -1, last_tok = -1;
-  float y_tok = 0.f, y_last = 0.f;
-  for (int it = 0; it < kIters && tok < 0; ++it) {
-    float y[8];
-    const long pos = cbase + it * 512 + lane * 8;
-    load8(x, pos, a.vocab, c, y);
-    float w[8], s = 0.f;
+  const long cbase = (long)chunk * kChunk + lane * 8;
+  u32x4 words[kIters];
+#pragma unroll
+  for (int it = 0; it < kIters; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
+  auto weights = [&](u32x4 v, float (&y)[8], float (&w)[8]) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      y[2 * d] = __uint_as_float(v[d] << 16) * c;
+      y[2 * d + 1] = __uint_as_float(v[d] & 0xffff0000u) * c;
+    }
+    float s = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) { w[e] = ex2_diff(y[e], M); s += w[e]; }
+    return s;
+  };
+  // the piece of 512 tokens in which the running sum passes (`at`), else the last one with any mass
+  float run = 0.f, cum_at = 0.f;
+  int at = -1, last = -1;
+#pragma unroll
+  for (int it = 0; it < kIters; ++it) {
+    float y[8], w[8];
+    const float s = weights(words[it], y, w);
     const float cum = run + wave_inclusive_scan(s);
-    const unsigned long long hit = __builtin_amdgcn_ballot_w64(cum > want);
-    const unsigned long long nz = __builtin_amdgcn_ballot_w64(s > 0.f);
-    if (nz) {   // remember the last token with non-zero probability seen so far
-      const int l = 63 - __builtin_clzll(nz);
-      int e_last = 0;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) if (w[e] > 0.f) e_last = e;
-      last_tok = __shfl((int)(pos + e_last), l);
-      float ysel = y[0];
-#pragma unroll
-      for (int e = 1; e < 8; ++e) if (e == e_last) ysel = y[e];
-      y_last = __shfl(ysel, l);
+    if (at < 0) {   // wave-uniform
+      if (__builtin_amdgcn_ballot_w64(s > 0.f)) last = it;
+      if (__builtin_amdgcn_ballot_w64(cum > want)) { at = it; cum_at = cum; }
     }
-    if (hit) {
-      const int l = __builtin_ctzll(hit);
-      float acc = cum - s;     // mass before this lane's 8 logits
-      int e_hit = 7;
+    run = from_lane(cum, 63);
+  }
+  const int piece = at >= 0 ? at : last;
+  int tok = -1;
+  float y_tok = 0.f;
+  if (piece >= 0) {   // wave-uniform
+    u32x4 v = words[0];
+#pragma unroll
+    for (int it = 1; it < kIters; ++it) v = it == piece ? words[it] : v;
+    float y[8], w[8];
+    const float s = weights(v, y, w);
+    int e_pick = 0, l;
+    if (at >= 0) {
+      l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(cum_at > want));
+      float acc = cum_at - s;     // mass before this lane's 8 logits
+      e_pick = 7;
       bool found = false;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         acc += w[e];
-        if (!found && acc > want) { e_hit = e; found = true; }
+        if (!found && acc > want) { e_pick = e; found = true; }
       }
-      float ysel = y[0];
+    } else {                      // the last token with non-zero probability
+      l = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(s > 0.f));
 #pragma unroll
-      for (int e = 1; e < 8; ++e) if (e == e_hit) ysel = y[e];
-      tok = __shfl((int)(pos + e_hit), l);
-      y_tok = __shfl(ysel, l);
-    } else {
-      run = __shfl(cum, 63);
+      for (int e = 0; e < 8; ++e) if (w[e] > 0.f) e_pick = e;
     }
+    float ysel = y[0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) if (e == e_pick) ysel = y[e];
+    tok = from_lane((int)(cbase + piece * 512) + e_pick, l);
+    y_tok = from_lane(ysel, l);
   }
-  if (tok < 0) { tok = last_tok; y_tok = y_last; }
   if (lane == 0) {
     if (tok < 0) {   // a row of -inf logits (or NaN): no token can be drawn
       a.out_tokens[row] = -1;

@@ -94,3 +94,11 @@ def test_full_size_rows_and_rerun_identical():
         t = int(tok1[r]); lo = cdf[t - 1] if t > 0 else 0.0
         uf = float(np.float32(u[r]))
         assert lo - CDF_TOL <= uf <= cdf[t] + CDF_TOL and abs(out1[r] - np.log(p[t])) <= 1e-3
+
+
+@pytest.mark.parametrize("vocab", [4095, 4097, 262144, 262145, 300001])
+def test_one_and_several_rounds_of_chunk_sums(vocab):
+    """Chunk sums in one register per lane (up to 64 chunks) and re-read beyond; the drawn token in the
+    first and the last piece of its chunk, rows at every alignment."""
+    print("case: sampling chunks", vocab, flush=True)
+    check(I.build_logprob_inputs(4, vocab, 3.0, vocab), np.array([0.0, 0.31, 0.77, np.nextafter(np.float32(1), np.float32(0))]))
