@@ -98,3 +98,25 @@ def test_copy_pages_bit_exact():
     torch.cuda.synchronize()
     assert int(flags.item()) == f == B.FLAG_BAD_PAGE
     assert np.array_equal(I.bf16_bits(dev.k_pages), kb) and np.array_equal(I.bf16_bits(dev.v_pages), vb)
+
+
+@pytest.mark.parametrize("Hkv", [1, 3, 8, 9, 17])
+def test_append_head_counts(Hkv):
+    """One round of eight heads, a partial round and several; a full row and a bad page stay untouched."""
+    print("case: kv append heads", Hkv, flush=True)
+    g = torch.Generator().manual_seed(Hkv)
+    NS, pages = 5, 9
+    k = torch.randn(pages, Hkv, 16, 128, generator=g).to(torch.bfloat16)
+    v = torch.randn(pages, Hkv, 128, 16, generator=g).to(torch.bfloat16)
+    table = torch.tensor([[0, 1], [2, 3], [4, 5], [6, 7], [8, 99]], dtype=torch.int32)
+    lens = torch.tensor([0, 15, 16, 32, 17], dtype=torch.int32)      # the fourth is full, the fifth names no page
+    k_new = torch.randn(NS, Hkv, 128, generator=g).to(torch.bfloat16)
+    v_new = torch.randn(NS, Hkv, 128, generator=g).to(torch.bfloat16)
+    kb, vb, want, f = ref.kv_append(I.bf16_bits(k), I.bf16_bits(v), table.numpy(), lens.numpy().copy(),
+                                    I.bf16_bits(k_new), I.bf16_bits(v_new))
+    shape = B.make_shape(NS, 1, Hkv, Hkv, pages, 1, 2)
+    kd, vd, ld, flags = k.cuda(), v.cuda(), lens.cuda(), torch.zeros(1, dtype=torch.int32, device="cuda")
+    B.marl_kv_append(shape, k_new.cuda(), v_new.cuda(), kd, vd, table.cuda(), ld, flags)
+    torch.cuda.synchronize()
+    assert np.array_equal(I.bf16_bits(kd), kb) and np.array_equal(I.bf16_bits(vd), vb)
+    assert np.array_equal(ld.cpu().numpy(), want) and int(flags.item()) == f
