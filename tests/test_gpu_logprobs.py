@@ -94,3 +94,9 @@ def test_rerun_bit_identical():
     lp = I.build_logprob_inputs(7, 152064, 3.0, 23)
     a, b = gpu_logprobs(lp), gpu_logprobs(lp)
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("rows,vocab", [(255, 20481), (256, 65536), (256, 65537), (511, 20481), (512, 70001)])
+def test_whole_rows_and_slices_on_both_sides_of_the_rule(rows, vocab):
+    print("case: logprobs rule", rows, vocab, flush=True)
+    check(I.build_logprob_inputs(rows, vocab, 3.0, rows + vocab, temperature=0.9))
