@@ -609,6 +609,7 @@ void fill_prefill_args(const marl_prefill_shape* s, marl::PrefillArgs& a) {
   a.Hq = s->num_q_heads;
   a.Hkv = s->num_kv_heads;
   a.R = a.Hq / a.Hkv;
+  a.inv_R = (65536 + a.R - 1) / a.R;
   a.num_pages = s->num_pages;
   a.max_pp = s->max_prefix_pages;
   a.out_dtype = s->out_dtype;

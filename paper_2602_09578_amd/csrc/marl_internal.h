@@ -140,6 +140,7 @@ struct PrefillArgs {
   uint16_t* v_pages_w;
   int32_t* flags;
   int32_t NT, NG, Hq, Hkv, R, num_pages, max_pp, out_dtype, max_blocks;
+  int32_t inv_R;                // ceil(65536 / R)
   float scale;
 };
 int prefill_rows_per_block();

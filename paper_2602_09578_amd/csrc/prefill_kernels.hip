@@ -20,9 +20,23 @@
 // beyond its rows.  A block sees all of its keys, so the output is normalised and written
 // directly (no partials, no merge).
 //
-// Work distribution: a one-workgroup plan kernel turns q_start into the running number of
-// row blocks per group and lists the blocks (group, first row), inside a group last-first
-// (most keys first); workgroups then draw (block, KV head) indices from a counter.
+// Work distribution: a one-workgroup plan kernel lists the row blocks group after group, inside a
+// group last-first (most keys first), so that blocks of a group run at the same time and its keys come
+// out of the caches; a list of at most kPfSorted blocks is put into falling order of cost instead
+// (so few items end evenly only if the long ones start first: 494 blocks x 4 heads of 47 short prompts
+// would take 1.20 times their even share, sorted 1.04).  Item i = (block i / Hkv, KV head i % Hkv); a
+// workgroup starts with the items b and b + G and draws every further one from a counter two items
+// ahead, so that it knows its next item while it works on one: that item's steps follow the
+// current one's in the ring without a gap, and its queries are requested before the current rows are
+// written.  (A fixed assignment instead of the counter left 3 to 13 % of the time to the longest share.)
+//
+// What bounds it: the issue of instructions.  A step of a wave is 48 matrix instructions (768 cycles
+// of the matrix core) and about 100 vector instructions, 24 of them exponentials (710 cycles of the
+// vector ALU), and the two waves of a SIMD overlap little of it: 1.58 us per step and workgroup at
+// two workgroups per CU with 141 vector and 105 scalar instructions, 1.50 with 120 and 50 (page
+// ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  256 prompts of
+// 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.65 ms (0.95 PFLOP/s; a large matrix product of this
+// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.384 ms.
 #include "marl_internal.h"
 #include "wave_ops.h"
 
@@ -45,12 +59,15 @@ constexpr int kPfThreads = 64 * kNW;
 constexpr int kPfStepBytes = 2 * kBlockTok * kD * 2;   // K + V of one 32-token step
 constexpr int kPlanThreadsPf = 1024;
 
-// LDS step buffers, filled by direct global-to-LDS loads (two workgroups of 64 KB per CU)
+// LDS step buffers, filled by direct global-to-LDS loads (two workgroups of at most 80 KB per CU)
 constexpr int kPfStages = 4;
 struct PrefillLds {
   __attribute__((aligned(16))) char buf[kPfStages][kPfStepBytes];
+  __attribute__((aligned(16))) char out[kNW][16 * kD];   // half a tile's output rows (64 channels) on their way to memory, per wave
+  int next[2];   // drawn item indices, by the parity of the item during which they were published
 };
 // s_waitcnt immediate that waits only for the vector-memory counter to drop to n (gfx9 encoding)
+constexpr int pf_lgkmcnt0 = 0xf | (3 << 14) | (7 << 4);   // waits only for LDS and scalar operations
 constexpr int pf_vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (7 << 4) | (0xf << 8); }
 
 // counters at the head of the workspace (same slots as the decode plan uses, so that
@@ -76,14 +93,24 @@ __device__ __forceinline__ int block_rows(long nrows) {
   return nb ? (int)(((nrows + nb - 1) / nb + 15) / 16 * 16) : 0;
 }
 
+// A list record: the group and the block's first row (a multiple of 16) with the number of 16-row
+// tiles of the group's blocks in the low four bits.
+static_assert(kQB / 16 < 16, "a block's tiles are packed into four bits");
+__device__ __forceinline__ int2 pack_item(int g, int row_begin, int qb) { return make_int2(g, row_begin | (qb >> 4)); }
+
+constexpr int kPfSorted = 512;    // a list of at most so many blocks is sorted
+constexpr int kPfClasses = 64;    // cost classes of that order
+
 __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArgs a) {
-  __shared__ long long part[kPlanThreadsPf];   // 64-bit: inconsistent inputs must not wrap the sums
-  __shared__ long long carry;
+  constexpr int kWavesPf = kPlanThreadsPf / 64;
+  __shared__ long long wave_sum[kWavesPf];   // 64-bit: inconsistent inputs must not wrap the sums
+  __shared__ int hist[kPfClasses];
   __shared__ int flags_all, end_all;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int flag = 0;
-  if (tid == 0) { carry = 0; flags_all = end_all = 0; }
+  if (tid == 0) flags_all = end_all = 0;
   __syncthreads();
+  long long carry = 0;
   for (int g0 = 0; g0 < a.NG; g0 += kPlanThreadsPf) {
     const int g = g0 + tid;
     int nb = 0;
@@ -95,16 +122,21 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
     // groups that overlap in q could ask for more blocks than the workspace was sized for
     // (its bound assumes they share no rows): such a group is dropped
     if (nb > a.max_blocks) { nb = 0; flag |= MARL_FLAG_BAD_GROUP; }
-    part[tid] = nb;
+    long long inc = nb;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const long long t = __shfl_up(inc, d);
+      if (lane >= d) inc += t;
+    }
+    if (lane == 63) wave_sum[wave] = inc;
     __syncthreads();
-    for (int d = 1; d < kPlanThreadsPf; d <<= 1) {   // inclusive scan
-      const long long v = tid >= d ? part[tid - d] : 0;
-      __syncthreads();
-      part[tid] += v;
-      __syncthreads();
+    long long before = carry, all = 0;
+    for (int w = 0; w < kWavesPf; ++w) {
+      if (w < wave) before += wave_sum[w];
+      all += wave_sum[w];
     }
     if (g < a.NG) {
-      const long long first64 = carry + part[tid] - nb;
+      const long long first64 = before + inc - nb;
       int first = a.max_blocks;
       if (first64 + nb > a.max_blocks) {   // as above; every later group then fails this test too
         flag |= MARL_FLAG_BAD_GROUP;
@@ -114,93 +146,186 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
         atomicMax(&end_all, first + nb);
       }
       a.block_start[g] = first;
-      // the group's work items, last row block (most keys) first
+      // the group's blocks, last (most keys) first
       const int qb = block_rows(nrows);
-      for (int k = 0; k < nb; ++k) a.items[first + k] = make_int2(g, (nb - 1 - k) * qb);
+      for (int k = 0; k < nb; ++k) a.items[first + k] = pack_item(g, (nb - 1 - k) * qb, qb);
     }
-    __syncthreads();
-    if (tid == kPlanThreadsPf - 1) carry += part[tid];
+    carry += all;
     __syncthreads();
   }
   if (flag) atomicOr(&flags_all, flag);
+  __threadfence();
   __syncthreads();
+  // The accepted groups' blocks are exactly [0, end_all).
+  const int total = end_all;
+  if (wave == 0 && total <= kPfSorted) {
+    // counting sort over kPfClasses classes between the fewest and the most keys, in registers
+    constexpr int kPer = kPfSorted / 64;
+    int2 rec[kPer];
+    int keys[kPer];
+    int lo = 0x7fffffff, hi = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      rec[u] = make_int2(0, 0);
+      keys[u] = -1;
+      if (u * 64 + lane < total) {   // (written by other threads of this kernel: read past the vector cache)
+        const int* p = reinterpret_cast<const int*>(a.items + u * 64 + lane);
+        rec[u].x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        rec[u].y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        keys[u] = a.q_pos0[rec[u].x] + ((rec[u].y & ~15) + (rec[u].y & 15) * 16) / a.R;
+        lo = min(lo, keys[u]);
+        hi = max(hi, keys[u]);
+      }
+    }
+    lo = wave_allreduce(lo, [](int x, int y) { return min(x, y); });
+    hi = wave_allreduce(hi, [](int x, int y) { return max(x, y); });
+    const int width = max(1, (hi - lo) / kPfClasses + 1);
+    hist[lane] = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (keys[u] >= 0) atomicAdd(&hist[(hi - keys[u]) / width], 1);
+    const int c = hist[lane];
+    int inc = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int t = __shfl_up(inc, d);
+      if (lane >= d) inc += t;
+    }
+    hist[lane] = inc - c;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (keys[u] >= 0) a.items[atomicAdd(&hist[(hi - keys[u]) / width], 1)] = rec[u];
+  }
   if (tid == 0) {
-    a.block_start[a.NG] = end_all;   // the accepted groups' blocks are exactly [0, end_all)
+    a.block_start[a.NG] = total;
     a.counters[kPfCursor] = 0;
     a.counters[kPfFlags] = flags_all;   // the attention kernel may add MARL_FLAG_BAD_PAGE
   }
 }
+static_assert(kPfClasses == 64, "one class per lane in the scan");
 
-__device__ __forceinline__ void prefill_item(const PrefillArgs& a, const int g, const int row_begin,
-                                             const int kvh, PrefillLds& lds, int& bad_page) {
+typedef const char __attribute__((address_space(1))) * GlobalBytes;
+// Scalar load of element `at` of a wave-uniform array (scalar base + 32-bit offset).
+__device__ __forceinline__ int ld_uniform_at(const int32_t* p, uint32_t at) {
+  const char __attribute__((address_space(4))) * base =
+      reinterpret_cast<const char __attribute__((address_space(4)))*>(reinterpret_cast<uintptr_t>(p));
+  return *reinterpret_cast<const int32_t __attribute__((address_space(4)))*>(base + at * 4u);
+}
+
+// What one item is, wave-uniform (scalar registers).
+struct PfItem {
+  const int32_t* table_row;   // page ids of the group
+  int kv_off;                 // byte offset of the KV head inside a page
+  int kvh, rows;
+  int tok0, rem0;             // the block's first row = tok0 * R + rem0
+  int qrow0, pos0;            // row of q and position of token tok0
+  int tok_end;                // keys the block needs: 0 .. position of its last row
+  int nsteps, slots;          // key steps; slots of the ring it takes (at least kPfStages)
+};
+
+// x / R for 0 <= x < 65536 / 16 with inv_R = ceil(65536 / R): exact, since x (inv_R R - 65536) < 65536
+__device__ __forceinline__ int div_R(int x, int inv_R) { return (x * inv_R) >> 16; }
+
+__device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
+  PfItem it;
+  const int block = qi / a.Hkv;
+  it.kvh = qi - block * a.Hkv;
+  const int32_t* rec = reinterpret_cast<const int32_t*>(a.items + block);
+  const int g = ld_uniform(rec), packed = ld_uniform(rec + 1);
+  const int b = ld_uniform(a.q_start + g), e = ld_uniform(a.q_start + g + 1);
+  const int pos0 = ld_uniform(a.q_pos0 + g);
+  const int row_begin = packed & ~15;
+  // (a listed group passed the plan's checks; its tokens are clamped to the table row as there)
+  const int nrows = (int)min((long)(e - b), (long)a.max_pp * kPage - pos0) * a.R;
+  it.rows = min((packed & 15) * 16, nrows - row_begin);
+  it.tok0 = row_begin / a.R;
+  it.rem0 = row_begin - it.tok0 * a.R;
+  it.qrow0 = b + it.tok0;
+  it.pos0 = pos0 + it.tok0;
+  it.tok_end = it.pos0 + div_R(it.rem0 + it.rows - 1, a.inv_R) + 1;
+  it.nsteps = (it.tok_end + kBlockTok - 1) / kBlockTok;
+  it.slots = max(it.nsteps, kPfStages);
+  it.kv_off = it.kvh * (kPage * kD * 2);
+  it.table_row = a.prefix_table + (size_t)g * a.max_pp;
+  return it;
+}
+
+// The items of one workgroup, one after the other.
+__device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_work, PrefillLds& lds, int& bad_page) {
   constexpr int kLoads = 1024 / (kNW * 64);     // 16-byte loads per thread and step (16 KB per step)
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, j = lane >> 4;
-  int unused = 0;
-  const int ntok = group_tokens(a, g, unused);
-  const int nrows = ntok * a.R;
-  const int qrow0 = a.q_start[g];
-  const int pos0 = a.q_pos0[g];
-  const int32_t* table_row = a.prefix_table + (size_t)g * a.max_pp;
   const float sc = fmaxf(fabsf(a.scale) * 1.44269504088896340736f, 1e-30f);
   const uint32_t sign_flip = a.scale < 0.f ? 0x80008000u : 0u;
-  const int rows_here = min(block_rows(nrows), nrows - row_begin);
-  // keys this block needs: 0 .. position of its last row
-  const int tok_end = pos0 + (row_begin + rows_here - 1) / a.R + 1;
-
   // this wave's tiles: wave, wave + kNW, ...; tile_lo / tile_hi: fewest / most keys any of its rows sees
-  int row_index[kMT], limit[kMT], tile_lo[kMT], tile_hi[kMT];
+  // (per-lane row data is computed where it is used, from a lane number the compiler cannot see
+  // through: kept, it would take registers through the loops that they do not have)
+  int tile_lo[kMT], tile_hi[kMT];
+  auto opaque_lane = [&] { int l = lane; asm volatile("" : "+v"(l)); return l; };
+  // this lane's row of a tile: its index in q and out (-1: none) and the number of keys it sees
+  auto row_of = [&](const PfItem& it, int qt, int row16, int& sees) {
+    const int r = (qt * kNW + wave) * 16 + row16;
+    const int rho = it.rem0 + r, tok = div_R(rho, a.inv_R);   // from the block's first token on
+    sees = r < it.rows ? it.pos0 + tok + 1 : 1;
+    return r < it.rows ? (it.qrow0 + tok) * a.Hq + it.kvh * a.R + (rho - tok * a.R) : -1;
+  };
   u32x4 qreg[kMT][4];
+  auto load_rows = [&](const PfItem& it) {
+    const int l = opaque_lane();
 #pragma unroll
-  for (int qt = 0; qt < kMT; ++qt) {
-    const int r0 = (qt * kNW + wave) * 16;            // first row of the tile within the block
-    const int rho = row_begin + r0 + i;
-    tile_lo[qt] = tile_hi[qt] = 0;                    // tile without rows: never computed
-    if (r0 < rows_here) {
-      tile_lo[qt] = pos0 + (row_begin + r0) / a.R + 1;
-      tile_hi[qt] = pos0 + (row_begin + min(r0 + 15, rows_here - 1)) / a.R + 1;
-    }
-    int idx = -1;
-    limit[qt] = 1;
-    if (r0 + i < rows_here) {
-      idx = (qrow0 + rho / a.R) * a.Hq + kvh * a.R + rho % a.R;
-      limit[qt] = pos0 + rho / a.R + 1;
-    }
-    row_index[qt] = idx;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (idx >= 0) {
-        v = *reinterpret_cast<const u32x4*>(a.q + (size_t)idx * kD + (4 * kk + j) * 8);
-        v ^= sign_flip;
+    for (int qt = 0; qt < kMT; ++qt) {
+      const int r0 = (qt * kNW + wave) * 16;            // first row of the tile within the block
+      tile_lo[qt] = tile_hi[qt] = 0;                    // tile without rows: never computed
+      if (r0 < it.rows) {
+        tile_lo[qt] = it.pos0 + div_R(it.rem0 + r0, a.inv_R) + 1;
+        tile_hi[qt] = it.pos0 + div_R(it.rem0 + min(r0 + 15, it.rows - 1), a.inv_R) + 1;
       }
-      qreg[qt][kk] = v;
+      int sees;
+      const int idx = row_of(it, qt, l & 15, sees);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (idx >= 0) v = *reinterpret_cast<const u32x4*>(a.q + (size_t)idx * kD + (4 * kk + (l >> 4)) * 8);
+        qreg[qt][kk] = v;
+      }
     }
-  }
+  };
   f32x4 acc[kMT][8];
   float m_run[kMT], l_run[kMT];
-#pragma unroll
-  for (int qt = 0; qt < kMT; ++qt) {
-    m_run[qt] = -INFINITY;
-    l_run[qt] = 0.f;
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  const uint32_t page_bytes = (uint32_t)a.Hkv * (kPage * kD * 2);
 
-  const int nsteps = (tok_end + kBlockTok - 1) / kBlockTok;
-  const size_t page_bytes = (size_t)a.Hkv * (kPage * kD * 2);
-
-  // Page ids of step n (wave-uniform scalar loads).  A step past the end repeats the last one:
-  // its loads fetch valid bytes that nobody uses, so the loop needs no conditional loads and
-  // every wait knows how many younger loads are in flight.
-  auto load_ids = [&](int n, int& p0, int& p1) {
-    const int t = min(n, nsteps - 1) * kBlockTok;
-    p0 = ld_uniform(table_row + (t >> 4));
-    p1 = (t + kPage < tok_end) ? ld_uniform(table_row + (t >> 4) + 1) : p0;
-    if ((unsigned)p0 >= (unsigned)a.num_pages) { p0 = 0; bad_page = 1; }
-    if ((unsigned)p1 >= (unsigned)a.num_pages) { p1 = 0; bad_page = 1; }
+  // The stream of steps whose loads are requested, kPfStages - 1 slots ahead of the step that is
+  // computed: page ids two at a time by scalar loads, one slot before they are used.  All of it is
+  // wave-uniform, and as short as it can be: a scalar instruction costs a wave about as much as a
+  // vector instruction (100 of them per step took 170 ns of 870 in a loop of this mix).  A slot past an
+  // item's last step repeats that step: its loads fetch valid bytes that nobody uses, so the loop
+  // needs no conditional loads and every wait knows how many younger loads are in flight.
+  const int32_t* st_table;          // the item's table row
+  int st_page, st_first_of_last, st_last, st_left, st_off;   // next page, the last step's first page, last page, slots left, KV head offset
+  int r0, r1, r_off;                // ids (in flight) and KV head offset of the slot that is requested next
+  uint32_t id_max = 0;              // largest id seen: compared with the pool size once, at the end
+  auto start_stream = [&](const PfItem& it) {
+    st_table = it.table_row;
+    st_page = 0;
+    st_last = (it.tok_end - 1) >> 4;
+    st_first_of_last = 2 * (it.nsteps - 1);
+    st_left = it.slots;
+    st_off = it.kv_off;
+  };
+  auto load_ids = [&] {
+    const uint32_t at = (uint32_t)min(st_page, st_first_of_last);
+    r0 = ld_uniform_at(st_table, at);
+    r1 = ld_uniform_at(st_table, min(at + 1, (uint32_t)st_last));
+    r_off = st_off;
+    st_page += 2;
+    --st_left;
+  };
+  // (behind the wait for the step's keys: a wait for LDS data waits for scalar loads in flight as well)
+  auto load_ids_after = [&](uint32_t key_word) {
+    asm volatile("" : "+s"(st_page) : "v"(key_word));
+    load_ids();
   };
   // A step is 1024 16-byte vectors: K of page 0, K of page 1, V of page 0, V of page 1 (256
   // each, contiguous in memory); thread tid fetches vectors tid + k * threads, so which of the
@@ -220,7 +345,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, const int g, 
   int region[kLoads];
 #pragma unroll
   for (int k = 0; k < kLoads; ++k) {
-    region[k] = k * (kNW / 4) + (wave >> 2);
+    region[k] = kNW == 4 ? k : k * (kNW / 4) + (wave >> 2);
     const int s_pos = w0 + lane;
     const int slot = s_pos >> 4;
     // swizzle key of K row tau = 16 * (region & 1) + slot: bits 0, 1, 3, 4 of tau (the 16 rows one
@@ -228,25 +353,31 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, const int g, 
     const int key = ((region[k] & 1) << 3) | ((slot >> 3) << 2) | (slot & 3);
     const int src = (region[k] >> 1) ? (s_pos ^ ((s_pos >> 3) & 1))
                                      : ((slot << 4) | ((s_pos & 15) ^ key));
-    src_off[k] = (uint32_t)kvh * (kPage * kD * 2) + (uint32_t)src * 16;
+    src_off[k] = (uint32_t)src * 16;
   }
-  auto issue = [&](int p0, int p1, char* buf) {
+  auto issue = [&](char* buf) {
+    // (an id outside the pool reads page 0)
+    id_max = max(id_max, max((uint32_t)r0, (uint32_t)r1));
+    const uint32_t p0 = (uint32_t)r0 < (uint32_t)a.num_pages ? r0 : 0, p1 = (uint32_t)r1 < (uint32_t)a.num_pages ? r1 : 0;
+    const uint64_t off0 = (uint64_t)p0 * page_bytes + (uint32_t)r_off, off1 = (uint64_t)p1 * page_bytes + (uint32_t)r_off;
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
-      const char* base = reinterpret_cast<const char*>((region[k] >> 1) ? a.v_pages : a.k_pages) +
-                         (size_t)((region[k] & 1) ? p1 : p0) * page_bytes;
+      // (scalar base + 32-bit lane offset)
+      const GlobalBytes base = reinterpret_cast<GlobalBytes>(reinterpret_cast<uintptr_t>((region[k] >> 1) ? a.v_pages : a.k_pages)) +
+                               ((region[k] & 1) ? off1 : off0);
       char* dst = buf + region[k] * 4096 + w0 * 16;   // wave-uniform; lane l lands at dst + 16 l
       __builtin_amdgcn_global_load_lds(
-          reinterpret_cast<const __attribute__((address_space(1))) void*>(reinterpret_cast<uintptr_t>(base + src_off[k])),
+          reinterpret_cast<const __attribute__((address_space(1))) void*>(base + src_off[k]),
           reinterpret_cast<__attribute__((address_space(3))) void*>((uint32_t)reinterpret_cast<uintptr_t>(dst)),
           16, 0, 0);
     }
   };
   const int k_rd = (8 * (i >> 2) + (i & 3)) * 256;
-  const int v_rd = 2 * kBlockTok * kD + (j >> 1) * 4096;
+  // value unit 2 * (16 * ct + i) + (j & 1) with its lowest bit XOR-ed: one address for all ct
+  const int v_rd = 2 * kBlockTok * kD + (j >> 1) * 4096 + (((2 * i + (j & 1)) ^ ((i >> 2) & 1)) << 4);
 
-  constexpr float kPfRescaleSlack = 8.0f;   // log2 units
-  auto compute_edge = [&](int n, const char* buf) {
+  constexpr float kPfRescaleSlack = 8.0f, kPfMaxWeight = 256.0f;   // log2 units; the same as a weight
+  auto compute_edge = [&](int n, const char* buf, const int tok_end, const int (&limit)[kMT]) {
     const int t0 = n * kBlockTok;
     const bool ragged = t0 + kBlockTok > tok_end;   // workgroup-uniform; only the last step
     u32x4 pb[kMT];   // set and used only for the tiles this step touches
@@ -256,6 +387,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, const int g, 
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
         kr[T][kk] = *reinterpret_cast<const u32x4*>(buf + k_rd + T * 4 * 256 + (((4 * kk + j) ^ i) << 4));
+    load_ids_after(kr[1][3][0]);
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
       if (t0 < tile_hi[qt]) {   // wave-uniform: some row of the tile sees a token of this step
@@ -299,8 +431,7 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, const int g, 
     u32x4 vr[8];
 #pragma unroll
     for (int ct = 0; ct < 8; ++ct) {
-      const int u = 2 * (16 * ct + i) + (j & 1);
-      vr[ct] = *reinterpret_cast<const u32x4*>(buf + v_rd + ((u ^ ((i >> 2) & 1)) << 4));
+      vr[ct] = *reinterpret_cast<const u32x4*>(buf + v_rd + ct * (16 * kPage * 2));
     }
     if (ragged) {
       // value slots past the block's last key may hold anything (NaN included): zero them
@@ -326,15 +457,15 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, const int g, 
   // products, the row maxima, ONE test whether any row's reference maximum has to move (rare after
   // the first steps; the accumulators are rescaled in that branch only), then per tile the exponentials
   // and that tile's output products.  About 150 vector-ALU instructions per step instead of 250.
-  auto compute_full = [&](int, const char* buf) {
+  auto compute_full = [&](const char* buf) {
     u32x4 kr[2][4];
 #pragma unroll
     for (int T = 0; T < 2; ++T)
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
         kr[T][kk] = *reinterpret_cast<const u32x4*>(buf + k_rd + T * 4 * 256 + (((4 * kk + j) ^ i) << 4));
+    load_ids_after(kr[1][3][0]);
     f32x4 s0[kMT], s1[kMT];
-    float m_new[kMT];
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
       s0[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -345,127 +476,181 @@ __device__ __forceinline__ void prefill_item(const PrefillArgs& a, const int g, 
         s1[qt] = mfma_16x16x32(kr[1][kk], qreg[qt][kk], s1[qt]);
       }
     }
-    // The reference maximum of a row moves only when the row's maximum exceeds it by more than
-    // 2^kPfRescaleSlack (weights then stay below that).  With an exact running maximum one of a
-    // wave's 48 rows sets a new record in most steps of a long prompt; with the slack the test below
-    // fails in nearly every step after the first few, and then neither the maxima of the rows (a
-    // reduction over four lanes each) nor new references nor rescaled accumulators are needed.
-    bool moved = false;
-    float mx[kMT];
-#pragma unroll
-    for (int qt = 0; qt < kMT; ++qt) {
-      mx[qt] = fmaxf(fmaxf(fmaxf(s0[qt][0], s0[qt][1]), fmaxf(s0[qt][2], s0[qt][3])),
-                     fmaxf(fmaxf(s1[qt][0], s1[qt][1]), fmaxf(s1[qt][2], s1[qt][3]))) * sc;   // this lane's 8 tokens
-      m_new[qt] = m_run[qt];
-      moved |= mx[qt] > m_run[qt] + kPfRescaleSlack;
-    }
-    if (__builtin_amdgcn_ballot_w64(moved) != 0) {   // wave-uniform
-#pragma unroll
-      for (int qt = 0; qt < kMT; ++qt) {
-        const float row_mx = rows_allreduce_max(mx[qt]);
-        if (row_mx > m_run[qt] + kPfRescaleSlack) m_new[qt] = row_mx;
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new[qt]);   // 1 where the row did not move
-        l_run[qt] *= alpha;
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
-      }
-    }
+    // The reference maximum of a row moves only when its weights grow past 2^kPfRescaleSlack.  With an
+    // exact running maximum one of a wave's 48 rows sets a new record in most steps of a long prompt; with
+    // the slack nearly no step after the first moves one, and then neither the rows' maxima nor new
+    // references nor rescaled accumulators are needed.  What is tested is the sum of a lane's eight
+    // weights, which is formed anyway (no weight exceeds a sum that passes; the eight scores'
+    // maximum cost six instructions per tile), and only a step that fails looks for maxima and takes
+    // its exponentials again.
     u32x4 vr[8];
 #pragma unroll
     for (int ct = 0; ct < 8; ++ct) {
-      const int u = 2 * (16 * ct + i) + (j & 1);
-      vr[ct] = *reinterpret_cast<const u32x4*>(buf + v_rd + ((u ^ ((i >> 2) & 1)) << 4));
+      vr[ct] = *reinterpret_cast<const u32x4*>(buf + v_rd + ct * (16 * kPage * 2));
     }
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
-      m_run[qt] = m_new[qt];
-      float p[8];
+      float p[8], psum;
+      auto weights = [&] {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[qt][e], sc, -m_new[qt]));
-        p[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[qt][e], sc, -m_new[qt]));
+        for (int e = 0; e < 4; ++e) {
+          p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[qt][e], sc, -m_run[qt]));
+          p[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[qt][e], sc, -m_run[qt]));
+        }
+        psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      };
+      weights();
+      if (__builtin_amdgcn_ballot_w64(psum > kPfMaxWeight) != 0) {   // wave-uniform; always so in the first step
+        const float mx = fmaxf(fmaxf(fmaxf(s0[qt][0], s0[qt][1]), fmaxf(s0[qt][2], s0[qt][3])),
+                               fmaxf(fmaxf(s1[qt][0], s1[qt][1]), fmaxf(s1[qt][2], s1[qt][3]))) * sc;   // this lane's 8 tokens
+        const float m_new = fmaxf(m_run[qt], rows_allreduce_max(mx));
+        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);   // 1 where the row did not move
+        l_run[qt] *= alpha;
+        m_run[qt] = m_new;
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
+        weights();
       }
-      l_run[qt] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      l_run[qt] += psum;
       const u32x4 pb = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
 #pragma unroll
       for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = mfma_16x16x32(vr[ct], pb, acc[qt][ct]);
     }
   };
 
-  // ring of kPfStages LDS buffers: per iteration wait until this wave's part of step n has landed
-  // (all but the youngest kPfStages-2 steps' loads), a bare workgroup barrier (everybody's part
-  // has landed and everybody has finished reading buffer (n-1) % kPfStages; a fence would wait
-  // for every outstanding load), then the loads of step n+kPfStages-1 go into that buffer
-  int p0, p1;
+  // Ring of kPfStages LDS buffers, one slot per step, that runs on from item to item: per slot wait
+  // until this wave's part of it has landed (all but the youngest kPfStages-2 slots' loads; stores and
+  // query loads in between only make the wait stricter), a bare workgroup barrier (everybody's part has
+  // landed and everybody has finished reading the slot before; a fence would wait for every
+  // outstanding load), then the loads of the slot kPfStages-1 ahead, which may be the next item's.
+  // An item takes at least kPfStages slots, so what is ahead is never further than the next item.
+  PfItem cur = read_item(a, blockIdx.x);
+  const int second = blockIdx.x + gridDim.x;
+  bool more = second < n_work;                                // workgroup-uniform: there is a next item
+  PfItem nxt = more ? read_item(a, second) : cur;             // (without one its slots are never used)
+  auto draw = [&] { return tid == 0 ? 2 * (int)gridDim.x + atomicAdd(&a.counters[kPfCursor], 1) : 0; };
+  int drawn = draw();                                         // (thread 0 only) the item after the next one
+  uint32_t ring = 0;                   // byte offset of the current slot's buffer
+  constexpr uint32_t kRingBytes = kPfStages * kPfStepBytes;
+  static_assert((kRingBytes & (kRingBytes - 1)) == 0, "the ring wraps by a mask");
+  start_stream(cur);
 #pragma unroll
   for (int s0 = 0; s0 < kPfStages - 1; ++s0) {
-    load_ids(s0, p0, p1);
-    issue(p0, p1, lds.buf[s0]);
+    load_ids();
+    issue(lds.buf[s0]);
   }
-  load_ids(kPfStages - 1, p0, p1);
-  auto ring_step = [&](int n, auto&& comp) {
-    __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm((kPfStages - 2) * kLoads));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    issue(p0, p1, lds.buf[(n + kPfStages - 1) % kPfStages]);
-    load_ids(n + kPfStages, p0, p1);
-    comp(n, lds.buf[n % kPfStages]);
-  };
-  // Two loops (their register allocations do not mix): a wave that owns kMT tiles of this block
-  // runs the steps before the causal edge of its first tile (tile_lo grows with the tile) in the
-  // mask-free code, all other steps in the general code.  Every wave passes the same number of
-  // barriers.
-  bool all_tiles = true;
+  load_ids();
+  load_rows(cur);
+  for (int round = 0;; ++round) {
+    // the queries are waited for here, once: with the loads still pending at the top of the loops the
+    // compiler would wait in every step, and for the steps in flight with them
 #pragma unroll
-  for (int qt = 0; qt < kMT; ++qt) all_tiles = all_tiles && (qt * kNW + wave) * 16 < rows_here;
-  const int n_full = all_tiles ? min(tile_lo[0] / kBlockTok, nsteps) : 0;
-  int n = 0;
-  for (; n < n_full; ++n) ring_step(n, compute_full);
-  for (; n < nsteps; ++n) ring_step(n, compute_edge);
-  __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm(0));
-  __syncthreads();
-  // lane (i, j) holds channels 16*ct + 4*j .. +3 of q-row i
+    for (int qt = 0; qt < kMT; ++qt)
 #pragma unroll
-  for (int qt = 0; qt < kMT; ++qt) {
-    const float l = rows_allreduce_sum(l_run[qt]);
-    if (row_index[qt] >= 0) {
-      const float inv = 1.0f / l;   // l >= 1: the row's own maximum contributes exp2(0)
+      for (int kk = 0; kk < 4; ++kk) {
+        qreg[qt][kk] ^= sign_flip;
+        asm volatile("" : "+v"(qreg[qt][kk]));
+      }
+    // (the draw was requested before the queries, so it has arrived; published by the next barrier)
+    if (tid == 0) lds.next[round & 1] = drawn;
+    __builtin_amdgcn_s_waitcnt(pf_lgkmcnt0);
+#pragma unroll
+    for (int qt = 0; qt < kMT; ++qt) {
+      m_run[qt] = -INFINITY;
+      l_run[qt] = 0.f;
+#pragma unroll
+      for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto ring_step = [&](auto&& comp) {
+      __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm((kPfStages - 2) * kLoads));
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      issue(lds.buf[0] + ((ring + kRingBytes - kPfStepBytes) & (kRingBytes - 1)));
+      if (st_left == 0) start_stream(nxt);                    // (wave-uniform)
+      comp(lds.buf[0] + ring);
+      ring = (ring + kPfStepBytes) & (kRingBytes - 1);
+    };
+    // Two loops (their register allocations do not mix): a wave that owns kMT tiles of this block
+    // runs the steps before the causal edge of its first tile (tile_lo grows with the tile) in the
+    // mask-free code, all other steps in the general code.  Every wave passes the same number of
+    // barriers.
+    bool all_tiles = true;
+#pragma unroll
+    for (int qt = 0; qt < kMT; ++qt) all_tiles = all_tiles && (qt * kNW + wave) * 16 < cur.rows;
+    const int n_full = all_tiles ? min(tile_lo[0] / kBlockTok, cur.nsteps) : 0;
+    int n = 0;
+    for (; n < n_full; ++n) ring_step(compute_full);
+    if (n < cur.nsteps) {
+      int limit[kMT];
+      const int l = opaque_lane();
+#pragma unroll
+      for (int qt = 0; qt < kMT; ++qt) row_of(cur, qt, l & 15, limit[qt]);
+      for (; n < cur.nsteps; ++n) ring_step([&](const char* buf) { compute_edge(n, buf, cur.tok_end, limit); });
+    }
+    for (; n < cur.slots; ++n) ring_step([&](const char*) { load_ids(); });
+    // the next item's queries are requested before this item's rows are written
+    const int after_next = __builtin_amdgcn_readfirstlane(lds.next[round & 1]);
+    if (more) {
+      drawn = draw();
+      load_rows(nxt);
+    }
+    // Lane (i, j) holds channels 16*ct + 4*j .. +3 of q-row i.  Written as they are held, an instruction
+    // stores 16 pieces of 32 bytes (8 per lane); through 2 KB of LDS half a bf16 tile leaves as 128-byte
+    // lines, 16 bytes per lane.  16-byte units of a row are XOR-ed with the row against bank conflicts;
+    // the lanes of a row then read its units in that order.  (256 prompts: 2 % of the whole.)
+    const int l2 = opaque_lane();
+#pragma unroll
+    for (int qt = 0; qt < kMT; ++qt) {
+      const float inv = 1.0f / rows_allreduce_sum(l_run[qt]);   // a row's sum >= 1: its own maximum contributes exp2(0)
+      const int i = l2 & 15, j = l2 >> 4, lane = l2;
+      int sees;
+      const int out_row = row_of(cur, qt, i, sees);
       if (a.out_dtype == MARL_OUT_F32) {
-        float* dst = reinterpret_cast<float*>(a.out) + (size_t)row_index[qt] * kD + 4 * j;
+        if (out_row >= 0) {
+          float* dst = reinterpret_cast<float*>(a.out) + (size_t)out_row * kD + 4 * j;
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) *reinterpret_cast<f32x4*>(dst + 16 * ct) = acc[qt][ct] * inv;
+          for (int ct = 0; ct < 8; ++ct) *reinterpret_cast<f32x4*>(dst + 16 * ct) = acc[qt][ct] * inv;
+        }
       } else {
-        uint16_t* dst = reinterpret_cast<uint16_t*>(a.out) + (size_t)row_index[qt] * kD + 4 * j;
+        char* mine = lds.out[wave];
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
-          const f32x4 r = acc[qt][ct] * inv;
-          *reinterpret_cast<uint2*>(dst + 16 * ct) = make_uint2(pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]));
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const f32x4 r = acc[qt][4 * h + c] * inv;
+            *reinterpret_cast<uint2*>(mine + i * 128 + (((2 * c + (j >> 1)) ^ (i & 7)) << 4) + (j & 1) * 8) =
+                make_uint2(pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]));
+          }
+          // (one wave's LDS operations are executed in order: no barrier)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int row = 8 * k + (lane >> 3);
+            const u32x4 v = *reinterpret_cast<const u32x4*>(mine + row * 128 + ((lane & 7) << 4));
+            const int at = __shfl(out_row, row);          // (lane `row` of the first 16 holds that row's index)
+            if (at >= 0)
+              *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(a.out) + (size_t)at * kD + 64 * h + (((lane & 7) ^ (row & 7)) << 3)) = v;
+          }
         }
       }
     }
+    if (!more) break;
+    cur = nxt;
+    more = after_next < n_work;
+    if (more) nxt = read_item(a, after_next);
   }
+  if (id_max >= (uint32_t)a.num_pages) bad_page = 1;
+  __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm(0));   // (the last slots' loads write to LDS: not past the kernel's end)
 }
 
+static_assert(sizeof(PrefillLds) <= 80 * 1024, "two workgroups share a CU's 160 KB");
 __global__ __launch_bounds__(kPfThreads)
 __attribute__((amdgpu_waves_per_eu(MARL_PREFILL_WAVES_PER_EU, MARL_PREFILL_WAVES_PER_EU)))
 void prefill_kernel(PrefillArgs a) {
   __shared__ PrefillLds lds;
-  __shared__ int next_item;
   const int n_work = a.block_start[a.NG] * a.Hkv;
   int bad_page = 0;
-  // The first item is the block index; later ones come from the counter, drawn when the
-  // workgroup is free (drawing the next index while an item runs measured 2-5 % slower).
-  int qi = blockIdx.x;
-  while (qi < n_work) {
-    const int2 it = a.items[qi / a.Hkv];
-    prefill_item(a, it.x, it.y, qi % a.Hkv, lds, bad_page);
-    // prefill_item ends with a workgroup barrier after its last LDS use
-    if (threadIdx.x == 0) next_item = gridDim.x + atomicAdd(&a.counters[kPfCursor], 1);
-    __syncthreads();
-    qi = next_item;
-    __syncthreads();
-  }
+  if ((int)blockIdx.x < n_work) prefill_items(a, n_work, lds, bad_page);
   if (bad_page) atomicOr(&a.counters[kPfFlags], MARL_FLAG_BAD_PAGE);
 }
 

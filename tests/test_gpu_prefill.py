@@ -259,3 +259,23 @@ def test_full_size_prompts_of_the_bench_workload_sampled_rows():
         assert excess.max() <= 0, (g, tau, excess.max())
         worst = max(worst, float(np.abs(got - want).max()))
     print("prefill full size: worst |delta| over sampled rows", worst, flush=True)
+
+
+@pytest.mark.parametrize("groups", [511, 512, 513, 700])
+def test_lists_sorted_and_in_group_order(groups):
+    """Row-block lists on both sides of the length up to which they are sorted; with two KV heads the
+    longer ones give every workgroup items drawn from the counter.  One token per group behind
+    contexts of different lengths: items of one step and of several, in any order."""
+    print("case: prefill list", groups, flush=True)
+    rng = np.random.default_rng(groups)
+    pos0 = rng.choice([0, 1, 31, 32, 95, 127, 128, 129, 200], groups)
+    check(I.build_prefill_inputs(6, 2, [1] * groups, pos0.tolist(), seed=groups), B.MARL_OUT_BF16)
+
+
+@pytest.mark.parametrize("R", [1, 3, 5, 7, 11, 13, 16])
+def test_rows_per_token(R):
+    """Every block boundary inside a token for group sizes that do not divide 16; both output types."""
+    print("case: prefill rows per token", R, flush=True)
+    inp = I.build_prefill_inputs(2 * R, 2, [193, 64, 97], [0, 33, 500], seed=R)
+    check(inp)
+    check(inp, B.MARL_OUT_BF16)
