@@ -56,7 +56,7 @@ int make_layout(const marl_attn_shape* s, marl_attn_plan_layout* L) {
   memset(L, 0, sizeof *L);
   const long NS = s->num_seqs, NG = s->num_groups, Hkv = s->num_kv_heads, Hq = s->num_q_heads;
   const long mst = (long)s->max_suffix_pages * marl::kPage, mpt = (long)s->max_prefix_pages * marl::kPage;
-  // Groups with more than 128 query rows (judged by the average group) use the 8-wave prefix
+  // Groups with more than 128 query rows (judged by the average group) use the wide prefix
   // kernel with blocks of 256 rows, so that their prefix KV is streamed once, not twice.
   const long rows = NG > 0 ? ceil_div(NS, NG) * (Hq / Hkv) : 0;   // query rows of an average group
   const long qb = rows > marl::kRowsPerQBlock ? marl::kRowsPerQBlockWide : marl::kRowsPerQBlock;

@@ -439,9 +439,9 @@ __device__ __forceinline__ void short_suffix_items(const AttnArgs& a, int& bad_p
 
 // ---------------------------------------------------------------------------------------
 // Prefix kernel: one work item = (group, chunk of prefix tokens, block of up to 128 (or 256)
-// query rows, KV head).  Query row rho of a group is (its rho / R -th sequence, head kvh*R + rho % R).
+// query rows, KV head); blocks of 256 rows are described at prefix_item_half below.  Query row rho of a group is (its rho / R -th sequence, head kvh*R + rho % R).
 //
-// Here the NW (4 or 8) waves split the QUERY rows (16-row tile t belongs to wave t % NW) and
+// Here the NW (4) waves split the QUERY rows (16-row tile t belongs to wave t % NW) and
 // every wave sees all tokens, so the group's K/V must reach all of them: each 32-token step (two
 // pages, 16 KB of K and V) is fetched once by the workgroup with fully coalesced 16-byte
 // loads (a wave reads 1 KB contiguous per instruction), staged in registers, written to a
@@ -456,9 +456,9 @@ __device__ __forceinline__ void short_suffix_items(const AttnArgs& a, int& bad_p
 // XOR-ed with (u>>3)&1 for the same reason.
 // ---------------------------------------------------------------------------------------
 constexpr int kStepBytes = 2 * kBlockTok * kD * 2;   // K + V of one 32-token step
-// the pipelined prefix item rescales its accumulators only when a row's score maximum exceeds the
-// running reference by more than this (log2 units): weights then stay below 2^kRescaleSlack
-constexpr float kRescaleSlack = 8.0f;
+// the prefix items of the wide shape rescale their accumulators only when a lane's eight weights sum to
+// more than this
+constexpr float kMaxWeight = 256.0f;
 // s_waitcnt immediate (gfx9 encoding): vector-memory counter <= vm, LDS/scalar counter <= lgkm
 constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 0xf) | ((vm >> 4) << 14) | (7 << 4) | ((lgkm & 0xf) << 8); }
 struct PrefixLds {
@@ -520,7 +520,7 @@ __device__ __forceinline__ void prefix_item(const AttnArgs& a, const int4 it, co
 
   // Page ids and page addresses are wave-uniform (scalar registers, a handful of scalar instructions
   // per step) and every lane adds one 32-bit offset that never changes: with two waves per SIMD the
-  // instruction count of a step is a cost of its own (measured on the 8-wave shape, whose loop it
+  // instruction count of a step is a cost of its own (measured on a shape with 8 waves per workgroup, whose loop it
   // bounds).
   //
   // Page ids of step n: two scalar loads, unconditional (a step past the end repeats the last page,
@@ -717,363 +717,265 @@ __device__ __forceinline__ void prefix_item(const AttnArgs& a, const int4 it, co
   }
 }
 
-// Prefix item, software-pipelined.  Data path as before (global memory -> staging registers, three
-// steps ahead -> LDS ring of three step buffers -> operand registers); what changes is the order
-// inside an iteration, chosen so that no LDS read is waited for where it is issued and so that the
-// K and V operand registers share one set of 32 registers:
-//   iteration n:  loads of step n+3 -> staging registers
-//                 output products of step n-1, first half  (its V and weights are in registers)
-//                 read K(n), first half   (into the V registers the first half has released)
-//                 output products of step n-1, second half
-//                 read K(n), second half
-//                 score products of step n (first the half whose K has arrived)
-//                 read V(n)               (into the K registers)
-//                 softmax of step n       (covers the V read; leaves the bf16 weights)
-//                 step n+1: staging registers -> LDS; workgroup barrier
-// The hot loop has no per-tile branch (the number of active tiles is a template parameter), the
-// ragged last step is peeled, and accumulators are rescaled only when a row's score maximum exceeds
-// the running reference by more than 2^tau (weights stay below 2^tau), right before the output
-// products that need it, so that branch is taken a handful of times per chunk.  Row sums come out
-// of the matrix core (a product with an all-ones tile), from the same bf16-rounded weights that
-// multiply V.
-template <int MTW, int NW>
-__device__ __forceinline__ void prefix_item_pipelined(const AttnArgs& a, const int4 it, const int kvh,
-                                               PrefixLds& lds, int& bad_page) {
-  constexpr int kQBlock = 32 * NW;
-  constexpr int kLoads = 1024 / (NW * 64);
+// Prefix item of the wide shape (blocks of up to 256 query rows), one half of its row tiles: the two
+// halves of an item are taken by two workgroups of the same XCD, usually of the same CU, so that the
+// second reads the group's keys and values out of the L2 and each SIMD has two waves that no barrier
+// keeps in step (one waits or runs its softmax while the other feeds the matrix core).
+//   Data path: global memory straight into an LDS ring of four steps (global_load_lds_dwordx4, the
+// swizzle of the LDS tile applied on the source side, no staging registers) -> operand registers.
+//   Iteration n: wait for slot n+1, workgroup barrier; loads of slot n+3; read V(n); score products of
+// step n (K(n) is in registers); read K(n+1) into the K registers; softmax of step n, which covers both
+// reads; output products.  No LDS read is waited for where it is issued.
+//   A row's reference maximum moves only when a lane's eight weights sum to more than kMaxWeight
+// (no weight exceeds a sum that passes): a branch taken in the first step and hardly ever after.
+// What bounds it: issue of matrix and vector instructions (180 flop per byte).  64 groups of 32 samples x
+// 7 rows on 4096 shared tokens: 177 -> 150 us (0.80 PFLOP/s); the 177 us were one workgroup of 8 waves per
+// CU with all of a group's rows, staged through registers and kept in step by one barrier per step.
+constexpr int kWideStages = 4;
+struct WideLds {
+  __attribute__((aligned(16))) char buf[kWideStages][kStepBytes];
+};
+typedef const char __attribute__((address_space(1))) * GlobalBytes;
+
+__device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 it, const int kvh, const int half,
+                                                 WideLds& lds, int& bad_page) {
+  constexpr int NW = 4, MTW = 2, kLoads = 4;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, j = lane >> 4;
-  const int g = it.x, tok_begin = it.y, tok_end = it.z, row_begin = it.w;
+  const int g = it.x, tok_begin = it.y, tok_end = it.z;
+  // this half's tiles: a block of at most eight tiles is not divided (its keys are then read once)
+  const int nrows = ld_uniform(a.group_count + g) * a.R;
+  const int tiles_all = (min(kRowsPerQBlockWide, nrows - it.w) + 15) >> 4;
+  const int tiles0 = tiles_all <= MTW * NW ? tiles_all : (tiles_all + 1) >> 1;
+  const int tiles = half ? tiles_all - tiles0 : tiles0;
+  if (tiles <= 0) return;                                    // workgroup-uniform
+  const int row_begin = it.w + (half ? tiles0 * 16 : 0);
+  const int nt = tiles > wave + NW ? 2 : tiles > wave ? 1 : 0;   // wave-uniform: tiles wave, wave + 4
+
   const int32_t* table_row = a.prefix_table + (size_t)g * a.max_pp;
   const int nsteps = (tok_end - tok_begin + kBlockTok - 1) / kBlockTok;
-  const size_t page_bytes = (size_t)a.Hkv * (kPage * kD * 2);
-
-  // Page ids, as in the plain item; here a wave's loads of a step all belong to one page (the
-  // waves of the lower half of the workgroup fetch the step's first page, the others its second),
-  // so a wave needs one id per step.
+  const uint32_t page_bytes = (uint32_t)a.Hkv * (kPage * kD * 2);
   const int first_page = tok_begin >> 4;
-  const int last_page = max(first_page, (tok_end - 1) >> 4);
-  const int my_half = NW == 8 ? (wave >> 2) : 0;
+  const int last_page = (tok_end - 1) >> 4;
+  // Page ids (scalar): fetched an iteration before they are used, checked once per item.  A slot past
+  // the end repeats the last page: valid bytes that nobody uses, so that every wait knows how many
+  // loads are in flight.
   uint32_t id_max = 0;
-  auto fetch_ids = [&](int n, int& r0, int& r1) {
-    if constexpr (NW == 8) {
-      r0 = ld_uniform(table_row + min(first_page + 2 * n + my_half, last_page));
-      r1 = r0;
-    } else {
-      r0 = ld_uniform(table_row + min(first_page + 2 * n, last_page));
-      r1 = ld_uniform(table_row + min(first_page + 2 * n + 1, last_page));
-    }
-  };
-  auto take_ids = [&](int n, int r0, int r1, int& p0, int& p1) {
-    id_max = max(id_max, max((uint32_t)r0, (uint32_t)r1));
-    const uint32_t limit = n < nsteps ? (uint32_t)a.num_pages : 0u;
-    p0 = (uint32_t)r0 < limit ? r0 : 0;
-    p1 = (uint32_t)r1 < limit ? r1 : 0;
-    asm volatile("" : "+s"(p0), "+s"(p1));   // (keeps the loads and the check where they are written)
+  int r0, r1;
+  auto fetch_ids = [&](int n) {
+    r0 = ld_uniform(table_row + min(first_page + 2 * n, last_page));
+    r1 = ld_uniform(table_row + min(first_page + 2 * n + 1, last_page));
   };
   // A step is 1024 16-byte vectors: K of page 0, K of page 1, V of page 0, V of page 1 (256 each,
-  // contiguous in memory).  Thread tid fetches vectors tid + k * threads, k < kLoads.  Of a page's
-  // 256 vectors, vector w is slot w/16, chunk w%16 of K, or 16-byte unit w of V.
-  // LDS tile: K as 32 token rows of 256 B, the 16-byte chunk index XOR-ed with a 4-bit key made of
-  // bits 0, 1, 3, 4 of the row (the 16 rows one operand read touches differ exactly in those bits,
-  // so its 16 lanes hit 16 different bank groups); V as [page][channel][2 halves of 8 slots], the
-  // unit index u XOR-ed with (u >> 3) & 1.
-  // Which of the four regions a load belongs to is the same for a whole wave (wave-uniform), so a
-  // page's base address is scalar arithmetic and every lane adds the same 32-bit offset for all loads.
-  static_assert(NW % 4 == 0, "a wave's 64 vectors must lie in one 256-vector region");
-  const int w = tid & 255;
-  const uint32_t lane_off = (uint32_t)kvh * (kPage * kD * 2) + (uint32_t)w * 16;
-  const int sl = w >> 4;
-  const int lds_k = sl * 256 + (((w & 15) ^ (((sl >> 3) << 2) | (sl & 3))) << 4);   // page 0; page 1: + 4096, chunk ^ 8
-  const int lds_v = 2 * kBlockTok * kD + ((w ^ ((w >> 3) & 1)) << 4);              // page 0; page 1: + 4096
-  auto region_of = [&](int k) { return NW == 4 ? k : k * (NW / 4) + (wave >> 2); };   // wave-uniform
-  // (unconditional loads: a step past the end reads page 0, bytes nobody uses, from cache, so that
-  // every wait knows how many loads are in flight)
-  auto issue = [&](int p0, int p1, u32x4 (&st)[kLoads]) {
+  // contiguous in memory); wave w fills slots 64 w .. + 63 of each region, in lane order.  K as 32 token
+  // rows of 256 B, the 16-byte chunk index XOR-ed with bits 0, 1, 3, 4 of the row; V as [page][channel][2
+  // halves of 8 slots], the unit index u XOR-ed with (u >> 3) & 1: both are undone on the source side.
+  uint32_t src_off[kLoads];
 #pragma unroll
-    for (int k = 0; k < kLoads; ++k) {
-      const int region = region_of(k);
-      const int pid = NW == 8 ? p0 : ((region & 1) ? p1 : p0);   // (with 8 waves p0 is this wave's page)
-      const char* base = reinterpret_cast<const char*>((region >> 1) ? a.v_pages : a.k_pages) +
-                         (size_t)(uint32_t)pid * page_bytes;   // scalar
-      st[k] = ld_stream(base + lane_off);
-    }
-  };
-  auto stage_to_lds = [&](const u32x4 (&st)[kLoads], char* buf) {
-#pragma unroll
-    for (int k = 0; k < kLoads; ++k) {
-      const int region = region_of(k);
-      const int off = (region >> 1) ? lds_v + (region & 1) * 4096 : (lds_k + (region & 1) * 4096) ^ ((region & 1) << 7);
-      *reinterpret_cast<u32x4*>(buf + off) = st[k];
-    }
-  };
-  // the first three steps are requested before anything else of the item: the chain of dependent
-  // loads that leads to the query rows then runs while they are in flight
-  u32x4 st[3][kLoads];   // steps in flight: three register stages
-  int p0, p1, r0, r1;
-#pragma unroll
-  for (int s0 = 0; s0 < 3; ++s0) {
-    fetch_ids(s0, r0, r1);
-    take_ids(s0, r0, r1, p0, p1);
-    issue(p0, p1, st[s0]);
+  for (int k = 0; k < kLoads; ++k) {
+    const int s_pos = wave * 64 + lane;
+    const int slot = s_pos >> 4;
+    const int key = ((k & 1) << 3) | ((slot >> 3) << 2) | (slot & 3);
+    src_off[k] = 16u * (uint32_t)((k >> 1) ? (s_pos ^ ((s_pos >> 3) & 1)) : ((slot << 4) | ((s_pos & 15) ^ key)));
   }
-  fetch_ids(3, r0, r1);
-  take_ids(3, r0, r1, p0, p1);
+  const uint32_t kv_off = (uint32_t)kvh * (kPage * kD * 2);
+  auto issue = [&](uint32_t ring) {
+    id_max = max(id_max, max((uint32_t)r0, (uint32_t)r1));
+    const uint32_t p0 = (uint32_t)r0 < (uint32_t)a.num_pages ? r0 : 0, p1 = (uint32_t)r1 < (uint32_t)a.num_pages ? r1 : 0;
+    const uint64_t off0 = (uint64_t)p0 * page_bytes + kv_off, off1 = (uint64_t)p1 * page_bytes + kv_off;
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k) {
+      const GlobalBytes base = reinterpret_cast<GlobalBytes>(reinterpret_cast<uintptr_t>((k >> 1) ? a.v_pages : a.k_pages)) +
+                               ((k & 1) ? off1 : off0);
+      char* dst = lds.buf[0] + (ring + k * 4096 + wave * 1024);   // wave-uniform; lane l lands at dst + 16 l
+      __builtin_amdgcn_global_load_lds(
+          reinterpret_cast<const __attribute__((address_space(1))) void*>(base + src_off[k]),
+          reinterpret_cast<__attribute__((address_space(3))) void*>((uint32_t)reinterpret_cast<uintptr_t>(dst)), 16, 0, 0);
+    }
+  };
+  constexpr uint32_t kRingBytes = kWideStages * kStepBytes;
+  static_assert((kRingBytes & (kRingBytes - 1)) == 0, "the ring wraps by a mask");
+  // the first three steps are requested before the chain of dependent loads that leads to the query rows
+#pragma unroll
+  for (int s0 = 0; s0 < kWideStages - 1; ++s0) {
+    fetch_ids(s0);
+    issue(s0 * kStepBytes);
+  }
+  fetch_ids(kWideStages - 1);
 
   const int gstart = a.group_start[g];
-  const int nrows = a.group_count[g] * a.R;
   const float sc = fmaxf(fabsf(a.scale) * 1.44269504088896340736f, 1e-30f);
   const uint32_t sign_flip = a.scale < 0.f ? 0x80008000u : 0u;
   const int nslot = a.NCp + a.NCs;
   const int slot = tok_begin / a.Cp;
-  const int tiles_total = (min(kQBlock, nrows - row_begin) + 15) >> 4;
-  const int nt = max(0, min(MTW, (tiles_total - wave + NW - 1) / NW));   // wave-uniform
   int row_index[MTW];
   u32x4 qreg[MTW][4];
 #pragma unroll
   for (int qt = 0; qt < MTW; ++qt) {
     const int rho = row_begin + (qt * NW + wave) * 16 + i;
     int idx = -1;
-    if (rho < nrows && (qt * NW + wave) * 16 < kQBlock)
-      idx = a.group_seqs[gstart + rho / a.R] * a.Hq + kvh * a.R + rho % a.R;
+    if (qt < nt && rho < nrows) idx = a.group_seqs[gstart + rho / a.R] * a.Hq + kvh * a.R + rho % a.R;
     row_index[qt] = idx;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (idx >= 0) {
-        v = *reinterpret_cast<const u32x4*>(a.q + (size_t)idx * kD + (4 * kk + j) * 8);
-        v ^= sign_flip;
-      }
+      if (idx >= 0) v = *reinterpret_cast<const u32x4*>(a.q + (size_t)idx * kD + (4 * kk + j) * 8);
+      v ^= sign_flip;
       qreg[qt][kk] = v;
     }
   }
+  // (waited for here, once: with loads pending at the top of the loop the compiler would wait in every
+  // step, and for the steps in flight with them)
+#pragma unroll
+  for (int qt = 0; qt < MTW; ++qt)
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(qreg[qt][kk]));
   f32x4 acc[MTW][8];
-  f32x4 lacc[MTW];          // row sums accumulated by the matrix core (all four elements equal)
-  float m_run[MTW];
+  float m_run[MTW], l_run[MTW];
 #pragma unroll
   for (int qt = 0; qt < MTW; ++qt) {
-    m_run[qt] = -INFINITY;
-    lacc[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (finite: with -inf a masked score of the first step, -inf + inf, would hide from the test of the sum)
+    m_run[qt] = -3.402823466e38f;
+    l_run[qt] = 0.f;
 #pragma unroll
     for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
   const int k_rd = (8 * (i >> 2) + (i & 3)) * 256;
-  const int v_rd = 2 * kBlockTok * kD + (j >> 1) * 4096;
-  auto read_k_half = [&](const char* buf, int T, u32x4 (&kr)[4]) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      kr[kk] = *reinterpret_cast<const u32x4*>(buf + k_rd + T * 4 * 256 + (((4 * kk + j) ^ i) << 4));
-  };
-  auto read_v_half = [&](const char* buf, int h, u32x4 (&vr)[4]) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int u = 2 * (16 * (4 * h + c) + i) + (j & 1);
-      vr[c] = *reinterpret_cast<const u32x4*>(buf + v_rd + ((u ^ ((i >> 2) & 1)) << 4));
-    }
-  };
-  const u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-
+  const int v_rd = 2 * kBlockTok * kD + (j >> 1) * 4096 + (((2 * i + (j & 1)) ^ ((i >> 2) & 1)) << 4);
   auto run = [&](auto nt_tag) {
     constexpr int NTraw = decltype(nt_tag)::value;
     constexpr int NT = NTraw > 0 ? NTraw : 1;   // (no zero-length arrays; a wave without tiles only moves data)
-    // xa / xb: the two halves of the operand registers: V(n-1) channel tiles 0-3 / 4-7 at the top of
-    // iteration n, then K(n) token half 0 / 1, then V(n)
-    u32x4 xa[4], xb[4], pb[NT];
-    float alpha_pending[NT];
-    bool rescale_pending = false;   // wave-uniform
-
-    auto rescale_if_pending = [&]() {
-      if (rescale_pending) {
+    u32x4 kr[2][4], vr[8];
+    auto read_k = [&](uint32_t ring) {
 #pragma unroll
-        for (int qt = 0; qt < NT; ++qt) {
+      for (int T = 0; T < 2; ++T)
 #pragma unroll
-          for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha_pending[qt];
-          lacc[qt] *= alpha_pending[qt];
-        }
-      }
+        for (int kk = 0; kk < 4; ++kk)
+          kr[T][kk] = *reinterpret_cast<const u32x4*>(lds.buf[0] + ring + k_rd + T * 4 * 256 + (((4 * kk + j) ^ i) << 4));
     };
-    auto output_half = [&](int h, const u32x4 (&vr)[4]) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int qt = 0; qt < NT; ++qt) acc[qt][4 * h + c] = mfma_16x16x32(vr[c], pb[qt], acc[qt][4 * h + c]);
-      if (h == 0) {
-#pragma unroll
-        for (int qt = 0; qt < NT; ++qt) lacc[qt] = mfma_16x16x32(ones, pb[qt], lacc[qt]);
-      }
-    };
-    auto scores_half = [&](int T, const u32x4 (&kr)[4], f32x4 (&s)[NT][2]) {
-#pragma unroll
-      for (int qt = 0; qt < NT; ++qt) s[qt][T] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int qt = 0; qt < NT; ++qt) s[qt][T] = mfma_16x16x32(kr[kk], qreg[qt][kk], s[qt][T]);
-    };
-    // softmax of step n from its scores: leaves the bf16 weights in pb (and masks, in the ragged last
-    // step, the scores and the value slots no token owns)
-    auto softmax = [&](auto last_tag, int n, f32x4 (&s)[NT][2]) {
+    // slot 0 has landed when at most the two younger slots' loads are in flight
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * kLoads, 15));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if constexpr (NTraw > 0) read_k(0);
+    uint32_t ring = 0;
+    auto iteration = [&](auto last_tag, int n) {
       constexpr bool kLast = decltype(last_tag)::value;
-      if constexpr (kLast) {
-        const int t0 = tok_begin + n * kBlockTok;
-        if (t0 + kBlockTok > tok_end) {   // wave-uniform: the ragged end of the chunk
+      __builtin_amdgcn_s_waitcnt(waitcnt_imm(kLoads, 15));   // slot n+1 has landed
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();                          // ... for every wave; all have read V(n-1)
+      asm volatile("" ::: "memory");
+      issue((ring + 3 * kStepBytes) & (kRingBytes - 1));
+      if constexpr (NTraw == 0) fetch_ids(n + 4);
+      if constexpr (NTraw > 0) {
 #pragma unroll
-          for (int qt = 0; qt < NT; ++qt)
+        for (int ct = 0; ct < 8; ++ct) vr[ct] = *reinterpret_cast<const u32x4*>(lds.buf[0] + ring + v_rd + ct * (16 * kPage * 2));
+        f32x4 s[NT][2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              if (t0 + 8 * j + e >= tok_end) s[qt][0][e] = -INFINITY;
-              if (t0 + 8 * j + 4 + e >= tok_end) s[qt][1][e] = -INFINITY;
-            }
-          // value slots no token owns may hold anything (NaN included): zero them
+        for (int qt = 0; qt < NT; ++qt) s[qt][0] = s[qt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            const int tok = t0 + 8 * j + 2 * d;
-            const uint32_t mask = (tok < tok_end ? 0x0000ffffu : 0u) | (tok + 1 < tok_end ? 0xffff0000u : 0u);
+        for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              xa[c][d] &= mask;
-              xb[c][d] &= mask;
+          for (int qt = 0; qt < NT; ++qt) {
+            s[qt][0] = mfma_16x16x32(kr[0][kk], qreg[qt][kk], s[qt][0]);
+            s[qt][1] = mfma_16x16x32(kr[1][kk], qreg[qt][kk], s[qt][1]);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!kLast) read_k((ring + kStepBytes) & (kRingBytes - 1));
+        fetch_ids(n + 4);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kLast) {
+          const int t0 = tok_begin + n * kBlockTok;
+          if (t0 + kBlockTok > tok_end) {   // wave-uniform: the ragged end of the chunk
+#pragma unroll
+            for (int qt = 0; qt < NT; ++qt)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                if (t0 + 8 * j + e >= tok_end) s[qt][0][e] = -INFINITY;
+                if (t0 + 8 * j + 4 + e >= tok_end) s[qt][1][e] = -INFINITY;
+              }
+            // value slots no token owns may hold anything (NaN included): zero them
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+              const int tok = t0 + 8 * j + 2 * d;
+              const uint32_t mask = (tok < tok_end ? 0x0000ffffu : 0u) | (tok + 1 < tok_end ? 0xffff0000u : 0u);
+#pragma unroll
+              for (int ct = 0; ct < 8; ++ct) vr[ct][d] &= mask;
             }
           }
         }
-      }
-      float mx[NT];
-      bool moved = false;
-#pragma unroll
-      for (int qt = 0; qt < NT; ++qt) {
-        const f32x4 s0 = s[qt][0], s1 = s[qt][1];
-        mx[qt] = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
-                       fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3]))) * sc;   // this lane's 8 tokens
-        moved |= mx[qt] > m_run[qt] + kRescaleSlack;
-      }
-      // (the rows' maxima, a reduction over the four lanes of a row, are needed only when some lane
-      // has seen a score that far above its row's reference)
-      rescale_pending = __builtin_amdgcn_ballot_w64(moved) != 0;   // wave-uniform; rare after a chunk's first step
-      if (rescale_pending) {
 #pragma unroll
         for (int qt = 0; qt < NT; ++qt) {
-          mx[qt] = rows_allreduce_max(mx[qt]);
-          const float m_new = mx[qt] > m_run[qt] + kRescaleSlack ? mx[qt] : m_run[qt];
-          alpha_pending[qt] = __builtin_amdgcn_exp2f(m_run[qt] - m_new);   // 1 where the row did not move
-          m_run[qt] = m_new;
-        }
-      }
+          float p[8], psum;
+          auto weights = [&] {
 #pragma unroll
-      for (int qt = 0; qt < NT; ++qt) {
-        float p[8];
+            for (int e = 0; e < 4; ++e) {
+              p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][0][e], sc, -m_run[qt]));
+              p[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][1][e], sc, -m_run[qt]));
+            }
+            psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+          };
+          weights();
+          if (__builtin_amdgcn_ballot_w64(psum > kMaxWeight) != 0) {   // wave-uniform
+            const f32x4 s0 = s[qt][0], s1 = s[qt][1];
+            const float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
+                                   fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3]))) * sc;   // this lane's 8 tokens
+            const float m_new = fmaxf(m_run[qt], rows_allreduce_max(mx));
+            const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);   // 1 where the row did not move
+            l_run[qt] *= alpha;
+            m_run[qt] = m_new;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][0][e], sc, -m_run[qt]));
-          p[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][1][e], sc, -m_run[qt]));
+            for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
+            weights();
+          }
+          l_run[qt] += psum;
+          const u32x4 pb = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
+#pragma unroll
+          for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = mfma_16x16x32(vr[ct], pb, acc[qt][ct]);
         }
-        pb[qt] = u32x4{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
       }
+      ring = (ring + kStepBytes) & (kRingBytes - 1);
     };
-    // iteration n (n % 3 == PH): buf[PH] holds step n; the staging set PH takes the loads of step
-    // n+3; set PH+1 (step n+1) goes to buf[PH+1]
-    auto iteration = [&](auto first_tag, auto last_tag, auto phase_tag, int n) {
-      constexpr bool kFirst = decltype(first_tag)::value;
-      constexpr int PH = decltype(phase_tag)::value;
-      const char* bufr = lds.buf[PH];
-      char* bufw = lds.buf[(PH + 1) % 3];
-      issue(p0, p1, st[PH]);
-      fetch_ids(n + 4, r0, r1);
-      if constexpr (NTraw == 0) take_ids(n + 4, r0, r1, p0, p1);
-      if constexpr (NTraw > 0) {
-        f32x4 s[NT][2];
-        if constexpr (!kFirst) {
-          rescale_if_pending();
-          output_half(0, xa);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        read_k_half(bufr, 0, xa);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!kFirst) {
-          output_half(1, xb);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        read_k_half(bufr, 1, xb);
-        __builtin_amdgcn_sched_barrier(0);
-        scores_half(0, xa, s);
-        __builtin_amdgcn_sched_barrier(0);
-        scores_half(1, xb, s);
-        take_ids(n + 4, r0, r1, p0, p1);   // (all of K has been waited for, and the scalar loads with it)
-        __builtin_amdgcn_sched_barrier(0);
-        read_v_half(bufr, 0, xa);
-        read_v_half(bufr, 1, xb);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (decltype(last_tag)::value)
-          __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, 0));   // the ragged step masks the values it has just read
-        softmax(last_tag, n, s);
-      }
-      // step n+1 goes from its staging registers to LDS once it has landed (the loads of the two
-      // younger steps stay in flight), then the barrier
-      __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * kLoads, 15));
-      stage_to_lds(st[(PH + 1) % 3], bufw);
-      __syncthreads();
-    };
-    const std::true_type yes{};
-    const std::false_type no{};
-    using P0 = std::integral_constant<int, 0>;
-
-    // step 0 into LDS
-    __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * kLoads, 15));
-    stage_to_lds(st[0], lds.buf[0]);
-    __syncthreads();
-    if (nsteps == 1) {
-      iteration(yes, yes, P0{}, 0);
-    } else {
-      iteration(yes, no, P0{}, 0);
-      int n = 1;
-      // the steps that are neither first nor last, phases 1, 2, ..., 3-1, 0 in turn
-      auto middle = [&](auto ph) {
-        if (n + 1 >= nsteps) return false;
-        iteration(no, no, ph, n);
-        ++n;
-        return true;
-      };
-      auto cycle = [&](auto... ph) { return (middle(ph) && ...); };
-      while (n + 1 < nsteps) {
-        cycle(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{}, P0{});
-      }
-      const int last = nsteps - 1;
-      const int lp = last % 3;
-      if (lp == 0) iteration(no, yes, P0{}, last);
-      else if (lp == 1) iteration(no, yes, std::integral_constant<int, 1>{}, last);
-      else iteration(no, yes, std::integral_constant<int, 2>{}, last);
-    }
-    if constexpr (NTraw > 0) {   // the last step's output products
-      rescale_if_pending();
-      output_half(0, xa);
-      output_half(1, xb);
-    }
-    // every wave has passed a barrier since its last LDS read: the next item may refill the ring
+    int n = 0;
+    for (; n + 1 < nsteps; ++n) iteration(std::false_type{}, n);
+    iteration(std::true_type{}, n);
   };
-  if (nt == MTW) run(std::integral_constant<int, MTW>{});
-  else if (MTW == 2 && nt == 1) run(std::integral_constant<int, 1>{});
+  if (nt == 2) run(std::integral_constant<int, 2>{});
+  else if (nt == 1) run(std::integral_constant<int, 1>{});
   else run(std::integral_constant<int, 0>{});
   if (id_max >= (uint32_t)a.num_pages) bad_page = 1;
 
 #pragma unroll
   for (int qt = 0; qt < MTW; ++qt) {
+    const float l = rows_allreduce_sum(l_run[qt]);
     if (row_index[qt] >= 0) {
       const size_t ps = (size_t)row_index[qt] * nslot + slot;
       float* dst = a.partial_o + ps * kD + 4 * j;
 #pragma unroll
       for (int ct = 0; ct < 8; ++ct) *reinterpret_cast<f32x4*>(dst + 16 * ct) = acc[qt][ct];
-      if (j == 0) a.partial_ml[ps] = make_float2(m_run[qt], lacc[qt][0]);
+      if (j == 0) a.partial_ml[ps] = make_float2(m_run[qt], l);
     }
   }
+  // the slots requested past the end write to LDS: the next item, or the end of the kernel, comes after
+  __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));
+  __syncthreads();
 }
 
-template <int NW>
+// Two shapes: blocks of 128 query rows, or, for groups with more than 128 rows, blocks of 256 rows whose
+// halves are taken separately; both with workgroups of 4 waves, two per CU.
+template <bool kWide>
 __device__ __forceinline__ void prefix_kernel_body(const AttnArgs& a) {
-  __shared__ PrefixLds lds;
+  __shared__ typename std::conditional<kWide, WideLds, PrefixLds>::type lds;
   __shared__ int next_item;
   const int n_work = a.counters[MARL_CTR_NUM_PREFIX_ITEMS] * a.Hkv;
+  // wide: entries of the queue come in groups of 16, the first halves of eight (item, KV head) pairs and
+  // their second halves: workgroups are dealt to the eight XCDs in turn, so the halves of a pair meet
+  // on one of them
+  const int n_queue = kWide ? (n_work + 7) / 8 * 16 : n_work;
   int bad_page = 0;
   // The short suffix items go first: each round is a chain of dependent memory accesses with
   // little data, which is cheap while every workgroup has other work to overlap it with and
@@ -1090,30 +992,27 @@ __device__ __forceinline__ void prefix_kernel_body(const AttnArgs& a) {
       qi = next_item;
       __syncthreads();
     }
-    if (qi >= n_work) break;
-    const int4 it = a.prefix_items[qi / a.Hkv];
-    const int kvh = qi % a.Hkv;
-    const int rows = min(32 * NW, a.group_count[it.x] * a.R - it.w);
-    // (workgroup-uniform)  The 8-wave shape, whose items are bound by the matrix and vector units,
-    // runs the pipelined item; the 4-wave shape, bound by HBM, the plain one (measured faster there).
-    if constexpr (NW == 8) {
-      if (rows <= 16 * NW) prefix_item_pipelined<1, NW>(a, it, kvh, lds, bad_page);
-      else prefix_item_pipelined<2, NW>(a, it, kvh, lds, bad_page);
+    if (qi >= n_queue) break;
+    if constexpr (kWide) {
+      const int pair = (qi >> 4) * 8 + (qi & 7);
+      if (pair >= n_work) continue;           // workgroup-uniform
+      const int4 it = a.prefix_items[pair / a.Hkv];
+      prefix_item_half(a, it, pair % a.Hkv, (qi >> 3) & 1, lds, bad_page);
     } else {
-      if (rows <= 16 * NW) prefix_item<1, NW>(a, it, kvh, lds, bad_page);
-      else prefix_item<2, NW>(a, it, kvh, lds, bad_page);
+      const int4 it = a.prefix_items[qi / a.Hkv];
+      const int kvh = qi % a.Hkv;
+      const int rows = min(kRowsPerQBlock, a.group_count[it.x] * a.R - it.w);
+      if (rows <= 64) prefix_item<1, 4>(a, it, kvh, lds, bad_page);
+      else prefix_item<2, 4>(a, it, kvh, lds, bad_page);
     }
   }
   if (bad_page) atomicOr(&a.counters[MARL_CTR_FLAGS], MARL_FLAG_BAD_PAGE);
 }
 
-// Two shapes of the same kernel: 4 waves and blocks of 128 query rows (two workgroups per CU),
-// or 8 waves and blocks of 256 rows (one workgroup per CU) for groups with more than 128 rows,
-// whose prefix KV would otherwise be streamed once per 128-row block.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void prefix_kernel(AttnArgs a) { prefix_kernel_body<4>(a); }
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void prefix_kernel_wide(AttnArgs a) { prefix_kernel_body<8>(a); }
+void prefix_kernel(AttnArgs a) { prefix_kernel_body<false>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void prefix_kernel_wide(AttnArgs a) { prefix_kernel_body<true>(a); }
 
 // ---------------------------------------------------------------------------------------
 // Merge kernel: the second reduction of split-KV decode attention.  For every (sequence,
@@ -1206,7 +1105,7 @@ void merge_kernel(AttnArgs a) {
 
 int prefix_blocks_per_cu(bool wide) {
   int n = 0;
-  const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, prefix_kernel_wide, 512, 0)
+  const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, prefix_kernel_wide, 256, 0)
                             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, prefix_kernel, 256, 0);
   if (e != hipSuccess || n < 1) n = 1;
   return n;
@@ -1218,7 +1117,7 @@ int suffix_blocks_per_cu() {
 }
 
 hipError_t launch_prefix(const AttnArgs& a, int grid, hipStream_t st) {
-  if (a.qblock_rows == 256) hipLaunchKernelGGL(prefix_kernel_wide, dim3(grid), dim3(512), 0, st, a);
+  if (a.qblock_rows == 256) hipLaunchKernelGGL(prefix_kernel_wide, dim3(grid), dim3(256), 0, st, a);
   else hipLaunchKernelGGL(prefix_kernel, dim3(grid), dim3(256), 0, st, a);
   return hipGetLastError();
 }

@@ -10,8 +10,8 @@ namespace marl {
 constexpr int kPage = 16;        // tokens per page
 constexpr int kD = 128;          // head dimension
 constexpr int kBlockTok = 32;    // tokens one MFMA step of a wave covers (two pages)
-constexpr int kRowsPerQBlock = 128;       // query rows one prefix work item covers (4-wave kernel)
-constexpr int kRowsPerQBlockWide = 256;   // ... in the 8-wave kernel
+constexpr int kRowsPerQBlock = 128;       // query rows one prefix work item covers
+constexpr int kRowsPerQBlockWide = 256;   // ... in the wide kernel
 // suffix items up to this many tokens are handled by one wave (build-time tuning knob)
 #ifndef MARL_SHORT_TOKENS
 #define MARL_SHORT_TOKENS 128

@@ -266,3 +266,15 @@ def test_full_size_sixteen_samples_per_prompt():
     w = I.WORKLOADS["qwen7b"]
     agents = tuple(I.Agent(a.prompts // 2, 16, a.prompt_len, a.gen_len) for a in w.agents)
     _full_size_every_row(dataclasses.replace(w, name="qwen7b/G16", agents=agents))
+
+
+@pytest.mark.parametrize("size", [128, 129, 136, 144, 145, 256, 257, 400])
+def test_halves_of_wide_row_blocks(size):
+    """One query row per sequence: blocks of 8, 9, 16 and 17 row tiles, an odd tile count, a second block
+    of one row; chunks of one step with a few tokens (the first step is also the ragged last one)."""
+    print("case: wide halves", size, flush=True)
+    rng = np.random.default_rng(size)
+    gos = np.concatenate([np.zeros(size, int), np.ones(140, int)])   # average above 128 rows: the wide kernel
+    inp = custom_inputs([71, 39], rng.integers(1, 20, len(gos)), gos, 2, 2, seed=size)
+    check_attn(inp, B.MARL_OUT_F32)
+    check_attn(inp, B.MARL_OUT_F32, prefix_chunk_tokens=32)
