@@ -22,7 +22,7 @@
 // loads; per instruction a wave reads 16 x 64 B of K or 2 x 512 B of V); LDS only combines
 // the four waves of a workgroup, which split the item's tokens between them.
 // Prefix kernel: the four waves split the query rows instead and share each K/V step
-// through a double-buffered LDS tile (described at the kernel).
+// through a ring of LDS tiles (described at the kernel).
 #include <type_traits>
 
 #include "marl_internal.h"
@@ -439,14 +439,14 @@ __device__ __forceinline__ void short_suffix_items(const AttnArgs& a, int& bad_p
 
 // ---------------------------------------------------------------------------------------
 // Prefix kernel: one work item = (group, chunk of prefix tokens, block of up to 128 (or 256)
-// query rows, KV head); blocks of 256 rows are described at prefix_item_half below.  Query row rho of a group is (its rho / R -th sequence, head kvh*R + rho % R).
+// query rows, KV head); two kernels, one for each block size.  Query row rho of a group is (its
+// rho / R -th sequence, head kvh*R + rho % R).
 //
-// Here the NW (4) waves split the QUERY rows (16-row tile t belongs to wave t % NW) and
-// every wave sees all tokens, so the group's K/V must reach all of them: each 32-token step (two
-// pages, 16 KB of K and V) is fetched once by the workgroup with fully coalesced 16-byte
-// loads (a wave reads 1 KB contiguous per instruction), staged in registers, written to a
-// triple-buffered LDS tile and read back in MFMA operand layout.  Loads run three steps
-// ahead (48 KB in flight per workgroup).  No cross-wave reduction is needed.
+// Here the four waves split the QUERY rows (16-row tile t belongs to wave t % 4) and every wave sees
+// all tokens, so the group's K/V must reach all of them: each 32-token step (two pages, 16 KB of K and V)
+// is fetched once by the workgroup with fully coalesced 16-byte loads (a wave reads 1 KB contiguous
+// per instruction) into a ring of LDS tiles and read back in MFMA operand layout.  No cross-wave
+// reduction is needed.
 //
 // LDS tile of one step (16 KB): K as 32 token rows of 256 B, the 16-byte chunk index of
 // row tau XOR-ed with a 4-bit key made of bits 0, 1, 3, 4 of tau: the 16 rows that the 16 lanes
@@ -456,289 +456,41 @@ __device__ __forceinline__ void short_suffix_items(const AttnArgs& a, int& bad_p
 // XOR-ed with (u>>3)&1 for the same reason.
 // ---------------------------------------------------------------------------------------
 constexpr int kStepBytes = 2 * kBlockTok * kD * 2;   // K + V of one 32-token step
-// the prefix items of the wide shape rescale their accumulators only when a lane's eight weights sum to
-// more than this
+// prefix items rescale their accumulators only when a lane's eight weights sum to more than this
 constexpr float kMaxWeight = 256.0f;
 // s_waitcnt immediate (gfx9 encoding): vector-memory counter <= vm, LDS/scalar counter <= lgkm
 constexpr int waitcnt_imm(int vm, int lgkm) { return (vm & 0xf) | ((vm >> 4) << 14) | (7 << 4) | ((lgkm & 0xf) << 8); }
+// Data path of an item: global memory straight into an LDS ring of four steps
+// (global_load_lds_dwordx4, the swizzle of the LDS tile applied on the source side, no staging registers)
+// -> operand registers.  Iteration n: wait for slot n+1, workgroup barrier; loads of slot n+3; read V(n);
+// score products of step n (K(n) is in registers); read K(n+1) into the K registers; softmax of step n,
+// which covers both reads; output products.  No LDS read is waited for where it is issued.
+//   Blocks of 256 rows, bound by instructions: a row's reference maximum moves only when a lane's eight
+// weights sum to more than kMaxWeight (no weight exceeds a sum that passes), a branch taken in the first
+// step and hardly ever after.  Blocks of 128 rows, bound by memory, keep the exact running maximum: a row's
+// largest weight is then 1, which bf16 holds exactly.
+//   Blocks of up to 256 rows (kHalves) are taken by two workgroups, half of the row tiles each, that run
+// on the same XCD, usually on the same CU: the second reads the group's keys and values out of the L2
+// (so these are ordinary cached loads), and each SIMD has two waves that no barrier keeps in step (one
+// waits or runs its softmax while the other feeds the matrix core).  Blocks of up to 128 rows stream
+// their keys and values once, with non-temporal loads (cached: 131 -> 141 and 343 -> 386 us on the first two
+// lists below).
+//   What bounds it, blocks of 128 rows: HBM, and on short lists the latency of an item's start and of its
+// steps.  256 groups of 8 samples x 7 rows, 512-2048 shared tokens: 131 us (5.4 TB/s); 64 groups of 4 x 8
+// rows, 8192 tokens: 343 us (6.5 TB/s), as with staging through registers; 4 groups of 16 x 8 rows, 512-2048
+// tokens: 28.8 -> 26.7 us, 4 groups of 4 x 4 rows, 256 tokens: 12.2 -> 10.1 us.  Blocks of 256 rows: issue of
+// matrix and vector instructions (180 flop per byte): 64 groups of 32 samples x 7 rows on 4096 shared tokens
+// 177 -> 150 us (0.80 PFLOP/s); the 177 us were one workgroup of 8 waves per CU with all of a group's rows,
+// staged through registers and kept in step by one barrier per step.
+constexpr int kPrefixStages = 4;
 struct PrefixLds {
-  __attribute__((aligned(16))) char buf[3][kStepBytes];
-};
-
-template <int MTW, int NW>
-__device__ __forceinline__ void prefix_item(const AttnArgs& a, const int4 it, const int kvh,
-                                            PrefixLds& lds, int& bad_page) {
-  constexpr int kQBlock = 32 * NW;              // query rows of one item: two 16-row tiles per wave
-  constexpr int kLoads = 1024 / (NW * 64);      // 16-byte loads per thread and step (16 KB per step)
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int i = lane & 15, j = lane >> 4;
-  const int g = it.x, tok_begin = it.y, tok_end = it.z, row_begin = it.w;
-  const int gstart = a.group_start[g];
-  const int nrows = a.group_count[g] * a.R;
-  const int32_t* table_row = a.prefix_table + (size_t)g * a.max_pp;
-  const float sc = fmaxf(fabsf(a.scale) * 1.44269504088896340736f, 1e-30f);
-  const uint32_t sign_flip = a.scale < 0.f ? 0x80008000u : 0u;
-  const int nslot = a.NCp + a.NCs;
-  const int slot = tok_begin / a.Cp;
-
-  // this wave's tiles: wave, wave + 4, ...; nt of them hold at least one real row
-  const int tiles_total = (min(kQBlock, nrows - row_begin) + 15) >> 4;
-  const int nt = max(0, min(MTW, (tiles_total - wave + NW - 1) / NW));   // wave-uniform
-  int row_index[MTW];
-  u32x4 qreg[MTW][4];
-#pragma unroll
-  for (int qt = 0; qt < MTW; ++qt) {
-    const int rho = row_begin + (qt * NW + wave) * 16 + i;
-    int idx = -1;
-    if (rho < nrows && (qt * NW + wave) * 16 < kQBlock)
-      idx = a.group_seqs[gstart + rho / a.R] * a.Hq + kvh * a.R + rho % a.R;
-    row_index[qt] = idx;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (idx >= 0) {
-        v = *reinterpret_cast<const u32x4*>(a.q + (size_t)idx * kD + (4 * kk + j) * 8);
-        v ^= sign_flip;
-      }
-      qreg[qt][kk] = v;
-    }
-  }
-  f32x4 acc[MTW][8];
-  float m_run[MTW], l_run[MTW];
-#pragma unroll
-  for (int qt = 0; qt < MTW; ++qt) {
-    m_run[qt] = -INFINITY;
-    l_run[qt] = 0.f;
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-
-  const int nsteps = (tok_end - tok_begin + kBlockTok - 1) / kBlockTok;
-  const size_t page_bytes = (size_t)a.Hkv * (kPage * kD * 2);
-
-  // Page ids and page addresses are wave-uniform (scalar registers, a handful of scalar instructions
-  // per step) and every lane adds one 32-bit offset that never changes: with two waves per SIMD the
-  // instruction count of a step is a cost of its own (measured on a shape with 8 waves per workgroup, whose loop it
-  // bounds).
-  //
-  // Page ids of step n: two scalar loads, unconditional (a step past the end repeats the last page,
-  // and so does the second page of a step that has only one).  They are issued at the top of an
-  // iteration and taken after its first wait for LDS data, which waits for scalar loads as well
-  // (one counter, and scalar loads return out of order); fetched and checked in one place they
-  // would cost two scalar-memory latencies per step, one after the other.
-  const int first_page = tok_begin >> 4;
-  const int last_page = max(first_page, (tok_end - 1) >> 4);
-  uint32_t id_max = 0;   // largest id seen (as unsigned): checked against the pool once, after the loop
-  auto fetch_ids = [&](int n, int& r0, int& r1) {
-    r0 = ld_uniform(table_row + min(first_page + 2 * n, last_page));
-    r1 = ld_uniform(table_row + min(first_page + 2 * n + 1, last_page));
-  };
-  // the ids as the loads use them: page 0 (bytes nobody uses, from cache) for a step past the end
-  // and for an id outside the pool
-  auto take_ids = [&](int n, int r0, int r1, int& p0, int& p1) {
-    id_max = max(id_max, max((uint32_t)r0, (uint32_t)r1));
-    const uint32_t limit = n < nsteps ? (uint32_t)a.num_pages : 0u;
-    p0 = (uint32_t)r0 < limit ? r0 : 0;
-    p1 = (uint32_t)r1 < limit ? r1 : 0;
-    // (an empty statement the compiler may not move: without it the loads and the check sink to
-    // the end of the iteration, in front of the next use, and are waited for there)
-    asm volatile("" : "+s"(p0), "+s"(p1));
-  };
-  // A step is 1024 16-byte vectors: K of page 0, K of page 1, V of page 0, V of page 1 (256
-  // each, contiguous in memory).  Thread tid fetches vectors tid + k * (threads), k < kLoads.
-  // Of a page's 256 vectors, vector w is slot w/16, chunk w%16 of K, or 16-byte unit w of V.
-  // Which of the four regions a load belongs to is the same for a whole wave.
-  static_assert(NW % 4 == 0, "a wave's 64 vectors must lie in one 256-vector region");
-  const int w = tid & 255;
-  const uint32_t lane_off = (uint32_t)kvh * (kPage * kD * 2) + (uint32_t)w * 16;
-  auto region_of = [&](int k) { return NW == 4 ? k : k * (NW / 4) + (wave >> 2); };   // wave-uniform
-  int lds_off[kLoads];
-#pragma unroll
-  for (int k = 0; k < kLoads; ++k) {
-    const int region = region_of(k);
-    const bool is_v = region >> 1;
-    // K rows of page 1 are tau = 16 + slot; swizzle key of row tau: bits 0, 1, 3, 4 of tau
-    const int slot = w >> 4;
-    const int key = ((region & 1) << 3) | ((slot >> 3) << 2) | (slot & 3);
-    lds_off[k] = is_v ? 2 * kBlockTok * kD + (region & 1) * 4096 + ((w ^ ((w >> 3) & 1)) << 4)
-                      : ((region & 1) * 16 + slot) * 256 + (((w & 15) ^ key) << 4);
-  }
-  // The loads are unconditional so that every wait in the loop knows exactly how many younger loads
-  // are in flight.
-  auto issue = [&](int p0, int p1, u32x4 (&st)[kLoads]) {
-#pragma unroll
-    for (int k = 0; k < kLoads; ++k) {
-      const int region = region_of(k);
-      const char* base = reinterpret_cast<const char*>((region >> 1) ? a.v_pages : a.k_pages) +
-                         (size_t)(uint32_t)((region & 1) ? p1 : p0) * page_bytes;   // scalar
-      st[k] = ld_stream(base + lane_off);
-    }
-  };
-  auto stage_to_lds = [&](const u32x4 (&st)[kLoads], char* buf) {
-#pragma unroll
-    for (int k = 0; k < kLoads; ++k) *reinterpret_cast<u32x4*>(buf + lds_off[k]) = st[k];
-  };
-  // operand reads: K row tau = 8*(i/4) + 4T + i%4, whose swizzle key is i
-  const int k_rd = (8 * (i >> 2) + (i & 3)) * 256;
-  const int v_rd = 2 * kBlockTok * kD + (j >> 1) * 4096;
-
-  int r0, r1;   // ids in flight: those of the step that the next iteration requests
-  int p0, p1;   // the ids the next request uses
-  auto compute = [&](int n, const char* buf) {
-    const int t0 = tok_begin + n * kBlockTok;
-    const bool ragged = t0 + kBlockTok > tok_end;   // wave-uniform; only the chunk's last step
-    u32x4 pb[MTW];
-    if (nt == 0) take_ids(n + 4, r0, r1, p0, p1);   // (a wave without tiles only moves data)
-    {
-      u32x4 kr[2][4];
-#pragma unroll
-      for (int T = 0; T < 2; ++T)
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          kr[T][kk] = *reinterpret_cast<const u32x4*>(buf + k_rd + T * 4 * 256 + (((4 * kk + j) ^ i) << 4));
-#pragma unroll
-      for (int qt = 0; qt < MTW; ++qt) {
-        pb[qt] = u32x4{0u, 0u, 0u, 0u};
-        if (qt < nt) {   // wave-uniform
-          f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            s0 = mfma_16x16x32(kr[0][kk], qreg[qt][kk], s0);
-            s1 = mfma_16x16x32(kr[1][kk], qreg[qt][kk], s1);
-          }
-          if (qt == 0) take_ids(n + 4, r0, r1, p0, p1);   // (the K reads have been waited for)
-          if (ragged) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              if (t0 + 8 * j + e >= tok_end) s0[e] = -INFINITY;
-              if (t0 + 8 * j + 4 + e >= tok_end) s1[e] = -INFINITY;
-            }
-          }
-          float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
-                           fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
-          mx = rows_allreduce_max(mx);
-          const float m_new = fmaxf(m_run[qt], mx * sc);
-          const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
-          float p[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[e], sc, -m_new));
-            p[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[e], sc, -m_new));
-          }
-          const float psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-          if (__builtin_amdgcn_ballot_w64(m_new > m_run[qt]) != 0) {   // wave-uniform
-#pragma unroll
-            for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
-          }
-          l_run[qt] = l_run[qt] * alpha + psum;
-          m_run[qt] = m_new;
-          pb[qt] = u32x4{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
-        }
-      }
-    }
-    u32x4 vr[8];
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) {
-      const int u = 2 * (16 * ct + i) + (j & 1);
-      vr[ct] = *reinterpret_cast<const u32x4*>(buf + v_rd + ((u ^ ((i >> 2) & 1)) << 4));
-    }
-    if (ragged) {
-      // value slots no token owns may hold anything (NaN included): zero them
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const int tok = t0 + 8 * j + 2 * d;
-        const uint32_t mask = (tok < tok_end ? 0x0000ffffu : 0u) | (tok + 1 < tok_end ? 0xffff0000u : 0u);
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct) vr[ct][d] &= mask;
-      }
-    }
-#pragma unroll
-    for (int qt = 0; qt < MTW; ++qt)
-      if (qt < nt) {
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = mfma_16x16x32(vr[ct], pb[qt], acc[qt][ct]);
-      }
-  };
-
-  // Three register stages and three LDS buffers: while step n is computed from buffer n%3,
-  // the loads of steps n+1, n+2 and n+3 are in flight (48 KB per workgroup); step n+1 moves
-  // from its registers to buffer (n+1)%3 at the end of the iteration, one barrier per step.
-  u32x4 st0[kLoads], st1[kLoads], st2[kLoads];
-  fetch_ids(0, r0, r1);
-  take_ids(0, r0, r1, p0, p1);
-  issue(p0, p1, st0);
-  fetch_ids(1, r0, r1);
-  take_ids(1, r0, r1, p0, p1);
-  issue(p0, p1, st1);
-  fetch_ids(2, r0, r1);
-  take_ids(2, r0, r1, p0, p1);
-  issue(p0, p1, st2);
-  fetch_ids(3, r0, r1);
-  take_ids(3, r0, r1, p0, p1);
-  stage_to_lds(st0, lds.buf[0]);
-  __syncthreads();
-  for (int n = 0; n < nsteps; n += 3) {
-    issue(p0, p1, st0);          // step n+3
-    fetch_ids(n + 4, r0, r1);
-    compute(n, lds.buf[0]);      // (takes the ids of step n+4)
-    stage_to_lds(st1, lds.buf[1]);
-    __syncthreads();
-    if (n + 1 < nsteps) {
-      issue(p0, p1, st1);        // step n+4
-      fetch_ids(n + 5, r0, r1);
-      compute(n + 1, lds.buf[1]);
-      stage_to_lds(st2, lds.buf[2]);
-      __syncthreads();
-    }
-    if (n + 2 < nsteps) {
-      issue(p0, p1, st2);        // step n+5
-      fetch_ids(n + 6, r0, r1);
-      compute(n + 2, lds.buf[2]);
-      stage_to_lds(st0, lds.buf[0]);
-      __syncthreads();
-    }
-  }
-  if (id_max >= (uint32_t)a.num_pages) bad_page = 1;
-  // a workgroup-wide barrier has been passed since the last LDS read: the next item may
-  // overwrite the buffers
-
-#pragma unroll
-  for (int qt = 0; qt < MTW; ++qt) {
-    const float l = rows_allreduce_sum(l_run[qt]);
-    if (row_index[qt] >= 0) {
-      const size_t ps = (size_t)row_index[qt] * nslot + slot;
-      float* dst = a.partial_o + ps * kD + 4 * j;
-#pragma unroll
-      for (int ct = 0; ct < 8; ++ct) *reinterpret_cast<f32x4*>(dst + 16 * ct) = acc[qt][ct];
-      if (j == 0) a.partial_ml[ps] = make_float2(m_run[qt], l);
-    }
-  }
-}
-
-// Prefix item of the wide shape (blocks of up to 256 query rows), one half of its row tiles: the two
-// halves of an item are taken by two workgroups of the same XCD, usually of the same CU, so that the
-// second reads the group's keys and values out of the L2 and each SIMD has two waves that no barrier
-// keeps in step (one waits or runs its softmax while the other feeds the matrix core).
-//   Data path: global memory straight into an LDS ring of four steps (global_load_lds_dwordx4, the
-// swizzle of the LDS tile applied on the source side, no staging registers) -> operand registers.
-//   Iteration n: wait for slot n+1, workgroup barrier; loads of slot n+3; read V(n); score products of
-// step n (K(n) is in registers); read K(n+1) into the K registers; softmax of step n, which covers both
-// reads; output products.  No LDS read is waited for where it is issued.
-//   A row's reference maximum moves only when a lane's eight weights sum to more than kMaxWeight
-// (no weight exceeds a sum that passes): a branch taken in the first step and hardly ever after.
-// What bounds it: issue of matrix and vector instructions (180 flop per byte).  64 groups of 32 samples x
-// 7 rows on 4096 shared tokens: 177 -> 150 us (0.80 PFLOP/s); the 177 us were one workgroup of 8 waves per
-// CU with all of a group's rows, staged through registers and kept in step by one barrier per step.
-constexpr int kWideStages = 4;
-struct WideLds {
-  __attribute__((aligned(16))) char buf[kWideStages][kStepBytes];
+  __attribute__((aligned(16))) char buf[kPrefixStages][kStepBytes];
 };
 typedef const char __attribute__((address_space(1))) * GlobalBytes;
 
-__device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 it, const int kvh, const int half,
-                                                 WideLds& lds, int& bad_page) {
+template <bool kHalves>
+__device__ __forceinline__ void prefix_item(const AttnArgs& a, const int4 it, const int kvh, const int half,
+                                            PrefixLds& lds, int& bad_page) {
   constexpr int NW = 4, MTW = 2, kLoads = 4;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -746,8 +498,9 @@ __device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 i
   const int i = lane & 15, j = lane >> 4;
   const int g = it.x, tok_begin = it.y, tok_end = it.z;
   // this half's tiles: a block of at most eight tiles is not divided (its keys are then read once)
+  constexpr int kBlockRows = kHalves ? kRowsPerQBlockWide : kRowsPerQBlock;
   const int nrows = ld_uniform(a.group_count + g) * a.R;
-  const int tiles_all = (min(kRowsPerQBlockWide, nrows - it.w) + 15) >> 4;
+  const int tiles_all = (min(kBlockRows, nrows - it.w) + 15) >> 4;
   const int tiles0 = tiles_all <= MTW * NW ? tiles_all : (tiles_all + 1) >> 1;
   const int tiles = half ? tiles_all - tiles0 : tiles0;
   if (tiles <= 0) return;                                    // workgroup-uniform
@@ -756,7 +509,6 @@ __device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 i
 
   const int32_t* table_row = a.prefix_table + (size_t)g * a.max_pp;
   const int nsteps = (tok_end - tok_begin + kBlockTok - 1) / kBlockTok;
-  const uint32_t page_bytes = (uint32_t)a.Hkv * (kPage * kD * 2);
   const int first_page = tok_begin >> 4;
   const int last_page = (tok_end - 1) >> 4;
   // Page ids (scalar): fetched an iteration before they are used, checked once per item.  A slot past
@@ -780,11 +532,11 @@ __device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 i
     const int key = ((k & 1) << 3) | ((slot >> 3) << 2) | (slot & 3);
     src_off[k] = 16u * (uint32_t)((k >> 1) ? (s_pos ^ ((s_pos >> 3) & 1)) : ((slot << 4) | ((s_pos & 15) ^ key)));
   }
-  const uint32_t kv_off = (uint32_t)kvh * (kPage * kD * 2);
   auto issue = [&](uint32_t ring) {
     id_max = max(id_max, max((uint32_t)r0, (uint32_t)r1));
     const uint32_t p0 = (uint32_t)r0 < (uint32_t)a.num_pages ? r0 : 0, p1 = (uint32_t)r1 < (uint32_t)a.num_pages ? r1 : 0;
-    const uint64_t off0 = (uint64_t)p0 * page_bytes + kv_off, off1 = (uint64_t)p1 * page_bytes + kv_off;
+    const uint64_t off0 = ((uint64_t)p0 * (uint32_t)a.Hkv + (uint32_t)kvh) * (kPage * kD * 2);
+    const uint64_t off1 = ((uint64_t)p1 * (uint32_t)a.Hkv + (uint32_t)kvh) * (kPage * kD * 2);
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
       const GlobalBytes base = reinterpret_cast<GlobalBytes>(reinterpret_cast<uintptr_t>((k >> 1) ? a.v_pages : a.k_pages)) +
@@ -792,18 +544,18 @@ __device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 i
       char* dst = lds.buf[0] + (ring + k * 4096 + wave * 1024);   // wave-uniform; lane l lands at dst + 16 l
       __builtin_amdgcn_global_load_lds(
           reinterpret_cast<const __attribute__((address_space(1))) void*>(base + src_off[k]),
-          reinterpret_cast<__attribute__((address_space(3))) void*>((uint32_t)reinterpret_cast<uintptr_t>(dst)), 16, 0, 0);
+          reinterpret_cast<__attribute__((address_space(3))) void*>((uint32_t)reinterpret_cast<uintptr_t>(dst)), 16, 0, kHalves ? 0 : 2);   // (2: non-temporal)
     }
   };
-  constexpr uint32_t kRingBytes = kWideStages * kStepBytes;
+  constexpr uint32_t kRingBytes = kPrefixStages * kStepBytes;
   static_assert((kRingBytes & (kRingBytes - 1)) == 0, "the ring wraps by a mask");
   // the first three steps are requested before the chain of dependent loads that leads to the query rows
 #pragma unroll
-  for (int s0 = 0; s0 < kWideStages - 1; ++s0) {
+  for (int s0 = 0; s0 < kPrefixStages - 1; ++s0) {
     fetch_ids(s0);
     issue(s0 * kStepBytes);
   }
-  fetch_ids(kWideStages - 1);
+  fetch_ids(kPrefixStages - 1);
 
   const int gstart = a.group_start[g];
   const float sc = fmaxf(fabsf(a.scale) * 1.44269504088896340736f, 1e-30f);
@@ -910,30 +662,44 @@ __device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 i
         }
 #pragma unroll
         for (int qt = 0; qt < NT; ++qt) {
-          float p[8], psum;
+          u32x4 pb;
+          float psum;
           auto weights = [&] {
+            float p[8];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][0][e], sc, -m_run[qt]));
               p[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[qt][1][e], sc, -m_run[qt]));
             }
-            psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+            pb = u32x4{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
+            // (256-row blocks: the rounded weights, the same that multiply V)
+            if constexpr (kHalves) psum = sum_bf16(pb);
+            else psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
           };
-          weights();
-          if (__builtin_amdgcn_ballot_w64(psum > kMaxWeight) != 0) {   // wave-uniform
+          auto move_reference = [&] {
             const f32x4 s0 = s[qt][0], s1 = s[qt][1];
             const float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
-                                   fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3]))) * sc;   // this lane's 8 tokens
-            const float m_new = fmaxf(m_run[qt], rows_allreduce_max(mx));
-            const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);   // 1 where the row did not move
-            l_run[qt] *= alpha;
-            m_run[qt] = m_new;
+                                   fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));   // this lane's 8 tokens
+            const float m_new = fmaxf(m_run[qt], rows_allreduce_max(mx) * sc);
+            if (kHalves || __builtin_amdgcn_ballot_w64(m_new > m_run[qt]) != 0) {      // wave-uniform
+              const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);           // 1 where the row did not move
+              l_run[qt] *= alpha;
+              m_run[qt] = m_new;
 #pragma unroll
-            for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
+              for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
+            }
+          };
+          if constexpr (kHalves) {
+            weights();
+            if (__builtin_amdgcn_ballot_w64(psum > kMaxWeight) != 0) {   // wave-uniform
+              move_reference();
+              weights();
+            }
+          } else {
+            move_reference();
             weights();
           }
           l_run[qt] += psum;
-          const u32x4 pb = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
 #pragma unroll
           for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = mfma_16x16x32(vr[ct], pb, acc[qt][ct]);
         }
@@ -969,7 +735,7 @@ __device__ __forceinline__ void prefix_item_half(const AttnArgs& a, const int4 i
 // halves are taken separately; both with workgroups of 4 waves, two per CU.
 template <bool kWide>
 __device__ __forceinline__ void prefix_kernel_body(const AttnArgs& a) {
-  __shared__ typename std::conditional<kWide, WideLds, PrefixLds>::type lds;
+  __shared__ PrefixLds lds;
   __shared__ int next_item;
   const int n_work = a.counters[MARL_CTR_NUM_PREFIX_ITEMS] * a.Hkv;
   // wide: entries of the queue come in groups of 16, the first halves of eight (item, KV head) pairs and
@@ -997,13 +763,10 @@ __device__ __forceinline__ void prefix_kernel_body(const AttnArgs& a) {
       const int pair = (qi >> 4) * 8 + (qi & 7);
       if (pair >= n_work) continue;           // workgroup-uniform
       const int4 it = a.prefix_items[pair / a.Hkv];
-      prefix_item_half(a, it, pair % a.Hkv, (qi >> 3) & 1, lds, bad_page);
+      prefix_item<true>(a, it, pair % a.Hkv, (qi >> 3) & 1, lds, bad_page);
     } else {
       const int4 it = a.prefix_items[qi / a.Hkv];
-      const int kvh = qi % a.Hkv;
-      const int rows = min(kRowsPerQBlock, a.group_count[it.x] * a.R - it.w);
-      if (rows <= 64) prefix_item<1, 4>(a, it, kvh, lds, bad_page);
-      else prefix_item<2, 4>(a, it, kvh, lds, bad_page);
+      prefix_item<false>(a, it, qi % a.Hkv, 0, lds, bad_page);
     }
   }
   if (bad_page) atomicOr(&a.counters[MARL_CTR_FLAGS], MARL_FLAG_BAD_PAGE);

@@ -215,7 +215,6 @@ __device__ __forceinline__ int ld_uniform_at(const int32_t* p, uint32_t at) {
 // What one item is, wave-uniform (scalar registers).
 struct PfItem {
   const int32_t* table_row;   // page ids of the group
-  int kv_off;                 // byte offset of the KV head inside a page
   int kvh, rows;
   int tok0, rem0;             // the block's first row = tok0 * R + rem0
   int qrow0, pos0;            // row of q and position of token tok0
@@ -245,7 +244,6 @@ __device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
   it.tok_end = it.pos0 + div_R(it.rem0 + it.rows - 1, a.inv_R) + 1;
   it.nsteps = (it.tok_end + kBlockTok - 1) / kBlockTok;
   it.slots = max(it.nsteps, kPfStages);
-  it.kv_off = it.kvh * (kPage * kD * 2);
   it.table_row = a.prefix_table + (size_t)g * a.max_pp;
   return it;
 }
@@ -294,7 +292,6 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
   };
   f32x4 acc[kMT][8];
   float m_run[kMT], l_run[kMT];
-  const uint32_t page_bytes = (uint32_t)a.Hkv * (kPage * kD * 2);
 
   // The stream of steps whose loads are requested, kPfStages - 1 slots ahead of the step that is
   // computed: page ids two at a time by scalar loads, one slot before they are used.  All of it is
@@ -303,8 +300,8 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
   // item's last step repeats that step: its loads fetch valid bytes that nobody uses, so the loop
   // needs no conditional loads and every wait knows how many younger loads are in flight.
   const int32_t* st_table;          // the item's table row
-  int st_page, st_first_of_last, st_last, st_left, st_off;   // next page, the last step's first page, last page, slots left, KV head offset
-  int r0, r1, r_off;                // ids (in flight) and KV head offset of the slot that is requested next
+  int st_page, st_first_of_last, st_last, st_left, st_kvh;   // next page, the last step's first page, last page, slots left, KV head
+  int r0, r1, r_kvh;                // ids (in flight) and KV head of the slot that is requested next
   uint32_t id_max = 0;              // largest id seen: compared with the pool size once, at the end
   auto start_stream = [&](const PfItem& it) {
     st_table = it.table_row;
@@ -312,13 +309,13 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
     st_last = (it.tok_end - 1) >> 4;
     st_first_of_last = 2 * (it.nsteps - 1);
     st_left = it.slots;
-    st_off = it.kv_off;
+    st_kvh = it.kvh;
   };
   auto load_ids = [&] {
     const uint32_t at = (uint32_t)min(st_page, st_first_of_last);
     r0 = ld_uniform_at(st_table, at);
     r1 = ld_uniform_at(st_table, min(at + 1, (uint32_t)st_last));
-    r_off = st_off;
+    r_kvh = st_kvh;
     st_page += 2;
     --st_left;
   };
@@ -359,7 +356,8 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
     // (an id outside the pool reads page 0)
     id_max = max(id_max, max((uint32_t)r0, (uint32_t)r1));
     const uint32_t p0 = (uint32_t)r0 < (uint32_t)a.num_pages ? r0 : 0, p1 = (uint32_t)r1 < (uint32_t)a.num_pages ? r1 : 0;
-    const uint64_t off0 = (uint64_t)p0 * page_bytes + (uint32_t)r_off, off1 = (uint64_t)p1 * page_bytes + (uint32_t)r_off;
+    const uint64_t off0 = ((uint64_t)p0 * (uint32_t)a.Hkv + (uint32_t)r_kvh) * (kPage * kD * 2);
+    const uint64_t off1 = ((uint64_t)p1 * (uint32_t)a.Hkv + (uint32_t)r_kvh) * (kPage * kD * 2);
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
       // (scalar base + 32-bit lane offset)

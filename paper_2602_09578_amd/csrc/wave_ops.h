@@ -24,6 +24,15 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
+// Sum of the eight bf16 values of a packed vector (v_dot2_f32_bf16 with ones: float32 accumulation; the
+// values that a matrix product is given, as it is given them).
+__device__ __forceinline__ float sum_bf16(u32x4 v) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
+  auto dot = [&](uint32_t w, float c) { return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), one, c, false); };
+  return dot(v[1], dot(v[0], 0.f)) + dot(v[3], dot(v[2], 0.f));
+}
+
 // All-reduce over the four lanes l, l^16, l^32, l^48 (the lanes that share a q-row) with the
 // gfx950 row-swap instructions, which stay in the vector ALU (a shuffle through the LDS
 // crossbar costs a round trip in the middle of the softmax dependency chain).
