@@ -294,7 +294,10 @@ int marl_sample_tokens_top_p(const void* logits, const float* uniforms, float te
  * (MARL_FLAG_BAD_GROUP), a page id out of range reads page 0 (MARL_FLAG_BAD_PAGE); read the
  * flags with marl_attn_read_flags on this call's workspace.
  * workspace: marl_prefill_workspace_bytes() bytes, 256-byte aligned, used from the start of the
- * call's work until its end on the stream.
+ * call's work until its end on the stream.  For shapes with few row blocks and long tables this includes up
+ * to about 100 MB for partial results (long blocks may be divided along their keys, with results that are the
+ * same in every run); a call whose workspace holds the list alone (256 bytes, num_groups + 1 integers, 8 bytes
+ * for each of num_tokens * R / 192 + num_groups blocks, each rounded up to 256) is served without.
  */
 typedef struct {
   int32_t num_tokens;        /* NT: query tokens of all groups together */

@@ -602,6 +602,19 @@ long prefill_max_blocks(const marl_prefill_shape* s) {   // row blocks of all gr
 size_t prefill_ws_bytes(const marl_prefill_shape* s) {
   return kPrefillHeaderBytes + prefill_start_bytes(s) + align_up((size_t)prefill_max_blocks(s) * sizeof(int2), 256);
 }
+// The same with room for blocks whose keys are divided: a longer list, then info, arrivals, maxima and sums,
+// outputs.  A workspace of only prefill_ws_bytes is served without divided blocks.
+marl::PrefillSplitLayout prefill_split(const marl_prefill_shape* s) {
+  return marl::prefill_split_layout(prefill_max_blocks(s), s->num_kv_heads, (long)s->max_prefix_pages * marl::kPage);
+}
+size_t prefill_split_off(const marl_prefill_shape* s, const marl::PrefillSplitLayout& L) {
+  return kPrefillHeaderBytes + prefill_start_bytes(s) + (size_t)L.entries * sizeof(int2);
+}
+size_t prefill_full_ws_bytes(const marl_prefill_shape* s) {
+  const marl::PrefillSplitLayout L = prefill_split(s);
+  if (L.entries == 0) return prefill_ws_bytes(s);
+  return prefill_split_off(s, L) + (size_t)L.entries * 4 + marl::kPfMaxParts * 4 + L.bytes;
+}
 void fill_prefill_args(const marl_prefill_shape* s, marl::PrefillArgs& a) {
   memset(&a, 0, sizeof a);
   a.NT = s->num_tokens;
@@ -620,7 +633,7 @@ int marl_prefill_workspace_bytes(const marl_prefill_shape* shape, size_t* bytes)
   const int rc = check_prefill_shape(shape);
   if (rc != MARL_OK) return rc;
   if (!bytes) return MARL_INVALID_ARG;
-  *bytes = prefill_ws_bytes(shape);
+  *bytes = prefill_full_ws_bytes(shape);
   return MARL_OK;
 }
 
@@ -659,9 +672,20 @@ int marl_prefill_attn(const marl_prefill_shape* shape, void* workspace, size_t w
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_fail(e, "device query");
-  // no more workgroups than the shape can have row blocks
-  const long max_items = prefill_max_blocks(shape) * a.Hkv;
   long grid = (long)cus * marl::prefill_blocks_per_cu();
+  long max_entries = prefill_max_blocks(shape);
+  const marl::PrefillSplitLayout L = prefill_split(shape);
+  if (L.entries > 0 && workspace_bytes >= prefill_full_ws_bytes(shape)) {
+    char* at = static_cast<char*>(workspace) + prefill_split_off(shape, L);
+    a.split_info = reinterpret_cast<int32_t*>(at);
+    a.split_arrived = a.split_info + L.entries;
+    a.split_o = reinterpret_cast<float*>(a.split_arrived + marl::kPfMaxParts);
+    a.split_bytes = (int32_t)L.bytes;
+    a.split_slots = (int32_t)grid;
+    max_entries = L.entries;
+  }
+  // no more workgroups than the shape can have items
+  const long max_items = max_entries * a.Hkv;
   if (grid > max_items) grid = max_items;
   if (grid < 1) grid = 1;
   e = marl::launch_prefill(a, (int)grid, static_cast<hipStream_t>(stream));

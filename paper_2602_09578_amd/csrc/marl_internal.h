@@ -133,6 +133,10 @@ struct PrefillArgs {
   int32_t* counters;            // workspace header
   int32_t* block_start;         // [NG + 1] running number of row blocks
   int2* items;                  // [blocks] (group, first row of the block)
+  // parts of blocks whose keys are divided; split_slots = 0: no room for them, none is
+  int32_t* split_info;          // [512] by list entry: first part << 8 | part << 4 | parts - 1
+  int32_t* split_arrived;       // [kPfMaxParts] by first part of a block and KV head: parts that are finished
+  float* split_o;               // a part's unnormalised outputs, running maxima and sums, as its lanes hold them
   // the prompt scatter only:
   const uint16_t* k_new;        // [NT][Hkv][128]
   const uint16_t* v_new;
@@ -141,8 +145,14 @@ struct PrefillArgs {
   int32_t* flags;
   int32_t NT, NG, Hq, Hkv, R, num_pages, max_pp, out_dtype, max_blocks;
   int32_t inv_R;                // ceil(65536 / R)
+  int32_t split_slots;          // workgroups that run at the same time
+  int32_t split_bytes;          // of split_o
   float scale;
 };
+constexpr int kPfMaxParts = 1024;     // parts (of all KV heads) of one call's divided blocks
+// Room for divided blocks behind the list's: entries of the list (0: the shape has no use for any), partial results.
+struct PrefillSplitLayout { int entries, parts; size_t bytes; };
+PrefillSplitLayout prefill_split_layout(long max_blocks, long Hkv, long max_keys);
 int prefill_rows_per_block();
 int prefill_blocks_per_cu();
 hipError_t launch_prefill(const PrefillArgs& a, int grid, hipStream_t st);

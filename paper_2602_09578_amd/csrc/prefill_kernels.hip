@@ -29,6 +29,15 @@
 // ahead, so that it knows its next item while it works on one: that item's steps follow the
 // current one's in the ring without a gap, and its queries are requested before the current rows are
 // written.  (A fixed assignment instead of the counter left 3 to 13 % of the time to the longest share.)
+//   A few long items (chunks of a few prompts behind long context) leave workgroups idle, or end unevenly,
+// whatever their order.  For a sorted list the plan kernel therefore weighs dividing long blocks along their
+// keys: a part's sums (float32, unnormalised) go to the workspace, and the workgroup that arrives last at a
+// block adds the parts.  Whole and divided: one chunk of 512 tokens behind 8192, 64 / 8 heads 220 -> 180 us,
+// 28 / 4 heads 255 -> 100 us; three chunks behind up to 6.6 k, 64 / 8 heads 229 -> 175 us; 64 tokens behind 2000 69 -> 42 us;
+// one prompt of 2048 tokens, 28 / 4 heads 79 -> 69 us; 9 chunks 340 -> 280 us.  Lists with more work than that stay
+// whole (12 and 16 chunks, 260 and 555 us either way), as does everything in this kernel's instance
+// without parts (a few scalar registers less; for shapes whose lists are not sorted).
+// A workspace with room for the list alone is served with whole blocks.
 //
 // What bounds it: the issue of instructions.  A step of a wave is 48 matrix instructions (768 cycles
 // of the matrix core) and about 100 vector instructions, 24 of them exponentials (710 cycles of the
@@ -36,7 +45,9 @@
 // two workgroups per CU with 141 vector and 105 scalar instructions, 1.50 with 120 and 50 (page
 // ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  256 prompts of
 // 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.65 ms (0.95 PFLOP/s; a large matrix product of this
-// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.384 ms.
+// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.
+#include <algorithm>
+
 #include "marl_internal.h"
 #include "wave_ops.h"
 
@@ -64,6 +75,7 @@ constexpr int kPfStages = 4;
 struct PrefillLds {
   __attribute__((aligned(16))) char buf[kPfStages][kPfStepBytes];
   __attribute__((aligned(16))) char out[kNW][16 * kD];   // half a tile's output rows (64 channels) on their way to memory, per wave
+  int arrived;   // parts of the current block that were finished before this one
   int next[2];   // drawn item indices, by the parity of the item during which they were published
 };
 // s_waitcnt immediate that waits only for the vector-memory counter to drop to n (gfx9 encoding)
@@ -98,17 +110,23 @@ __device__ __forceinline__ int block_rows(long nrows) {
 static_assert(kQB / 16 < 16, "a block's tiles are packed into four bits");
 __device__ __forceinline__ int2 pack_item(int g, int row_begin, int qb) { return make_int2(g, row_begin | (qb >> 4)); }
 
-constexpr int kPfSorted = 512;    // a list of at most so many blocks is sorted
+constexpr int kPfSorted = 512;    // a list of at most so many entries is sorted
 constexpr int kPfClasses = 64;    // cost classes of that order
+constexpr int kPfMaxDiv = 16;     // most parts of one block's keys (four bits of a list record)
+constexpr int kPfMinPart = 512;   // keys: no part is meant to be shorter
+// lengths of parts that are considered, in even shares of a workgroup
+__constant__ constexpr float kPfLens[16] = {0.f, 0.5f, 0.625f, 0.75f, 0.875f, 1.f, 1.125f, 1.25f, 1.5f, 1.75f, 2.f, 2.5f, 3.f, 4.f, 6.f, 8.f};
+constexpr int kPfSplitBit = (int)0x80000000u;   // in a record's group: the entry is one part of the block's keys
 
 __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArgs a) {
   constexpr int kWavesPf = kPlanThreadsPf / 64;
   __shared__ long long wave_sum[kWavesPf];   // 64-bit: inconsistent inputs must not wrap the sums
   __shared__ int hist[kPfClasses];
-  __shared__ int flags_all, end_all;
+  __shared__ int flags_all, end_all, parts_used;
+  __shared__ float estimate[kWavesPf];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int flag = 0;
-  if (tid == 0) flags_all = end_all = 0;
+  if (tid == 0) flags_all = end_all = parts_used = 0;
   __syncthreads();
   long long carry = 0;
   for (int g0 = 0; g0 < a.NG; g0 += kPlanThreadsPf) {
@@ -157,33 +175,92 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
   __threadfence();
   __syncthreads();
   // The accepted groups' blocks are exactly [0, end_all).
-  const int total = end_all;
-  if (wave == 0 && total <= kPfSorted) {
+  int total = end_all;   // (then entries of the list)
+  if (a.split_slots > 0)
+    for (int k = tid; k < kPfMaxParts; k += kPlanThreadsPf) a.split_arrived[k] = 0;
+  // Every wave holds the list's blocks (keys: what a block's rows see, rounded up to whole rows of it).
+  constexpr int kPer = kPfSorted / 64;
+  int2 rec[kPer];
+  int keys[kPer], parts[kPer];
+  const bool sorted = total <= kPfSorted;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    rec[u] = make_int2(0, 0);
+    keys[u] = -1;
+    parts[u] = 1;
+    if (sorted && u * 64 + lane < total) {   // (written by other threads of this kernel: read past the vector cache)
+      const int* p = reinterpret_cast<const int*>(a.items + u * 64 + lane);
+      rec[u].x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      rec[u].y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      keys[u] = a.q_pos0[rec[u].x] + ((rec[u].y & ~15) + (rec[u].y & 15) * 16) / a.R;
+    }
+  }
+  if (sorted && a.split_slots > 0) {
+    // Wave w estimates the time, in keys, with blocks divided into parts of at most kPfLens[w] even shares
+    // (wave 0: whole blocks): the longest item if all run at once, else an even share of
+    // all items and half an item.  An item costs 128 keys beside its own, a part 288 (measured: 6.6 and 14 us).
+    auto sum_all = [](float v) { return wave_allreduce(v, [](float x, float y) { return x + y; }); };
+    float all = 0.f;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) all += (float)max(keys[u], 0);
+    const float slots = (float)a.split_slots, share = sum_all(all) * (float)a.Hkv / slots;
+    auto divide = [&](int w) {
+      const float len = fmaxf((float)kPfMinPart, kPfLens[w] * share);
+#pragma unroll
+      for (int u = 0; u < kPer; ++u)
+        if (w > 0 && keys[u] > 0) parts[u] = min(kPfMaxDiv, (int)ceilf((float)keys[u] / len));
+    };
+    divide(wave);
+    float items = 0.f, in_parts = 0.f, work = 0.f, longest = 0.f;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (keys[u] >= 0) {
+        const float n = (float)parts[u], extra = parts[u] > 1 ? 288.f : 128.f;
+        items += n;
+        in_parts += parts[u] > 1 ? n : 0.f;
+        work += (float)keys[u] + n * extra;
+        longest = fmaxf(longest, (float)keys[u] / n + extra);
+      }
+    const float entries = sum_all(items);
+    items = entries * (float)a.Hkv;
+    in_parts = sum_all(in_parts) * (float)a.Hkv;
+    work = sum_all(work) * (float)a.Hkv;
+    longest = wave_allreduce(longest, [](float x, float y) { return fmaxf(x, y); });
+    const float time = items <= slots ? longest : fmaxf(longest, work / slots + 0.5f * work / items);
+    // (no more than the list and the partial results have room for; whole blocks unless 5 % are gained)
+    const bool fits = entries <= (float)kPfSorted && in_parts <= (float)kPfMaxParts;
+    if (lane == 0) estimate[wave] = wave == 0 ? 0.95f * time : fits ? time : INFINITY;
+    __syncthreads();
+    int best = 0;
+    for (int w = 1; w < kWavesPf; ++w)
+      if (estimate[w] < estimate[best]) best = w;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) parts[u] = 1;
+    divide(best);
+    if (best > 0) {
+      int n = 0;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) n += keys[u] >= 0 ? parts[u] : 0;
+      total = wave_allreduce(n, [](int x, int y) { return x + y; });
+    }
+  }
+  if (wave == 0 && sorted) {
     // counting sort over kPfClasses classes between the fewest and the most keys, in registers
-    constexpr int kPer = kPfSorted / 64;
-    int2 rec[kPer];
-    int keys[kPer];
     int lo = 0x7fffffff, hi = 0;
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      rec[u] = make_int2(0, 0);
-      keys[u] = -1;
-      if (u * 64 + lane < total) {   // (written by other threads of this kernel: read past the vector cache)
-        const int* p = reinterpret_cast<const int*>(a.items + u * 64 + lane);
-        rec[u].x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        rec[u].y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        keys[u] = a.q_pos0[rec[u].x] + ((rec[u].y & ~15) + (rec[u].y & 15) * 16) / a.R;
+    for (int u = 0; u < kPer; ++u)
+      if (keys[u] >= 0) {
+        keys[u] /= parts[u];
         lo = min(lo, keys[u]);
         hi = max(hi, keys[u]);
       }
-    }
     lo = wave_allreduce(lo, [](int x, int y) { return min(x, y); });
     hi = wave_allreduce(hi, [](int x, int y) { return max(x, y); });
     const int width = max(1, (hi - lo) / kPfClasses + 1);
     hist[lane] = 0;
 #pragma unroll
     for (int u = 0; u < kPer; ++u)
-      if (keys[u] >= 0) atomicAdd(&hist[(hi - keys[u]) / width], 1);
+      if (keys[u] >= 0) atomicAdd(&hist[(hi - keys[u]) / width], parts[u]);
     const int c = hist[lane];
     int inc = c;
 #pragma unroll
@@ -194,7 +271,18 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
     hist[lane] = inc - c;
 #pragma unroll
     for (int u = 0; u < kPer; ++u)
-      if (keys[u] >= 0) a.items[atomicAdd(&hist[(hi - keys[u]) / width], 1)] = rec[u];
+      if (keys[u] >= 0) {
+        const int at = atomicAdd(&hist[(hi - keys[u]) / width], parts[u]);
+        if (parts[u] == 1) {
+          a.items[at] = rec[u];
+        } else {
+          const int first_part = atomicAdd(&parts_used, parts[u]);
+          for (int k = 0; k < parts[u]; ++k) {
+            a.items[at + k] = make_int2(rec[u].x | kPfSplitBit, rec[u].y);
+            a.split_info[at + k] = (first_part << 8) | (k << 4) | (parts[u] - 1);
+          }
+        }
+      }
   }
   if (tid == 0) {
     a.block_start[a.NG] = total;
@@ -205,6 +293,7 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
 static_assert(kPfClasses == 64, "one class per lane in the scan");
 
 typedef const char __attribute__((address_space(1))) * GlobalBytes;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // Scalar load of element `at` of a wave-uniform array (scalar base + 32-bit offset).
 __device__ __forceinline__ int ld_uniform_at(const int32_t* p, uint32_t at) {
   const char __attribute__((address_space(4))) * base =
@@ -219,18 +308,21 @@ struct PfItem {
   int tok0, rem0;             // the block's first row = tok0 * R + rem0
   int qrow0, pos0;            // row of q and position of token tok0
   int tok_end;                // keys the block needs: 0 .. position of its last row
-  int nsteps, slots;          // key steps; slots of the ring it takes (at least kPfStages)
+  int step0, nsteps, slots;   // key steps step0 .. nsteps - 1; the slot of the ring behind its last (at least kPfStages after step0)
+  int split;                  // -1: all of the block's keys; else first part << 8 | this part << 4 | parts - 1
 };
 
 // x / R for 0 <= x < 65536 / 16 with inv_R = ceil(65536 / R): exact, since x (inv_R R - 65536) < 65536
 __device__ __forceinline__ int div_R(int x, int inv_R) { return (x * inv_R) >> 16; }
 
+template <bool kSplit>
 __device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
   PfItem it;
   const int block = qi / a.Hkv;
   it.kvh = qi - block * a.Hkv;
   const int32_t* rec = reinterpret_cast<const int32_t*>(a.items + block);
-  const int g = ld_uniform(rec), packed = ld_uniform(rec + 1);
+  const int g_rec = ld_uniform(rec), packed = ld_uniform(rec + 1);
+  const int g = kSplit ? g_rec & ~kPfSplitBit : g_rec;
   const int b = ld_uniform(a.q_start + g), e = ld_uniform(a.q_start + g + 1);
   const int pos0 = ld_uniform(a.q_pos0 + g);
   const int row_begin = packed & ~15;
@@ -243,12 +335,21 @@ __device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
   it.pos0 = pos0 + it.tok0;
   it.tok_end = it.pos0 + div_R(it.rem0 + it.rows - 1, a.inv_R) + 1;
   it.nsteps = (it.tok_end + kBlockTok - 1) / kBlockTok;
-  it.slots = max(it.nsteps, kPfStages);
+  it.step0 = 0;
+  it.split = -1;
+  if (kSplit && g_rec < 0) {
+    it.split = ld_uniform(a.split_info + block);
+    const uint32_t k = (it.split >> 4) & 15, parts = (it.split & 15) + 1, all = it.nsteps;
+    it.step0 = (int)(all * k / parts);
+    it.nsteps = (int)(all * (k + 1) / parts);
+  }
+  it.slots = max(it.nsteps, it.step0 + kPfStages);
   it.table_row = a.prefix_table + (size_t)g * a.max_pp;
   return it;
 }
 
 // The items of one workgroup, one after the other.
+template <bool kSplit>
 __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_work, PrefillLds& lds, int& bad_page) {
   constexpr int kLoads = 1024 / (kNW * 64);     // 16-byte loads per thread and step (16 KB per step)
   const int tid = threadIdx.x;
@@ -305,10 +406,10 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
   uint32_t id_max = 0;              // largest id seen: compared with the pool size once, at the end
   auto start_stream = [&](const PfItem& it) {
     st_table = it.table_row;
-    st_page = 0;
+    st_page = 2 * it.step0;
     st_last = (it.tok_end - 1) >> 4;
     st_first_of_last = 2 * (it.nsteps - 1);
-    st_left = it.slots;
+    st_left = it.slots - it.step0;
     st_kvh = it.kvh;
   };
   auto load_ids = [&] {
@@ -405,8 +506,7 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
         float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
                          fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
         mx = rows_allreduce_max(mx);
-        // every row sees token 0, so after step 0 the reference maximum is finite and a fully masked
-        // row of a later step gives alpha = 1, p = 0; the reference moves only when the row's maximum
+        // the reference maximum is finite, so a fully masked row gives alpha = 1, p = 0; it moves only when the row's maximum
         // exceeds it by more than 2^kPfRescaleSlack (as in the loop before the edge)
         const float m_new = mx * sc > m_run[qt] + kPfRescaleSlack ? mx * sc : m_run[qt];
         const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
@@ -522,10 +622,10 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
   // landed and everybody has finished reading the slot before; a fence would wait for every
   // outstanding load), then the loads of the slot kPfStages-1 ahead, which may be the next item's.
   // An item takes at least kPfStages slots, so what is ahead is never further than the next item.
-  PfItem cur = read_item(a, blockIdx.x);
+  PfItem cur = read_item<kSplit>(a, blockIdx.x);
   const int second = blockIdx.x + gridDim.x;
   bool more = second < n_work;                                // workgroup-uniform: there is a next item
-  PfItem nxt = more ? read_item(a, second) : cur;             // (without one its slots are never used)
+  PfItem nxt = more ? read_item<kSplit>(a, second) : cur;             // (without one its slots are never used)
   auto draw = [&] { return tid == 0 ? 2 * (int)gridDim.x + atomicAdd(&a.counters[kPfCursor], 1) : 0; };
   int drawn = draw();                                         // (thread 0 only) the item after the next one
   uint32_t ring = 0;                   // byte offset of the current slot's buffer
@@ -554,7 +654,8 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
     __builtin_amdgcn_s_waitcnt(pf_lgkmcnt0);
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
-      m_run[qt] = -INFINITY;
+      // (finite: a row that sees no key of a part keeps it, with weights exp2(-inf) = 0)
+      m_run[qt] = -3.402823466e38f;
       l_run[qt] = 0.f;
 #pragma unroll
       for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -577,7 +678,7 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) all_tiles = all_tiles && (qt * kNW + wave) * 16 < cur.rows;
     const int n_full = all_tiles ? min(tile_lo[0] / kBlockTok, cur.nsteps) : 0;
-    int n = 0;
+    int n = cur.step0;
     for (; n < n_full; ++n) ring_step(compute_full);
     if (n < cur.nsteps) {
       int limit[kMT];
@@ -598,6 +699,58 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
     // lines, 16 bytes per lane.  16-byte units of a row are XOR-ed with the row against bank conflicts;
     // the lanes of a row then read its units in that order.  (256 prompts: 2 % of the whole.)
     const int l2 = opaque_lane();
+    // A part of a block's keys: its sums go to memory in the layout of the registers; the workgroup that
+    // finds all parts there adds them in their order and writes the rows (nobody waits for another).
+    // Stores and loads of the sums carry the device scope (sc1: past the caches that are not shared), and a
+    // workgroup counts itself in when its stores are acknowledged.  (With fences, which write back and
+    // invalidate caches as a whole, the six chunks took 0.49 ms.)
+    bool write_rows = true;
+    if (kSplit && cur.split >= 0) {                                    // workgroup-uniform
+      const int first = cur.split >> 8, parts = (cur.split & 15) + 1;
+      constexpr int kSc1 = 16;
+      const auto rs_o = __builtin_amdgcn_make_buffer_rsrc(a.split_o, 0, a.split_bytes, 0x27000);
+      // a part's bytes: per wave kMT x 8 fragments of 64 x 16 bytes, then kMT x 64 (maximum, sum)
+      constexpr int kWaveBytes = kMT * (8 * 64 * 16 + 64 * 8);
+      auto part_at = [&](int k) { return (((first + k) * a.Hkv + cur.kvh) * kNW + wave) * kWaveBytes; };
+      {
+        const int at = part_at((cur.split >> 4) & 15);
+#pragma unroll
+        for (int qt = 0; qt < kMT; ++qt) {
+#pragma unroll
+          for (int ct = 0; ct < 8; ++ct)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[qt][ct]), rs_o, l2 * 16 + (qt * 8 + ct) * 1024, at, kSc1);
+          __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(m_run[qt]), __float_as_uint(l_run[qt])}, rs_o,
+                                                l2 * 8 + kMT * 8192 + qt * 512, at, kSc1);
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm(0));
+      __syncthreads();
+      if (tid == 0) lds.arrived = __hip_atomic_fetch_add(a.split_arrived + first * a.Hkv + cur.kvh, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __syncthreads();
+      write_rows = __builtin_amdgcn_readfirstlane(lds.arrived) == parts - 1;
+      if (write_rows) {
+#pragma unroll
+        for (int qt = 0; qt < kMT; ++qt) {
+          auto ml_of = [&](int k) { return __builtin_amdgcn_raw_buffer_load_b64(rs_o, l2 * 8 + kMT * 8192 + qt * 512, part_at(k), kSc1); };
+          float m = -3.402823466e38f;
+          for (int k = 0; k < parts; ++k) m = fmaxf(m, __uint_as_float(ml_of(k)[0]));
+          l_run[qt] = 0.f;
+#pragma unroll
+          for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int k = 0; k < parts; ++k) {
+            const u32x2 ml = ml_of(k);
+            u32x4 o[8];
+#pragma unroll
+            for (int ct = 0; ct < 8; ++ct) o[ct] = __builtin_amdgcn_raw_buffer_load_b128(rs_o, l2 * 16 + (qt * 8 + ct) * 1024, part_at(k), kSc1);
+            const float f = __builtin_amdgcn_exp2f(__uint_as_float(ml[0]) - m);
+            l_run[qt] = __builtin_fmaf(__uint_as_float(ml[1]), f, l_run[qt]);
+#pragma unroll
+            for (int ct = 0; ct < 8; ++ct) acc[qt][ct] += __builtin_bit_cast(f32x4, o[ct]) * f;
+          }
+        }
+      }
+    }
+    if (write_rows)
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
       const float inv = 1.0f / rows_allreduce_sum(l_run[qt]);   // a row's sum >= 1: its own maximum contributes exp2(0)
@@ -635,20 +788,21 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
     if (!more) break;
     cur = nxt;
     more = after_next < n_work;
-    if (more) nxt = read_item(a, after_next);
+    if (more) nxt = read_item<kSplit>(a, after_next);
   }
   if (id_max >= (uint32_t)a.num_pages) bad_page = 1;
   __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm(0));   // (the last slots' loads write to LDS: not past the kernel's end)
 }
 
 static_assert(sizeof(PrefillLds) <= 80 * 1024, "two workgroups share a CU's 160 KB");
+template <bool kSplit>
 __global__ __launch_bounds__(kPfThreads)
 __attribute__((amdgpu_waves_per_eu(MARL_PREFILL_WAVES_PER_EU, MARL_PREFILL_WAVES_PER_EU)))
-void prefill_kernel(PrefillArgs a) {
+void prefill_kernel(PrefillArgs a) {   // kSplit: the list may hold parts of blocks
   __shared__ PrefillLds lds;
   const int n_work = a.block_start[a.NG] * a.Hkv;
   int bad_page = 0;
-  if ((int)blockIdx.x < n_work) prefill_items(a, n_work, lds, bad_page);
+  if ((int)blockIdx.x < n_work) prefill_items<kSplit>(a, n_work, lds, bad_page);
   if (bad_page) atomicOr(&a.counters[kPfFlags], MARL_FLAG_BAD_PAGE);
 }
 
@@ -717,9 +871,18 @@ __global__ __launch_bounds__(kD) void kv_write_prompt_kernel(PrefillArgs a) {
 
 int prefill_rows_per_block() { return kQB; }
 
+PrefillSplitLayout prefill_split_layout(long max_blocks, long Hkv, long max_keys) {
+  PrefillSplitLayout L = {};
+  if (max_blocks > kPfSorted || max_keys <= kPfMinPart) return L;
+  L.entries = kPfSorted;
+  L.parts = (int)std::min<long>(kPfMaxParts, max_blocks * kPfMaxDiv * std::min<long>(Hkv, kPfMaxParts));
+  L.bytes = (size_t)L.parts * kNW * kMT * 64 * (sizeof(float2) + 8 * sizeof(f32x4));   // (about 100 MB at most)
+  return L;
+}
+
 int prefill_blocks_per_cu() {
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, prefill_kernel, kPfThreads, 0) != hipSuccess || n < 1) n = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, prefill_kernel<true>, kPfThreads, 0) != hipSuccess || n < 1) n = 1;
   return n;
 }
 
@@ -727,7 +890,8 @@ hipError_t launch_prefill(const PrefillArgs& a, int grid, hipStream_t st) {
   hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreadsPf), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(prefill_kernel, dim3(grid), dim3(kPfThreads), 0, st, a);
+  if (a.split_slots > 0) hipLaunchKernelGGL(prefill_kernel<true>, dim3(grid), dim3(kPfThreads), 0, st, a);
+  else hipLaunchKernelGGL(prefill_kernel<false>, dim3(grid), dim3(kPfThreads), 0, st, a);
   return hipGetLastError();
 }
 
