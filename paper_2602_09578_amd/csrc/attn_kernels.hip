@@ -798,6 +798,10 @@ constexpr int kEager = 4;   // partials fetched up front
 
 __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void merge_kernel(AttnArgs a) {
+  // (the row's chunk counts are requested before the short items: most workgroups have none of these, and
+  // where every row is finished with them a workgroup is one load long instead of two)
+  const int row = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 5);
+  const int info = row < a.NS * a.Hq ? a.seq_chunks[row / a.Hq] : 0x10000;
   // first the sequences whose own tokens are one short item: attention over those tokens and
   // the merge with the group's prefix partials in one go, one item per wave
   {
@@ -806,10 +810,6 @@ void merge_kernel(AttnArgs a) {
     if (bad_page) atomicOr(&a.counters[MARL_CTR_FLAGS], MARL_FLAG_BAD_PAGE);
   }
   const int sub = threadIdx.x & 31;   // lane within the half wave: channels 4*sub .. 4*sub+3
-  const int row = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 5);
-  if (row >= a.NS * a.Hq) return;
-  const int s = row / a.Hq;
-  const int info = a.seq_chunks[s];
   const int npc = info & 0xffff, nsc = info >> 16;
   // a sequence whose own tokens are one item was finished where that item was processed: above
   // (at most kShortTokens tokens) or in the suffix kernel
