@@ -673,6 +673,7 @@ int marl_prefill_attn(const marl_prefill_shape* shape, void* workspace, size_t w
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_fail(e, "device query");
   long grid = (long)cus * marl::prefill_blocks_per_cu();
+  a.slots = (int32_t)grid;
   long max_entries = prefill_max_blocks(shape);
   const marl::PrefillSplitLayout L = prefill_split(shape);
   if (L.entries > 0 && workspace_bytes >= prefill_full_ws_bytes(shape)) {

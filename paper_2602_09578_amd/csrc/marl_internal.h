@@ -145,7 +145,8 @@ struct PrefillArgs {
   int32_t* flags;
   int32_t NT, NG, Hq, Hkv, R, num_pages, max_pp, out_dtype, max_blocks;
   int32_t inv_R;                // ceil(65536 / R)
-  int32_t split_slots;          // workgroups that run at the same time
+  int32_t slots;                // workgroups that run at the same time
+  int32_t split_slots;          // the same where there is room for parts, else 0
   int32_t split_bytes;          // of split_o
   float scale;
 };

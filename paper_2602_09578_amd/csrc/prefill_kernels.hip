@@ -22,7 +22,7 @@
 //
 // Work distribution: a one-workgroup plan kernel lists the row blocks group after group, inside a
 // group last-first (most keys first), so that blocks of a group run at the same time and its keys come
-// out of the caches; a list of at most kPfSorted blocks is put into falling order of cost instead
+// out of the caches; a list of at most kPfSorted blocks, but more items than workgroups, is put into falling order of cost instead
 // (so few items end evenly only if the long ones start first: 494 blocks x 4 heads of 47 short prompts
 // would take 1.20 times their even share, sorted 1.04).  Item i = (block i / Hkv, KV head i % Hkv); a
 // workgroup starts with the items b and b + G and draws every further one from a counter two items
@@ -33,9 +33,9 @@
 // whatever their order.  For a sorted list the plan kernel therefore weighs dividing long blocks along their
 // keys: a part's sums (float32, unnormalised) go to the workspace, and the workgroup that arrives last at a
 // block adds the parts.  Whole and divided: one chunk of 512 tokens behind 8192, 64 / 8 heads 220 -> 180 us,
-// 28 / 4 heads 255 -> 100 us; three chunks behind up to 6.6 k, 64 / 8 heads 229 -> 175 us; 64 tokens behind 2000 69 -> 42 us;
-// one prompt of 2048 tokens, 28 / 4 heads 79 -> 69 us; 9 chunks 340 -> 280 us.  Lists with more work than that stay
-// whole (12 and 16 chunks, 260 and 555 us either way), as does everything in this kernel's instance
+// 28 / 4 heads 255 -> 100 us; three chunks behind up to 6.6 k, 64 / 8 heads 229 -> 175 us; 64 tokens behind 2000 66 -> 40 us;
+// one prompt of 2048 tokens, 28 / 4 heads 79 -> 70 us; 9 chunks 340 -> 280 us.  Lists with more work than that stay
+// whole (12 and 16 chunks, 260 and 540 us either way), as does everything in this kernel's instance
 // without parts (a few scalar registers less; for shapes whose lists are not sorted).
 // A workspace with room for the list alone is served with whole blocks.
 //
@@ -113,6 +113,7 @@ __device__ __forceinline__ int2 pack_item(int g, int row_begin, int qb) { return
 constexpr int kPfSorted = 512;    // a list of at most so many entries is sorted
 constexpr int kPfClasses = 64;    // cost classes of that order
 constexpr int kPfMaxDiv = 16;     // most parts of one block's keys (four bits of a list record)
+constexpr int kPfLongKeys = 960;  // keys: a list of shorter blocks stays whole (820 keys each, 228 items: 38 us, divided 47; 1000 keys: 43.8 and 42)
 constexpr int kPfMinPart = 512;   // keys: no part is meant to be shorter
 // lengths of parts that are considered, in even shares of a workgroup
 __constant__ constexpr float kPfLens[16] = {0.f, 0.5f, 0.625f, 0.75f, 0.875f, 1.f, 1.125f, 1.25f, 1.5f, 1.75f, 2.f, 2.5f, 3.f, 4.f, 6.f, 8.f};
@@ -122,11 +123,13 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
   constexpr int kWavesPf = kPlanThreadsPf / 64;
   __shared__ long long wave_sum[kWavesPf];   // 64-bit: inconsistent inputs must not wrap the sums
   __shared__ int hist[kPfClasses];
-  __shared__ int flags_all, end_all, parts_used;
+  __shared__ int2 list[kPfSorted];     // the first blocks and their groups' q_pos0: a short list never goes through memory
+  __shared__ int list_pos0[kPfSorted];
+  __shared__ int flags_all, end_all, parts_used, most_keys;
   __shared__ float estimate[kWavesPf];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int flag = 0;
-  if (tid == 0) flags_all = end_all = parts_used = 0;
+  if (tid == 0) flags_all = end_all = parts_used = most_keys = 0;
   __syncthreads();
   long long carry = 0;
   for (int g0 = 0; g0 < a.NG; g0 += kPlanThreadsPf) {
@@ -162,43 +165,55 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
       } else {
         first = (int)first64;
         atomicMax(&end_all, first + nb);
+        if (nb) atomicMax(&most_keys, a.q_pos0[g] + (int)(nrows / a.R));
       }
       a.block_start[g] = first;
       // the group's blocks, last (most keys) first
       const int qb = block_rows(nrows);
-      for (int k = 0; k < nb; ++k) a.items[first + k] = pack_item(g, (nb - 1 - k) * qb, qb);
+      for (int k = 0; k < nb; ++k) {
+        const int2 rec = pack_item(g, (nb - 1 - k) * qb, qb);
+        if (first + k < kPfSorted) {
+          list[first + k] = rec;
+          list_pos0[first + k] = a.q_pos0[g];
+        } else {
+          a.items[first + k] = rec;
+        }
+      }
     }
     carry += all;
     __syncthreads();
   }
   if (flag) atomicOr(&flags_all, flag);
-  __threadfence();
   __syncthreads();
   // The accepted groups' blocks are exactly [0, end_all).
   int total = end_all;   // (then entries of the list)
-  if (a.split_slots > 0)
-    for (int k = tid; k < kPfMaxParts; k += kPlanThreadsPf) a.split_arrived[k] = 0;
+  // A list of at most one item per workgroup needs no order; blocks of up to kPfLongKeys keys are not divided.
+  const bool weigh = total <= kPfSorted && a.split_slots > 0 && most_keys > kPfLongKeys;
+  const bool sorted = total <= kPfSorted && (weigh || (long)total * a.Hkv > a.slots);
+  if (!sorted)
+    for (int k = tid; k < min(total, kPfSorted); k += kPlanThreadsPf) a.items[k] = list[k];
   // Every wave holds the list's blocks (keys: what a block's rows see, rounded up to whole rows of it).
   constexpr int kPer = kPfSorted / 64;
   int2 rec[kPer];
   int keys[kPer], parts[kPer];
-  const bool sorted = total <= kPfSorted;
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
     rec[u] = make_int2(0, 0);
     keys[u] = -1;
     parts[u] = 1;
-    if (sorted && u * 64 + lane < total) {   // (written by other threads of this kernel: read past the vector cache)
-      const int* p = reinterpret_cast<const int*>(a.items + u * 64 + lane);
-      rec[u].x = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      rec[u].y = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      keys[u] = a.q_pos0[rec[u].x] + ((rec[u].y & ~15) + (rec[u].y & 15) * 16) / a.R;
+    if (sorted && u * 64 + lane < total) {
+      rec[u] = list[u * 64 + lane];
+      keys[u] = list_pos0[u * 64 + lane] + ((rec[u].y & ~15) + (rec[u].y & 15) * 16) / a.R;
     }
   }
-  if (sorted && a.split_slots > 0) {
+  if (weigh) {
+    for (int k = tid; k < kPfMaxParts; k += kPlanThreadsPf) a.split_arrived[k] = 0;
     // Wave w estimates the time, in keys, with blocks divided into parts of at most kPfLens[w] even shares
     // (wave 0: whole blocks): the longest item if all run at once, else an even share of
-    // all items and half an item.  An item costs 128 keys beside its own, a part 288 (measured: 6.6 and 14 us).
+    // all items and half an item.  An item costs 128 keys beside its own, a part 228, and a part's sums
+    // written and read back 1.1 keys of everybody's time (200 KB at 4 TB/s); 0.4 in lists that take several
+    // rounds also whole, whose other items run meanwhile (with 0.4 everywhere one prompt of 2048 tokens, 28 / 4
+    // heads, took 80 us instead of 70, with 1.1 the six chunks 387 instead of 382).
     auto sum_all = [](float v) { return wave_allreduce(v, [](float x, float y) { return x + y; }); };
     float all = 0.f;
 #pragma unroll
@@ -215,7 +230,7 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
 #pragma unroll
     for (int u = 0; u < kPer; ++u)
       if (keys[u] >= 0) {
-        const float n = (float)parts[u], extra = parts[u] > 1 ? 288.f : 128.f;
+        const float n = (float)parts[u], extra = parts[u] > 1 ? 228.f : 128.f;
         items += n;
         in_parts += parts[u] > 1 ? n : 0.f;
         work += (float)keys[u] + n * extra;
@@ -226,10 +241,11 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
     in_parts = sum_all(in_parts) * (float)a.Hkv;
     work = sum_all(work) * (float)a.Hkv;
     longest = wave_allreduce(longest, [](float x, float y) { return fmaxf(x, y); });
-    const float time = items <= slots ? longest : fmaxf(longest, work / slots + 0.5f * work / items);
-    // (no more than the list and the partial results have room for; whole blocks unless 5 % are gained)
+    const bool rounds = (long)total * a.Hkv > a.split_slots;
+    const float time = (items <= slots ? longest : fmaxf(longest, work / slots + 0.5f * work / items)) + (rounds ? 0.4f : 1.1f) * in_parts;
+    // (no more than the list and the partial results have room for; whole blocks unless 3 % of such a list's time, else 7 %, are gained)
     const bool fits = entries <= (float)kPfSorted && in_parts <= (float)kPfMaxParts;
-    if (lane == 0) estimate[wave] = wave == 0 ? 0.95f * time : fits ? time : INFINITY;
+    if (lane == 0) estimate[wave] = wave == 0 ? (rounds ? 0.97f : 0.93f) * time : fits ? time : INFINITY;
     __syncthreads();
     int best = 0;
     for (int w = 1; w < kWavesPf; ++w)

@@ -271,7 +271,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
 // tokens at the threshold value": the kernel finds the threshold with exact counts per value
 // instead of sorting 150 k tokens.
 //
-// One workgroup of 512 threads owns a row, two of them share a CU.  The row is cut into groups of
+// One workgroup of 512 threads owns a row, three of them share a CU.  The row is cut into groups of
 // 2048 tokens, group k * 8 + w belongs to wave w.  Passes over the row:
 //   1. maximum value and Z = sum 2^(y - M)  (running (max, sum) per thread, fixed-order merge);
 //   2. short list: the mass of the unlikely tokens is estimated from a sample of the row (it is made
@@ -282,15 +282,15 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
 //      top_p * Z.  The cut only decides what is looked at: counts above it are complete, so a
 //      threshold found in the list is THE threshold.  If none is found (the estimate was too high),
 //      the list would be too long or the cut is not positive, the counts are taken of the whole row
-//      instead, over windows of 16384 values from the maximum down;
+//      instead, over windows of 8192 values from the maximum down;
 //   3. per group the nucleus mass and the number of threshold-value tokens (from the list, else one
 //      more pass over the row); a scan over the group sums finds the group in which the scaled
 //      uniform is passed, a workgroup scan over the group's 2048 tokens finds the token.
 // What bounds it: the vector ALU.  An instruction on 64 lanes takes 4 cycles of a SIMD, v_exp_f32 16;
 // pass 1 is 7 of the 4-cycle units per logit, the list pass 3.5, and ten would fill the time in
 // which the row arrives from HBM.  The second read of the row comes out of the memory-side cache
-// (two rows per CU, 156 MB of 256 at a vocabulary of 152064).  Measured on 2048 x 152064, sigma 3,
-// top_p 0.9: 205 us; with the row held in registers by one workgroup per CU, a count of all values in
+// (three rows per CU, 234 MB of 256 at a vocabulary of 152064).  Measured on 2048 x 152064, sigma 3,
+// top_p 0.9: 196 us (two workgroups per CU 212); with the row held in registers by one workgroup per CU, a count of all values in
 // LDS (an LDS atomic on 64 lanes takes about 25 cycles) and a third pass over all tokens 508 us; the
 // same with the list but still in registers 316 us (nothing to overlap the short phases with).
 // ---------------------------------------------------------------------------------------

@@ -281,11 +281,10 @@ def test_rows_per_token(R):
     check(inp, B.MARL_OUT_BF16)
 
 
-@pytest.mark.parametrize("Hq,Hkv,chunks,context", [(1, 1, [700], [0]), (8, 1, [100], [3000]), (16, 1, [30], [9000]),
+@pytest.mark.parametrize("Hq,Hkv,chunks,context", [(1, 1, [1300], [0]), (8, 1, [100], [3000]), (16, 1, [30], [9000]),
                                                    (14, 2, [200, 33, 1], [1500, 40, 511])])
 def test_few_long_items_are_divided_along_their_keys(Hq, Hkv, chunks, context):
-    """Blocks of up to 16 parts (a block of the first case has rows that see no key of its last part; the last
-    mixes divided and whole blocks).  The parts are added in their order whoever finishes last: runs agree bit
+    """Blocks of up to 16 parts; the first and the last case mix divided and whole blocks.  The parts are added in their order whoever finishes last: runs agree bit
     for bit.  A workspace with room for the list alone gives the same results from whole blocks."""
     print("case: prefill parts", Hq, Hkv, chunks, context, flush=True)
     inp = I.build_prefill_inputs(Hq, Hkv, chunks, context, seed=Hq)
@@ -296,6 +295,9 @@ def test_few_long_items_are_divided_along_their_keys(Hq, Hkv, chunks, context):
     first = B.run_prefill(dev, shape, ws, out).clone()
     for _ in range(3):
         assert torch.equal(B.run_prefill(dev, shape, ws, out.zero_()), first)
+    entries = lambda: int(ws[256:512].view(torch.int32)[len(chunks)])   # of the list, behind the header
+    divided = entries()
     whole = B.run_prefill(dev, shape, ws[:4096], out.zero_())   # 256 header + 256 starts + 8 bytes for each block
+    assert divided > entries()
     want, want_abs = reference(inp)
     assert (np.abs(whole.cpu().numpy() - want) <= 1e-3 + 2.0 ** -8 * want_abs).all()
