@@ -642,7 +642,10 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
   const int second = blockIdx.x + gridDim.x;
   bool more = second < n_work;                                // workgroup-uniform: there is a next item
   PfItem nxt = more ? read_item<kSplit>(a, second) : cur;             // (without one its slots are never used)
-  auto draw = [&] { return tid == 0 ? 2 * (int)gridDim.x + atomicAdd(&a.counters[kPfCursor], 1) : 0; };
+  // (a list of at most two items per workgroup has none to draw: the counter, asked by all workgroups at once,
+  // would only delay their first items: 472 items 48.2 -> 43.4 us, 608 items 44.9 -> 40.3 us)
+  const bool any_drawn = n_work > 2 * (int)gridDim.x;
+  auto draw = [&] { return 2 * (int)gridDim.x + (any_drawn && tid == 0 ? atomicAdd(&a.counters[kPfCursor], 1) : 0); };
   int drawn = draw();                                         // (thread 0 only) the item after the next one
   uint32_t ring = 0;                   // byte offset of the current slot's buffer
   constexpr uint32_t kRingBytes = kPfStages * kPfStepBytes;
