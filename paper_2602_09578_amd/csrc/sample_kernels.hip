@@ -8,7 +8,9 @@
 // Pass 2 (one wave per row, re-reads 8 KB): an ordered scan over the chunk sums finds the chunk
 //   in which the cumulative probability passes u, an ordered scan inside that chunk finds the
 //   token.  Token = first t with sum_{v <= t} p_v > u; if rounding leaves none, the last token
-//   with non-zero probability.
+//   with non-zero probability.  The running sums of a scan are associated differently from lane to
+//   lane, so a lane without mass (masked tokens, positions past the end) can be the first whose sum
+//   passes: only chunks, lanes and tokens that have mass are ever taken.
 #include <type_traits>
 
 #include "marl_internal.h"
@@ -19,6 +21,9 @@ namespace {
 
 constexpr int kChunk = 4096;          // logits per wave chunk: 8 iterations x 64 lanes x 8
 constexpr int kIters = kChunk / 512;
+// A chunk of less mass than this, relative to the row's largest weight, holds no token that can be drawn: a sum of
+// up to 4096 weights above it has one of at least 2^-124, which is not flushed to zero where weights are formed again.
+constexpr double kLeastMass = 0x1p-112;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef u32x4 u32x4_any __attribute__((aligned(2)));   // 16-byte access at any element (the GPU's global loads take any alignment)
 
@@ -166,16 +171,17 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   for (int base = 0; base < a.num_chunks; base += 64)   // fixed order: tiles of 64 chunks
     total += from_lane(wave_inclusive_scan(chunk_mass(base)), 63);
   const double target = (double)u * total;
+  const double least = kLeastMass * fmin(total, 1.0);
   // the chunk in which the running sum passes the target
   double before = 0.0;
   bool take_last = false;
   int chunk = -1, last_nonzero = -1;
   for (int base = 0; base < a.num_chunks && chunk < 0; base += 64) {
-    const int k = base + lane;
     const double v = chunk_mass(base);
     const double cum = before + wave_inclusive_scan(v);
-    const unsigned long long hit = __builtin_amdgcn_ballot_w64(k < a.num_chunks && cum > target);
-    const unsigned long long nz = __builtin_amdgcn_ballot_w64(v > 0.0);
+    const bool some = v > least;
+    const unsigned long long hit = __builtin_amdgcn_ballot_w64(some && cum > target);
+    const unsigned long long nz = __builtin_amdgcn_ballot_w64(some);
     if (nz) last_nonzero = base + 63 - __builtin_clzll(nz);
     if (hit) {
       const int l = __builtin_ctzll(hit);
@@ -195,15 +201,17 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   u32x4 words[kIters];
 #pragma unroll
   for (int it = 0; it < kIters; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
+  // y relative to the row's maximum and the weight 2^y of 8 logits, the same each time they are formed
+  const float ms = M == -INFINITY ? 0.f : M;
   auto weights = [&](u32x4 v, float (&y)[8], float (&w)[8]) {
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      y[2 * d] = __uint_as_float(v[d] << 16) * c;
-      y[2 * d + 1] = __uint_as_float(v[d] & 0xffff0000u) * c;
+      y[2 * d] = __builtin_fmaf(__uint_as_float(v[d] << 16), c, -ms);
+      y[2 * d + 1] = __builtin_fmaf(__uint_as_float(v[d] & 0xffff0000u), c, -ms);
     }
     float s = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { w[e] = ex2_diff(y[e], M); s += w[e]; }
+    for (int e = 0; e < 8; ++e) { w[e] = ex2(y[e]); s += w[e]; }
     return s;
   };
   // the piece of 512 tokens in which the running sum passes (`at`), else the last one with any mass
@@ -216,7 +224,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
     const float cum = run + wave_inclusive_scan(s);
     if (at < 0) {   // wave-uniform
       if (__builtin_amdgcn_ballot_w64(s > 0.f)) last = it;
-      if (__builtin_amdgcn_ballot_w64(cum > want)) { at = it; cum_at = cum; }
+      if (__builtin_amdgcn_ballot_w64(s > 0.f && cum > want)) { at = it; cum_at = cum; }
     }
     run = from_lane(cum, 63);
   }
@@ -229,21 +237,17 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
     for (int it = 1; it < kIters; ++it) v = it == piece ? words[it] : v;
     float y[8], w[8];
     const float s = weights(v, y, w);
-    int e_pick = 0, l;
-    if (at >= 0) {
-      l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(cum_at > want));
-      float acc = cum_at - s;     // mass before this lane's 8 logits
-      e_pick = 7;
-      bool found = false;
+    // the lane's first token with mass that passes; if rounding leaves none (or no lane passed), its last one
+    const unsigned long long mass = __builtin_amdgcn_ballot_w64(s > 0.f);
+    const unsigned long long hit = __builtin_amdgcn_ballot_w64(s > 0.f && cum_at > want);
+    const int l = at >= 0 ? __builtin_ctzll(hit) : 63 - __builtin_clzll(mass);
+    float acc = at >= 0 ? cum_at - s : -INFINITY;     // mass before this lane's 8 logits
+    int e_pick = 0;
+    bool found = false;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        acc += w[e];
-        if (!found && acc > want) { e_pick = e; found = true; }
-      }
-    } else {                      // the last token with non-zero probability
-      l = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(s > 0.f));
-#pragma unroll
-      for (int e = 0; e < 8; ++e) if (w[e] > 0.f) e_pick = e;
+    for (int e = 0; e < 8; ++e) {
+      acc += w[e];
+      if (!found && w[e] > 0.f) { e_pick = e; found = acc > want; }
     }
     float ysel = y[0];
 #pragma unroll
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
       a.out_logprobs[row] = __uint_as_float(0x7fc00000u);
     } else {
       a.out_tokens[row] = tok;
-      a.out_logprobs[row] = (y_tok - (M + __builtin_amdgcn_logf((float)total))) * 0.69314718055994530942f;
+      a.out_logprobs[row] = (y_tok - __builtin_amdgcn_logf((float)total)) * 0.69314718055994530942f;
     }
   }
 }

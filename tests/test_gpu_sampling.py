@@ -102,3 +102,24 @@ def test_one_and_several_rounds_of_chunk_sums(vocab):
     first and the last piece of its chunk, rows at every alignment."""
     print("case: sampling chunks", vocab, flush=True)
     check(I.build_logprob_inputs(4, vocab, 3.0, vocab), np.array([0.0, 0.31, 0.77, np.nextafter(np.float32(1), np.float32(0))]))
+
+
+@pytest.mark.parametrize("vocab", [37, 4099, 20481, 152065])
+def test_only_possible_tokens_are_drawn(vocab):
+    """Most of a row masked and a vocabulary that ends inside a chunk, with uniforms where the running
+    float32 sums may first pass the target at a lane without any mass: just below 1, and on steps of the
+    CDF.  check() asserts that the token exists and has non-zero probability."""
+    print("case: sampling masked", vocab, flush=True)
+    rows = 192
+    rng = np.random.default_rng(vocab)
+    x = (rng.standard_normal((rows, vocab)) * 3).astype(np.float32)
+    x[rng.random((rows, vocab)) < 0.6] = -np.inf
+    x[:, vocab // 2] = 1.0                                  # (no row without a token)
+    x[::2, vocab - vocab // 5:] = -np.inf                   # a masked tail on every other row
+    logits = torch.from_numpy(x).to(torch.bfloat16)
+    bits = I.bf16_bits(logits)
+    u = np.full(rows, 1.0 - 2.0 ** -24)
+    for r in range(rows // 3, rows):
+        p, cdf = ref.softmax_cdf(bits[r], 1.0)
+        u[r] = min(float(np.float32(rng.choice(cdf[p > 0]))), 1.0 - 2.0 ** -24)
+    check(I.LogprobInputs(logits, torch.zeros(rows, dtype=torch.int32), 1.0), u)
