@@ -658,7 +658,9 @@ void sample_top_p_kernel(TopPArgs a) {
     // Counts of the whole row over a window of values.  First the window that starts at the estimated
     // cut: the mass of the values above it is summed in the same pass, so one pass is enough unless the
     // threshold lies outside; then the windows from the maximum down.
-    auto count_window = [&](int hi, int lo, float x_hi, double& above) {   // above: mass of the values > x_hi
+    // x_above: the smallest value above the window (one key further up: not every pattern is a value of its own,
+    // the one below +0 is -0), `above`: the mass from it on; +inf where nothing lies above
+    auto count_window = [&](int hi, int lo, float x_above, double& above) {
       __syncthreads();                        // what this memory held before has been read
       for (int i = tid; i < kWin; i += kTpThreads) sh.hist[i] = 0;
       __syncthreads();
@@ -671,9 +673,9 @@ void sample_top_p_kernel(TopPArgs a) {
 #pragma unroll
           for (int d = 0; d < 4; ++d) {
             const float r0 = lo_val(v[j][d]), r1 = hi_val(v[j][d]);
-            if (x_hi < xmax) {   // workgroup-uniform
-              s[d] += r0 > x_hi ? ex2(__builtin_fmaf(r0, c, -M)) : 0.f;
-              s[d] += r1 > x_hi ? ex2(__builtin_fmaf(r1, c, -M)) : 0.f;
+            if (x_above <= xmax) {   // workgroup-uniform
+              s[d] += r0 >= x_above ? ex2(__builtin_fmaf(r0, c, -M)) : 0.f;
+              s[d] += r1 >= x_above ? ex2(__builtin_fmaf(r1, c, -M)) : 0.f;
             }
             const int k0 = key_of(v[j][d] & 0xffffu), k1 = key_of(v[j][d] >> 16);
             if ((unsigned)(k0 - lo_eff) <= span) atomicAdd(&sh.hist[k0 - lo], 1u);
@@ -687,14 +689,14 @@ void sample_top_p_kernel(TopPArgs a) {
     if (cut_key > kLowestKey && cut_key + kWin <= kmax) {
       const int hi = cut_key + kWin - 1;
       double mine = 0.0, above;
-      count_window(hi, cut_key, value_of_key(hi), mine);
+      count_window(hi, cut_key, value_of_key(hi + 1), mine);
       block_excl_scan_d(mine, above, sh);
       if (above < tau) found = find_threshold(sh.hist, hi, cut_key, kWin, tau, above, weight, sh);
     }
     double above = 0.0;                       // mass of the values above the window
     for (int hi = kmax; hi >= kLowestKey && !found; hi -= kWin) {
       double none = 0.0;
-      count_window(hi, hi - (kWin - 1), xmax, none);
+      count_window(hi, hi - (kWin - 1), INFINITY, none);
       found = find_threshold(sh.hist, hi, hi - (kWin - 1), kWin, tau, above, weight, sh);
     }
   }

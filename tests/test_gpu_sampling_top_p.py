@@ -175,3 +175,20 @@ def test_longest_row_with_a_list(V):
     print("case: top-p list limit", V, flush=True)
     rng = np.random.default_rng(V)
     check(_route_rows("normal", V, rng)[:2], np.array([0.3, 0.8]), 0.7, 0.9)
+
+
+@pytest.mark.parametrize("top_p", [0.98, 0.983, 0.986])
+def test_threshold_just_below_zero(top_p):
+    """Logits and a temperature near 1e-19, one logit in 500 exactly +0 or -0, the threshold value
+    negative: over the rows (equal shapes whose maxima lie 2^-72 apart) the estimated cut passes the value at
+    which a window of 8192 values ends right below zero, so that the zeros are what lies above it."""
+    print("case: top-p window below zero", top_p, flush=True)
+    L, V, rows = 2.0 ** -63, 20481, 256
+    rng = np.random.default_rng(17)
+    x = np.empty((rows, V))
+    for r in range(rows):
+        x[r] = (0.25 + r % 128 / 512.0) - rng.random(V) * 1.7
+        x[r, rng.random(V) < 0.002] = 0.0
+        x[r, 5] = 0.25 + r % 128 / 512.0
+    x[:, 1::2][x[:, 1::2] == 0.0] = -0.0
+    check(torch.from_numpy(x * L).to(torch.bfloat16), rng.random(rows), 1.4426950408889634 * L / 4, top_p)
