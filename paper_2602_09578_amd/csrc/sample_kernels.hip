@@ -667,21 +667,19 @@ void sample_top_p_kernel(TopPArgs a) {
       const int lo_eff = max(lo, kLowestKey);
       const unsigned span = (unsigned)(hi - lo_eff);
       sweep([&](int, const u32x4 (&v)[4]) {
-        float s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int d = 0; d < 4; ++d) {
             const float r0 = lo_val(v[j][d]), r1 = hi_val(v[j][d]);
             if (x_above <= xmax) {   // workgroup-uniform
-              s[d] += r0 >= x_above ? ex2(__builtin_fmaf(r0, c, -M)) : 0.f;
-              s[d] += r1 >= x_above ? ex2(__builtin_fmaf(r1, c, -M)) : 0.f;
+              above += (double)((r0 >= x_above ? ex2(__builtin_fmaf(r0, c, -M)) : 0.f) +
+                                (r1 >= x_above ? ex2(__builtin_fmaf(r1, c, -M)) : 0.f));
             }
             const int k0 = key_of(v[j][d] & 0xffffu), k1 = key_of(v[j][d] >> 16);
             if ((unsigned)(k0 - lo_eff) <= span) atomicAdd(&sh.hist[k0 - lo], 1u);
             if ((unsigned)(k1 - lo_eff) <= span) atomicAdd(&sh.hist[k1 - lo], 1u);
           }
-        above += (double)((s[0] + s[1]) + (s[2] + s[3]));
       }, forwards);
       __syncthreads();
     };
@@ -732,27 +730,27 @@ void sample_top_p_kernel(TopPArgs a) {
     for (int k0 = 0; k0 < my_groups; k0 += 16) {   // wave-uniform
       const int k = min(k0 + (lane >> 2), my_groups - 1);
       const int begin = k + 1 < my_groups ? sh.seg_end[wave][k + 1] : 0, end = sh.seg_end[wave][k];   // (listed backwards)
-      float m[4] = {0.f, 0.f, 0.f, 0.f};
+      double mg = 0.0;
       int n = 0;
       for (int p = begin + (lane & 3); p < end; p += 16) {
-        float r[4];
+        float r[4], w[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) r[u] = __uint_as_float((uint32_t)sh.list[wave][min(p + 4 * u, end - 1)] << 16);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const bool in = p + 4 * u < end;
-          const float w = ex2(__builtin_fmaf(r[u], c, -M));
-          m[u] += in && r[u] > thr_x ? w : 0.f;
+          const float e = ex2(__builtin_fmaf(r[u], c, -M));
+          w[u] = in && r[u] > thr_x ? e : 0.f;
           n += in && r[u] == thr_x;
         }
+        mg += (double)((w[0] + w[1]) + (w[2] + w[3]));
       }
-      float mg = (m[0] + m[1]) + (m[2] + m[3]);
       mg += dpp_or_zero<0xB1, 0xf>(mg);   // quad_perm [1, 0, 3, 2]
       mg += dpp_or_zero<0x4E, 0xf>(mg);   // quad_perm [2, 3, 0, 1]
       n += dpp_or_zero<0xB1, 0xf>(n);
       n += dpp_or_zero<0x4E, 0xf>(n);
       if ((lane & 3) == 0 && k0 + (lane >> 2) < my_groups) {
-        part_m[k * kTpWaves + wave] = mg;
+        part_m[k * kTpWaves + wave] = (float)mg;
         part_n[k * kTpWaves + wave] = n;
       }
     }
@@ -770,9 +768,9 @@ void sample_top_p_kernel(TopPArgs a) {
           m[d] += r1 > thr_x ? w1 : 0.f;
           n8 += (r0 == thr_x) + (r1 == thr_x);
         }
-      const float mg = wave_sum((m[0] + m[1]) + (m[2] + m[3]));
+      const double mg = wave_inclusive_scan(((double)m[0] + (double)m[1]) + ((double)m[2] + (double)m[3]));
       n8 = wave_allreduce_sum(n8);
-      if (lane == 0) { part_m[g] = mg; part_n[g] = n8; }
+      if (lane == 63) { part_m[g] = (float)mg; part_n[g] = n8; }
     }, backwards);
   }
   __syncthreads();
