@@ -285,8 +285,12 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
 //      count * 2^(y(value) - M) from the top finds the value at which the cumulative mass reaches
 //      top_p * Z.  The cut only decides what is looked at: counts above it are complete, so a
 //      threshold found in the list is THE threshold.  If none is found (the estimate was too high),
-//      the list would be too long or the cut is not positive, the counts are taken of the whole row
-//      instead, over windows of 8192 values from the maximum down;
+//      the list is too long, or the threshold is likely to be zero, negative or more than 2048 values
+//      below the maximum, the counts are taken of the whole row instead, over windows of 8192 values: first
+//      the one that starts at the cut, if the threshold is likely to lie in it, with the mass of what is
+//      above it, then from the maximum down.  (Nuclei of half of a long row or more, rows of negative
+//      logits.  64 x 152064, sigma 3, top_p 0.95: 37 us at T 1, with the list, and 52 at T 1.3, without;
+//      2048 x 152064, top_p 0.9: 200 us, and 304 with 40 subtracted from every logit, which changes nothing else.)
 //   3. per group the nucleus mass and the number of threshold-value tokens (from the list, else one
 //      more pass over the row); a scan over the group sums finds the group in which the scaled
 //      uniform is passed, a workgroup scan over the group's 2048 tokens finds the token.
@@ -515,7 +519,13 @@ void sample_top_p_kernel(TopPArgs a) {
   // ---- pass 1: largest value and Z relative to it -----------------------------------------------
   // per thread a running (largest logit so far, sum relative to it); merged in thread order
   float xrun = -INFINITY, mrun = -INFINITY, zrun = 0.f;   // largest raw logit, the same times c, sum
-  sweep([&](int g, const u32x4 (&v)[4]) {
+  // the sample: a word per thread and group, two or four in short rows (fewer give a vague cut); of long rows every
+  // second, third ... group, so that the whole row is in it
+  const int most_groups = (ngroups + kTpWaves - 1) / kTpWaves;   // of a wave
+  const int sample_of_group = most_groups == 1 ? 4 : most_groups == 2 ? 2 : 1;
+  const int sample_every = (most_groups + kSampleWords - 1) / kSampleWords;
+  int sample_words = 0, sample_wait = 0;   // of this wave so far; groups until the next one that is looked at
+  sweep([&](int, const u32x4 (&v)[4]) {
     float x8 = xrun;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -536,9 +546,14 @@ void sample_top_p_kernel(TopPArgs a) {
     zrun = zrun * ex2(mrun - ms) + ((s[0] + s[1]) + (s[2] + s[3]));   // mrun = -inf: zrun was 0
     xrun = x8;
     mrun = m8;
-    sh.sample[(g / kTpWaves) % kSampleWords][tid] = v[0][0];
+    if (--sample_wait < 0) {   // wave-uniform
+      sample_wait = sample_every - 1;
+      sh.sample[sample_words][tid] = v[0][0];
+      if (sample_of_group > 1) sh.sample[sample_words + 1][tid] = v[2][0];
+      if (sample_of_group > 2) { sh.sample[sample_words + 2][tid] = v[1][0]; sh.sample[sample_words + 3][tid] = v[3][0]; }
+      sample_words += sample_of_group;
+    }
   }, forwards);
-  const int sample_words = min(my_groups, kSampleWords);
   float xmax = wave_max(xrun);
   if (lane == 0) sh.wave_m[wave] = xmax;
   if (tid < kBins) sh.bins[tid] = 0;
@@ -572,7 +587,7 @@ void sample_top_p_kernel(TopPArgs a) {
   // ---- pass 2: the threshold value --------------------------------------------------------
   // thr_key = -1: every token with a finite logit is in the nucleus
   bool from_list = false;
-  int cut_key = 0;
+  int cut_key = 0, likely_key = 0;   // where the estimate puts the threshold at the lowest, and where it puts it
   const double tau = (double)a.top_p * Z;
   if (a.top_p < 1.f && ngroups <= kListGroups * kTpWaves) {
     // the cut: the largest bin boundary below which the sample promises at most 1 - top_p: its sum (every
@@ -592,17 +607,31 @@ void sample_top_p_kernel(TopPArgs a) {
     const float mine_m = (mass[0] + mass[1]) + (mass[2] + mass[3]), mine_s = (square[0] + square[1]) + (square[2] + square[3]);
     float tail = wave_inclusive_scan(mine_m) - mine_m, var = fmaxf(wave_inclusive_scan(mine_s) - mine_s, 0.f);
     const float allowed = (float)((1.0 - (double)a.top_p) * Z * (double)sampled / ((double)ngroups * kTpGroup));
-    int skip = 0;        // bins left out
+    int skip = 0, unlikely = 0;        // bins left out, by the estimate with its deviations and by itself
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       tail += mass[e];
       var += square[e];
       skip += (int)__popcll(__builtin_amdgcn_ballot_w64(tail + 3.f * __builtin_sqrtf(var) <= allowed));
+      unlikely += (int)__popcll(__builtin_amdgcn_ballot_w64(tail <= allowed));
     }
-    const float cut_y = 0.125f * (float)max(1, kBins - skip);
-    const int lkey = cut_key = uniform_i(min(kmax, max(kLowestKey, key_of(__float_as_uint(xmax - cut_y / c) >> 16))));
+    auto key_below = [&](int bins) {   // the largest key that lies below so many bins from the maximum on
+      return uniform_i(min(kmax, max(kLowestKey, key_of(__float_as_uint(xmax - 0.125f * (float)max(1, bins) / c) >> 16))));
+    };
+    cut_key = key_below(kBins - skip);
+    likely_key = key_below(kBins - unlikely);
+    // The list starts at the cut, or where its counts still span it if the threshold is likely to lie above that
+    // (short rows give a vague estimate, whose cut may be zero or negative), and is not begun if the
+    // sample has more tokens above than a wave's list takes.
+    const int lkey = max(cut_key, kmax - (kListWin - 1));
     const int span = kmax - lkey + 1;
-    if (lkey >= 0x8080 && span <= kListWin) {   // workgroup-uniform: a positive, normal cut
+    const float bins_listed = 8.f * c * (xmax - value_of_key(lkey));
+    int listed = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) listed += (float)(kBins - 1 - 4 * lane - e) < bins_listed ? count[e] : 0;
+    listed = from_lane(wave_inclusive_scan(listed), 63);
+    const bool fits = (float)listed * (float)(most_groups * kTpGroup) <= (float)kListCap * (float)sampled;
+    if (lkey >= 0x8080 && likely_key >= lkey && fits) {   // workgroup-uniform: a positive, normal cut
       const int cut = lkey - 0x8000;           // its bits
       const float cut_f = uniform_f(value_of_key(lkey));
       // (the list takes the sample's place: it was read before the barriers of the sum)
@@ -614,6 +643,7 @@ void sample_top_p_kernel(TopPArgs a) {
       bool full = false;
       // a lane's entries of a group are adjacent: one scan per group places them
       sweep([&](int g, const u32x4 (&v)[4]) {
+        if (full) return;   // wave-uniform
         int below[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -625,7 +655,7 @@ void sample_top_p_kernel(TopPArgs a) {
         const int mine = 32 - ((below[0] + below[1]) + (below[2] + below[3]));
         const int inc = wave_inclusive_scan(mine);
         const int total = from_lane(inc, 63);
-        full = full || n + total > kListCap;
+        full = n + total > kListCap;
         if (!full) {   // wave-uniform
           uint32_t at = list_at + 2u * (uint32_t)(n + inc - mine);
 #pragma unroll
@@ -657,7 +687,7 @@ void sample_top_p_kernel(TopPArgs a) {
   if (a.top_p < 1.f && !from_list) {
     // Counts of the whole row over a window of values.  First the window that starts at the estimated
     // cut: the mass of the values above it is summed in the same pass, so one pass is enough unless the
-    // threshold lies outside; then the windows from the maximum down.
+    // threshold lies outside (not tried where it is likely to lie above); then the windows from the maximum down.
     // x_above: the smallest value above the window (one key further up: not every pattern is a value of its own,
     // the one below +0 is -0), `above`: the mass from it on; +inf where nothing lies above
     auto count_window = [&](int hi, int lo, float x_above, double& above) {
@@ -684,7 +714,7 @@ void sample_top_p_kernel(TopPArgs a) {
       __syncthreads();
     };
     bool found = false;
-    if (cut_key > kLowestKey && cut_key + kWin <= kmax) {
+    if (cut_key > kLowestKey && cut_key + kWin <= kmax && likely_key < cut_key + kWin) {
       const int hi = cut_key + kWin - 1;
       double mine = 0.0, above;
       count_window(hi, cut_key, value_of_key(hi + 1), mine);
@@ -725,31 +755,47 @@ void sample_top_p_kernel(TopPArgs a) {
   if (from_list) {
     part_m = sh.group_mass;
     part_n = sh.group_ties;
-    // four lanes per group, 16 groups at a time (a group after the other, reduced over the wave, took
-    // five times as long: a chain of LDS reads and reductions per group)
-    for (int k0 = 0; k0 < my_groups; k0 += 16) {   // wave-uniform
-      const int k = min(k0 + (lane >> 2), my_groups - 1);
+    // Four lanes per group where a wave has more than four of them, 16 groups at a time (a group after the
+    // other, reduced over the wave, took five times as long: a chain of LDS reads and reductions per group);
+    // in shorter rows, where four lanes would walk through hundreds of entries, 16 or all (1 row x 4096,
+    // sigma 2, top_p 0.95, half of the row listed: 28.3 us with four lanes, 14.5 with all; 32003 logits 32.6 and 21.6).
+    const int per = most_groups > 4 ? 4 : most_groups > 1 ? 16 : 64, at_once = 64 / per, mine = lane & (per - 1);
+    for (int k0 = 0; k0 < my_groups; k0 += at_once) {   // wave-uniform
+      const int slot = k0 + lane / per, k = min(slot, my_groups - 1);
       const int begin = k + 1 < my_groups ? sh.seg_end[wave][k + 1] : 0, end = sh.seg_end[wave][k];   // (listed backwards)
       double mg = 0.0;
       int n = 0;
-      for (int p = begin + (lane & 3); p < end; p += 16) {
+      for (int p = begin + mine; p < end; p += 4 * per) {
         float r[4], w[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] = __uint_as_float((uint32_t)sh.list[wave][min(p + 4 * u, end - 1)] << 16);
+        for (int u = 0; u < 4; ++u) r[u] = __uint_as_float((uint32_t)sh.list[wave][min(p + per * u, end - 1)] << 16);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const bool in = p + 4 * u < end;
+          const bool in = p + per * u < end;
           const float e = ex2(__builtin_fmaf(r[u], c, -M));
           w[u] = in && r[u] > thr_x ? e : 0.f;
           n += in && r[u] == thr_x;
         }
         mg += (double)((w[0] + w[1]) + (w[2] + w[3]));
       }
-      mg += dpp_or_zero<0xB1, 0xf>(mg);   // quad_perm [1, 0, 3, 2]
-      mg += dpp_or_zero<0x4E, 0xf>(mg);   // quad_perm [2, 3, 0, 1]
-      n += dpp_or_zero<0xB1, 0xf>(n);
-      n += dpp_or_zero<0x4E, 0xf>(n);
-      if ((lane & 3) == 0 && k0 + (lane >> 2) < my_groups) {
+      // the sum of a group's lanes in the last of them
+      mg += dpp_or_zero<0x111, 0xf>(mg);   // row_shr:1
+      n += dpp_or_zero<0x111, 0xf>(n);
+      mg += dpp_or_zero<0x112, 0xf>(mg);   // row_shr:2
+      n += dpp_or_zero<0x112, 0xf>(n);
+      if (per > 4) {
+        mg += dpp_or_zero<0x114, 0xf>(mg);   // row_shr:4
+        n += dpp_or_zero<0x114, 0xf>(n);
+        mg += dpp_or_zero<0x118, 0xf>(mg);   // row_shr:8
+        n += dpp_or_zero<0x118, 0xf>(n);
+      }
+      if (per > 16) {
+        mg += dpp_or_zero<0x142, 0xa>(mg);   // row_bcast:15 into rows 1 and 3
+        n += dpp_or_zero<0x142, 0xa>(n);
+        mg += dpp_or_zero<0x143, 0xc>(mg);   // row_bcast:31 into rows 2 and 3
+        n += dpp_or_zero<0x143, 0xc>(n);
+      }
+      if (mine == per - 1 && slot < my_groups) {
         part_m[k * kTpWaves + wave] = (float)mg;
         part_n[k * kTpWaves + wave] = n;
       }

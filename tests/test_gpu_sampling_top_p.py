@@ -192,3 +192,13 @@ def test_threshold_just_below_zero(top_p):
         x[r, 5] = 0.25 + r % 128 / 512.0
     x[:, 1::2][x[:, 1::2] == 0.0] = -0.0
     check(torch.from_numpy(x * L).to(torch.bfloat16), rng.random(rows), 1.4426950408889634 * L / 4, top_p)
+
+
+@pytest.mark.parametrize("V", [1, 513, 2048, 16384, 16385, 32768, 65536, 65537, 155648, 163841])
+@pytest.mark.parametrize("sigma,T,top_p", [(2.0, 1.0, 0.95), (2.0, 1.3, 0.95), (3.0, 0.7, 0.8)])
+def test_wide_nuclei_at_every_row_length(V, sigma, T, top_p):
+    """A third of the row or most of it in the nucleus, its threshold just above zero or negative, at the row
+    lengths where the sample's density and the number of lanes that share a group's list change."""
+    print("case: top-p row lengths", V, sigma, T, top_p, flush=True)
+    lp = I.build_logprob_inputs(4, V, sigma, V, temperature=T)
+    check(lp.logits, np.array([0.0, 0.37, 0.71, 0.999999]), T, top_p)
