@@ -441,23 +441,37 @@ int marl_kv_copy_pages(const marl_attn_shape* shape, void* k_pages, void* v_page
 }
 
 // ---- log-probabilities ------------------------------------------------------------------------
-static int logprob_split(int32_t rows, int32_t vocab, int32_t* slices, int32_t* slice_len) {
+// How a call is divided: the slices that the caller's workspace is sized for, and whether the rows are taken whole all
+// the same.  Whole rows need no second kernel (2-3 us) and pay once one workgroup of 1024 threads per CU is enough: from
+// 256 rows (333 x 20481: 11.6 -> 9.1 us, 700 x 32000: 15.6 -> 13.4), long rows from 512 (512 x 152064: 28.4 -> 27.4,
+// 700 x 100003: 29.2 -> 25.1; below, two workgroups on some CUs and one on the others: 300 x 152064 would go
+// from 20.1 to 22.8).  The 256 are the CUs of an MI355X and not asked of the device: sizes are answered without one.
+// What is asked for stays the slices' room, so that a workspace sized for a batch also serves smaller ones.
+struct LogprobSplit {
+  int32_t slices, slice_len;
+  bool whole;
+};
+static int logprob_split(int32_t rows, int32_t vocab, LogprobSplit* s) {
   if (rows < 0 || vocab < 1) return MARL_INVALID_ARG;
   long want = rows > 0 ? (1024 + rows - 1) / rows : 1;     // aim for >= 1024 workgroups (of 1024 threads)
   long len = (vocab + want - 1) / want;
   if (len < 8192) len = 8192;                              // but keep slices worth a workgroup
   len = (len + 2047) / 2048 * 2048;
-  *slice_len = (int32_t)(len > vocab ? ((long)vocab + 7) / 8 * 8 : len);
-  *slices = (int32_t)(((long)vocab + *slice_len - 1) / *slice_len);
+  s->slice_len = (int32_t)(len > vocab ? ((long)vocab + 7) / 8 * 8 : len);
+  s->slices = (int32_t)(((long)vocab + s->slice_len - 1) / s->slice_len);
+  s->whole = s->slices == 1 || rows >= 512 || (rows >= 256 && vocab <= 65536);
   return MARL_OK;
+}
+static size_t logprob_ws_bytes(int32_t rows, const LogprobSplit& s) {
+  return s.slices > 1 ? (size_t)rows * s.slices * sizeof(float2) : 0;
 }
 
 int marl_logprobs_workspace_bytes(int32_t rows, int32_t vocab, size_t* bytes) {
   if (!bytes) return MARL_INVALID_ARG;
-  int32_t slices, slice_len;
-  const int rc = logprob_split(rows, vocab, &slices, &slice_len);
+  LogprobSplit s;
+  const int rc = logprob_split(rows, vocab, &s);
   if (rc != MARL_OK) return rc;
-  *bytes = slices > 1 ? (size_t)rows * slices * sizeof(float2) : 0;
+  *bytes = logprob_ws_bytes(rows, s);
   return MARL_OK;
 }
 
@@ -466,27 +480,21 @@ int marl_token_logprobs(const void* logits, const int32_t* tokens, float tempera
                         void* stream) {
   marl::LogprobArgs a;
   memset(&a, 0, sizeof a);
-  const int rc = logprob_split(rows, vocab, &a.slices, &a.slice_len);
+  LogprobSplit split;
+  const int rc = logprob_split(rows, vocab, &split);
   if (rc != MARL_OK) return rc;
   if (!isfinite(temperature) || !(temperature > 0.f)) return MARL_INVALID_ARG;
-  if ((long)rows * a.slices >= (1L << 31)) return MARL_UNSUPPORTED;
+  if ((long)rows * split.slices >= (1L << 31)) return MARL_UNSUPPORTED;
   if (rows == 0) return MARL_OK;
   if (!logits || !tokens || !out) return MARL_INVALID_ARG;
   if (reinterpret_cast<uintptr_t>(logits) % 2 != 0) return MARL_INVALID_ARG;
-  const size_t need = a.slices > 1 ? (size_t)rows * a.slices * sizeof(float2) : 0;
+  const size_t need = logprob_ws_bytes(rows, split);
   if (need > 0) {
     if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 8 != 0) return MARL_INVALID_ARG;
     if (workspace_bytes < need) return MARL_WORKSPACE_TOO_SMALL;
   }
-  // Whole rows need no second kernel (2-3 us) and pay once one workgroup of 1024 threads per CU is enough:
-  // from 256 rows (333 x 20481: 11.6 -> 9.1 us, 700 x 32000: 15.6 -> 13.4), long rows from 512 (512 x
-  // 152064: 28.4 -> 27.4, 700 x 100003: 29.2 -> 25.1; below, two workgroups on some CUs and one on
-  // the others: 300 x 152064 would go from 20.1 to 22.8).  The workspace the caller is asked for
-  // stays that of the slices.
-  if (rows >= 512 || (rows >= 256 && vocab <= 65536)) {
-    a.slices = 1;
-    a.slice_len = (int32_t)(((long)vocab + 7) / 8 * 8);
-  }
+  a.slices = split.whole ? 1 : split.slices;
+  a.slice_len = split.whole ? vocab : split.slice_len;
   a.logits = static_cast<const uint16_t*>(logits);
   a.tokens = tokens;
   a.out = out;

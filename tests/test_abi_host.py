@@ -106,6 +106,18 @@ def test_logprobs_argument_errors_without_gpu():
     assert lib.marl_status_string(-3) == b"workspace too small"
 
 
+@pytest.mark.parametrize("rows,vocab,slices", [(255, 20481, 3), (256, 20481, 3), (511, 70001, 3), (512, 152064, 2), (1023, 152064, 2)])
+def test_logprobs_size_query_and_check_agree(rows, vocab, slices):
+    """Also for the rows that are taken whole: what the size query answers is what the call asks for."""
+    lib = B.load_library()
+    need = B.marl_logprobs_workspace_bytes(rows, vocab)
+    assert need == rows * slices * 8
+    buf = ctypes.create_string_buffer(1024)
+    p = ctypes.c_void_p((ctypes.addressof(buf) + 255) // 256 * 256)
+    f = lambda ws, n: lib.marl_token_logprobs(p, p, ctypes.c_float(1.0), p, rows, vocab, ws, n, None)
+    assert f(None, 0) == -1 and f(p, need - 1) == -3
+
+
 def test_profile_argument_errors():
     lib = B.load_library()
     assert lib.marl_profile_begin(0) == -1
