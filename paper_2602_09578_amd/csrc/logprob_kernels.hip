@@ -69,8 +69,7 @@ __device__ __forceinline__ float bf16_at(const uint16_t* p) { return __uint_as_f
 __device__ __forceinline__ float finish_row(const LogprobArgs& a, int row, MaxSum t) {
   const int tok = a.tokens[row];
   if ((unsigned)tok >= (unsigned)a.vocab) return __uint_as_float(0x7fc00000u);
-  const float y = bf16_at(a.logits + (size_t)row * a.vocab + tok) * a.inv_temp_log2e;
-  return (y - (t.m + __builtin_amdgcn_logf(t.s))) * 0.69314718055994530942f;   // v_log_f32 is log2
+  return logprob_of(bf16_at(a.logits + (size_t)row * a.vocab + tok), a.inv_temp_log2e, t.m, (double)t.s);
 }
 
 __global__ __launch_bounds__(kLpThreads) void logprob_kernel(LogprobArgs a) {

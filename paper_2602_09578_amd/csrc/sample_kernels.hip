@@ -201,17 +201,17 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   u32x4 words[kIters];
 #pragma unroll
   for (int it = 0; it < kIters; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
-  // y relative to the row's maximum and the weight 2^y of 8 logits, the same each time they are formed
+  // the weights 2^(y - M) of 8 logits, the same each time they are formed
   const float ms = M == -INFINITY ? 0.f : M;
-  auto weights = [&](u32x4 v, float (&y)[8], float (&w)[8]) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      y[2 * d] = __builtin_fmaf(__uint_as_float(v[d] << 16), c, -ms);
-      y[2 * d + 1] = __builtin_fmaf(__uint_as_float(v[d] & 0xffff0000u), c, -ms);
-    }
+  auto weights = [&](u32x4 v, float (&w)[8]) {
     float s = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { w[e] = ex2(y[e]); s += w[e]; }
+    for (int d = 0; d < 4; ++d) {
+      w[2 * d] = ex2(__builtin_fmaf(__uint_as_float(v[d] << 16), c, -ms));
+      w[2 * d + 1] = ex2(__builtin_fmaf(__uint_as_float(v[d] & 0xffff0000u), c, -ms));
+      s += w[2 * d];
+      s += w[2 * d + 1];
+    }
     return s;
   };
   // the piece of 512 tokens in which the running sum passes (`at`), else the last one with any mass
@@ -219,8 +219,8 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   int at = -1, last = -1;
 #pragma unroll
   for (int it = 0; it < kIters; ++it) {
-    float y[8], w[8];
-    const float s = weights(words[it], y, w);
+    float w[8];
+    const float s = weights(words[it], w);
     const float cum = run + wave_inclusive_scan(s);
     if (at < 0) {   // wave-uniform
       if (__builtin_amdgcn_ballot_w64(s > 0.f)) last = it;
@@ -230,13 +230,13 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   }
   const int piece = at >= 0 ? at : last;
   int tok = -1;
-  float y_tok = 0.f;
+  float x_tok = 0.f;
   if (piece >= 0) {   // wave-uniform
     u32x4 v = words[0];
 #pragma unroll
     for (int it = 1; it < kIters; ++it) v = it == piece ? words[it] : v;
-    float y[8], w[8];
-    const float s = weights(v, y, w);
+    float w[8];
+    const float s = weights(v, w);
     // the lane's first token with mass that passes; if rounding leaves none (or no lane passed), its last one
     const unsigned long long mass = __builtin_amdgcn_ballot_w64(s > 0.f);
     const unsigned long long hit = __builtin_amdgcn_ballot_w64(s > 0.f && cum_at > want);
@@ -249,11 +249,11 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
       acc += w[e];
       if (!found && w[e] > 0.f) { e_pick = e; found = acc > want; }
     }
-    float ysel = y[0];
+    uint32_t word = v[0];
 #pragma unroll
-    for (int e = 1; e < 8; ++e) if (e == e_pick) ysel = y[e];
+    for (int d = 1; d < 4; ++d) word = d == e_pick >> 1 ? v[d] : word;
     tok = from_lane((int)(cbase + piece * 512) + e_pick, l);
-    y_tok = from_lane(ysel, l);
+    x_tok = from_lane(__uint_as_float(e_pick & 1 ? word & 0xffff0000u : word << 16), l);
   }
   if (lane == 0) {
     if (tok < 0) {   // a row of -inf logits (or NaN): no token can be drawn
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
       a.out_logprobs[row] = __uint_as_float(0x7fc00000u);
     } else {
       a.out_tokens[row] = tok;
-      a.out_logprobs[row] = (y_tok - __builtin_amdgcn_logf((float)total)) * 0.69314718055994530942f;
+      a.out_logprobs[row] = logprob_of(x_tok, c, M, total);
     }
   }
 }
@@ -917,7 +917,7 @@ void sample_top_p_kernel(TopPArgs a) {
 #pragma unroll
       for (int e = 1; e < 4; ++e) if (e == e_pick) r_pick = r[e];
       a.out_tokens[row] = (int)(pos + e_pick);
-      a.out_logprobs[row] = (__builtin_fmaf(r_pick, c, -M) - __builtin_amdgcn_logf((float)Z)) * 0.69314718055994530942f;
+      a.out_logprobs[row] = logprob_of(r_pick, c, M, Z);
     }
   }
 }

@@ -100,3 +100,17 @@ def test_rerun_bit_identical():
 def test_whole_rows_and_slices_on_both_sides_of_the_rule(rows, vocab):
     print("case: logprobs rule", rows, vocab, flush=True)
     check(I.build_logprob_inputs(rows, vocab, 3.0, rows + vocab, temperature=0.9))
+
+
+@pytest.mark.parametrize("rows,vocab", [(333, 20481), (300, 65536), (256, 152064), (700, 100003)])
+def test_error_is_little_more_than_the_results_rounding(rows, vocab):
+    """2-norm of the error over that of the result.  Rounding the result to float32 alone gives 2.1e-8 (evenly
+    distributed within half a unit of the last place, over a binade), log2(e) in float32 another 1.3e-8, the
+    float32 sums of thousands of terms about as much: 3e-8 together, 4e-8 allowed."""
+    print("case: logprobs error", rows, vocab, flush=True)
+    lp = I.build_logprob_inputs(rows, vocab, 3.0, 41)
+    want = ref.token_logprobs(I.bf16_bits(lp.logits), lp.tokens.numpy(), 1.0)
+    got = gpu_logprobs(lp)
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print("relative error", err, flush=True)
+    assert err <= 4e-8
