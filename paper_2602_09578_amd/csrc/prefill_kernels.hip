@@ -892,7 +892,7 @@ int prefill_rows_per_block() { return kQB; }
 
 PrefillSplitLayout prefill_split_layout(long max_blocks, long Hkv, long max_keys) {
   PrefillSplitLayout L = {};
-  if (max_blocks > kPfSorted || max_keys <= kPfMinPart) return L;
+  if (max_blocks > kPfSorted || max_keys <= kPfLongKeys) return L;   // (the plan divides nothing then)
   L.entries = kPfSorted;
   L.parts = (int)std::min<long>(kPfMaxParts, max_blocks * kPfMaxDiv * std::min<long>(Hkv, kPfMaxParts));
   L.bytes = (size_t)L.parts * kNW * kMT * 64 * (sizeof(float2) + 8 * sizeof(f32x4));   // (about 100 MB at most)

@@ -187,6 +187,15 @@ def test_prefill_argument_errors_without_gpu():
     assert wr5(off, p, p) == -1 and wr5(p, off, p) == -1 and wr5(p, p, off) == -1
 
 
+def test_prefill_workspace_has_room_for_parts_only_where_blocks_may_be_divided():
+    """Blocks of up to 960 keys are never divided: a table of 60 pages needs the list alone."""
+    need = lambda pages, tokens=64: B.marl_prefill_workspace_bytes(
+        B.make_prefill_shape(num_tokens=tokens, num_groups=2, num_q_heads=28, num_kv_heads=4, num_pages=16, max_prefix_pages=pages))
+    assert need(32) == need(33) == need(60) == 768
+    assert need(61) > (1 << 20)
+    assert need(61, tokens=1 << 20) < (1 << 20)              # too many blocks for a sorted list: none is divided
+
+
 def test_balancer_takes_sparse_request_ids_and_reports_status_codes():
     """Request ids are arbitrary non-negative int32 values (a hash, say): the id map must not be
     sized by the largest id, and no error may leave the library as an exception."""
