@@ -296,8 +296,9 @@ int marl_sample_tokens_top_p(const void* logits, const float* uniforms, float te
  * workspace: marl_prefill_workspace_bytes() bytes, 256-byte aligned, used from the start of the
  * call's work until its end on the stream.  For shapes with few row blocks and long tables this includes up
  * to about 100 MB for partial results (long blocks may be divided along their keys, with results that are the
- * same in every run); a call whose workspace holds the list alone (256 bytes, num_groups + 1 integers, 8 bytes
- * for each of num_tokens * R / 192 + num_groups blocks, each rounded up to 256) is served without.
+ * same in every run); a call whose workspace holds the list alone (256 bytes, num_groups + 1 integers, of which
+ * only the last is used, 8 bytes for each of num_tokens * R / 192 + num_groups blocks, each rounded up to 256)
+ * is served without.
  */
 typedef struct {
   int32_t num_tokens;        /* NT: query tokens of all groups together */

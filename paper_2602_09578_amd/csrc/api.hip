@@ -671,7 +671,7 @@ int marl_prefill_attn(const marl_prefill_shape* shape, void* workspace, size_t w
   a.q_pos0 = q_pos0;
   a.out = out;
   a.counters = static_cast<int32_t*>(workspace);
-  a.block_start = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + kPrefillHeaderBytes);
+  a.list_length = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + kPrefillHeaderBytes) + a.NG;
   a.items = reinterpret_cast<int2*>(static_cast<char*>(workspace) + kPrefillHeaderBytes + prefill_start_bytes(shape));
   if (prefill_max_blocks(shape) >= (1L << 28)) return MARL_UNSUPPORTED;
   a.max_blocks = (int32_t)prefill_max_blocks(shape);

@@ -131,8 +131,8 @@ struct PrefillArgs {
   const int32_t* q_pos0;        // [NG]
   void* out;                    // [NT][Hq][128]
   int32_t* counters;            // workspace header
-  int32_t* block_start;         // [NG + 1] running number of row blocks
-  int2* items;                  // [blocks] (group, first row of the block)
+  int32_t* list_length;         // entries of the list: row blocks, or parts of them
+  int2* items;                  // [entries] (group, first row of the block)
   // parts of blocks whose keys are divided; split_slots = 0: no room for them, none is
   int32_t* split_info;          // [512] by list entry: first part << 8 | part << 4 | parts - 1
   int32_t* split_arrived;       // [kPfMaxParts] by first part of a block and KV head: parts that are finished

@@ -83,7 +83,8 @@ constexpr int pf_lgkmcnt0 = 0xf | (3 << 14) | (7 << 4);   // waits only for LDS 
 constexpr int pf_vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (7 << 4) | (0xf << 8); }
 
 // counters at the head of the workspace (same slots as the decode plan uses, so that
-// marl_attn_read_flags reads this workspace too); block_start[NG + 1] follows the header
+// marl_attn_read_flags reads this workspace too); the header is followed by num_groups + 1 words, of which the last is
+// the length of the list
 constexpr int kPfCursor = MARL_CTR_PREFIX_CURSOR, kPfFlags = MARL_CTR_FLAGS;
 
 // n_g usable query tokens of group g (clamped to the q array and to the table row)
@@ -167,7 +168,6 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
         atomicMax(&end_all, first + nb);
         if (nb) atomicMax(&most_keys, a.q_pos0[g] + (int)(nrows / a.R));
       }
-      a.block_start[g] = first;
       // the group's blocks, last (most keys) first
       const int qb = block_rows(nrows);
       for (int k = 0; k < nb; ++k) {
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
       }
   }
   if (tid == 0) {
-    a.block_start[a.NG] = total;
+    *a.list_length = total;
     a.counters[kPfCursor] = 0;
     a.counters[kPfFlags] = flags_all;   // the attention kernel may add MARL_FLAG_BAD_PAGE
   }
@@ -819,7 +819,7 @@ __global__ __launch_bounds__(kPfThreads)
 __attribute__((amdgpu_waves_per_eu(MARL_PREFILL_WAVES_PER_EU, MARL_PREFILL_WAVES_PER_EU)))
 void prefill_kernel(PrefillArgs a) {   // kSplit: the list may hold parts of blocks
   __shared__ PrefillLds lds;
-  const int n_work = a.block_start[a.NG] * a.Hkv;
+  const int n_work = *a.list_length * a.Hkv;
   int bad_page = 0;
   if ((int)blockIdx.x < n_work) prefill_items<kSplit>(a, n_work, lds, bad_page);
   if (bad_page) atomicOr(&a.counters[kPfFlags], MARL_FLAG_BAD_PAGE);

@@ -301,3 +301,25 @@ def test_few_long_items_are_divided_along_their_keys(Hq, Hkv, chunks, context):
     assert divided > entries()
     want, want_abs = reference(inp)
     assert (np.abs(whole.cpu().numpy() - want) <= 1e-3 + 2.0 ** -8 * want_abs).all()
+
+
+@pytest.mark.parametrize("Hq,Hkv,chunks,context", [(8, 8, [2] * 140 + [100] * 2, [100] * 140 + [2500] * 2),
+                                                   (16, 16, [1] * 66 + [96] * 2, [100] * 66 + [2500] * 2),
+                                                   (16, 8, [1] * 120 + [90] * 4, [300] * 120 + [3000] * 4)])
+def test_divided_blocks_among_items_drawn_from_the_counter(Hq, Hkv, chunks, context):
+    """A few long blocks in parts among many short ones: more items than two for every workgroup, so parts and
+    whole blocks are drawn while others run."""
+    print("case: prefill parts drawn", Hq, Hkv, len(chunks), flush=True)
+    inp = I.build_prefill_inputs(Hq, Hkv, chunks, context, seed=Hkv)
+    check(inp)
+    dev = inp.to("cuda")
+    shape, ws, out = B.prepare_prefill(dev, B.MARL_OUT_F32)
+    first = B.run_prefill(dev, shape, ws, out).clone()
+    for _ in range(3):
+        assert torch.equal(B.run_prefill(dev, shape, ws, out.zero_()), first)
+    starts = (len(chunks) + 1 + 63) // 64 * 256
+    entries = lambda: int(ws[256:256 + starts].view(torch.int32)[len(chunks)])   # of the list, behind the header
+    divided = entries()
+    assert divided * Hkv > 2 * 2 * torch.cuda.get_device_properties(0).multi_processor_count   # two workgroups per CU
+    B.run_prefill(dev, shape, ws[:256 + starts + 4096], out)   # room for the list alone
+    assert divided > entries()
