@@ -86,6 +86,7 @@ constexpr int pf_vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (7 << 
 // marl_attn_read_flags reads this workspace too); the header is followed by num_groups + 1 words, of which the last is
 // the length of the list
 constexpr int kPfCursor = MARL_CTR_PREFIX_CURSOR, kPfFlags = MARL_CTR_FLAGS;
+constexpr int kPfDivided = 16;   // not zero: the list holds parts of blocks (a word that the decode plan does not use)
 
 // n_g usable query tokens of group g (clamped to the q array and to the table row)
 __device__ __forceinline__ int group_tokens(const PrefillArgs& a, int g, int& flag) {
@@ -303,6 +304,7 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
   if (tid == 0) {
     *a.list_length = total;
     a.counters[kPfCursor] = 0;
+    a.counters[kPfDivided] = parts_used;
     a.counters[kPfFlags] = flags_all;   // the attention kernel may add MARL_FLAG_BAD_PAGE
   }
 }
@@ -821,7 +823,10 @@ void prefill_kernel(PrefillArgs a) {   // kSplit: the list may hold parts of blo
   __shared__ PrefillLds lds;
   const int n_work = *a.list_length * a.Hkv;
   int bad_page = 0;
-  if ((int)blockIdx.x < n_work) prefill_items<kSplit>(a, n_work, lds, bad_page);
+  if ((int)blockIdx.x < n_work) {
+    if (kSplit && a.counters[kPfDivided] != 0) prefill_items<true>(a, n_work, lds, bad_page);
+    else prefill_items<false>(a, n_work, lds, bad_page);
+  }
   if (bad_page) atomicOr(&a.counters[kPfFlags], MARL_FLAG_BAD_PAGE);
 }
 
