@@ -211,10 +211,16 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
     for (int k = tid; k < kPfMaxParts; k += kPlanThreadsPf) a.split_arrived[k] = 0;
     // Wave w estimates the time, in keys, with blocks divided into parts of at most kPfLens[w] even shares
     // (wave 0: whole blocks): the longest item if all run at once, else an even share of
-    // all items and half an item.  An item costs 128 keys beside its own, a part 228, and a part's sums
-    // written and read back 1.1 keys of everybody's time (200 KB at 4 TB/s); 0.4 in lists that take several
-    // rounds also whole, whose other items run meanwhile (with 0.4 everywhere one prompt of 2048 tokens, 28 / 4
-    // heads, took 80 us instead of 70, with 1.1 the six chunks 387 instead of 382).
+    // all items and half an item.  An item costs 128 keys beside its own, a part more, and a part's sums are
+    // written and read back in everybody's time (200 KB at 4 TB/s): 400 and 0.9 keys, or, in lists that take several
+    // rounds also whole, whose other items run meanwhile, 228 and 0.4.  Checked on 434 drawn shapes that none
+    // of this was chosen by (1 to 64 chunks of up to 4096 tokens behind up to 8192), each timed with all of the sixteen
+    // lengths: the time of the length that is taken is 1.5 % above the best one's in the geometric mean, whole
+    // lists' is 26 %; 9 shapes are slower than whole by more than 2 %, the worst by 9 %.  The optimum is flat: 228 and
+    // 1.1 in both kinds of list gave 1.5 % and 10 shapes, among others a prompt of 1172 tokens, 64 / 8 heads, 47.5 us
+    // (whole 45.2), 60 of up to 78 behind up to 991, 16 / 1 heads, 49.5 (now 47.6).
+    const bool rounds = (long)total * a.Hkv > a.split_slots;
+    const float part_extra = rounds ? 228.f : 400.f, part_all = rounds ? 0.4f : 0.9f;
     auto sum_all = [](float v) { return wave_allreduce(v, [](float x, float y) { return x + y; }); };
     float all = 0.f;
 #pragma unroll
@@ -231,7 +237,7 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
 #pragma unroll
     for (int u = 0; u < kPer; ++u)
       if (keys[u] >= 0) {
-        const float n = (float)parts[u], extra = parts[u] > 1 ? 228.f : 128.f;
+        const float n = (float)parts[u], extra = parts[u] > 1 ? part_extra : 128.f;
         items += n;
         in_parts += parts[u] > 1 ? n : 0.f;
         work += (float)keys[u] + n * extra;
@@ -242,8 +248,7 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
     in_parts = sum_all(in_parts) * (float)a.Hkv;
     work = sum_all(work) * (float)a.Hkv;
     longest = wave_allreduce(longest, [](float x, float y) { return fmaxf(x, y); });
-    const bool rounds = (long)total * a.Hkv > a.split_slots;
-    const float time = (items <= slots ? longest : fmaxf(longest, work / slots + 0.5f * work / items)) + (rounds ? 0.4f : 1.1f) * in_parts;
+    const float time = (items <= slots ? longest : fmaxf(longest, work / slots + 0.5f * work / items)) + part_all * in_parts;
     // (no more than the list and the partial results have room for; whole blocks unless 3 % of such a list's time, else 7 %, are gained)
     const bool fits = entries <= (float)kPfSorted && in_parts <= (float)kPfMaxParts;
     if (lane == 0) estimate[wave] = wave == 0 ? (rounds ? 0.97f : 0.93f) * time : fits ? time : INFINITY;
