@@ -13,30 +13,30 @@
 // LDS step buffers, 32 tokens (two pages, 16 KB) per step, in the XOR-swizzled layout of the
 // decode prefix kernel; the four waves split the block's 16-row tiles (up to three each).  The
 // steps go from global memory straight into LDS (global_load_lds_dwordx4, no staging
-// registers), which is what leaves room for the third tile: the kernel is bound by the LDS
-// operand reads (every wave reads the whole step for its rows), so more rows per wave is what
-// makes it faster.  Causality costs little: a block spans kQB / R consecutive tokens, so only
-// its last one or two steps need the per-row mask, and a tile skips steps that lie entirely
-// beyond its rows.  A block sees all of its keys, so the output is normalised and written
-// directly (no partials, no merge).
+// registers), which is what leaves room for the third tile: every wave reads the whole step out
+// of LDS for its rows, so more rows per wave make the same reads do more work.  Causality
+// costs little: a block spans kQB / R consecutive tokens, so only its last one or two steps need
+// the per-row mask, and a tile skips steps that lie entirely beyond its rows.  A block that is
+// taken whole sees all of its keys, so its output is normalised and written directly.
 //
 // Work distribution: a one-workgroup plan kernel lists the row blocks group after group, inside a
 // group last-first (most keys first), so that blocks of a group run at the same time and its keys come
 // out of the caches; a list of at most kPfSorted blocks, but more items than workgroups, is put into falling order of cost instead
 // (so few items end evenly only if the long ones start first: 494 blocks x 4 heads of 47 short prompts
-// would take 1.20 times their even share, sorted 1.04).  Item i = (block i / Hkv, KV head i % Hkv); a
-// workgroup starts with the items b and b + G (2 G - 1 - b in lists of at most 2 G) and draws every further one
-// from a counter two items ahead, so that it knows its next item while it works on one: that item's steps follow the
-// current one's in the ring without a gap, and its queries are requested before the current rows are
-// written.  (A fixed assignment instead of the counter left 3 to 13 % of the time to the longest share.)
+// would take 1.20 times their even share, sorted 1.04).  Item i = (block i / Hkv, KV head i % Hkv).  A
+// workgroup starts with item b and knows its next item while it works on one: that item's steps follow
+// the current one's in the ring without a gap, and its queries are requested before the current rows
+// are written.  The second item is fixed, every further one is drawn from a counter when the one before
+// the one before it ends.  (A fixed assignment instead of the counter left 3 to 13 % of the time to the
+// longest share; items drawn another item earlier left the ends of short lists uneven.)
 //   A few long items (chunks of a few prompts behind long context) leave workgroups idle, or end unevenly,
 // whatever their order.  For a sorted list the plan kernel therefore weighs dividing long blocks along their
 // keys: a part's sums (float32, unnormalised) go to the workspace, and the workgroup that arrives last at a
-// block adds the parts.  Whole and divided: one chunk of 512 tokens behind 8192, 64 / 8 heads 220 -> 180 us,
-// 28 / 4 heads 255 -> 100 us; three chunks behind up to 6.6 k, 64 / 8 heads 229 -> 175 us; 64 tokens behind 2000 66 -> 40 us;
-// one prompt of 2048 tokens, 28 / 4 heads 79 -> 70 us; 9 chunks 340 -> 280 us.  Lists with more work than that stay
-// whole (12 and 16 chunks, 260 and 540 us either way), as does everything in this kernel's instance
-// without parts (a few scalar registers less; for shapes whose lists are not sorted).
+// block adds the parts.  Whole and divided: one chunk of 512 tokens behind 8192, 64 / 8 heads 215 -> 175 us,
+// 28 / 4 heads 253 -> 94 us; 64 tokens behind 2000, 64 / 8 heads, 70 -> 40 us; one prompt of 2048 tokens, 28 / 4 heads,
+// 79 -> 66 us; six chunks of up to 512 behind up to 8192, 64 / 8 heads, 382 -> 357 us.  Lists with more work than that
+// stay whole (9 chunks of 512 behind up to 8000, 591 and 584 us), and run the code without parts (22 spilled
+// scalar registers instead of 86; 2 to 3 % of such a list's time).
 // A workspace with room for the list alone is served with whole blocks.
 //
 // What bounds it: the issue of instructions.  A step of a wave is 48 matrix instructions (768 cycles
@@ -44,8 +44,10 @@
 // vector ALU), and the two waves of a SIMD overlap little of it: 1.58 us per step and workgroup at
 // two workgroups per CU with 141 vector and 105 scalar instructions, 1.50 with 120 and 50 (page
 // ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  256 prompts of
-// 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.65 ms (0.95 PFLOP/s; a large matrix product of this
-// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.
+// 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.58 ms (0.96 PFLOP/s; a large matrix product of this
+// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.  Memory is second: with items
+// bound ahead a prompt's blocks run further apart in time than one after the other did, and the 256 prompts fetch
+// 16.7 GB instead of 8.2; with all groups on the pages of one prompt, which stay in the caches, they take 4 % less.
 #include <algorithm>
 
 #include "marl_internal.h"
@@ -76,7 +78,8 @@ struct PrefillLds {
   __attribute__((aligned(16))) char buf[kPfStages][kPfStepBytes];
   __attribute__((aligned(16))) char out[kNW][16 * kD];   // half a tile's output rows (64 channels) on their way to memory, per wave
   int arrived;   // parts of the current block that were finished before this one
-  int next[2];   // drawn item indices, by the parity of the item during which they were published
+  int next;      // a drawn item
+  int late;      // an item drawn when nothing was left to do
 };
 // s_waitcnt immediate that waits only for the vector-memory counter to drop to n (gfx9 encoding)
 constexpr int pf_lgkmcnt0 = 0xf | (3 << 14) | (7 << 4);   // waits only for LDS and scalar operations
@@ -86,6 +89,8 @@ constexpr int pf_vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (7 << 
 // marl_attn_read_flags reads this workspace too); the header is followed by num_groups + 1 words, of which the last is
 // the length of the list
 constexpr int kPfCursor = MARL_CTR_PREFIX_CURSOR, kPfFlags = MARL_CTR_FLAGS;
+constexpr int kPfLate = 17;      // items that were drawn late
+constexpr int kPfIsSorted = 18;  // not zero: the list is in falling order of cost
 constexpr int kPfDivided = 16;   // not zero: the list holds parts of blocks (a word that the decode plan does not use)
 
 // n_g usable query tokens of group g (clamped to the q array and to the table row)
@@ -309,6 +314,8 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
   if (tid == 0) {
     *a.list_length = total;
     a.counters[kPfCursor] = 0;
+    a.counters[kPfLate] = 0;
+    a.counters[kPfIsSorted] = sorted;
     a.counters[kPfDivided] = parts_used;
     a.counters[kPfFlags] = flags_all;   // the attention kernel may add MARL_FLAG_BAD_PAGE
   }
@@ -371,9 +378,10 @@ __device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
   return it;
 }
 
-// The items of one workgroup, one after the other.
+// Items of one workgroup, one after the other: `first`, `second` and the drawn ones, as far as they are less than n_ahead.
 template <bool kSplit>
-__device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_work, PrefillLds& lds, int& bad_page) {
+__device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int first, const int second, const int n_ahead,
+                                              PrefillLds& lds, int& bad_page) {
   constexpr int kLoads = 1024 / (kNW * 64);     // 16-byte loads per thread and step (16 KB per step)
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -645,18 +653,10 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
   // landed and everybody has finished reading the slot before; a fence would wait for every
   // outstanding load), then the loads of the slot kPfStages-1 ahead, which may be the next item's.
   // An item takes at least kPfStages slots, so what is ahead is never further than the next item.
-  PfItem cur = read_item<kSplit>(a, blockIdx.x);
-  // (lists of at most two items per workgroup: the longest of them meet the shortest.  As in longer lists, where draws
-  // even it out, a prompt of 3008 tokens, 64 / 8 heads, took 161.5 us instead of 150.0, two of up to 3294, 32 / 8
-  // heads, 101.5 instead of 87.7)
-  const int second = n_work > 2 * (int)gridDim.x ? blockIdx.x + gridDim.x : 2 * gridDim.x - 1 - blockIdx.x;
-  bool more = second < n_work;                                // workgroup-uniform: there is a next item
+  PfItem cur = read_item<kSplit>(a, first);
+  bool more = second < n_ahead;                               // workgroup-uniform: there is a next item
   PfItem nxt = more ? read_item<kSplit>(a, second) : cur;             // (without one its slots are never used)
-  // (a list of at most two items per workgroup has none to draw: the counter, asked by all workgroups at once,
-  // would only delay their first items: 472 items 48.2 -> 43.4 us, 608 items 44.9 -> 40.3 us)
-  const bool any_drawn = n_work > 2 * (int)gridDim.x;
-  auto draw = [&] { return 2 * (int)gridDim.x + (any_drawn && tid == 0 ? atomicAdd(&a.counters[kPfCursor], 1) : 0); };
-  int drawn = draw();                                         // (thread 0 only) the item after the next one
+  int drawn = 0;                                              // (thread 0 only) the item after the next one
   uint32_t ring = 0;                   // byte offset of the current slot's buffer
   constexpr uint32_t kRingBytes = kPfStages * kPfStepBytes;
   static_assert((kRingBytes & (kRingBytes - 1)) == 0, "the ring wraps by a mask");
@@ -668,7 +668,7 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
   }
   load_ids();
   load_rows(cur);
-  for (int round = 0;; ++round) {
+  for (bool drawn_next = false;; drawn_next = true) {
     // the queries are waited for here, once: with the loads still pending at the top of the loops the
     // compiler would wait in every step, and for the steps in flight with them
 #pragma unroll
@@ -678,9 +678,17 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
         qreg[qt][kk] ^= sign_flip;
         asm volatile("" : "+v"(qreg[qt][kk]));
       }
-    // (the draw was requested before the queries, so it has arrived; published by the next barrier)
-    if (tid == 0) lds.next[round & 1] = drawn;
-    __builtin_amdgcn_s_waitcnt(pf_lgkmcnt0);
+    if (drawn_next) {
+      // the next item (the draw was requested before the queries, so it has arrived)
+      if (tid == 0) lds.next = drawn;
+      __builtin_amdgcn_s_waitcnt(pf_lgkmcnt0);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      const int next = __builtin_amdgcn_readfirstlane(lds.next);
+      more = next < n_ahead;
+      if (more) nxt = read_item<kSplit>(a, next);
+    }
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
       // (finite: a row that sees no key of a part keeps it, with weights exp2(-inf) = 0)
@@ -716,11 +724,11 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
       for (int qt = 0; qt < kMT; ++qt) row_of(cur, qt, l & 15, limit[qt]);
       for (; n < cur.nsteps; ++n) ring_step([&](const char* buf) { compute_edge(n, buf, cur.tok_end, limit); });
     }
-    for (; n < cur.slots; ++n) ring_step([&](const char*) { load_ids(); });
+    if (more)   // (without a next item nobody waits for the slots that are left)
+      for (; n < cur.slots; ++n) ring_step([&](const char*) { load_ids(); });
     // the next item's queries are requested before this item's rows are written
-    const int after_next = __builtin_amdgcn_readfirstlane(lds.next[round & 1]);
     if (more) {
-      drawn = draw();
+      if (tid == 0) drawn = 2 * (int)gridDim.x + atomicAdd(&a.counters[kPfCursor], 1);
       load_rows(nxt);
     }
     // Lane (i, j) holds channels 16*ct + 4*j .. +3 of q-row i.  Written as they are held, an instruction
@@ -816,8 +824,6 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int n_
     }
     if (!more) break;
     cur = nxt;
-    more = after_next < n_work;
-    if (more) nxt = read_item<kSplit>(a, after_next);
   }
   if (id_max >= (uint32_t)a.num_pages) bad_page = 1;
   __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm(0));   // (the last slots' loads write to LDS: not past the kernel's end)
@@ -829,11 +835,34 @@ __global__ __launch_bounds__(kPfThreads)
 __attribute__((amdgpu_waves_per_eu(MARL_PREFILL_WAVES_PER_EU, MARL_PREFILL_WAVES_PER_EU)))
 void prefill_kernel(PrefillArgs a) {   // kSplit: the list may hold parts of blocks
   __shared__ PrefillLds lds;
+  const int grid = (int)gridDim.x;
   const int n_work = *a.list_length * a.Hkv;
+  // A workgroup's second item: in a sorted list, and in one of at most two items per workgroup (of which none is drawn), the
+  // longest meet the shortest.  (In their order again a prompt of 3008 tokens, 64 / 8 heads, took 161.5 us instead
+  // of 150.0, two of up to 3294, 32 / 8 heads, 101.5 instead of 87.7; the counter, asked by all workgroups at once,
+  // would only delay their first items: 472 items 48.2 -> 43.4 us, 608 items 44.9 -> 40.3 us.)
+  // A list in group order may end with long blocks: its last two items per workgroup are not bound ahead of time but
+  // drawn by whoever has nothing left to do, and start with an empty ring.  (16 prompts of up to 3801 tokens, 16 / 1
+  // heads: 377 -> 332 us; 26 of up to 2024, 8 / 2 heads, 156 -> 132; 60 of up to 400, 16 / 1 heads, 63 -> 58.  In
+  // sorted lists, whose last items are short, the empty ring costs more than it evens out: 20 prompts of up to 798
+  // behind 709, 32 / 8 heads, 143 us, so 165.)
+  const bool in_group_order = n_work > 2 * grid && a.counters[kPfIsSorted] == 0;
+  const int n_ahead = in_group_order ? max(grid, n_work - 2 * grid) : n_work;
+  int first = (int)blockIdx.x, second = in_group_order ? first + grid : 2 * grid - 1 - first;
   int bad_page = 0;
-  if ((int)blockIdx.x < n_work) {
-    if (kSplit && a.counters[kPfDivided] != 0) prefill_items<true>(a, n_work, lds, bad_page);
-    else prefill_items<false>(a, n_work, lds, bad_page);
+  while (first < n_work) {   // workgroup-uniform
+    // (the arguments are read again for each run: kept through the loop they would cost the registers of another
+    // twenty spilled values)
+    auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kernarg));
+    const PrefillArgs run = *(const PrefillArgs*)kernarg;
+    if (kSplit && run.counters[kPfDivided] != 0) prefill_items<true>(run, first, second, n_ahead, lds, bad_page);
+    else prefill_items<false>(run, first, second, n_ahead, lds, bad_page);
+    if (!in_group_order) break;
+    if (threadIdx.x == 0) lds.late = n_ahead + atomicAdd(&a.counters[kPfLate], 1);
+    __syncthreads();   // (the loads of slots past the end have landed: prefill_items ends with their wait)
+    first = __builtin_amdgcn_readfirstlane(lds.late);
+    second = n_work;
   }
   if (bad_page) atomicOr(&a.counters[kPfFlags], MARL_FLAG_BAD_PAGE);
 }

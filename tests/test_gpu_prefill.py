@@ -323,3 +323,20 @@ def test_divided_blocks_among_items_drawn_from_the_counter(Hq, Hkv, chunks, cont
     assert divided * Hkv > 2 * 2 * torch.cuda.get_device_properties(0).multi_processor_count   # two workgroups per CU
     B.run_prefill(dev, shape, ws[:256 + starts + 4096], out)   # room for the list alone
     assert divided > entries()
+
+
+@pytest.mark.parametrize("Hkv,groups", [(1, 600), (1, 1100), (2, 1100), (2, 1700)])
+def test_lists_in_group_order_end_with_a_long_group(Hkv, groups):
+    """Lists too long to be sorted: up to two items per workgroup, and more, of which the last two per workgroup
+    are drawn by whoever is done, with none, some and many items bound ahead before them.  Short items, then a
+    prompt of several blocks."""
+    print("case: prefill late items", Hkv, groups, flush=True)
+    rng = np.random.default_rng(groups + Hkv)
+    pos0 = rng.choice([0, 1, 31, 95, 127, 200], groups).tolist() + [40]
+    inp = I.build_prefill_inputs(2 * Hkv, Hkv, [1] * groups + [300], pos0, seed=groups)
+    check(inp, B.MARL_OUT_BF16)
+    dev = inp.to("cuda")
+    shape, ws, out = B.prepare_prefill(dev, B.MARL_OUT_F32)
+    first = B.run_prefill(dev, shape, ws, out).clone()
+    for _ in range(3):
+        assert torch.equal(B.run_prefill(dev, shape, ws, out.zero_()), first)
