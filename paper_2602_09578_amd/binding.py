@@ -155,13 +155,17 @@ def _check(rc: int, where: str):
 
 # The calls' own host time matters for small calls: 8.4 us of a log-probability call (3.4 in the library) and
 # 19.6 us of an attention call.  Pointers and streams go to ctypes as the integers they are, and the
-# current stream of a tensor's device is read without building a Stream object (2.1 -> 0.1 us).
+# current stream of a tensor's device is read without building a Stream object (2.1 -> 0.1 us), where torch has
+# the function for that, which is not part of its documented interface.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
 def _stream(device) -> int:
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    return _raw_stream(device.index) if _raw_stream is not None else torch.cuda.current_stream(device).cuda_stream
 
 
 def make_shape(num_seqs, num_groups, num_q_heads, num_kv_heads, num_pages, max_prefix_pages,

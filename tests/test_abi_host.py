@@ -250,6 +250,15 @@ def test_binding_refuses_wrong_dtypes_and_extents():
         call()                                 # everything right except that these are host tensors
 
 
+def test_stream_without_torchs_undocumented_function(monkeypatch):
+    import types
+    import torch
+    asked = []
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d: asked.append(d) or types.SimpleNamespace(cuda_stream=77))
+    assert B._stream(torch.device("cuda:0")) == 77 and asked == [torch.device("cuda:0")]
+
+
 def test_bench_refuses_more_than_one_gpu():
     """The benchmark measures one GPU; asked for more it says so and exits without touching a device."""
     import subprocess
