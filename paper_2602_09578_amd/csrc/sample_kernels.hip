@@ -298,9 +298,11 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
 // pass 1 is 7 of the 4-cycle units per logit, the list pass 3.5, and ten would fill the time in
 // which the row arrives from HBM.  The second read of the row comes out of the memory-side cache
 // (three rows per CU, 234 MB of 256 at a vocabulary of 152064).  Measured on 2048 x 152064, sigma 3,
-// top_p 0.9: 196 us (two workgroups per CU 212); with the row held in registers by one workgroup per CU, a count of all values in
+// top_p 0.9: 197 us (two workgroups per CU 212); with the row held in registers by one workgroup per CU, a count of all values in
 // LDS (an LDS atomic on 64 lanes takes about 25 cycles) and a third pass over all tokens 508 us; the
 // same with the list but still in registers 316 us (nothing to overlap the short phases with).
+// Three workgroups per CU leave 80 vector registers: two are spilled (12 bytes of scratch per lane), outside the passes,
+// and 46 scalar registers to lanes of vector registers, which the counts over windows read back.
 // ---------------------------------------------------------------------------------------
 constexpr int kTpThreads = 512;
 constexpr int kTpWaves = kTpThreads / 64;
@@ -628,7 +630,7 @@ void sample_top_p_kernel(TopPArgs a) {
     const float bins_listed = 8.f * c * (xmax - value_of_key(lkey));
     int listed = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) listed += (float)(kBins - 1 - 4 * lane - e) < bins_listed ? count[e] : 0;
+    for (int e = 0; e < 4; ++e) listed += (float)(kBins - 4 * lane - e) <= bins_listed ? count[e] : 0;   // (whole bins)
     listed = from_lane(wave_inclusive_scan(listed), 63);
     const bool fits = (float)listed * (float)(most_groups * kTpGroup) <= (float)kListCap * (float)sampled;
     if (lkey >= 0x8080 && likely_key >= lkey && fits) {   // workgroup-uniform: a positive, normal cut
