@@ -45,9 +45,9 @@
 // two workgroups per CU with 141 vector and 105 scalar instructions, 1.50 with 120 and 50 (page
 // ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  256 prompts of
 // 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.58 ms (0.96 PFLOP/s; a large matrix product of this
-// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.  Memory is second: with items
+// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.  Memory is second: with an item
 // bound ahead a prompt's blocks run further apart in time than one after the other did, and the 256 prompts fetch
-// 16.7 GB instead of 8.2; with all groups on the pages of one prompt, which stay in the caches, they take 4 % less.
+// 14.8 GB instead of 8.2; with all groups on the pages of one prompt, which stay in the caches, they take 4 % less.
 #include <algorithm>
 
 #include "marl_internal.h"
