@@ -837,10 +837,10 @@ void prefill_kernel(PrefillArgs a) {   // kSplit: the list may hold parts of blo
   __shared__ PrefillLds lds;
   const int grid = (int)gridDim.x;
   const int n_work = *a.list_length * a.Hkv;
-  // A workgroup's second item: in a sorted list, and in one of at most two items per workgroup (of which none is drawn), the
-  // longest meet the shortest.  (In their order again a prompt of 3008 tokens, 64 / 8 heads, took 161.5 us instead
-  // of 150.0, two of up to 3294, 32 / 8 heads, 101.5 instead of 87.7; the counter, asked by all workgroups at once,
-  // would only delay their first items: 472 items 48.2 -> 43.4 us, 608 items 44.9 -> 40.3 us.)
+  // A workgroup's second item: in a sorted list, and in any of at most two items per workgroup, the longest first items
+  // meet the shortest second ones.  (In their order again a prompt of 3008 tokens, 64 / 8 heads, took 161.5 us instead
+  // of 150.0, two of up to 3294, 32 / 8 heads, 101.5 instead of 87.7.)  It is not drawn: the counter, asked by all
+  // workgroups at their start, delayed their first items (472 items 48.2 -> 43.4 us, 608 items 44.9 -> 40.3 us).
   // A list in group order may end with long blocks: its last two items per workgroup are not bound ahead of time but
   // drawn by whoever has nothing left to do, and start with an empty ring.  (16 prompts of up to 3801 tokens, 16 / 1
   // heads: 377 -> 332 us; 26 of up to 2024, 8 / 2 heads, 156 -> 132; 60 of up to 400, 16 / 1 heads, 63 -> 58.  In
