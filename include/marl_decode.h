@@ -156,6 +156,10 @@ int marl_workspace_bytes(const marl_attn_shape* shape, size_t* bytes);
  * the group's prefix partials and its own result and writes the output rows.  Short items of
  * sequences with several suffix chunks are taken by the prefix kernel's workgroups before they
  * start on the prefix items.
+ * Small calls (both chunk sizes left at 0, at most 512 sequences and groups, and table rows that hold at most about
+ * 1.5 M tokens x KV heads in all) are one kernel that takes prefix and own tokens of a (sequence, KV head)
+ * together, and for long rows a second one that adds up to 16 parts of a row; the work list is built beside them
+ * and left in the workspace all the same, the partials then hold those parts or nothing.
  */
 int marl_decode_attn(const marl_attn_shape* shape, void* workspace, size_t workspace_bytes,
                      const void* q, const void* k_pages, const void* v_pages,
@@ -500,7 +504,8 @@ int marl_unpack_tensors(const marl_pack_entry* entries, int32_t n, int64_t total
  * kernels on the call's stream (no synchronisation).  marl_profile_end() synchronises the
  * device, writes the average duration in milliseconds of each stage over the recorded
  * calls (MARL_STAGE_* indices; stages that never ran stay 0), the number of recorded
- * attention calls and log-prob calls, and switches recording off.
+ * attention calls and log-prob calls, and switches recording off.  The one kernel of a small attention call counts as
+ * MARL_STAGE_PREFIX, the kernel that adds its parts as MARL_STAGE_MERGE.
  */
 enum {
   MARL_STAGE_PLAN = 0, MARL_STAGE_PREFIX = 1, MARL_STAGE_SUFFIX = 2, MARL_STAGE_MERGE = 3,

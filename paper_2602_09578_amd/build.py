@@ -11,7 +11,7 @@ _ROOT = os.path.dirname(_PKG)
 CSRC = os.path.join(_PKG, "csrc")
 LIB_DIR = os.path.join(_PKG, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libmarl_decode.so")
-SOURCES = ["api.hip", "plan_kernel.hip", "attn_kernels.hip", "logprob_kernels.hip",
+SOURCES = ["api.hip", "plan_kernel.hip", "attn_kernels.hip", "attn_small_kernel.hip", "logprob_kernels.hip",
            "kv_cache_kernels.hip", "sample_kernels.hip", "grpo_kernels.hip", "prefill_kernels.hip", "balancer.hip", "pack_kernels.hip", "page_pool.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -22,7 +22,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 # the canonicalising v_max it otherwise puts in front of every maximum of a matrix-core result:
 # the vector ALU is the busiest unit of the attention kernels.  Host code keeps its NaN checks.
 _NO_NANS = ["-Xarch_device", "-fno-honor-nans"]
-FILE_FLAGS = {"prefill_kernels.hip": _NO_NANS, "attn_kernels.hip": _NO_NANS}
+FILE_FLAGS = {"prefill_kernels.hip": _NO_NANS, "attn_kernels.hip": _NO_NANS, "attn_small_kernel.hip": _NO_NANS}
 
 
 def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PATH) -> str:

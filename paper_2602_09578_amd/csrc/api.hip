@@ -221,9 +221,12 @@ int take_attn_operands(marl::AttnArgs& a, const void* q, const void* k_pages, co
   return MARL_OK;
 }
 
+bool default_chunks(const marl_attn_shape* s) { return s->suffix_chunk_tokens == 0 && s->prefix_chunk_tokens == 0; }
+
 // Enqueues the kernels of one decode-attention call.  `may_time`: the call takes part in the
 // per-kernel event timing when that is switched on (events are created then).
-int enqueue_decode_attn(const marl::AttnArgs& a, hipStream_t st, bool may_time) {
+// default_chunks: the caller left both chunk sizes to the library (one that names them wants them).
+int enqueue_decode_attn(marl::AttnArgs& a, bool default_chunks, hipStream_t st, bool may_time) {
   std::call_once(g_dev_once, query_device);
   if (g_dev_err != hipSuccess) return hip_fail(g_dev_err, "device query");
 
@@ -236,6 +239,13 @@ int enqueue_decode_attn(const marl::AttnArgs& a, hipStream_t st, bool may_time) 
   }
   StageTimer T(st, timed);
   hipError_t e;
+  if (default_chunks && (a.splits = marl::small_attn_splits(a)) > 0) {
+    if ((e = T.run(MARL_STAGE_PREFIX, [&] { return marl::launch_small_attn(a, st); })) != hipSuccess)
+      return hip_fail(e, "small attention kernel");
+    if (a.splits > 1 && (e = T.run(MARL_STAGE_MERGE, [&] { return marl::launch_merge_parts(a, st); })) != hipSuccess)
+      return hip_fail(e, "merge kernel");
+    return MARL_OK;
+  }
   if ((e = T.run(MARL_STAGE_PLAN, [&] { return marl::launch_plan(a, st); })) != hipSuccess)
     return hip_fail(e, "plan kernel");
   {  // always launched: its workgroups also process the short suffix items
@@ -340,7 +350,7 @@ int marl_decode_attn(const marl_attn_shape* shape, void* workspace, size_t works
                           suffix_lens, group_of_seq, scale, out);
   if (rc != MARL_OK) return rc;
   if (a.NS == 0) return MARL_OK;
-  return enqueue_decode_attn(a, static_cast<hipStream_t>(stream), /*may_time=*/true);
+  return enqueue_decode_attn(a, default_chunks(shape), static_cast<hipStream_t>(stream), /*may_time=*/true);
 }
 
 int marl_decode_attn_static(const marl_attn_shape* shape,
@@ -373,7 +383,7 @@ int marl_decode_attn_static(const marl_attn_shape* shape,
   rc = static_scratch_of_current_device(&ws);
   if (rc != MARL_OK) return rc;
   point_workspace(L, ws, a);   // the plan kernel clears the counters and flags it finds there
-  rc = enqueue_decode_attn(a, st, /*may_time=*/false);
+  rc = enqueue_decode_attn(a, default_chunks(shape), st, /*may_time=*/false);
   if (rc != MARL_OK) return rc;
   if (flags) {
     const hipError_t e = hipMemcpyAsync(flags, a.counters + MARL_CTR_FLAGS, sizeof(int32_t),

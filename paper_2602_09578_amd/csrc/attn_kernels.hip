@@ -3,7 +3,7 @@
 // sequence's own generated tokens) and the merge kernel.  The first two produce
 // flash-decoding style partials (running max, running sum, unnormalised output) per (query
 // row, chunk of tokens), which the merge kernel combines; a sequence whose own tokens are a
-// single work item is finished by whoever processes that item instead.
+// single work item is finished by whoever processes that item instead.  (Small calls: attn_small_kernel.hip.)
 //
 // Context in the paper: rollout is memory-bound on KV caches (Section 4.1), every prompt is
 // expanded into several samples that share its prefix (Section 5.1) and lengths are skewed

@@ -18,6 +18,7 @@ constexpr int kRowsPerQBlockWide = 256;   // ... in the wide kernel
 #endif
 constexpr int kShortTokens = MARL_SHORT_TOKENS;
 constexpr int kAttnThreads = 256;  // 4 waves per workgroup
+constexpr int kSmallAttnSeqs = 512;   // most sequences, and groups, of a call that the small kernel serves
 constexpr int kPlanThreads = 1024;
 constexpr int kNumClasses = 2048;  // upper bound on cost classes (chunk / 32)
 
@@ -48,6 +49,7 @@ struct AttnArgs {
   int32_t Cs, Cp, NCs, NCp;
   int32_t qblock_rows;   // kRowsPerQBlock or kRowsPerQBlockWide
   int32_t out_dtype;
+  int32_t splits;        // small calls only
   float scale;
 };
 
@@ -55,6 +57,10 @@ hipError_t launch_plan(const AttnArgs& a, hipStream_t st);
 hipError_t launch_prefix(const AttnArgs& a, int grid, hipStream_t st);
 hipError_t launch_suffix(const AttnArgs& a, int grid, hipStream_t st);
 hipError_t launch_merge(const AttnArgs& a, hipStream_t st);
+// Parts into which a small call divides each sequence's tokens, 0 where the call is left to the kernels above.
+int small_attn_splits(const AttnArgs& a);
+hipError_t launch_small_attn(const AttnArgs& a, hipStream_t st);
+hipError_t launch_merge_parts(const AttnArgs& a, hipStream_t st);
 int prefix_blocks_per_cu(bool wide);
 int suffix_blocks_per_cu();
 

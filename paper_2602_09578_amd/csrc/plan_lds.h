@@ -1,0 +1,307 @@
+// The plan of a decode-attention call (group -> sequences CSR, the two work lists) built by one workgroup with its
+// bookkeeping in LDS: device code shared by the plan kernels and by the kernel that serves a small call alone.
+#ifndef MARL_PLAN_LDS_H
+#define MARL_PLAN_LDS_H
+#include "marl_internal.h"
+#include "wave_ops.h"
+
+namespace marl {
+namespace {
+
+__device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+__device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
+
+// Inside the vector ALU: shifts by 1, 2, 4, 8 within the rows of 16 lanes, then the last lane of a row to
+// the row behind it and of the first half to the second (six shuffles through the LDS crossbar are six
+// dependent round trips).
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+__device__ __forceinline__ int wave_sum(int v) {
+  return wave_allreduce(v, [](int x, int y) { return x + y; });
+}
+
+__device__ __forceinline__ int clamp_len(int v, int hi, int& flags) {
+  const int c = min(max(v, 0), hi);
+  if (c != v) flags |= MARL_FLAG_LEN_CLAMPED;
+  return c;
+}
+
+// ---------------------------------------------------------------------------------------
+// Same plan for shapes whose bookkeeping fits in LDS (NS <= 8192, NG <= 2048, chunks <= 8192
+// tokens): inputs are read once into registers, counts, offsets, member lists and histograms
+// live in LDS, and global memory only sees the final stores.  The general plan kernel pays
+// a chain of ~30 dependent global round trips; this one pays one.  What bounds it is the chain of
+// barriers and LDS round trips of its one workgroup: the three scans (groups, suffix and prefix classes)
+// share one pass and stay in the vector ALU.  16 sequences 9.9 -> 7.2 us, 2048 sequences 12.0 -> 9.9 us (13.5 where
+// they are of two cost classes: atomics on the same word), launch included; the former time had a block-wide scan
+// with shuffles and three barriers for each of the three.
+// ---------------------------------------------------------------------------------------
+// Two sizes: up to 8192 sequences in 2048 groups (56 KB of LDS), and up to 32768 sequences in
+// 8192 groups with 16-bit member ids (130 KB of the 160 KB).
+constexpr int kSmallMaxClasses = 256;
+
+// kCheckPages: the plan's workgroup also looks for block-table entries outside the pool among those of addressed
+// tokens (where nobody else reports them); at most a few entries per thread are expected.
+template <int kThreads, int kSmallMaxSeqs, int kSmallMaxGroups, class MemberId, bool kCheckPages = false>
+__device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
+  constexpr int kSeqsPerThread = kSmallMaxSeqs / kThreads;
+  constexpr int kGroupsPerThread = kSmallMaxGroups / kThreads;
+  __shared__ int cnt[kSmallMaxGroups];
+  __shared__ int start[kSmallMaxGroups];
+  __shared__ MemberId members[kSmallMaxSeqs];
+  __shared__ int hist_s[kSmallMaxClasses];
+  __shared__ int hist_p[kSmallMaxClasses];
+  __shared__ int tmp[kThreads / 64];
+  __shared__ int n_long_items, n_short_partial_items, n_suffix_items, n_prefix_items;
+  // clamped prefix lengths, where there is room for them (else they are re-read from global memory)
+  constexpr bool kPrefixLensInLds = kSmallMaxGroups <= 2048;
+  __shared__ int prefix_len[kPrefixLensInLds ? kSmallMaxGroups : 1];
+  const int tid = threadIdx.x;
+  const int Cs = a.Cs, Cp = a.Cp, R = a.R, QB = a.qblock_rows;
+  const int max_st = a.max_sp * kPage, max_pt = a.max_pp * kPage;
+  int flags = 0;
+
+  // inputs -> registers (the only loads from global memory).  The larger size has no room for
+  // 3 x 32 values per thread: it keeps only the ranks and re-reads group ids and lengths (cache
+  // hits) in the later phases.
+  constexpr bool kKeep = kSeqsPerThread <= 8;
+  int g_keep[kKeep ? kSeqsPerThread : 1], S_keep[kKeep ? kSeqsPerThread : 1], rank_of[kSeqsPerThread];
+  if constexpr (kKeep) {
+#pragma unroll
+    for (int k = 0; k < kSeqsPerThread; ++k) {
+      const int s = tid + k * kThreads;
+      g_keep[k] = s < a.NS ? a.group_of_seq[s] : -1;
+      S_keep[k] = s < a.NS ? a.suffix_lens[s] : 0;
+    }
+  }
+  int ignored = 0;
+  auto G = [&](int k) {   // group id of this thread's k-th sequence (only called for s < NS)
+    if constexpr (kKeep) return g_keep[k]; else return a.group_of_seq[tid + k * kThreads];
+  };
+  auto S_len = [&](int k) {   // its clamped suffix length
+    if constexpr (kKeep) return S_keep[k]; else return clamp_len(a.suffix_lens[tid + k * kThreads], max_st, ignored);
+  };
+  int P_of[kGroupsPerThread];
+#pragma unroll
+  for (int k = 0; k < kGroupsPerThread; ++k) {
+    const int g = tid + k * kThreads;
+    P_of[k] = g < a.NG ? a.prefix_lens[g] : 0;
+  }
+  for (int i = tid; i < kSmallMaxGroups; i += kThreads) cnt[i] = 0;
+  for (int i = tid; i < kSmallMaxClasses; i += kThreads) { hist_s[i] = 0; hist_p[i] = 0; }
+  if (tid == 0) { n_long_items = 0; n_short_partial_items = 0; }
+  if (tid < 64) a.counters[tid] = 0;
+  __syncthreads();
+
+  // full chunks and long items are counted per thread and added once per wave: nearly every
+  // sequence contributes to these two words, and same-address LDS atomics run one lane at a time
+  int nfull_mine = 0, nlong_mine = 0, nshort_partial_mine = 0;
+#pragma unroll
+  for (int k = 0; k < kSeqsPerThread; ++k) {
+    const int s = tid + k * kThreads;
+    rank_of[k] = -1;
+    if (s < a.NS) {
+      const int g = G(k);
+      if ((unsigned)g < (unsigned)a.NG) rank_of[k] = atomicAdd(&cnt[g], 1);
+      else flags |= MARL_FLAG_BAD_GROUP;
+      int S;
+      if constexpr (kKeep) S = S_keep[k] = clamp_len(S_keep[k], max_st, flags);
+      else S = clamp_len(a.suffix_lens[s], max_st, flags);
+      const int nfull = S / Cs, tail = S % Cs;
+      nfull_mine += nfull;
+      if (tail) atomicAdd(&hist_s[(Cs - tail) / 32], 1);
+      nlong_mine += (Cs > kShortTokens ? nfull : 0) + (tail > kShortTokens ? 1 : 0);
+    // short items (at most kShortTokens tokens) of sequences with several suffix chunks: they become partials
+    if (nfull + (tail > 0) >= 2)
+      nshort_partial_mine += (Cs <= kShortTokens ? nfull : 0) + ((tail > 0 && tail <= kShortTokens) ? 1 : 0);
+    }
+  }
+  nfull_mine = wave_sum(nfull_mine);
+  nlong_mine = wave_sum(nlong_mine);
+  nshort_partial_mine = wave_sum(nshort_partial_mine);
+  if (lane_id() == 0) {
+    if (nfull_mine) atomicAdd(&hist_s[0], nfull_mine);
+    if (nlong_mine) atomicAdd(&n_long_items, nlong_mine);
+    if (nshort_partial_mine) atomicAdd(&n_short_partial_items, nshort_partial_mine);
+  }
+  __syncthreads();
+
+  // prefix items by class; the counts' sums inside a wave (thread t: groups kGroupsPerThread t ..)
+#pragma unroll
+  for (int k = 0; k < kGroupsPerThread; ++k) {
+    const int g = tid + k * kThreads;
+    if (g < a.NG) {
+      P_of[k] = clamp_len(P_of[k], max_pt, flags);
+      if constexpr (kPrefixLensInLds) prefix_len[g] = P_of[k];
+      const int nqb = (cnt[g] * R + QB - 1) / QB;
+      const int nfull = P_of[k] / Cp, tail = P_of[k] % Cp;
+      if (nqb) {
+        if (nfull) atomicAdd(&hist_p[0], nfull * nqb);
+        if (tail) atomicAdd(&hist_p[(Cp - tail) / 32], nqb);
+      }
+    }
+  }
+  int own = 0;
+#pragma unroll
+  for (int k = 0; k < kGroupsPerThread; ++k) own += cnt[tid * kGroupsPerThread + k];   // (zero from NG on)
+  const int own_end = wave_inclusive_scan(own);
+  if (lane_id() == 63) tmp[wave_id()] = own_end;
+  __syncthreads();
+
+  // starts of the groups, of the suffix classes (wave 0) and of the prefix classes (wave 1); afterwards
+  // the histograms serve as per-class cursors
+  constexpr int kPlanWaves = kThreads / 64;
+  const int upto = wave_inclusive_scan(lane_id() < kPlanWaves ? tmp[lane_id()] : 0);
+  const int nseq_grouped = __builtin_amdgcn_readlane(upto, kPlanWaves - 1);
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave_id());
+  int at = own_end - own + (wave_s > 0 ? __builtin_amdgcn_readlane(upto, wave_s - 1) : 0);
+#pragma unroll
+  for (int k = 0; k < kGroupsPerThread; ++k) {
+    start[tid * kGroupsPerThread + k] = at;
+    at += cnt[tid * kGroupsPerThread + k];
+  }
+  if (wave_s < 2) {
+    constexpr int kPer = kSmallMaxClasses / 64;
+    int* hist = (wave_s == 0 ? hist_s : hist_p) + lane_id() * kPer;
+    int v[kPer], mine = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) mine += v[k] = hist[k];   // (zero from the number of classes on)
+    const int end = wave_inclusive_scan(mine);
+    int first = end - mine;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      hist[k] = first;
+      first += v[k];
+    }
+    if (lane_id() == 63) (wave_s == 0 ? n_suffix_items : n_prefix_items) = end;
+  }
+  __syncthreads();
+
+#pragma unroll
+  for (int k = 0; k < kSeqsPerThread; ++k) {
+    const int s = tid + k * kThreads;
+    if (s < a.NS) {
+      const int g = G(k);
+      if (rank_of[k] >= 0) members[start[g] + rank_of[k]] = (MemberId)s;
+      const int S = S_len(k);
+      int P = 0;
+      if (rank_of[k] >= 0) {
+        int dummy = 0;
+        if constexpr (kPrefixLensInLds) P = prefix_len[g];
+        else P = clamp_len(a.prefix_lens[g], max_pt, dummy);
+      }
+      a.seq_chunks[s] = ((P + Cp - 1) / Cp) | (((S + Cs - 1) / Cs) << 16);
+      const int nfull = S / Cs, tail = S % Cs;
+      if (nfull) {
+        const int pos = atomicAdd(&hist_s[0], nfull);
+        for (int i = 0; i < nfull; ++i) a.suffix_items[pos + i] = make_int4(s, i * Cs, (i + 1) * Cs, 0);
+      }
+      if (tail) {
+        const int pos = atomicAdd(&hist_s[(Cs - tail) / 32], 1);
+        a.suffix_items[pos] = make_int4(s, nfull * Cs, S, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kGroupsPerThread; ++k) {
+    const int g = tid + k * kThreads;
+    if (g < a.NG) {
+      a.group_count[g] = cnt[g];
+      a.group_start[g] = start[g];
+      const int P = P_of[k];
+      const int nqb = (cnt[g] * R + QB - 1) / QB;
+      const int nfull = P / Cp, tail = P % Cp;
+      if (nqb) {
+        if (nfull) {
+          const int pos = atomicAdd(&hist_p[0], nfull * nqb);
+          for (int i = 0; i < nfull; ++i)
+            for (int b = 0; b < nqb; ++b)
+              a.prefix_items[pos + i * nqb + b] = make_int4(g, i * Cp, (i + 1) * Cp, b * QB);
+        }
+        if (tail) {
+          const int pos = atomicAdd(&hist_p[(Cp - tail) / 32], nqb);
+          for (int b = 0; b < nqb; ++b)
+            a.prefix_items[pos + b] = make_int4(g, nfull * Cp, P, b * QB);
+        }
+      }
+    }
+  }
+  if (tid == 0) a.group_start[a.NG] = nseq_grouped;
+  __syncthreads();
+
+  // ascending sequence id inside every group of at most 64 members (as in the general kernel)
+#pragma unroll
+  for (int k = 0; k < kSeqsPerThread; ++k) {
+    const int s = tid + k * kThreads;
+    if (s < a.NS && rank_of[k] >= 0) {
+      const int g = G(k);
+      const int b = start[g], n = cnt[g];
+      int place = rank_of[k];
+      if (n <= 64) {
+        place = 0;
+        for (int m0 = 0; m0 < n; m0 += 8) {   // (eight reads in flight)
+          int v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = (int)members[b + min(m0 + u, n - 1)];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) place += m0 + u < n && v[u] < s;
+        }
+      }
+      a.group_seqs[b + place] = s;
+    }
+  }
+  if constexpr (kCheckPages) {
+    static_assert(kPrefixLensInLds && kKeep, "lengths at hand");
+    __shared__ int suffix_len[kSmallMaxSeqs];
+#pragma unroll
+    for (int k = 0; k < kSeqsPerThread; ++k)
+      if (tid + k * kThreads < a.NS) suffix_len[tid + k * kThreads] = S_keep[k];
+    __syncthreads();
+    // (the whole table in 16-byte pieces: its rows may be tens of thousands of entries for this one workgroup)
+    auto check = [&](const int32_t* table, int rows, int pages, auto&& tokens) {
+      typedef int int4_any __attribute__((ext_vector_type(4), aligned(4)));
+      constexpr int kAtOnce = 8;
+      const int n = rows * pages;
+      auto look = [&](int e, int id) {
+        const int row = e / pages;
+        if ((e - row * pages) * kPage < tokens(row) && (unsigned)id >= (unsigned)a.num_pages) flags |= MARL_FLAG_BAD_PAGE;
+      };
+      for (int p0 = tid; p0 < n / 4; p0 += kAtOnce * kThreads) {
+        int4_any ids[kAtOnce];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) ids[u] = *reinterpret_cast<const int4_any*>(table + 4 * min(p0 + u * kThreads, n / 4 - 1));
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+          const int p = min(p0 + u * kThreads, n / 4 - 1);
+          // (entries past a row's pages are -1 by convention: only pieces with an id outside the pool are looked at)
+          if (max(max((unsigned)ids[u][0], (unsigned)ids[u][1]), max((unsigned)ids[u][2], (unsigned)ids[u][3])) >= (unsigned)a.num_pages) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) look(4 * p + e, ids[u][e]);
+          }
+        }
+      }
+      if (tid < (n & 3)) look((n & ~3) + tid, table[(n & ~3) + tid]);
+    };
+    check(a.suffix_table, a.NS, a.max_sp, [&](int s) { return suffix_len[s]; });
+    check(a.prefix_table, a.NG, a.max_pp, [&](int g) { return cnt[g] ? prefix_len[g] : 0; });
+  }
+  if (flags) atomicOr(&a.counters[MARL_CTR_FLAGS], flags);
+  if (tid == 0) {
+    a.counters[MARL_CTR_NUM_SUFFIX_ITEMS] = n_suffix_items;
+    a.counters[MARL_CTR_NUM_PREFIX_ITEMS] = n_prefix_items;
+    a.counters[MARL_CTR_NUM_LONG_SUFFIX_ITEMS] = n_long_items;
+    a.counters[MARL_CTR_NUM_SHORT_PARTIAL_ITEMS] = n_short_partial_items;
+  }
+}
+
+}  // namespace
+}  // namespace marl
+#endif  // MARL_PLAN_LDS_H
