@@ -91,6 +91,12 @@ def dominant_kernel_roofline(w, attn, call, stage_ms):
     Cs = call.layout.suffix_chunk_tokens
     tail = S % Cs
     long_tok = int(((S // Cs) * Cs * (Cs > 128) + tail * (tail > 128)).sum())
+    if stage_ms["prefix"] == 0:   # prefix items and long suffix items share a launch
+        all_bytes = (long_tok + int(attn.prefix_lens.sum())) * bpt
+        gbps = all_bytes / (stage_ms["suffix"] * 1e-3) / 1e9
+        return {"kernel": "items_kernel", "bound": "hbm", "achieved": gbps, "peak": HBM_PEAK_GBPS,
+                "unit": "GB/s", "frac": gbps / HBM_PEAK_GBPS, "traffic": None,
+                "algorithmic_bytes_per_launch": all_bytes, "avg_launch_ms": stage_ms["suffix"]}
     if long_tok and stage_ms["suffix"] >= stage_ms["prefix"]:
         gbps = long_tok * bpt / (stage_ms["suffix"] * 1e-3) / 1e9
         return {"kernel": "suffix_kernel", "bound": "hbm", "achieved": gbps, "peak": HBM_PEAK_GBPS,

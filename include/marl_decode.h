@@ -93,8 +93,9 @@ enum {
   MARL_CTR_FLAGS = 4,            /* MARL_FLAG_* bits set by the kernels */
   MARL_CTR_NUM_LONG_SUFFIX_ITEMS = 5, /* suffix items of more than 128 tokens: they head the list */
   MARL_CTR_SHORT_CURSOR = 6,     /* work-queue cursor of the remaining (short) suffix items */
-  MARL_CTR_NUM_SHORT_PARTIAL_ITEMS = 7 /* suffix items of at most 128 tokens that belong to sequences with
+  MARL_CTR_NUM_SHORT_PARTIAL_ITEMS = 7, /* suffix items of at most 128 tokens that belong to sequences with
                                      several suffix chunks (the only short items that become partials) */
+  MARL_CTR_NUM_FIRST_SUFFIX_ITEMS = 8 /* suffix items at the head of the list that are taken before the prefix items */
 };
 enum {
   MARL_FLAG_BAD_GROUP = 1,       /* a group_of_seq entry was outside [0, NG) */
@@ -156,6 +157,8 @@ int marl_workspace_bytes(const marl_attn_shape* shape, size_t* bytes);
  * the group's prefix partials and its own result and writes the output rows.  Short items of
  * sequences with several suffix chunks are taken by the prefix kernel's workgroups before they
  * start on the prefix items.
+ * Calls of up to 6144 (sequence, KV head) pairs take the items of both lists in one kernel; there the own tokens of
+ * a sequence with a prefix are always a partial (but for the short items that the merge kernel finishes).
  * Small calls (both chunk sizes left at 0, at most 512 sequences and groups, and table rows that hold at most about
  * 1.5 M tokens x KV heads in all) are one kernel that takes prefix and own tokens of a (sequence, KV head)
  * together, and for long rows a second one that adds up to 16 parts of a row; the work list is built beside them
@@ -505,7 +508,8 @@ int marl_unpack_tensors(const marl_pack_entry* entries, int32_t n, int64_t total
  * device, writes the average duration in milliseconds of each stage over the recorded
  * calls (MARL_STAGE_* indices; stages that never ran stay 0), the number of recorded
  * attention calls and log-prob calls, and switches recording off.  The one kernel of a small attention call counts as
- * MARL_STAGE_PREFIX, the kernel that adds its parts as MARL_STAGE_MERGE.
+ * MARL_STAGE_PREFIX, the kernel that adds its parts as MARL_STAGE_MERGE, the kernel that takes prefix and suffix items as
+ * MARL_STAGE_SUFFIX (as MARL_STAGE_PREFIX where no suffix item can be long).
  */
 enum {
   MARL_STAGE_PLAN = 0, MARL_STAGE_PREFIX = 1, MARL_STAGE_SUFFIX = 2, MARL_STAGE_MERGE = 3,

@@ -132,7 +132,7 @@ struct StageTimer {
   }
 };
 
-int g_num_cus = 0, g_prefix_bpc = 0, g_prefix_wide_bpc = 0, g_suffix_bpc = 0;
+int g_num_cus = 0, g_prefix_bpc = 0, g_prefix_wide_bpc = 0, g_suffix_bpc = 0, g_items_bpc = 0, g_items_wide_bpc = 0;
 
 std::once_flag g_dev_once;
 hipError_t g_dev_err = hipSuccess;
@@ -148,6 +148,8 @@ void query_device() {
   g_prefix_bpc = marl::prefix_blocks_per_cu(false);
   g_prefix_wide_bpc = marl::prefix_blocks_per_cu(true);
   g_suffix_bpc = marl::suffix_blocks_per_cu();
+  g_items_bpc = marl::items_blocks_per_cu(false);
+  g_items_wide_bpc = marl::items_blocks_per_cu(true);
 }
 
 // Points the workspace arrays of `a` into `ws` as the layout says.
@@ -221,6 +223,9 @@ int take_attn_operands(marl::AttnArgs& a, const void* q, const void* k_pages, co
   return MARL_OK;
 }
 
+// The suffix kernel takes the items of more than kShortTokens tokens: none can exist when neither a table row nor a
+// chunk holds that many.
+bool can_have_long_items(const marl::AttnArgs& a) { return (long)a.max_sp * marl::kPage > marl::kShortTokens && a.Cs > marl::kShortTokens; }
 bool default_chunks(const marl_attn_shape* s) { return s->suffix_chunk_tokens == 0 && s->prefix_chunk_tokens == 0; }
 
 // Enqueues the kernels of one decode-attention call.  `may_time`: the call takes part in the
@@ -248,13 +253,21 @@ int enqueue_decode_attn(marl::AttnArgs& a, bool default_chunks, hipStream_t st, 
   }
   if ((e = T.run(MARL_STAGE_PLAN, [&] { return marl::launch_plan(a, st); })) != hipSuccess)
     return hip_fail(e, "plan kernel");
+  const bool wide = a.qblock_rows == marl::kRowsPerQBlockWide;
+  a.one_queue = (long)a.NS * a.Hkv <= marl::kOneQueueItems;
+  if (a.one_queue) {
+    if ((e = T.run(a.NG > 0 && a.max_pp > 0 && !can_have_long_items(a) ? MARL_STAGE_PREFIX : MARL_STAGE_SUFFIX,
+                   [&] { return marl::launch_items(a, g_num_cus * (wide ? g_items_wide_bpc : g_items_bpc), st); })) != hipSuccess)
+      return hip_fail(e, "items kernel");
+    if ((e = T.run(MARL_STAGE_MERGE, [&] { return marl::launch_merge(a, st); })) != hipSuccess)
+      return hip_fail(e, "merge kernel");
+    return MARL_OK;
+  }
   {  // always launched: its workgroups also process the short suffix items
-    if ((e = T.run(MARL_STAGE_PREFIX, [&] { return marl::launch_prefix(a, g_num_cus * (a.qblock_rows == marl::kRowsPerQBlockWide ? g_prefix_wide_bpc : g_prefix_bpc), st); })) != hipSuccess)
+    if ((e = T.run(MARL_STAGE_PREFIX, [&] { return marl::launch_prefix(a, g_num_cus * (wide ? g_prefix_wide_bpc : g_prefix_bpc), st); })) != hipSuccess)
       return hip_fail(e, "prefix kernel");
   }
-  // the suffix kernel takes the items of more than kShortTokens tokens: none can exist when
-  // neither a table row nor a chunk holds that many
-  if ((long)a.max_sp * marl::kPage > marl::kShortTokens && a.Cs > marl::kShortTokens) {
+  if (can_have_long_items(a)) {
     if ((e = T.run(MARL_STAGE_SUFFIX, [&] { return marl::launch_suffix(a, g_num_cus * g_suffix_bpc, st); })) != hipSuccess)
       return hip_fail(e, "suffix kernel");
   }

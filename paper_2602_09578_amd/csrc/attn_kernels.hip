@@ -383,6 +383,7 @@ void suffix_kernel(AttnArgs a) {
   for (bool first = true;; first = false) {
     int qi = blockIdx.x;
     if (!first) {
+      if (n_work <= (int)gridDim.x) break;   // every item has a workgroup of its own: no draw
       if (threadIdx.x == 0) next_item = gridDim.x + atomicAdd(&a.counters[MARL_CTR_SUFFIX_CURSOR], 1);
       __syncthreads();
       qi = next_item;
@@ -500,10 +501,11 @@ __device__ __forceinline__ void prefix_item(const AttnArgs& a, const int4 it, co
   // this half's tiles: a block of at most eight tiles is not divided (its keys are then read once)
   constexpr int kBlockRows = kHalves ? kRowsPerQBlockWide : kRowsPerQBlock;
   const int nrows = ld_uniform(a.group_count + g) * a.R;
+  const int gstart = ld_uniform(a.group_start + g);
   const int tiles_all = (min(kBlockRows, nrows - it.w) + 15) >> 4;
   const int tiles0 = tiles_all <= MTW * NW ? tiles_all : (tiles_all + 1) >> 1;
   const int tiles = half ? tiles_all - tiles0 : tiles0;
-  if (tiles <= 0) return;                                    // workgroup-uniform
+  if (kHalves && tiles <= 0) return;                         // workgroup-uniform (a first half is never empty)
   const int row_begin = it.w + (half ? tiles0 * 16 : 0);
   const int nt = tiles > wave + NW ? 2 : tiles > wave ? 1 : 0;   // wave-uniform: tiles wave, wave + 4
 
@@ -557,7 +559,6 @@ __device__ __forceinline__ void prefix_item(const AttnArgs& a, const int4 it, co
   }
   fetch_ids(kPrefixStages - 1);
 
-  const int gstart = a.group_start[g];
   const float sc = fmaxf(fabsf(a.scale) * 1.44269504088896340736f, 1e-30f);
   const uint32_t sign_flip = a.scale < 0.f ? 0x80008000u : 0u;
   const int nslot = a.NCp + a.NCs;
@@ -753,6 +754,7 @@ __device__ __forceinline__ void prefix_kernel_body(const AttnArgs& a) {
   for (bool first = true;; first = false) {   // first item = block index, as in the suffix kernel
     int qi = blockIdx.x;
     if (!first) {
+      if (n_queue <= (int)gridDim.x) break;   // every entry has a workgroup of its own: no draw (hundreds of atomics on one word)
       if (threadIdx.x == 0) next_item = gridDim.x + atomicAdd(&a.counters[MARL_CTR_PREFIX_CURSOR], 1);
       __syncthreads();
       qi = next_item;
@@ -776,6 +778,69 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void prefix_kernel(AttnArgs a) { prefix_kernel_body<false>(a); }
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void prefix_kernel_wide(AttnArgs a) { prefix_kernel_body<true>(a); }
+
+// ---------------------------------------------------------------------------------------
+// Items kernel: prefix and suffix items of calls of up to kOneQueueItems (sequence, KV head) pairs in one launch.
+// Apart, the two kernels leave most of the GPU idle while the last items of the one and the first loads of
+// the other are on their way; together they fill each other's gaps: 64 sequences in 4 groups, 64 / 8 heads, 512-2048 + about
+// 1200 tokens: 25 + 54 us apart, 56 us in one.  Mean gain over 1371 random batches by the call's time: 15 % below 100 us,
+// 13 % to 200, 6 % to 400.  From about 6144 pairs on there are enough items to fill the GPU, and the suffix kernel's
+// three workgroups per CU (here two, for the prefix items' registers and LDS) are the better use of it: 1002 us apart and
+// 1038 here for 2048 sequences x 4 KV heads, mean of that size 1.03, above 16384 0.96.
+// One queue: the head of the suffix list, then the prefix items, then the other suffix items, so that the items that take
+// longest come first (a prefix token keeps a workgroup busy about four times as long as a token of a suffix
+// item, whose steps the waves share; the plan counts the head by that).  A sequence's suffix item may be done before
+// the group's prefix partials are, so it is always left as a partial (but for sequences without a prefix) and the
+// merge kernel adds them.  (Row tiles of the prefix as further suffix-like items, without the LDS ring: 88 instead of
+// 72 us for the attention of the batch above, up to three times the time where groups are large.  Two steps in
+// flight per wave, for which there are registers: 2-3 % slower, by batches of short items.)
+// ---------------------------------------------------------------------------------------
+template <bool kWide>
+__device__ __forceinline__ void items_kernel_body(const AttnArgs& a) {
+  __shared__ union { PrefixLds ring; ItemLds<1> item; } lds;
+  __shared__ int next_item;
+  const int n_long = a.counters[MARL_CTR_NUM_LONG_SUFFIX_ITEMS] * a.Hkv;
+  // short items become partials only where their sequence has several chunks; the merge kernel takes the others
+  const int n_suffix = a.counters[MARL_CTR_NUM_SHORT_PARTIAL_ITEMS] > 0 ? a.counters[MARL_CTR_NUM_SUFFIX_ITEMS] * a.Hkv : n_long;
+  const int pairs = a.counters[MARL_CTR_NUM_PREFIX_ITEMS] * a.Hkv;
+  const int n_prefix = kWide ? (pairs + 7) / 8 * 16 : pairs;   // (halves of a wide block meet on an XCD, as in prefix_kernel_body)
+  const int head = a.counters[MARL_CTR_NUM_FIRST_SUFFIX_ITEMS] * a.Hkv;
+  const int i = threadIdx.x & 15;
+  int bad_page = 0;
+  for (int e = blockIdx.x; e < n_prefix + n_suffix;) {   // workgroup-uniform
+    if (e >= head && e < head + n_prefix) {
+      const int qi = e - head;
+      if constexpr (kWide) {
+        const int pair = (qi >> 4) * 8 + (qi & 7);
+        if (pair < pairs) prefix_item<true>(a, a.prefix_items[pair / a.Hkv], pair % a.Hkv, (qi >> 3) & 1, lds.ring, bad_page);
+      } else {
+        prefix_item<false>(a, a.prefix_items[qi / a.Hkv], qi % a.Hkv, 0, lds.ring, bad_page);
+      }
+    } else {
+      const int qi = e < head ? e : e - n_prefix;
+      const int4 it = a.suffix_items[qi / a.Hkv];
+      const int kvh = qi % a.Hkv;
+      const int s = it.x;
+      const int row_index[1] = {i < a.R ? s * a.Hq + kvh * a.R + i : -1};
+      const int chunks = ld_uniform(a.seq_chunks + s);
+      if (qi < n_long || chunks >> 16 != 1)
+        process_item<1, kSuffixWaves>(a, a.suffix_table + (size_t)s * a.max_sp, it.y, it.z, kvh, row_index,
+                                      a.NCp + it.y / a.Cs, lds.item, bad_page, chunks == 1 << 16, 0);
+    }
+    if (n_prefix + n_suffix <= (int)gridDim.x) break;   // every item has a workgroup of its own
+    if (threadIdx.x == 0) next_item = gridDim.x + atomicAdd(&a.counters[MARL_CTR_SUFFIX_CURSOR], 1);
+    __syncthreads();
+    e = next_item;
+    __syncthreads();
+  }
+  if (bad_page) atomicOr(&a.counters[MARL_CTR_FLAGS], MARL_FLAG_BAD_PAGE);
+}
+
+static_assert(kSuffixWaves == 4, "prefix and suffix items share workgroups");
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void items_kernel(AttnArgs a) { items_kernel_body<false>(a); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void items_kernel_wide(AttnArgs a) { items_kernel_body<true>(a); }
 
 // ---------------------------------------------------------------------------------------
 // Merge kernel: the second reduction of split-KV decode attention.  For every (sequence,
@@ -802,6 +867,7 @@ void merge_kernel(AttnArgs a) {
   // where every row is finished with them a workgroup is one load long instead of two)
   const int row = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 5);
   const int info = row < a.NS * a.Hq ? a.seq_chunks[row / a.Hq] : 0x10000;
+  const int own = a.one_queue && row < a.NS * a.Hq ? min(a.suffix_lens[row / a.Hq], a.max_sp * kPage) : 0;
   // first the sequences whose own tokens are one short item: attention over those tokens and
   // the merge with the group's prefix partials in one go, one item per wave
   {
@@ -812,8 +878,8 @@ void merge_kernel(AttnArgs a) {
   const int sub = threadIdx.x & 31;   // lane within the half wave: channels 4*sub .. 4*sub+3
   const int npc = info & 0xffff, nsc = info >> 16;
   // a sequence whose own tokens are one item was finished where that item was processed: above
-  // (at most kShortTokens tokens) or in the suffix kernel
-  if (nsc == 1) return;
+  // (at most kShortTokens tokens) or in the suffix kernel; the items kernel finishes only those without a prefix
+  if (nsc == 1 && (npc == 0 || own <= kShortTokens)) return;
   const int n = npc + nsc;
   const int nslot = a.NCp + a.NCs;
   const float2* ml = a.partial_ml + (size_t)row * nslot;
@@ -873,6 +939,13 @@ int prefix_blocks_per_cu(bool wide) {
   if (e != hipSuccess || n < 1) n = 1;
   return n;
 }
+int items_blocks_per_cu(bool wide) {
+  int n = 0;
+  const hipError_t e = wide ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, items_kernel_wide, 256, 0)
+                            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, items_kernel, 256, 0);
+  if (e != hipSuccess || n < 1) n = 1;
+  return n;
+}
 int suffix_blocks_per_cu() {
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, suffix_kernel, kSuffixWaves * 64, 0) != hipSuccess || n < 1) n = 1;
@@ -886,6 +959,11 @@ hipError_t launch_prefix(const AttnArgs& a, int grid, hipStream_t st) {
 }
 hipError_t launch_suffix(const AttnArgs& a, int grid, hipStream_t st) {
   hipLaunchKernelGGL(suffix_kernel, dim3(grid), dim3(kSuffixWaves * 64), 0, st, a);
+  return hipGetLastError();
+}
+hipError_t launch_items(const AttnArgs& a, int grid, hipStream_t st) {
+  if (a.qblock_rows == kRowsPerQBlockWide) hipLaunchKernelGGL(items_kernel_wide, dim3(grid), dim3(256), 0, st, a);
+  else hipLaunchKernelGGL(items_kernel, dim3(grid), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 hipError_t launch_merge(const AttnArgs& a, hipStream_t st) {

@@ -19,6 +19,8 @@ constexpr int kRowsPerQBlockWide = 256;   // ... in the wide kernel
 constexpr int kShortTokens = MARL_SHORT_TOKENS;
 constexpr int kAttnThreads = 256;  // 4 waves per workgroup
 constexpr int kSmallAttnSeqs = 512;   // most sequences, and groups, of a call that the small kernel serves
+constexpr int kPrefixTokenCost = 4;   // time of a prefix item's token in tokens of a suffix item, of a workgroup that takes both
+constexpr int kOneQueueItems = 6144;  // most (sequence, KV head) pairs of a call whose prefix and suffix items share a launch
 constexpr int kPlanThreads = 1024;
 constexpr int kNumClasses = 2048;  // upper bound on cost classes (chunk / 32)
 
@@ -50,18 +52,21 @@ struct AttnArgs {
   int32_t qblock_rows;   // kRowsPerQBlock or kRowsPerQBlockWide
   int32_t out_dtype;
   int32_t splits;        // small calls only
+  int32_t one_queue;     // prefix and suffix items are taken by one kernel
   float scale;
 };
 
 hipError_t launch_plan(const AttnArgs& a, hipStream_t st);
 hipError_t launch_prefix(const AttnArgs& a, int grid, hipStream_t st);
 hipError_t launch_suffix(const AttnArgs& a, int grid, hipStream_t st);
+hipError_t launch_items(const AttnArgs& a, int grid, hipStream_t st);
 hipError_t launch_merge(const AttnArgs& a, hipStream_t st);
 // Parts into which a small call divides each sequence's tokens, 0 where the call is left to the kernels above.
 int small_attn_splits(const AttnArgs& a);
 hipError_t launch_small_attn(const AttnArgs& a, hipStream_t st);
 hipError_t launch_merge_parts(const AttnArgs& a, hipStream_t st);
 int prefix_blocks_per_cu(bool wide);
+int items_blocks_per_cu(bool wide);
 int suffix_blocks_per_cu();
 
 struct KvAppendArgs {

@@ -97,7 +97,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
   }
   for (int i = tid; i < kSmallMaxGroups; i += kThreads) cnt[i] = 0;
   for (int i = tid; i < kSmallMaxClasses; i += kThreads) { hist_s[i] = 0; hist_p[i] = 0; }
-  if (tid == 0) { n_long_items = 0; n_short_partial_items = 0; }
+  __shared__ int longest_prefix;
+  if (tid == 0) { n_long_items = 0; n_short_partial_items = 0; longest_prefix = 0; }
   if (tid < 64) a.counters[tid] = 0;
   __syncthreads();
 
@@ -134,6 +135,7 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
   }
   __syncthreads();
 
+  int longest = 0;
   // prefix items by class; the counts' sums inside a wave (thread t: groups kGroupsPerThread t ..)
 #pragma unroll
   for (int k = 0; k < kGroupsPerThread; ++k) {
@@ -146,9 +148,11 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       if (nqb) {
         if (nfull) atomicAdd(&hist_p[0], nfull * nqb);
         if (tail) atomicAdd(&hist_p[(Cp - tail) / 32], nqb);
+        longest = max(longest, min(P_of[k], Cp));
       }
     }
   }
+  if (longest > 0) atomicMax(&longest_prefix, longest);
   int own = 0;
 #pragma unroll
   for (int k = 0; k < kGroupsPerThread; ++k) own += cnt[tid * kGroupsPerThread + k];   // (zero from NG on)
@@ -299,6 +303,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
     a.counters[MARL_CTR_NUM_PREFIX_ITEMS] = n_prefix_items;
     a.counters[MARL_CTR_NUM_LONG_SUFFIX_ITEMS] = n_long_items;
     a.counters[MARL_CTR_NUM_SHORT_PARTIAL_ITEMS] = n_short_partial_items;
+    const int len = longest_prefix * kPrefixTokenCost;
+    a.counters[MARL_CTR_NUM_FIRST_SUFFIX_ITEMS] = len <= Cs && Cs > kShortTokens && longest_prefix > 0 ? hist_s[min((Cs - max(len, kShortTokens + 1)) / 32, kSmallMaxClasses - 1)] : 0;
   }
 }
 
