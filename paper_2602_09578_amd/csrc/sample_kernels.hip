@@ -3,9 +3,10 @@
 // number supplied by the caller, and that token's log-probability (rollout produces both for
 // every generated token; the paper trains with GRPO, Section 8.1, which consumes the latter).
 //
+// Rows are taken whole by a workgroup each, or divided between workgroups (launch_sample), which takes two kernels.
 // Pass 1 (streaming, the cost of the log-prob kernel): every wave takes contiguous chunks of
-//   4096 logits and stores each chunk's (max, sum of 2^(y - max)), y = x * log2(e) / T.
-// Pass 2 (one wave per row, re-reads 8 KB): an ordered scan over the chunk sums finds the chunk
+//   4096 logits (whole rows: 2048) and stores each chunk's (max, sum of 2^(y - max)), y = x * log2(e) / T.
+// Pass 2 (one wave per row, re-reads the chunk): an ordered scan over the chunk sums finds the chunk
 //   in which the cumulative probability passes u, an ordered scan inside that chunk finds the
 //   token.  Token = first t with sum_{v <= t} p_v > u; if rounding leaves none, the last token
 //   with non-zero probability.  The running sums of a scan are associated differently from lane to
@@ -86,6 +87,42 @@ __device__ __forceinline__ double from_lane(double v, int l) {
   return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
 }
 
+// The logits of a chunk of kIts x 512, as a wave holds them.
+template <int kIts>
+__device__ __forceinline__ void fetch_chunk(const uint16_t* x, long base, int lane, long vocab, u32x4 (&w)[kIts]) {
+#pragma unroll
+  for (int it = 0; it < kIts; ++it) w[it] = load8_words(x, base + it * 512 + lane * 8, vocab);
+}
+// (max, sum of 2^(y - max)) of a chunk.  Per lane a running (largest raw logit, sum relative to it), 16 logits at
+// a time as they arrive: with the wave's maximum first, all of a batch's waves waited for whole chunks and then
+// summed together.
+template <int kIts>
+__device__ __forceinline__ float2 chunk_sum(const u32x4 (&w)[kIts], float c) {
+  float xr = -INFINITY, sr = 0.f;
+#pragma unroll
+  for (int it = 0; it < kIts; it += 2) {
+    float xn = xr;
+#pragma unroll
+    for (int i = it; i < it + 2; ++i)
+#pragma unroll
+      for (int d = 0; d < 4; ++d)
+        xn = fmaxf(xn, fmaxf(__uint_as_float(w[i][d] << 16), __uint_as_float(w[i][d] & 0xffff0000u)));
+    const float ms = xn == -INFINITY ? 0.f : xn * c;   // c > 0: the scaled maximum is the maximum of the scaled values
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int i = it; i < it + 2; ++i)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        s0 += ex2(__builtin_fmaf(__uint_as_float(w[i][d] << 16), c, -ms));
+        s1 += ex2(__builtin_fmaf(__uint_as_float(w[i][d] & 0xffff0000u), c, -ms));
+      }
+    sr = sr * ex2(xr * c - ms) + (s0 + s1);
+    xr = xn;
+  }
+  const float m = wave_max(xr) * c;
+  return make_float2(m, wave_sum(sr * ex2_diff(xr * c, m)));
+}
+
 // grid: rows * groups_per_row workgroups of 4 waves; a workgroup covers 4 * chunks_per_wave
 // consecutive chunks of one row, wave w taking chunks first + w, first + w + 4, ...
 __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
@@ -93,46 +130,16 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
   const int row = blockIdx.x / a.groups_per_row;
   const int first = (blockIdx.x % a.groups_per_row) * 4 * a.chunks_per_wave;
   const uint16_t* x = a.logits + (size_t)row * a.vocab;
-  const float c = a.inv_temp_log2e;
   // the words of the wave's next chunk are requested before the current chunk is reduced
   u32x4 cur[kIters], nxt[kIters];
-  auto fetch = [&](int chunk, u32x4 (&w)[kIters]) {
-    const long base = (long)chunk * kChunk;
-#pragma unroll
-    for (int it = 0; it < kIters; ++it) w[it] = load8_words(x, base + it * 512 + lane * 8, a.vocab);
-  };
-  if (first + wave < a.num_chunks) fetch(first + wave, cur);
+  if (first + wave < a.num_chunks) fetch_chunk(x, (long)(first + wave) * kChunk, lane, a.vocab, cur);
   for (int k = 0; k < a.chunks_per_wave; ++k) {
     const int chunk = first + wave + 4 * k;
     if (chunk >= a.num_chunks) break;
     const bool more = k + 1 < a.chunks_per_wave && chunk + 4 < a.num_chunks;   // wave-uniform
-    if (more) fetch(chunk + 4, nxt);
-    // per lane a running (largest raw logit, sum relative to it), 16 logits at a time as they arrive: with
-    // the wave's maximum first, all of a batch's waves waited for whole chunks and then summed together
-    float xr = -INFINITY, sr = 0.f;
-#pragma unroll
-    for (int it = 0; it < kIters; it += 2) {
-      float xn = xr;
-#pragma unroll
-      for (int i = it; i < it + 2; ++i)
-#pragma unroll
-        for (int d = 0; d < 4; ++d)
-          xn = fmaxf(xn, fmaxf(__uint_as_float(cur[i][d] << 16), __uint_as_float(cur[i][d] & 0xffff0000u)));
-      const float ms = xn == -INFINITY ? 0.f : xn * c;   // c > 0: the scaled maximum is the maximum of the scaled values
-      float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-      for (int i = it; i < it + 2; ++i)
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          s0 += ex2(__builtin_fmaf(__uint_as_float(cur[i][d] << 16), c, -ms));
-          s1 += ex2(__builtin_fmaf(__uint_as_float(cur[i][d] & 0xffff0000u), c, -ms));
-        }
-      sr = sr * ex2(xr * c - ms) + (s0 + s1);
-      xr = xn;
-    }
-    const float m = wave_max(xr) * c;
-    const float s = wave_sum(sr * ex2_diff(xr * c, m));
-    if (lane == 0) a.partials[(size_t)row * a.num_chunks + chunk] = make_float2(m, s);
+    if (more) fetch_chunk(x, (long)(chunk + 4) * kChunk, lane, a.vocab, nxt);
+    const float2 v = chunk_sum(cur, a.inv_temp_log2e);
+    if (lane == 0) a.partials[(size_t)row * a.num_chunks + chunk] = v;
     if (more) {
 #pragma unroll
       for (int it = 0; it < kIters; ++it) cur[it] = nxt[it];
@@ -140,35 +147,33 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
   }
 }
 
-// One wave per row.  It is a chain of dependent reads (chunk sums, then the chosen chunk), so each of
-// them is one round trip: the sums of the first 64 chunks (all of them up to a vocabulary of 262144)
-// are read once and stay in a register, and the chunk's 4096 logits are requested together
-// (256 rows x 152064: 10.5 us with the sums re-read for every use and the chunk in eight dependent
-// pieces, 4.8 us now).
-__global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
-  const int lane = threadIdx.x;
-  const int row = blockIdx.x;
-  const float2* part = a.partials + (size_t)row * a.num_chunks;
+// Draws the row's token from its chunks' sums (global memory or LDS), one wave.  It is a chain of dependent
+// reads (chunk sums, then the chosen chunk), so each of them is one round trip: the sums of the first 64 chunks (all of
+// them up to a vocabulary of 262144 in chunks of 4096) are read once and stay in a register, and the chunk's logits
+// are requested together (256 rows x 152064: 10.5 us with the sums re-read for every use and the chunk in eight
+// dependent pieces, 4.8 us as a kernel of its own).
+template <int kIts>
+__device__ __forceinline__ void pick_token(const SampleArgs& a, const float2* part, const int num_chunks, const int row, const float u) {
+  const int lane = threadIdx.x & 63;
   const uint16_t* x = a.logits + (size_t)row * a.vocab;
   const float c = a.inv_temp_log2e;
-  const float u = a.uniforms[row];
-  const float2 first = lane < a.num_chunks ? part[lane] : make_float2(-INFINITY, 0.f);
+  const float2 first = lane < num_chunks ? part[lane] : make_float2(-INFINITY, 0.f);
   auto chunk_sum = [&](int base) {   // (max, sum) of chunk base + lane
     if (base == 0) return first;
-    return base + lane < a.num_chunks ? part[base + lane] : make_float2(-INFINITY, 0.f);
+    return base + lane < num_chunks ? part[base + lane] : make_float2(-INFINITY, 0.f);
   };
   // global max and total, chunk sums rescaled to the global max.  The few dozen chunk sums are
   // accumulated in double precision: they decide in which chunk the uniform number falls, and a
   // float32 running sum over the whole vocabulary would move a CDF step by up to ~1e-5.
   float M = -INFINITY;
-  for (int base = 0; base < a.num_chunks; base += 64) M = fmaxf(M, chunk_sum(base).x);
+  for (int base = 0; base < num_chunks; base += 64) M = fmaxf(M, chunk_sum(base).x);
   M = wave_max(M);
   auto chunk_mass = [&](int base) -> double {
     const float2 p = chunk_sum(base);
-    return base + lane < a.num_chunks ? (double)(p.y * ex2_diff(p.x, M)) : 0.0;
+    return base + lane < num_chunks ? (double)(p.y * ex2_diff(p.x, M)) : 0.0;
   };
   double total = 0.0;
-  for (int base = 0; base < a.num_chunks; base += 64)   // fixed order: tiles of 64 chunks
+  for (int base = 0; base < num_chunks; base += 64)   // fixed order: tiles of 64 chunks
     total += from_lane(wave_inclusive_scan(chunk_mass(base)), 63);
   const double target = (double)u * total;
   const double least = kLeastMass * fmin(total, 1.0);
@@ -176,7 +181,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   double before = 0.0;
   bool take_last = false;
   int chunk = -1, last_nonzero = -1;
-  for (int base = 0; base < a.num_chunks && chunk < 0; base += 64) {
+  for (int base = 0; base < num_chunks && chunk < 0; base += 64) {
     const double v = chunk_mass(base);
     const double cum = before + wave_inclusive_scan(v);
     const bool some = v > least;
@@ -197,10 +202,10 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   }
   // remaining mass to pass inside the chunk (inf: nothing passes, the last non-zero token is taken)
   const float want = take_last ? INFINITY : (float)(target - before);
-  const long cbase = (long)chunk * kChunk + lane * 8;
-  u32x4 words[kIters];
+  const long cbase = (long)chunk * (kIts * 512) + lane * 8;
+  u32x4 words[kIts];
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
+  for (int it = 0; it < kIts; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
   // the weights 2^(y - M) of 8 logits, the same each time they are formed
   const float ms = M == -INFINITY ? 0.f : M;
   auto weights = [&](u32x4 v, float (&w)[8]) {
@@ -218,7 +223,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   float run = 0.f, cum_at = 0.f;
   int at = -1, last = -1;
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) {
+  for (int it = 0; it < kIts; ++it) {
     float w[8];
     const float s = weights(words[it], w);
     const float cum = run + wave_inclusive_scan(s);
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   if (piece >= 0) {   // wave-uniform
     u32x4 v = words[0];
 #pragma unroll
-    for (int it = 1; it < kIters; ++it) v = it == piece ? words[it] : v;
+    for (int it = 1; it < kIts; ++it) v = it == piece ? words[it] : v;
     float w[8];
     const float s = weights(v, w);
     // the lane's first token with mass that passes; if rounding leaves none (or no lane passed), its last one
@@ -264,6 +269,43 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
       a.out_logprobs[row] = logprob_of(x_tok, c, M, total);
     }
   }
+}
+
+__global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
+  const int row = blockIdx.x;
+  pick_token<kIters>(a, a.partials + (size_t)row * a.num_chunks, a.num_chunks, row, a.uniforms[row]);
+}
+
+// Whole rows: a workgroup of 8 waves sums a row's chunks of 2048 into LDS and its first wave draws the token, so
+// there is one launch, and the chunk sums do not go through memory.  What bounds it: the read (256 x 152064: 78 MB in
+// 17.1 us, 21.0 with two kernels) with the vector ALU close behind it (7 issue slots of 4 cycles per logit), and 3 us of
+// dependent steps at a row's end, which other rows of the CU cover from 512 on (2048 rows: 6.25 TB/s).
+constexpr int kRowIters = 4;
+constexpr int kRowWaves = 8;
+constexpr int kRowMaxChunks = 1024;   // (a vocabulary of 2 M)
+__global__ __launch_bounds__(kRowWaves * 64) void sample_rows_kernel(SampleArgs a) {
+  __shared__ float2 part[kRowMaxChunks];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = blockIdx.x;
+  const uint16_t* x = a.logits + (size_t)row * a.vocab;
+  constexpr int kRowChunk = kRowIters * 512;
+  const int chunks = (int)(((long)a.vocab + kRowChunk - 1) / kRowChunk);
+  const float u = a.uniforms[row];
+  u32x4 cur[kRowIters], nxt[kRowIters];
+  if (wave < chunks) fetch_chunk(x, (long)wave * kRowChunk, lane, a.vocab, cur);
+  for (int chunk = wave; chunk < chunks; chunk += kRowWaves) {
+    const bool more = chunk + kRowWaves < chunks;   // wave-uniform
+    if (more) fetch_chunk(x, (long)(chunk + kRowWaves) * kRowChunk, lane, a.vocab, nxt);
+    const float2 v = chunk_sum(cur, a.inv_temp_log2e);
+    if (lane == 0) part[chunk] = v;
+    if (more) {
+#pragma unroll
+      for (int it = 0; it < kRowIters; ++it) cur[it] = nxt[it];
+    }
+  }
+  __syncthreads();
+  if (wave == 0) pick_token<kRowIters>(a, part, chunks, row, u);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -936,8 +978,22 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Short rows are taken whole at any number of them: the second launch is most of the call (1 to 1024 rows x 4096: 8.6 us
+// divided, 6.0 whole; 512 x 32000 12.5 and 10.2).  Long rows, which one CU sums in 13 us (152064 logits), are
+// divided while there are fewer than CUs (64 x 152064: 10.6 divided, 15.8 whole; 200: 18.3 and 16.6, 256: 21.0 and 17.1), and
+// again where some CUs would have a second row and most would wait for them (300: 24.0 and 25.8; 400: 27.9 and 26.2,
+// 2048: 110.6 and 99.6).  The 256 are the CUs of an MI355X.
+static bool sample_whole_rows(int rows, int vocab) {
+  if (vocab <= 40960) return true;
+  return vocab <= kRowMaxChunks * kRowIters * 512 && ((rows >= 200 && rows <= 256) || rows >= 384);
+}
+
 hipError_t launch_sample(const SampleArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
+  if (sample_whole_rows(a.rows, a.vocab)) {
+    hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)a.rows), dim3(kRowWaves * 64), 0, st, a);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(sample_scan_kernel, dim3((unsigned)a.rows * a.groups_per_row), dim3(256), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
