@@ -274,9 +274,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       typedef int int4_any __attribute__((ext_vector_type(4), aligned(4)));
       constexpr int kAtOnce = 8;
       const int n = rows * pages;
-      auto look = [&](int e, int id) {
-        const int row = e / pages;
-        if ((e - row * pages) * kPage < tokens(row) && (unsigned)id >= (unsigned)a.num_pages) flags |= MARL_FLAG_BAD_PAGE;
+      auto look = [&](int row, int page, int id) {
+        if ((unsigned)id >= (unsigned)a.num_pages && page * kPage < tokens(row)) flags |= MARL_FLAG_BAD_PAGE;
       };
       for (int p0 = tid; p0 < n / 4; p0 += kAtOnce * kThreads) {
         int4_any ids[kAtOnce];
@@ -284,15 +283,22 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
         for (int u = 0; u < kAtOnce; ++u) ids[u] = *reinterpret_cast<const int4_any*>(table + 4 * min(p0 + u * kThreads, n / 4 - 1));
 #pragma unroll
         for (int u = 0; u < kAtOnce; ++u) {
-          const int p = min(p0 + u * kThreads, n / 4 - 1);
+          const int p = p0 + u * kThreads;
           // (entries past a row's pages are -1 by convention: only pieces with an id outside the pool are looked at)
-          if (max(max((unsigned)ids[u][0], (unsigned)ids[u][1]), max((unsigned)ids[u][2], (unsigned)ids[u][3])) >= (unsigned)a.num_pages) {
+          if (p < n / 4 && max(max((unsigned)ids[u][0], (unsigned)ids[u][1]), max((unsigned)ids[u][2], (unsigned)ids[u][3])) >= (unsigned)a.num_pages) {
+            int row = 4 * p / pages, page = 4 * p - row * pages;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) look(4 * p + e, ids[u][e]);
+            for (int e = 0; e < 4; ++e) {
+              look(row, page, ids[u][e]);
+              if (++page == pages) { page = 0; ++row; }
+            }
           }
         }
       }
-      if (tid < (n & 3)) look((n & ~3) + tid, table[(n & ~3) + tid]);
+      if (tid < (n & 3)) {
+        const int e = (n & ~3) + tid, row = e / pages;
+        look(row, e - row * pages, table[e]);
+      }
     };
     check(a.suffix_table, a.NS, a.max_sp, [&](int s) { return suffix_len[s]; });
     check(a.prefix_table, a.NG, a.max_pp, [&](int g) { return cnt[g] ? prefix_len[g] : 0; });
