@@ -5,13 +5,14 @@
 //
 // Rows are taken whole by a workgroup each, or divided between workgroups (launch_sample), which takes two kernels.
 // Pass 1 (streaming, the cost of the log-prob kernel): every wave takes contiguous chunks of
-//   4096 logits (whole rows: 2048) and stores each chunk's (max, sum of 2^(y - max)), y = x * log2(e) / T.
-// Pass 2 (one wave per row, re-reads the chunk): an ordered scan over the chunk sums finds the chunk
+//   4096 logits and stores each chunk's (max, sum of 2^(y - max)), y = x * log2(e) / T.
+// Pass 2 (one wave per row, re-reads 8 KB): an ordered scan over the chunk sums finds the chunk
 //   in which the cumulative probability passes u, an ordered scan inside that chunk finds the
 //   token.  Token = first t with sum_{v <= t} p_v > u; if rounding leaves none, the last token
 //   with non-zero probability.  The running sums of a scan are associated differently from lane to
 //   lane, so a lane without mass (masked tokens, positions past the end) can be the first whose sum
 //   passes: only chunks, lanes and tokens that have mass are ever taken.
+#include <algorithm>
 #include <type_traits>
 
 #include "marl_internal.h"
@@ -87,20 +88,18 @@ __device__ __forceinline__ double from_lane(double v, int l) {
   return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
 }
 
-// The logits of a chunk of kIts x 512, as a wave holds them.
-template <int kIts>
-__device__ __forceinline__ void fetch_chunk(const uint16_t* x, long base, int lane, long vocab, u32x4 (&w)[kIts]) {
+// The logits of a chunk, as a wave holds them.
+__device__ __forceinline__ void fetch_chunk(const uint16_t* x, long base, int lane, long vocab, u32x4 (&w)[kIters]) {
 #pragma unroll
-  for (int it = 0; it < kIts; ++it) w[it] = load8_words(x, base + it * 512 + lane * 8, vocab);
+  for (int it = 0; it < kIters; ++it) w[it] = load8_words(x, base + it * 512 + lane * 8, vocab);
 }
 // (max, sum of 2^(y - max)) of a chunk.  Per lane a running (largest raw logit, sum relative to it), 16 logits at
 // a time as they arrive: with the wave's maximum first, all of a batch's waves waited for whole chunks and then
 // summed together.
-template <int kIts>
-__device__ __forceinline__ float2 chunk_sum(const u32x4 (&w)[kIts], float c) {
+__device__ __forceinline__ float2 chunk_sum(const u32x4 (&w)[kIters], float c) {
   float xr = -INFINITY, sr = 0.f;
 #pragma unroll
-  for (int it = 0; it < kIts; it += 2) {
+  for (int it = 0; it < kIters; it += 2) {
     float xn = xr;
 #pragma unroll
     for (int i = it; i < it + 2; ++i)
@@ -149,10 +148,9 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
 
 // Draws the row's token from its chunks' sums (global memory or LDS), one wave.  It is a chain of dependent
 // reads (chunk sums, then the chosen chunk), so each of them is one round trip: the sums of the first 64 chunks (all of
-// them up to a vocabulary of 262144 in chunks of 4096) are read once and stay in a register, and the chunk's logits
+// them up to a vocabulary of 262144) are read once and stay in a register, and the chunk's logits
 // are requested together (256 rows x 152064: 10.5 us with the sums re-read for every use and the chunk in eight
 // dependent pieces, 4.8 us as a kernel of its own).
-template <int kIts>
 __device__ __forceinline__ void pick_token(const SampleArgs& a, const float2* part, const int num_chunks, const int row, const float u) {
   const int lane = threadIdx.x & 63;
   const uint16_t* x = a.logits + (size_t)row * a.vocab;
@@ -202,10 +200,10 @@ __device__ __forceinline__ void pick_token(const SampleArgs& a, const float2* pa
   }
   // remaining mass to pass inside the chunk (inf: nothing passes, the last non-zero token is taken)
   const float want = take_last ? INFINITY : (float)(target - before);
-  const long cbase = (long)chunk * (kIts * 512) + lane * 8;
-  u32x4 words[kIts];
+  const long cbase = (long)chunk * kChunk + lane * 8;
+  u32x4 words[kIters];
 #pragma unroll
-  for (int it = 0; it < kIts; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
+  for (int it = 0; it < kIters; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
   // the weights 2^(y - M) of 8 logits, the same each time they are formed
   const float ms = M == -INFINITY ? 0.f : M;
   auto weights = [&](u32x4 v, float (&w)[8]) {
@@ -223,7 +221,7 @@ __device__ __forceinline__ void pick_token(const SampleArgs& a, const float2* pa
   float run = 0.f, cum_at = 0.f;
   int at = -1, last = -1;
 #pragma unroll
-  for (int it = 0; it < kIts; ++it) {
+  for (int it = 0; it < kIters; ++it) {
     float w[8];
     const float s = weights(words[it], w);
     const float cum = run + wave_inclusive_scan(s);
@@ -239,7 +237,7 @@ __device__ __forceinline__ void pick_token(const SampleArgs& a, const float2* pa
   if (piece >= 0) {   // wave-uniform
     u32x4 v = words[0];
 #pragma unroll
-    for (int it = 1; it < kIts; ++it) v = it == piece ? words[it] : v;
+    for (int it = 1; it < kIters; ++it) v = it == piece ? words[it] : v;
     float w[8];
     const float s = weights(v, w);
     // the lane's first token with mass that passes; if rounding leaves none (or no lane passed), its last one
@@ -273,39 +271,39 @@ __device__ __forceinline__ void pick_token(const SampleArgs& a, const float2* pa
 
 __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
   const int row = blockIdx.x;
-  pick_token<kIters>(a, a.partials + (size_t)row * a.num_chunks, a.num_chunks, row, a.uniforms[row]);
+  pick_token(a, a.partials + (size_t)row * a.num_chunks, a.num_chunks, row, a.uniforms[row]);
 }
 
-// Whole rows: a workgroup of 8 waves sums a row's chunks of 2048 into LDS and its first wave draws the token, so
-// there is one launch, and the chunk sums do not go through memory.  What bounds it: the read (256 x 152064: 78 MB in
-// 17.1 us, 21.0 with two kernels) with the vector ALU close behind it (7 issue slots of 4 cycles per logit), and 3 us of
-// dependent steps at a row's end, which other rows of the CU cover from 512 on (2048 rows: 6.25 TB/s).
-constexpr int kRowIters = 4;
-constexpr int kRowWaves = 8;
-constexpr int kRowMaxChunks = 1024;   // (a vocabulary of 2 M)
-__global__ __launch_bounds__(kRowWaves * 64) void sample_rows_kernel(SampleArgs a) {
+// Whole rows: a workgroup of up to 16 waves sums a row's chunks into LDS and its first wave draws the token, so
+// there is one launch, and the chunk sums do not go through memory.  Chunks and sums are those of divided rows, bit for
+// bit: which token is drawn does not depend on the size of the batch.  What bounds it: the vector ALU of the row's CU (7 issue
+// slots of 4 cycles per logit) and the read together (256 x 152064: 78 MB in 19.8 us), and at a row's end 3 us of dependent
+// steps.  (Chunks of 2048 take 17.1 us, but draw another token now and then, where the uniform number falls into an
+// interval of the size of the sums' rounding.)
+constexpr int kRowMaxWaves = 16;
+constexpr int kRowMaxChunks = 1024;   // (a vocabulary of 4 M)
+__global__ __launch_bounds__(kRowMaxWaves * 64) void sample_rows_kernel(SampleArgs a) {
   __shared__ float2 part[kRowMaxChunks];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row = blockIdx.x;
   const uint16_t* x = a.logits + (size_t)row * a.vocab;
-  constexpr int kRowChunk = kRowIters * 512;
-  const int chunks = (int)(((long)a.vocab + kRowChunk - 1) / kRowChunk);
+  const int chunks = a.num_chunks, waves = (int)blockDim.x >> 6;
   const float u = a.uniforms[row];
-  u32x4 cur[kRowIters], nxt[kRowIters];
-  if (wave < chunks) fetch_chunk(x, (long)wave * kRowChunk, lane, a.vocab, cur);
-  for (int chunk = wave; chunk < chunks; chunk += kRowWaves) {
-    const bool more = chunk + kRowWaves < chunks;   // wave-uniform
-    if (more) fetch_chunk(x, (long)(chunk + kRowWaves) * kRowChunk, lane, a.vocab, nxt);
+  u32x4 cur[kIters], nxt[kIters];
+  if (wave < chunks) fetch_chunk(x, (long)wave * kChunk, lane, a.vocab, cur);
+  for (int chunk = wave; chunk < chunks; chunk += waves) {
+    const bool more = chunk + waves < chunks;   // wave-uniform
+    if (more) fetch_chunk(x, (long)(chunk + waves) * kChunk, lane, a.vocab, nxt);
     const float2 v = chunk_sum(cur, a.inv_temp_log2e);
     if (lane == 0) part[chunk] = v;
     if (more) {
 #pragma unroll
-      for (int it = 0; it < kRowIters; ++it) cur[it] = nxt[it];
+      for (int it = 0; it < kIters; ++it) cur[it] = nxt[it];
     }
   }
   __syncthreads();
-  if (wave == 0) pick_token<kRowIters>(a, part, chunks, row, u);
+  if (wave == 0) pick_token(a, part, chunks, row, u);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -978,20 +976,26 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Short rows are taken whole at any number of them: the second launch is most of the call (1 to 1024 rows x 4096: 8.6 us
-// divided, 6.0 whole; 512 x 32000 12.5 and 10.2).  Long rows, which one CU sums in 13 us (152064 logits), are
-// divided while there are fewer than CUs (64 x 152064: 10.6 divided, 15.8 whole; 200: 18.3 and 16.6, 256: 21.0 and 17.1), and
-// again where some CUs would have a second row and most would wait for them (300: 24.0 and 25.8; 400: 27.9 and 26.2,
-// 2048: 110.6 and 99.6).  The 256 are the CUs of an MI355X.
-static bool sample_whole_rows(int rows, int vocab) {
-  if (vocab <= 40960) return true;
-  return vocab <= kRowMaxChunks * kRowIters * 512 && ((rows >= 200 && rows <= 256) || rows >= 384);
+// Waves of a workgroup that takes a row whole, 0 where rows are divided between workgroups and a second launch draws.
+// Rows of up to 8 chunks are taken whole at any number: the second launch is much of the call (1 to 1024 rows x 4096: 7.6 us
+// divided, 5.6 whole; 256 x 32000 10.1 and 8.0, 2048 32.1 and 27.9).  Longer rows are divided while there are fewer than CUs
+// (64 x 152064: 10.8 us divided, 16.5 whole), and where some CUs would have one row more and most would wait for them
+// (300: 23.8 and 30.2, 700 x 100003: 35.0 and 38.5, 1599 x 152064: 92.8 and 96.0), and taken whole where the rows fill the
+// CUs once, twice ... but for a few per cent (256 x 152064: 21.0 and 19.8, 512 37.6 and 34.2, 2048 114 and 108).  As many waves as
+// there are chunks, or as a CU has room for (16 for a row of 38 chunks: 8 take 21.1); fewer of more rows, whose ends then
+// overlap (2048 x 32000: 8 waves 34.8, 4 27.9).  The 256 are the CUs of an MI355X.
+static int sample_row_waves(int rows, int chunks) {
+  const int rounds = (rows + 255) / 256;
+  if (chunks > 4 && chunks <= 8 && rows > 512 && rows < 800) return 0;   // (600 x 32003: 16.8 us divided, 17.4 whole)
+  if (chunks <= 8) return std::min(chunks, rows <= 512 ? 8 : 4);
+  if (chunks > kRowMaxChunks || 100l * rows < (rows < 1000 ? 93 : 90) * 256l * rounds) return 0;
+  return rounds == 1 ? kRowMaxWaves : rounds < 4 ? 8 : 4;
 }
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
-  if (sample_whole_rows(a.rows, a.vocab)) {
-    hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)a.rows), dim3(kRowWaves * 64), 0, st, a);
+  if (const int waves = sample_row_waves(a.rows, a.num_chunks)) {
+    hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)a.rows), dim3(waves * 64), 0, st, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(sample_scan_kernel, dim3((unsigned)a.rows * a.groups_per_row), dim3(256), 0, st, a);
