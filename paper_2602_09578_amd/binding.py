@@ -4,6 +4,8 @@ kernels.  There is no fallback: if the library is missing or a call fails, this 
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -11,7 +13,7 @@ from typing import Optional
 import numpy as np
 import torch
 
-from .build import LIB_PATH, build_library
+from .build import FAST_PATH, LIB_PATH, build_fast_calls, build_library
 
 I32 = ctypes.c_int32
 SZ = ctypes.c_size_t
@@ -67,11 +69,25 @@ class MarlError(RuntimeError):
 
 
 _lib = None
+_fast = None   # the short way of the decode loop's calls (csrc/fast_calls.cpp); None: every call goes the long way
+
+
+def _load_fast_calls(lib):
+    """Binds the short way to the functions of `lib`, where it is built and torch can tell the current stream."""
+    if _raw_stream is None or not os.path.exists(FAST_PATH):
+        return None
+    loader = importlib.machinery.ExtensionFileLoader("fast_calls", FAST_PATH)
+    m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("fast_calls", FAST_PATH, loader=loader))
+    loader.exec_module(m)
+    m.bind(_raw_stream, *(ctypes.cast(f, VP).value for f in (
+        lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
+        lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)))
+    return m
 
 
 def load_library(build_if_missing: bool = True):
     """Loads the in-tree shared library; builds it first only if no built library exists."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     path = os.environ.get("MARL_DECODE_LIB", LIB_PATH)   # an explicitly chosen build, if any
@@ -79,6 +95,7 @@ def load_library(build_if_missing: bool = True):
         if not build_if_missing or path != LIB_PATH:
             raise FileNotFoundError(path)
         build_library()
+        build_fast_calls()
     lib = ctypes.CDLL(path)
     PS, PL = ctypes.POINTER(AttnShape), ctypes.POINTER(PlanLayout)
     lib.marl_version.restype = ctypes.c_int
@@ -140,6 +157,7 @@ def load_library(build_if_missing: bool = True):
               "marl_attn_read_flags", "marl_logprobs_workspace_bytes", "marl_token_logprobs",
               "marl_profile_begin", "marl_profile_end"):
         getattr(lib, f).restype = ctypes.c_int
+    _fast = _load_fast_calls(lib)
     _lib = lib
     return lib
 
@@ -153,8 +171,10 @@ def _check(rc: int, where: str):
         raise MarlError(rc, where, detail)
 
 
-# The calls' own host time matters for small calls: 8.4 us of a log-probability call (3.4 in the library) and
-# 19.6 us of an attention call.  Pointers and streams go to ctypes as the integers they are, and the
+# The calls' own host time matters for small calls.  Those of a decode loop have a short way (load_library binds it):
+# one call into native code that makes the checks below on the tensors themselves and calls the library, 7.9 -> 3.5 us for
+# an attention call of one launch, 5.8 -> 3.0 for a log-probability call; whatever it does not find plainly right comes
+# here.  The long way: pointers and streams go to ctypes as the integers they are, and the
 # current stream of a tensor's device is read without building a Stream object (2.1 -> 0.1 us), where torch has
 # the function for that, which is not part of its documented interface.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -235,6 +255,13 @@ def _require_attn_operands(shape: AttnShape, q, k_pages, v_pages, prefix_block_t
 def marl_decode_attn(shape: AttnShape, workspace: torch.Tensor, q, k_pages, v_pages, prefix_block_table,
                      suffix_block_table, prefix_lens, suffix_lens, group_of_seq, scale: float,
                      out: torch.Tensor) -> torch.Tensor:
+    if _fast is not None:
+        rc = _fast.decode_attn(shape, workspace, q, k_pages, v_pages, prefix_block_table, suffix_block_table, prefix_lens,
+                               suffix_lens, group_of_seq, scale, out)
+        if rc is not None:
+            if rc:
+                _check(rc, "marl_decode_attn")
+            return out
     _require_attn_operands(shape, q, k_pages, v_pages, prefix_block_table, suffix_block_table, prefix_lens,
                            suffix_lens, group_of_seq, out)
     _require_cuda(workspace, q, k_pages, v_pages, prefix_block_table, suffix_block_table, prefix_lens,
@@ -294,6 +321,12 @@ def marl_logprobs_workspace_bytes(rows: int, vocab: int) -> int:
 
 def marl_token_logprobs(logits: torch.Tensor, tokens: torch.Tensor, temperature: float, out: torch.Tensor,
                         workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if _fast is not None:
+        rc = _fast.token_logprobs(logits, tokens, temperature, out, workspace)
+        if rc is not None:
+            if rc:
+                _check(rc, "marl_token_logprobs")
+            return out
     _require(logits, "logits", torch.bfloat16, (None, None))
     rows, vocab = logits.shape
     _require(tokens, "tokens", torch.int32, (rows,))
@@ -308,6 +341,10 @@ def marl_token_logprobs(logits: torch.Tensor, tokens: torch.Tensor, temperature:
 
 def marl_kv_append(shape: AttnShape, k_new, v_new, k_pages, v_pages, suffix_block_table, suffix_lens,
                    flags: Optional[torch.Tensor] = None):
+    if _fast is not None:
+        rc = _fast.kv_append(shape, k_new, v_new, k_pages, v_pages, suffix_block_table, suffix_lens, flags)
+        if rc is not None:
+            return _check(rc, "marl_kv_append")
     _require_cuda(k_new, v_new, k_pages, v_pages, suffix_block_table, suffix_lens, flags)
     NS, Hkv = shape.num_seqs, shape.num_kv_heads
     _require(k_new, "k_new", torch.bfloat16, (NS, Hkv, 128))
@@ -343,6 +380,12 @@ def marl_sample_workspace_bytes(rows: int, vocab: int) -> int:
 
 def marl_sample_tokens(logits: torch.Tensor, uniforms: torch.Tensor, temperature: float, out_tokens: torch.Tensor,
                        out_logprobs: torch.Tensor, workspace: torch.Tensor):
+    if _fast is not None:
+        rc = _fast.sample_tokens(logits, uniforms, temperature, None, out_tokens, out_logprobs, workspace)
+        if rc is not None:
+            if rc:
+                _check(rc, "marl_sample_tokens")
+            return out_tokens, out_logprobs
     _require_cuda(logits, uniforms, out_tokens, out_logprobs, workspace)
     _require(logits, "logits", torch.bfloat16, (None, None))
     rows, vocab = logits.shape
@@ -358,6 +401,12 @@ def marl_sample_tokens(logits: torch.Tensor, uniforms: torch.Tensor, temperature
 
 def marl_sample_tokens_top_p(logits: torch.Tensor, uniforms: torch.Tensor, temperature: float, top_p: float,
                              out_tokens: torch.Tensor, out_logprobs: torch.Tensor):
+    if _fast is not None and top_p is not None:
+        rc = _fast.sample_tokens(logits, uniforms, temperature, top_p, out_tokens, out_logprobs, None)
+        if rc is not None:
+            if rc:
+                _check(rc, "marl_sample_tokens_top_p")
+            return out_tokens, out_logprobs
     _require_cuda(logits, uniforms, out_tokens, out_logprobs)
     _require(logits, "logits", torch.bfloat16, (None, None))
     rows, vocab = logits.shape
@@ -400,6 +449,12 @@ def marl_prefill_workspace_bytes(shape: PrefillShape) -> int:
 
 def marl_prefill_attn(shape: PrefillShape, workspace, q, k_pages, v_pages, prefix_block_table, q_start, q_pos0,
                       scale: float, out):
+    if _fast is not None:
+        rc = _fast.prefill_attn(shape, workspace, q, k_pages, v_pages, prefix_block_table, q_start, q_pos0, scale, out)
+        if rc is not None:
+            if rc:
+                _check(rc, "marl_prefill_attn")
+            return out
     _require_cuda(workspace, q, k_pages, v_pages, prefix_block_table, q_start, q_pos0, out)
     NT, NG, Hq, Hkv = shape.num_tokens, shape.num_groups, shape.num_q_heads, shape.num_kv_heads
     _require(q, "q", torch.bfloat16, (NT, Hq, 128))

@@ -11,6 +11,7 @@ _ROOT = os.path.dirname(_PKG)
 CSRC = os.path.join(_PKG, "csrc")
 LIB_DIR = os.path.join(_PKG, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libmarl_decode.so")
+FAST_PATH = os.path.join(LIB_DIR, "fast_calls.so")   # the binding's host code (a Python module)
 SOURCES = ["api.hip", "plan_kernel.hip", "attn_kernels.hip", "attn_small_kernel.hip", "logprob_kernels.hip",
            "kv_cache_kernels.hip", "sample_kernels.hip", "grpo_kernels.hip", "prefill_kernels.hip", "balancer.hip", "pack_kernels.hip", "page_pool.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -51,5 +52,22 @@ def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PAT
     return out_path
 
 
+def build_fast_calls(out_path: str = FAST_PATH) -> str:
+    """Compiles the binding's host code against torch's headers (always)."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    os.makedirs(LIB_DIR, exist_ok=True)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(_ROOT, "include"), "-I" + sysconfig.get_paths()["include"], *["-I" + p for p in include_paths()],
+           os.path.join(CSRC, "fast_calls.cpp"), "-o", out_path, *["-L" + p for p in library_paths()],
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for fast_calls.cpp:\n" + r.stdout)
+    return out_path
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True, extra_flags=sys.argv[1:]))
+    print(build_fast_calls())

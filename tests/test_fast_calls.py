@@ -1,0 +1,103 @@
+"""The binding's short way (native checks and call in one step) against its long way: the same results, the same
+refusals, and nothing taken that is not plainly right."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_09578_amd import binding as B
+from paper_2602_09578_amd import inputs as I
+
+ENTRIES = ("decode_attn", "token_logprobs", "sample_tokens", "kv_append", "prefill_attn")
+
+
+def test_what_is_not_a_device_tensor_goes_the_long_way():
+    B.load_library()
+    if B._fast is None:
+        pytest.skip("torch does not tell the current stream")
+    shape = B.make_shape(2, 1, 4, 2, 3, 1, 1)
+    x = torch.zeros(2, 4, 128, dtype=torch.bfloat16)
+    for name in ENTRIES:
+        f = getattr(B._fast, name)
+        for n in range(14):
+            for filler in (None, 3, "no", x, shape):
+                assert f(*([shape] + [filler] * (n - 1) if n else [])) is None
+    with pytest.raises(ValueError, match="device tensors required"):
+        B.marl_token_logprobs(torch.zeros(1, 8, dtype=torch.bfloat16), torch.zeros(1, dtype=torch.int32), 1.0, torch.zeros(1))
+
+
+def _calls():
+    """(name, function, arguments) of one right call of each entry; outputs are cleared by the caller."""
+    dev = "cuda"
+    gen = torch.Generator(device=dev).manual_seed(1)
+    attn = I.build_attn_inputs(I.WORKLOADS["tiny"], device=dev)
+    call = B.prepare_attn(attn, B.MARL_OUT_F32)
+    a = [call.shape, call.workspace, attn.q, attn.k_pages, attn.v_pages, attn.prefix_block_table, attn.suffix_block_table,
+         attn.prefix_lens, attn.suffix_lens, attn.group_of_seq, attn.scale, call.out]
+    x = I.randn_bf16((5, 1000), 3.0, gen, dev)
+    u = torch.rand(5, generator=gen, device=dev)
+    i32, f32 = (lambda: torch.zeros(5, dtype=torch.int32, device=dev)), (lambda: torch.zeros(5, device=dev))
+    ws = B.alloc_workspace(B.marl_sample_workspace_bytes(5, 1000), dev)
+    NS, Hkv = attn.num_seqs, attn.Hkv
+    new = [I.randn_bf16((NS, Hkv, 128), 1.0, gen, dev) for _ in range(2)]
+    lens = torch.full((NS,), 2, dtype=torch.int32, device=dev)
+    pre = I.build_prefill_inputs(8, 2, np.array([20, 33]), np.array([0, 16]), device=dev, seed=1, poison=False)
+    pshape, pws, pout = B.prepare_prefill(pre, B.MARL_OUT_BF16)
+    return [("decode_attn", B.marl_decode_attn, a, [11]),
+            ("token_logprobs", B.marl_token_logprobs, [x, i32(), 0.9, f32(), None], [3]),
+            ("sample_tokens", B.marl_sample_tokens, [x, u, 0.9, i32(), f32(), ws], [3, 4]),
+            ("sample_tokens_top_p", B.marl_sample_tokens_top_p, [x, u, 0.9, 0.8, i32(), f32()], [4, 5]),
+            ("kv_append", B.marl_kv_append, [call.shape, *new, attn.k_pages, attn.v_pages, attn.suffix_block_table, lens], [3, 4]),
+            ("prefill_attn", B.marl_prefill_attn, [pshape, pws, pre.q, pre.k_pages, pre.v_pages, pre.prefix_block_table, pre.q_start,
+                                                   pre.q_pos0, pre.scale, pout], [9])]
+
+
+def _outcome(f, args, outs):
+    try:
+        f(*args)
+    except Exception as e:      # noqa: BLE001 (what is compared is which)
+        return type(e).__name__ + ": " + str(e)
+    torch.cuda.synchronize()
+    return [args[k].clone() for k in outs]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", range(6))
+def test_both_ways_give_the_same(which, monkeypatch):
+    name, f, right, outs = _calls()[which]
+    print("case: fast calls", name, flush=True)
+    fast = B._fast
+    assert fast is not None
+    taken = getattr(fast, "sample_tokens" if name == "sample_tokens_top_p" else name)
+
+    def both(args):
+        monkeypatch.setattr(B, "_fast", fast)
+        short = _outcome(f, args, outs)
+        monkeypatch.setattr(B, "_fast", None)
+        return short, _outcome(f, args, outs)
+
+    def state():   # (appending changes the lengths: each way gets them as they were)
+        return [a.clone() if torch.is_tensor(a) and k == 6 and name == "kv_append" else a for k, a in enumerate(right)]
+    short, long = both(state()) if name != "kv_append" else (_outcome(f, state(), outs), None)
+    if name == "kv_append":
+        monkeypatch.setattr(B, "_fast", None)
+        long = _outcome(f, state(), outs)
+    assert isinstance(short, list) and all(torch.equal(s.view(torch.uint8), g.view(torch.uint8)) for s, g in zip(short, long))
+    # one argument wrong at a time: another type, another extent, a stride, host memory, nothing, a number that is none
+    for k, a in enumerate(right):
+        if torch.is_tensor(a):
+            wrong = [a.to(torch.float64), a[:-1], a.cpu(), None, 5]
+            if a.dim() > 1:
+                wrong.append(a.transpose(0, 1).contiguous().transpose(0, 1))
+            if a.dtype == torch.uint8:
+                wrong = [a[:100], a.cpu(), a[::2]]   # (a workspace: any number of bytes is looked at by the library)
+        elif isinstance(a, float):
+            wrong = ["x", float("nan")]
+        else:
+            continue
+        for w in wrong:
+            args = state()
+            args[k] = w
+            short, long = both(args)
+            if isinstance(short, str) or isinstance(long, str):
+                assert short == long, (k, short, long)
+    assert taken(*right[:1]) is None
