@@ -465,10 +465,10 @@ int marl_kv_copy_pages(const marl_attn_shape* shape, void* k_pages, void* v_page
 
 // ---- log-probabilities ------------------------------------------------------------------------
 // How a call is divided: the slices that the caller's workspace is sized for, and whether the rows are taken whole all
-// the same.  Whole rows need no second kernel (2-3 us) and pay once one workgroup of 1024 threads per CU is enough: from
-// 256 rows (333 x 20481: 11.6 -> 9.1 us, 700 x 32000: 15.6 -> 13.4), long rows from 512 (512 x 152064: 28.4 -> 27.4,
-// 700 x 100003: 29.2 -> 25.1; below, two workgroups on some CUs and one on the others: 300 x 152064 would go
-// from 20.1 to 22.8).  The 256 are the CUs of an MI355X and not asked of the device: sizes are answered without one.
+// the same.  Whole rows need no second kernel: short rows at any number (16 x 20481: 6.1 us in slices, 4.1 whole), up to
+// 65536 logits once there is one for each CU (256 x 65536: 8.9 us in slices at 128 rows, 6.9 whole at 256), long ones from 512
+// on (512 x 152064: 28.4 -> 24.6; below, two workgroups on some CUs and one on the others: 300 x 152064 16.9 us in
+// slices).  The 256 are the CUs of an MI355X and not asked of the device: sizes are answered without one.
 // What is asked for stays the slices' room, so that a workspace sized for a batch also serves smaller ones.
 struct LogprobSplit {
   int32_t slices, slice_len;
@@ -482,7 +482,7 @@ static int logprob_split(int32_t rows, int32_t vocab, LogprobSplit* s) {
   len = (len + 2047) / 2048 * 2048;
   s->slice_len = (int32_t)(len > vocab ? ((long)vocab + 7) / 8 * 8 : len);
   s->slices = (int32_t)(((long)vocab + s->slice_len - 1) / s->slice_len);
-  s->whole = s->slices == 1 || rows >= 512 || (rows >= 256 && vocab <= 65536);
+  s->whole = s->slices == 1 || rows >= 512 || vocab <= 40960 || (rows >= 256 && vocab <= 65536);
   return MARL_OK;
 }
 static size_t logprob_ws_bytes(int32_t rows, const LogprobSplit& s) {

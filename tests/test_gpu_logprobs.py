@@ -96,7 +96,8 @@ def test_rerun_bit_identical():
     assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("rows,vocab", [(255, 20481), (256, 65536), (256, 65537), (511, 20481), (512, 70001)])
+@pytest.mark.parametrize("rows,vocab", [(255, 20481), (256, 65536), (256, 65537), (511, 20481), (512, 70001),
+                                        (5, 8192), (5, 8193), (7, 40960), (7, 40961), (520, 49152), (520, 49153)])
 def test_whole_rows_and_slices_on_both_sides_of_the_rule(rows, vocab):
     print("case: logprobs rule", rows, vocab, flush=True)
     check(I.build_logprob_inputs(rows, vocab, 3.0, rows + vocab, temperature=0.9))
