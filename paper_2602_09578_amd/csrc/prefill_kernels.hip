@@ -106,10 +106,9 @@ __device__ __forceinline__ int group_tokens(const PrefillArgs& a, int g, int& fl
 // A group's nrows query rows are cut into ceil(nrows / kQB) blocks of equal size (a multiple of
 // 16 rows), not into full blocks and a remainder: 224 rows are two blocks of 112 (7 tiles each
 // over the waves), not 192 + 32.
-__device__ __forceinline__ int blocks_of(long nrows) { return (int)((nrows + kQB - 1) / kQB); }
-__device__ __forceinline__ int block_rows(long nrows) {
-  const long nb = (nrows + kQB - 1) / kQB;
-  return nb ? (int)(((nrows + nb - 1) / nb + 15) / 16 * 16) : 0;
+__device__ __forceinline__ int blocks_of(int nrows) { return (int)(((uint32_t)nrows + kQB - 1) / kQB); }
+__device__ __forceinline__ int block_rows(int nrows, int nb) {
+  return (int)((((uint32_t)nrows + nb - 1) / (uint32_t)nb + 15) / 16 * 16);
 }
 
 // A list record: the group and the block's first row (a multiple of 16) with the number of 16-row
@@ -126,64 +125,82 @@ constexpr int kPfMinPart = 512;   // keys: no part is meant to be shorter
 __constant__ constexpr float kPfLens[16] = {0.f, 0.5f, 0.625f, 0.75f, 0.875f, 1.f, 1.125f, 1.25f, 1.5f, 1.75f, 2.f, 2.5f, 3.f, 4.f, 6.f, 8.f};
 constexpr int kPfSplitBit = (int)0x80000000u;   // in a record's group: the entry is one part of the block's keys
 
+// What bounds it: the chain of its one workgroup's barriers and LDS round trips, and the stores of the list.  A group per
+// thread wrote hundreds of blocks one after the other, and one wave sorted a list and wrote its parts: now a wave writes a long
+// group, and eight waves have an entry per thread.  (16 prompts of up to 3798 tokens, 16 / 1 heads, 5000 blocks: 61.4 us,
+// now 5.6; 6 of up to 3132, 64 / 8 heads: 22.6, now 5.2; 3 of up to 1635, 28 / 4, weighed and in parts: 15.6, now 8.5;
+// 13 of up to 46, 28 / 4: 4.3, now 4.0.)
 __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArgs a) {
   constexpr int kWavesPf = kPlanThreadsPf / 64;
   __shared__ long long wave_sum[kWavesPf];   // 64-bit: inconsistent inputs must not wrap the sums
-  __shared__ int hist[kPfClasses];
+  __shared__ int hist[kPfClasses], starts[kPfClasses];
+  __shared__ int4 groups[kPlanThreadsPf];   // first entry, blocks, rows of a block, q_pos0
   __shared__ int2 list[kPfSorted];     // the first blocks and their groups' q_pos0: a short list never goes through memory
   __shared__ int list_pos0[kPfSorted];
-  __shared__ int flags_all, end_all, parts_used, most_keys;
+  __shared__ int flags_all, end_all, parts_used, most_keys, fewest, most, entries_all;
   __shared__ float estimate[kWavesPf];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int flag = 0;
-  if (tid == 0) flags_all = end_all = parts_used = most_keys = 0;
+  if (tid == 0) {
+    flags_all = end_all = parts_used = most_keys = most = entries_all = 0;
+    fewest = 0x7fffffff;
+  }
+  if (tid < kPfClasses) hist[tid] = 0;
   __syncthreads();
+  auto put = [&](int at, int2 rec, int pos0) {
+    if (at < kPfSorted) {
+      list[at] = rec;
+      list_pos0[at] = pos0;
+    } else {
+      a.items[at] = rec;
+    }
+  };
   long long carry = 0;
   for (int g0 = 0; g0 < a.NG; g0 += kPlanThreadsPf) {
     const int g = g0 + tid;
-    int nb = 0;
-    long nrows = 0;
+    int nb = 0, nrows = 0, pos0 = 0;
     if (g < a.NG) {
-      nrows = (long)group_tokens(a, g, flag) * a.R;
+      nrows = group_tokens(a, g, flag) * a.R;   // (at most all rows of q: less than 2^31)
       nb = blocks_of(nrows);
+      pos0 = a.q_pos0[g];
     }
     // groups that overlap in q could ask for more blocks than the workspace was sized for
     // (its bound assumes they share no rows): such a group is dropped
     if (nb > a.max_blocks) { nb = 0; flag |= MARL_FLAG_BAD_GROUP; }
-    long long inc = nb;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const long long t = __shfl_up(inc, d);
-      if (lane >= d) inc += t;
-    }
+    const long long inc = wave_inclusive_scan((long long)nb);
     if (lane == 63) wave_sum[wave] = inc;
-    __syncthreads();
+    const bool long_groups = __syncthreads_or(nb > 16);
     long long before = carry, all = 0;
+#pragma unroll
     for (int w = 0; w < kWavesPf; ++w) {
-      if (w < wave) before += wave_sum[w];
-      all += wave_sum[w];
+      const long long v = wave_sum[w];
+      before += w < wave ? v : 0;
+      all += v;
     }
+    int first = a.max_blocks;
     if (g < a.NG) {
       const long long first64 = before + inc - nb;
-      int first = a.max_blocks;
       if (first64 + nb > a.max_blocks) {   // as above; every later group then fails this test too
         flag |= MARL_FLAG_BAD_GROUP;
         nb = 0;
       } else {
         first = (int)first64;
-        atomicMax(&end_all, first + nb);
-        if (nb) atomicMax(&most_keys, a.q_pos0[g] + (int)(nrows / a.R));
-      }
-      // the group's blocks, last (most keys) first
-      const int qb = block_rows(nrows);
-      for (int k = 0; k < nb; ++k) {
-        const int2 rec = pack_item(g, (nb - 1 - k) * qb, qb);
-        if (first + k < kPfSorted) {
-          list[first + k] = rec;
-          list_pos0[first + k] = a.q_pos0[g];
-        } else {
-          a.items[first + k] = rec;
+        if (nb) {
+          atomicMax(&end_all, first + nb);
+          atomicMax(&most_keys, pos0 + nrows / a.R);
         }
+      }
+    }
+    // the groups' blocks, last (most keys) first
+    const int qb = nb ? block_rows(nrows, nb) : 0;
+    if (!long_groups) {   // workgroup-uniform
+      for (int k = 0; k < nb; ++k) put(first + k, pack_item(g, (nb - 1 - k) * qb, qb), pos0);
+    } else {
+      groups[tid] = make_int4(first, nb, qb, pos0);
+      __syncthreads();
+      for (int k0 = wave; k0 < min(kPlanThreadsPf, a.NG - g0); k0 += kWavesPf) {   // wave-uniform
+        const int4 v = groups[k0];
+        for (int k = lane; k < v.y; k += 64) put(v.x + k, pack_item(g0 + k0, (v.y - 1 - k) * v.z, v.z), v.w);
       }
     }
     carry += all;
@@ -193,27 +210,28 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
   __syncthreads();
   // The accepted groups' blocks are exactly [0, end_all).
   int total = end_all;   // (then entries of the list)
+  const int blocks = total;
   // A list of at most one item per workgroup needs no order; blocks of up to kPfLongKeys keys are not divided.
   const bool weigh = total <= kPfSorted && a.split_slots > 0 && most_keys > kPfLongKeys;
   const bool sorted = total <= kPfSorted && (weigh || (long)total * a.Hkv > a.slots);
   if (!sorted)
     for (int k = tid; k < min(total, kPfSorted); k += kPlanThreadsPf) a.items[k] = list[k];
-  // Every wave holds the list's blocks (keys: what a block's rows see, rounded up to whole rows of it).
-  constexpr int kPer = kPfSorted / 64;
-  int2 rec[kPer];
-  int keys[kPer], parts[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    rec[u] = make_int2(0, 0);
-    keys[u] = -1;
-    parts[u] = 1;
-    if (sorted && u * 64 + lane < total) {
-      rec[u] = list[u * 64 + lane];
-      keys[u] = list_pos0[u * 64 + lane] + ((rec[u].y & ~15) + (rec[u].y & 15) * 16) / a.R;
-    }
-  }
+  // keys of a block: what its rows see, rounded up to whole rows of it
+  auto keys_of = [&](int k) { return list_pos0[k] + ((list[k].y & ~15) + (list[k].y & 15) * 16) / a.R; };
+  float part_len = 0.f;   // keys that a part has at most; 0: whole blocks
+  auto parts_of = [&](int keys, float len) { return len > 0.f && keys > 0 ? min(kPfMaxDiv, (int)ceilf((float)keys / len)) : 1; };
   if (weigh) {
     for (int k = tid; k < kPfMaxParts; k += kPlanThreadsPf) a.split_arrived[k] = 0;
+    // Every wave holds the list's blocks.
+    constexpr int kPer = kPfSorted / 64;
+    int keys[kPer];
+    float all = 0.f;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      keys[u] = -1;
+      if (u * 64 < blocks) keys[u] = u * 64 + lane < blocks ? keys_of(u * 64 + lane) : -1;
+      all += (float)max(keys[u], 0);
+    }
     // Wave w estimates the time, in keys, with blocks divided into parts of at most kPfLens[w] even shares
     // (wave 0: whole blocks): the longest item if all run at once, else an even share of
     // all items and half an item.  An item costs 128 keys beside its own, a part more, and a part's sums are
@@ -224,27 +242,20 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
     // lists' is 26 %; 9 shapes are slower than whole by more than 2 %, the worst by 9 %.  The optimum is flat: 228 and
     // 1.1 in both kinds of list gave 1.5 % and 10 shapes, among others a prompt of 1172 tokens, 64 / 8 heads, 47.5 us
     // (whole 45.2), 60 of up to 78 behind up to 991, 16 / 1 heads, 49.5 (now 47.6).
-    const bool rounds = (long)total * a.Hkv > a.split_slots;
+    const bool rounds = (long)blocks * a.Hkv > a.split_slots;
     const float part_extra = rounds ? 228.f : 400.f, part_all = rounds ? 0.4f : 0.9f;
     auto sum_all = [](float v) { return wave_allreduce(v, [](float x, float y) { return x + y; }); };
-    float all = 0.f;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) all += (float)max(keys[u], 0);
     const float slots = (float)a.split_slots, share = sum_all(all) * (float)a.Hkv / slots;
-    auto divide = [&](int w) {
-      const float len = fmaxf((float)kPfMinPart, kPfLens[w] * share);
-#pragma unroll
-      for (int u = 0; u < kPer; ++u)
-        if (w > 0 && keys[u] > 0) parts[u] = min(kPfMaxDiv, (int)ceilf((float)keys[u] / len));
-    };
-    divide(wave);
+    auto len_of = [&](int w) { return w > 0 ? fmaxf((float)kPfMinPart, kPfLens[w] * share) : 0.f; };
+    const float len = len_of(wave);
     float items = 0.f, in_parts = 0.f, work = 0.f, longest = 0.f;
 #pragma unroll
     for (int u = 0; u < kPer; ++u)
       if (keys[u] >= 0) {
-        const float n = (float)parts[u], extra = parts[u] > 1 ? part_extra : 128.f;
+        const int parts = parts_of(keys[u], len);
+        const float n = (float)parts, extra = parts > 1 ? part_extra : 128.f;
         items += n;
-        in_parts += parts[u] > 1 ? n : 0.f;
+        in_parts += parts > 1 ? n : 0.f;
         work += (float)keys[u] + n * extra;
         longest = fmaxf(longest, (float)keys[u] / n + extra);
       }
@@ -258,58 +269,49 @@ __global__ __launch_bounds__(kPlanThreadsPf) void prefill_plan_kernel(PrefillArg
     const bool fits = entries <= (float)kPfSorted && in_parts <= (float)kPfMaxParts;
     if (lane == 0) estimate[wave] = wave == 0 ? (rounds ? 0.97f : 0.93f) * time : fits ? time : INFINITY;
     __syncthreads();
-    int best = 0;
-    for (int w = 1; w < kWavesPf; ++w)
-      if (estimate[w] < estimate[best]) best = w;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) parts[u] = 1;
-    divide(best);
-    if (best > 0) {
-      int n = 0;
-#pragma unroll
-      for (int u = 0; u < kPer; ++u) n += keys[u] >= 0 ? parts[u] : 0;
-      total = wave_allreduce(n, [](int x, int y) { return x + y; });
-    }
+    const float mine = estimate[lane & (kWavesPf - 1)];
+    const float least = wave_allreduce(mine, [](float x, float y) { return fminf(x, y); });
+    part_len = len_of(__builtin_ctzll(__builtin_amdgcn_ballot_w64(mine == least)));   // (the first of the least)
   }
-  if (wave == 0 && sorted) {
-    // counting sort over kPfClasses classes between the fewest and the most keys, in registers
-    int lo = 0x7fffffff, hi = 0;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      if (keys[u] >= 0) {
-        keys[u] /= parts[u];
-        lo = min(lo, keys[u]);
-        hi = max(hi, keys[u]);
+  if (sorted) {   // workgroup-uniform: a counting sort over kPfClasses classes between the fewest and the most keys
+    const bool entry = tid < blocks;   // (at most kPfSorted)
+    int keys = entry ? keys_of(tid) : 0;
+    const int parts = entry ? parts_of(keys, part_len) : 0;
+    if (entry) keys /= parts;
+    if (wave < kPfSorted / 64) {
+      const int lo = wave_allreduce(entry ? keys : 0x7fffffff, [](int x, int y) { return min(x, y); });
+      const int hi = wave_allreduce(keys, [](int x, int y) { return max(x, y); });
+      const int n = wave_allreduce(parts, [](int x, int y) { return x + y; });
+      if (lane == 0) {
+        atomicMin(&fewest, lo);
+        atomicMax(&most, hi);
+        atomicAdd(&entries_all, n);
       }
-    lo = wave_allreduce(lo, [](int x, int y) { return min(x, y); });
-    hi = wave_allreduce(hi, [](int x, int y) { return max(x, y); });
-    const int width = max(1, (hi - lo) / kPfClasses + 1);
-    hist[lane] = 0;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      if (keys[u] >= 0) atomicAdd(&hist[(hi - keys[u]) / width], parts[u]);
-    const int c = hist[lane];
-    int inc = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int t = __shfl_up(inc, d);
-      if (lane >= d) inc += t;
     }
-    hist[lane] = inc - c;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      if (keys[u] >= 0) {
-        const int at = atomicAdd(&hist[(hi - keys[u]) / width], parts[u]);
-        if (parts[u] == 1) {
-          a.items[at] = rec[u];
-        } else {
-          const int first_part = atomicAdd(&parts_used, parts[u]);
-          for (int k = 0; k < parts[u]; ++k) {
-            a.items[at + k] = make_int2(rec[u].x | kPfSplitBit, rec[u].y);
-            a.split_info[at + k] = (first_part << 8) | (k << 4) | (parts[u] - 1);
-          }
+    __syncthreads();
+    const int width = max(1, (most - fewest) / kPfClasses + 1), cls = (most - keys) / width;
+    if (entry) atomicAdd(&hist[cls], parts);
+    __syncthreads();
+    if (wave == 0) {
+      const int c = hist[lane];
+      starts[lane] = wave_inclusive_scan(c) - c;
+    }
+    __syncthreads();
+    if (entry) {
+      const int at = atomicAdd(&starts[cls], parts);
+      const int2 rec = list[tid];
+      if (parts == 1) {
+        a.items[at] = rec;
+      } else {
+        const int first_part = atomicAdd(&parts_used, parts);
+        for (int k = 0; k < parts; ++k) {
+          a.items[at + k] = make_int2(rec.x | kPfSplitBit, rec.y);
+          a.split_info[at + k] = (first_part << 8) | (k << 4) | (parts - 1);
         }
       }
+    }
+    __syncthreads();
+    total = entries_all;
   }
   if (tid == 0) {
     *a.list_length = total;

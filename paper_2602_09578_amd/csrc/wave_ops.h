@@ -78,6 +78,30 @@ __device__ __forceinline__ T wave_allreduce(T v, Op op) {
   const uint32_t b0 = b[0], b1 = b[1];
   return op(__builtin_bit_cast(T, b0), __builtin_bit_cast(T, b1));
 }
+// Inclusive scans over the wave in the vector ALU: four DPP row shifts scan each row of 16 lanes,
+// two row broadcasts add the totals of the rows before.  (A shuffle goes through the LDS crossbar,
+// a dependent round trip per step, two per step for a double.)
+template <int ctrl, int row_mask, class T>
+__device__ __forceinline__ T dpp_or_zero(T v) {
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), ctrl, row_mask, 0xf, false));
+  } else {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, ctrl, row_mask, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), ctrl, row_mask, 0xf, false);
+    return __builtin_bit_cast(T, (unsigned long long)lo | ((unsigned long long)hi << 32));
+  }
+}
+template <class T>
+__device__ __forceinline__ T wave_inclusive_scan(T v) {
+  v += dpp_or_zero<0x111, 0xf>(v);   // row_shr:1
+  v += dpp_or_zero<0x112, 0xf>(v);   // row_shr:2
+  v += dpp_or_zero<0x114, 0xf>(v);   // row_shr:4
+  v += dpp_or_zero<0x118, 0xf>(v);   // row_shr:8
+  v += dpp_or_zero<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
 // log p = ln 2 (x c - M - log2 S) of a logit x, with c = log2(e) / T, the maximum M of the row's scaled logits and the sum S of
 // their 2^(y - M).  One thread forms it per row, so in 64 bits: with M + log2 S and the differences in float32 their
 // roundings were most of the result's error (300 x 65536, T 1: 4.8e-8 -> 2.9e-8 of the value, of which the result's own

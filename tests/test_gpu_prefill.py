@@ -340,3 +340,14 @@ def test_lists_in_group_order_end_with_a_long_group(Hkv, groups):
     first = B.run_prefill(dev, shape, ws, out).clone()
     for _ in range(3):
         assert torch.equal(B.run_prefill(dev, shape, ws, out.zero_()), first)
+
+
+@pytest.mark.parametrize("blocks", [15, 16, 17, 64, 65, 130, 520])
+@pytest.mark.parametrize("before", [0, 3, 1030])
+def test_groups_of_many_blocks_are_listed_whole(blocks, before):
+    """A group's blocks are listed by one thread up to 16 and by a wave above that, 64 at a time; the long groups stand in
+    the plan's first round or its second, alone or among short ones, in lists that are sorted and that are not.  12 tokens
+    of 16 heads fill a block."""
+    print("case: prefill group of", blocks, "blocks behind", before, "groups", flush=True)
+    inp = I.build_prefill_inputs(16, 1, [1] * before + [12 * blocks, 5, 12 * blocks - 11], [9] * before + [0, 40, 7], seed=blocks)
+    check(inp)
