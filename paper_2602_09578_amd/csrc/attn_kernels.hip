@@ -73,16 +73,28 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int32_t* _
 
   // Q^T operand: lane (i, j) holds channels 8*(4*kk + j) .. +8 of q-row i
   u32x4 qreg[MT][4];
+  auto ready_q = [&] {
+#pragma unroll
+    for (int qt = 0; qt < MT; ++qt)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qreg[qt][kk][e] = row_index[qt] >= 0 ? qreg[qt][kk][e] ^ sign_flip : 0u;
+  };
 #pragma unroll
   for (int qt = 0; qt < MT; ++qt) {
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (row_index[qt] >= 0) {
-        v = *reinterpret_cast<const u32x4*>(a.q + (size_t)row_index[qt] * kD + (4 * kk + j) * 8);
-        v ^= sign_flip;
+      if constexpr (NW == 1) {   // without a branch, and used only once the first keys and values are requested too
+        qreg[qt][kk] = *reinterpret_cast<const u32x4*>(a.q + (size_t)max(row_index[qt], 0) * kD + (4 * kk + j) * 8);
+      } else {
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (row_index[qt] >= 0) {
+          v = *reinterpret_cast<const u32x4*>(a.q + (size_t)row_index[qt] * kD + (4 * kk + j) * 8);
+          v ^= sign_flip;
+        }
+        qreg[qt][kk] = v;
       }
-      qreg[qt][kk] = v;
     }
   }
 
@@ -134,6 +146,14 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int32_t* _
   int tn = t0 + stride;
   int n0 = 0, n1 = 0;
 
+  // a one-wave item's first prefix partial: max and sum with the queries, values in the place of the last keys
+  float2 ml0 = make_float2(-INFINITY, 0.f);
+  f32x4 o0[8];
+  const float* const o0_src = a.partial_o + (size_t)max(row_index[0], 0) * nslot * kD + 4 * j;
+  if constexpr (NW == 1) {
+    if (finish && n_prefix_partials > 0) ml0 = a.partial_ml[(size_t)max(row_index[0], 0) * nslot];
+  }
+
   auto step = [&](auto has_next_tag) {
     constexpr bool kHasNext = decltype(has_next_tag)::value;
     f32x4 s[MT][2];
@@ -148,6 +168,12 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int32_t* _
     if constexpr (kHasNext) issue_k(n0, n1);
 
     if constexpr (!kHasNext) {
+      if constexpr (NW == 1) {
+        if (finish && n_prefix_partials > 0) {   // wave-uniform
+#pragma unroll
+          for (int ct = 0; ct < 8; ++ct) o0[ct] = *reinterpret_cast<const f32x4*>(o0_src + 16 * ct);
+        }
+      }
       if (t0 + kBlockTok > tok_end) {   // wave-uniform: the ragged end of a chunk
         // tokens past the end: score -inf (weight 0), and zero their value slots, which may
         // hold anything (NaN included)
@@ -210,6 +236,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int32_t* _
     issue_k(n0, n1);
     issue_v(n0, n1);
     if (tn < tok_end) load_pages(tn, n0, n1);
+    if constexpr (NW == 1) ready_q();
     while (tn < tok_end) step(std::true_type{});
     step(std::false_type{});
   }
@@ -303,13 +330,19 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int32_t* _
           if (j == 0) a.partial_ml[ps] = make_float2(m_run[qt], l_run[qt]);
         } else {
           const size_t p0 = (size_t)row_index[qt] * nslot;
-          float mstar = m_run[qt];
-          for (int k = 0; k < n_prefix_partials; ++k) mstar = fmaxf(mstar, a.partial_ml[p0 + k].x);
+          float mstar = fmaxf(m_run[qt], ml0.x);
+          for (int k = 1; k < n_prefix_partials; ++k) mstar = fmaxf(mstar, a.partial_ml[p0 + k].x);
           float denom = 0.f;
           f32x4 sum[8];
 #pragma unroll
           for (int ct = 0; ct < 8; ++ct) sum[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-          for (int k = 0; k < n_prefix_partials; ++k) {
+          if (n_prefix_partials > 0) {
+            const float f = (ml0.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml0.x - mstar);
+            denom = __builtin_fmaf(ml0.y, f, denom);
+#pragma unroll
+            for (int ct = 0; ct < 8; ++ct) sum[ct] += o0[ct] * f;
+          }
+          for (int k = 1; k < n_prefix_partials; ++k) {
             const float2 v = a.partial_ml[p0 + k];
             const float f = (v.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(v.x - mstar);
             denom = __builtin_fmaf(v.y, f, denom);
@@ -411,6 +444,11 @@ void suffix_kernel(AttnArgs a) {
 // suffix chunks, as partials.  kFinish = true (first phase of the merge kernel, after the
 // prefix partials are complete): the items of sequences whose own tokens are that one item,
 // finished to output rows, so that they never travel through a partial.
+// What bounds a finished item is its chain of dependent loads (record, page ids, keys and values of each step, prefix partials)
+// with three waves per SIMD.  So nothing waits between the queries' request and the keys', and the first prefix partial is under way
+// while the last step is computed, in the last keys' registers (with the queries it had spilled): 8192 sequences of 40 tokens
+// behind 256, 28 / 4 heads, 228 -> 220 us (1.0 GB); of up to 60 behind 64: 200 -> 193; 64 x 32 of up to 64 behind 4096: 50.4 ->
+// 47.  (Records and page ids an item ahead, in three workgroups per CU that stay: the same to 1 us.)
 template <bool kFinish>
 __device__ __forceinline__ void short_suffix_items(const AttnArgs& a, int& bad_page) {
   const int n_long = a.counters[MARL_CTR_NUM_LONG_SUFFIX_ITEMS] * a.Hkv;

@@ -54,3 +54,15 @@ def test_pairs_at_the_rule(seqs):
     inp = custom_inputs(rng.integers(0, 90, 40), rng.integers(0, 200, seqs), gos, 8, 8, seed=4)
     call = check(inp, dict(suffix_chunk_tokens=8192))
     assert used_kernels(inp.to("cuda"), call) == ({"plan", "suffix", "merge"} if seqs * 8 <= 6144 else {"plan", "prefix", "suffix", "merge"})
+
+
+@pytest.mark.parametrize("Hq,Hkv,scale", [(28, 4, None), (16, 1, -0.1), (4, 4, None)])
+def test_short_items_behind_none_one_and_several_prefix_partials(Hq, Hkv, scale):
+    """Items of one wave, of one step and of several, with and without a ragged end: their first prefix partial is requested
+    before the last step is done, further ones after it."""
+    print("case: short items", Hq, Hkv, scale, flush=True)
+    plens = [0, 1, 64, 65, 200, 300]   # 0, 1, 1, 2, 4 and 5 chunks
+    own = [1, 16, 17, 31, 32, 33, 48, 64, 65, 127, 128]
+    gos = np.repeat(np.arange(6), len(own))
+    inp = custom_inputs(plens, own * 6, gos, Hq, Hkv, seed=Hq, scale=scale)
+    check(inp, dict(suffix_chunk_tokens=512, prefix_chunk_tokens=64))
