@@ -27,9 +27,9 @@ __device__ __forceinline__ int clamp_len(int v, int hi, int& flags) {
 // live in LDS, and global memory only sees the final stores.  The general plan kernel pays
 // a chain of ~30 dependent global round trips; this one pays one.  What bounds it is the chain of
 // barriers and LDS round trips of its one workgroup: the three scans (groups, suffix and prefix classes)
-// share one pass and stay in the vector ALU.  16 sequences 9.9 -> 7.2 us, 2048 sequences 12.0 -> 9.9 us (13.5 where
-// they are of two cost classes: atomics on the same word), launch included; the former time had a block-wide scan
-// with shuffles and three barriers for each of the three.
+// share one pass and stay in the vector ALU.  16 sequences 9.9 -> 7.2 us, 2048 sequences 12.0 -> 9.9 us, launch
+// included; the former time had a block-wide scan with shuffles and three barriers for each of the three.  (One LDS atomic
+// for all lanes of a wave that count in the same word: 11.9 -> 16.5 us, 2048 sequences; 14.4 -> 23.6, 4096.)
 // ---------------------------------------------------------------------------------------
 // Two sizes: up to 8192 sequences in 2048 groups (56 KB of LDS), and up to 32768 sequences in
 // 8192 groups with 16-bit member ids (130 KB of the 160 KB).
@@ -84,8 +84,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
   }
   for (int i = tid; i < kSmallMaxGroups; i += kThreads) cnt[i] = 0;
   for (int i = tid; i < kSmallMaxClasses; i += kThreads) { hist_s[i] = 0; hist_p[i] = 0; }
-  __shared__ int longest_prefix;
-  if (tid == 0) { n_long_items = 0; n_short_partial_items = 0; longest_prefix = 0; }
+  __shared__ int longest_prefix, any_ranked;
+  if (tid == 0) { n_long_items = 0; n_short_partial_items = 0; longest_prefix = 0; any_ranked = 0; }
   if (tid < 64) a.counters[tid] = 0;
   __syncthreads();
 
@@ -201,11 +201,13 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       }
     }
   }
+  bool ranked = false;   // a group that has an order
 #pragma unroll
   for (int k = 0; k < kGroupsPerThread; ++k) {
     const int g = tid + k * kThreads;
     if (g < a.NG) {
       a.group_count[g] = cnt[g];
+      ranked |= cnt[g] >= 2 && cnt[g] <= 64;
       a.group_start[g] = start[g];
       const int P = P_of[k];
       const int nqb = (cnt[g] * R + QB - 1) / QB;
@@ -226,17 +228,33 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
     }
   }
   if (tid == 0) a.group_start[a.NG] = nseq_grouped;
+  if (ranked) any_ranked = 1;
   __syncthreads();
 
-  // ascending sequence id inside every group of at most 64 members (as in the general kernel)
+  // ascending sequence id inside every group of at most 64 members (as in the general kernel).  Lanes of a wave usually get their
+  // ranks in order, so a group whose members stand side by side is in order already: only one where a member finds
+  // a later sequence before it is ranked by counting (launch included, 128 groups of 64: 52.6 -> 31 us, 64 of 32: 14.8 -> 12.6,
+  // 20 of 64: 13.6 -> 10.8; 85 of 24, of which some lie in two waves: 13.0 and 12.9; none to order: the same).
+  constexpr int kOutOfOrder = 1 << 30;
+  if (any_ranked) {   // workgroup-uniform
+#pragma unroll
+    for (int k = 0; k < kSeqsPerThread; ++k) {
+      const int s = tid + k * kThreads;
+      if (s < a.NS && rank_of[k] > 0) {
+        const int g = G(k);
+        if ((int)members[start[g] + rank_of[k] - 1] > s) atomicOr(&cnt[g], kOutOfOrder);
+      }
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int k = 0; k < kSeqsPerThread; ++k) {
     const int s = tid + k * kThreads;
     if (s < a.NS && rank_of[k] >= 0) {
       const int g = G(k);
-      const int b = start[g], n = cnt[g];
+      const int b = start[g], n = cnt[g] & (kOutOfOrder - 1);
       int place = rank_of[k];
-      if (n <= 64) {
+      if (n <= 64 && n != cnt[g]) {
         place = 0;
         for (int m0 = 0; m0 < n; m0 += 8) {   // (eight reads in flight)
           int v[8];

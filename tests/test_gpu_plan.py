@@ -137,3 +137,26 @@ def test_plan_general_kernel_for_shapes_beyond_the_lds_variants():
     shape, pl, sl, gos = big_case(4000, 8, 10, 14)       # too many sequences
     assert len(gos) > 32768
     compare(shape, pl, sl, gos, 8, 2)
+
+
+@pytest.mark.parametrize("NS,size", [(2048, 64), (2048, 1), (1100, 2), (1500, 24), (2016, 63), (2050, 65), (9000, 3)])
+@pytest.mark.parametrize("layout", ["side by side", "turned round", "every NG-th", "one stray"])
+def test_plan_members_in_order_however_they_stand(NS, size, layout):
+    """Groups whose members' ranks are in order already, and groups that have to be ranked, alone and among the others."""
+    print("case: plan members", NS, size, layout, flush=True)
+    NG = -(-NS // size)
+    gos = (np.arange(NS) // size).astype(np.int32)
+    if layout == "turned round":
+        gos = gos[::-1].copy()
+    elif layout == "every NG-th":
+        gos = (np.arange(NS) % NG).astype(np.int32)
+    elif layout == "one stray":
+        gos[[0, NS - 1]] = gos[[NS - 1, 0]]
+    shape = B.make_shape(NS, NG, 8, 2, 10, 2, 2, suffix_chunk_tokens=32)
+    pl, sl = np.full(NG, 20, np.int32), np.arange(NS, dtype=np.int32) % 33
+    if size <= 64:
+        compare(shape, pl, sl, gos, 8, 2)
+    else:   # groups above 64 sequences are sets
+        got = read_plan(shape, pl, sl, gos)
+        for g in range(NG):
+            assert sorted(got["seqs"][got["start"][g]:got["start"][g + 1]]) == list(np.nonzero(gos == g)[0])
