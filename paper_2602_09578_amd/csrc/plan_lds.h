@@ -139,7 +139,9 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       }
     }
   }
-  if (longest > 0) atomicMax(&longest_prefix, longest);
+  // (one atomic per wave: one per group took 1.7 us of the plan of 256 groups)
+  longest = wave_allreduce(longest, [](int x, int y) { return max(x, y); });
+  if (lane_id() == 0 && longest > 0) atomicMax(&longest_prefix, longest);
   int own = 0;
 #pragma unroll
   for (int k = 0; k < kGroupsPerThread; ++k) own += cnt[tid * kGroupsPerThread + k];   // (zero from NG on)
