@@ -32,7 +32,7 @@ HBM_PEAK_GBPS = 8000.0
 # run, gives).  Valid only for the kernel source and flags it was taken
 # with: reported as null when either has changed since.
 SUFFIX_TRAFFIC = {"workload": "qwen7b", "bytes": 5556.7e6 + 14.1e6,
-                  "kernel_sources_sha256": "ada12b6bb75c60a457e30a968aff96477c2deb863ec35bb0787cfb8515aed77c"}
+                  "kernel_sources_sha256": "9dad4206dfdb085ea6e08a80ebcfe6623e803e51c88d6687ed0921ab46aa370d"}
 SUFFIX_SOURCES = ("attn_kernels.hip", "wave_ops.h")
 
 
@@ -109,7 +109,9 @@ def dominant_kernel_roofline(w, attn, call, stage_ms):
     flops = int(4 * 128 * w.Hq * (P * counts).sum())
     tf = flops / (stage_ms["prefix"] * 1e-3) / 1e12
     pbytes = int(P.sum()) * bpt
-    return {"kernel": "prefix_kernel", "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
+    kernel = ("decode_small_kernel" if stage_ms["plan"] == 0 else   # one kernel for the whole call
+              "items_kernel" if w.num_seqs * w.Hkv <= 6144 else "prefix_kernel")
+    return {"kernel": kernel, "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
             "frac": tf / 2500.0, "traffic": None, "algorithmic_flops_per_launch": flops,
             "avg_launch_ms": stage_ms["prefix"],
             "hbm_frac_on_unique_prefix_bytes": pbytes / (stage_ms["prefix"] * 1e-3) / 1e9 / HBM_PEAK_GBPS}

@@ -9,8 +9,9 @@
 // time).  The general kernels' three or four dependent launches (plan 5, prefix 9, merge 9 us of kernel time at the first
 // size) pass the work list and the partials through memory.  A prefix is read once per sequence here and not once per
 // group; the L2s serve that (see the order of the workgroups below).  Measured per call, general kernels and this one:
-// 16 sequences in 4 groups, 8 / 2 heads, 256 + 128 tokens: 22.0 and 8.1 us; 32 heads' worth of items with 4096 + 4096
-// tokens: 45 and 19 us (8 parts); 256 sequences in 64 groups, 8 / 2 heads, 1024 + 1024 tokens: 66 and 42 us.
+// 16 sequences in 4 groups, 8 / 2 heads, 256 + 128 tokens: 22.0 and 8.1 us (6.4 since the plan looks at padded page tables in
+// pieces and the binding's calls are lighter); 32 heads' worth of items with 4096 + 4096 tokens: 45 and 19 us (8
+// parts); 256 sequences in 64 groups, 8 / 2 heads, 1024 + 1024 tokens: 66 and 42 us.
 //
 // Wave-level scheme as in attn_kernels.hip (v_mfma_f32_16x16x32_bf16, K and V straight into operand registers).
 #include <algorithm>

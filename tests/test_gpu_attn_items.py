@@ -1,4 +1,4 @@
-"""The kernel that takes prefix and suffix items from one queue: against the float64 checker where its queue, its
+"""The kernel that takes prefix and suffix items from one queue: against the float64 oracle where its queue, its
 rule and what it leaves to the merge kernel change."""
 import numpy as np
 import pytest

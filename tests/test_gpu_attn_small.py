@@ -1,4 +1,4 @@
-"""The one-launch kernel that serves small decode calls: against the float64 checker and against the general
+"""The one-launch kernel that serves small decode calls: against the float64 oracle and against the general
 kernels (which calls that name their chunk sizes take), at the edges of its rule and of its parts."""
 import numpy as np
 import pytest
