@@ -838,13 +838,21 @@ __device__ __forceinline__ void items_kernel_body(const AttnArgs& a) {
   __shared__ union { PrefixLds ring; ItemLds<1> item; } lds;
   __shared__ int next_item;
   const int n_long = a.counters[MARL_CTR_NUM_LONG_SUFFIX_ITEMS] * a.Hkv;
-  // short items become partials only where their sequence has several chunks; the merge kernel takes the others
-  const int n_suffix = a.counters[MARL_CTR_NUM_SHORT_PARTIAL_ITEMS] > 0 ? a.counters[MARL_CTR_NUM_SUFFIX_ITEMS] * a.Hkv : n_long;
   const int pairs = a.counters[MARL_CTR_NUM_PREFIX_ITEMS] * a.Hkv;
   const int n_prefix = kWide ? (pairs + 7) / 8 * 16 : pairs;   // (halves of a wide block meet on an XCD, as in prefix_kernel_body)
+  // Short items become partials only where their sequence has several chunks (the merge kernel takes the others).  In short
+  // lists they are entries of the queue, else the waves take them first: drawn one by one they cost a draw each, and
+  // so do those that are left to the merge kernel (1760 pairs of up to 283 tokens, 46.7 us apart: 60.4, now 46.4; 512
+  // sequences of up to 1024 in chunks of 64, 28 / 4 heads, 273 apart: 404, now 268; by waves in short lists: 17.4 -> 23.1 for 117
+  // pairs).  One draw per workgroup is about where the two meet: lists of 640 to 800 entries 4 % apart, either way.
+  const bool partials = a.counters[MARL_CTR_NUM_SHORT_PARTIAL_ITEMS] > 0;
+  const int n_all = a.counters[MARL_CTR_NUM_SUFFIX_ITEMS] * a.Hkv;
+  const bool as_entries = partials && n_prefix + n_all <= (int)(gridDim.x + gridDim.x / 2);
+  const int n_suffix = as_entries ? n_all : n_long;
   const int head = a.counters[MARL_CTR_NUM_FIRST_SUFFIX_ITEMS] * a.Hkv;
   const int i = threadIdx.x & 15;
   int bad_page = 0;
+  if (partials && !as_entries) short_suffix_items<false>(a, bad_page);
   for (int e = blockIdx.x; e < n_prefix + n_suffix;) {   // workgroup-uniform
     if (e >= head && e < head + n_prefix) {
       const int qi = e - head;

@@ -9,11 +9,16 @@ from tests.test_gpu_attn import custom_inputs
 from tests.test_gpu_attn_small import used_kernels
 
 pytestmark = pytest.mark.gpu
+CTR_DRAWN = 2   # items that were drawn from the queue
 CTR_FIRST = 8   # suffix items that the queue has before the prefix items
 
 
+def counter(call, which):
+    return int(call.workspace[:256].cpu().numpy().view(np.int32)[which])
+
+
 def first_items(call):
-    return int(call.workspace[:256].cpu().numpy().view(np.int32)[CTR_FIRST])
+    return counter(call, CTR_FIRST)
 
 
 def check(inp, call_args, tol=ATTN_TOL):
@@ -66,3 +71,20 @@ def test_short_items_behind_none_one_and_several_prefix_partials(Hq, Hkv, scale)
     gos = np.repeat(np.arange(6), len(own))
     inp = custom_inputs(plens, own * 6, gos, Hq, Hkv, seed=Hq, scale=scale)
     check(inp, dict(suffix_chunk_tokens=512, prefix_chunk_tokens=64))
+
+
+@pytest.mark.parametrize("seqs,Hkv,drawn", [(30, 4, 0), (600, 4, 0), (600, 8, 1)])
+def test_short_items_are_not_drawn(seqs, Hkv, drawn):
+    """Two sequences of several chunks with a short tail among many of one short item: entries of a short
+    queue, else taken by waves before it, and what the merge kernel finishes costs no draw.  (The last case draws for
+    its prefix items.)"""
+    print("case: short items and draws", seqs, Hkv, flush=True)
+    rng = np.random.default_rng(seqs)
+    slens = rng.integers(1, 129, seqs)
+    slens[[3, seqs - 1]] = [2 * 160 + 40, 160 + 128]
+    groups = seqs // 4 if drawn else 8
+    inp = custom_inputs(rng.integers(1, 90, groups), slens, np.arange(seqs) % groups, 2 * Hkv, Hkv, seed=seqs)
+    call = check(inp, dict(suffix_chunk_tokens=160, prefix_chunk_tokens=96))
+    prefix = groups * Hkv
+    assert counter(call, CTR_DRAWN) <= drawn * (prefix + 3 * Hkv)
+    check(inp, dict(suffix_chunk_tokens=32, prefix_chunk_tokens=32))
