@@ -274,8 +274,7 @@ __global__ __launch_bounds__(kAttnThreads) void merge_parts_kernel(AttnArgs a) {
 // at most 1536 workgroups come of it (768 run at a time; 768 or 512 in all lose 2-4 %, as lengths differ).
 int small_attn_splits(const AttnArgs& a) {
   const long items = (long)a.NS * a.Hkv, prefix = (long)a.max_pp * kPage, own = (long)a.max_sp * kPage;
-  const long entries = (long)a.NS * a.max_sp + (long)a.NG * a.max_pp;   // (which the plan's workgroup looks through)
-  if (a.NS > kSmallAttnSeqs || a.NG > kSmallAttnSeqs || items > 1l << 16 || entries > 1l << 17) return 0;
+  if (a.NS > kSmallAttnSeqs || a.NG > kSmallAttnSeqs || items > 1l << 16) return 0;
   if (items * (prefix + own) > 3l << 19 || items * prefix > 1l << 20) return 0;
   if (prefix + own < 1024) return 1;
   const long n = std::min({(prefix + own) / 384, 1536 / items, 16l, (long)a.NCp + a.NCs});

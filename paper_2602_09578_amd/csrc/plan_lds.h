@@ -2,6 +2,8 @@
 // bookkeeping in LDS: device code shared by the plan kernels and by the kernel that serves a small call alone.
 #ifndef MARL_PLAN_LDS_H
 #define MARL_PLAN_LDS_H
+#include <type_traits>
+
 #include "marl_internal.h"
 #include "wave_ops.h"
 
@@ -36,7 +38,7 @@ __device__ __forceinline__ int clamp_len(int v, int hi, int& flags) {
 constexpr int kSmallMaxClasses = 256;
 
 // kCheckPages: the plan's workgroup also looks for block-table entries outside the pool among those of addressed
-// tokens (where nobody else reports them); at most a few entries per thread are expected.
+// tokens (where nobody else reports them).
 template <int kThreads, int kSmallMaxSeqs, int kSmallMaxGroups, class MemberId, bool kCheckPages = false>
 __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
   constexpr int kSeqsPerThread = kSmallMaxSeqs / kThreads;
@@ -276,36 +278,41 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
     for (int k = 0; k < kSeqsPerThread; ++k)
       if (tid + k * kThreads < a.NS) suffix_len[tid + k * kThreads] = S_keep[k];
     __syncthreads();
-    // (the whole table in 16-byte pieces: its rows may be tens of thousands of entries for this one workgroup)
-    auto check = [&](const int32_t* table, int rows, int pages, auto&& tokens) {
-      typedef int int4_any __attribute__((ext_vector_type(4), aligned(4)));
-      constexpr int kAtOnce = 8;
-      const int n = rows * pages;
-      auto look = [&](int row, int page, int id) {
-        if ((unsigned)id >= (unsigned)a.num_pages && page * kPage < tokens(row)) flags |= MARL_FLAG_BAD_PAGE;
-      };
-      for (int p0 = tid; p0 < n / 4; p0 += kAtOnce * kThreads) {
-        int4_any ids[kAtOnce];
+    // Entries of addressed tokens only: tables of a fixed capacity are mostly padding, and looking through all of it took one
+    // workgroup longer than the attention (one sequence of 40 tokens in a row for 2^20: 29.7 us, now 8.4, general kernels 14.6; 512
+    // of up to 40 in rows for 2048: 33.8, now 13.1, 23.4).  A power of two lanes share a row, as many as there are for each; with a row or less
+    // for each eight pieces of it are requested together, else two pieces of four rows.
+    auto check = [&](const int32_t* table, const int rows, const int pages, auto&& tokens) {
+      if (rows == 0 || pages == 0) return;   // workgroup-uniform, as all of the loops' bounds but the lengths
+      int lanes = 8;
+      while (2 * lanes * rows <= kThreads) lanes *= 2;
+      const int teams = kThreads / lanes, team = tid / lanes, lane = tid & (lanes - 1);
+      auto look = [&](auto rows_tag) {
+        constexpr int kRows = decltype(rows_tag)::value, kPieces = 8 / kRows;
+        for (int r0 = team; r0 < rows; r0 += kRows * teams) {
+          int n[kRows], longest = 0;
 #pragma unroll
-        for (int u = 0; u < kAtOnce; ++u) ids[u] = *reinterpret_cast<const int4_any*>(table + 4 * min(p0 + u * kThreads, n / 4 - 1));
+          for (int u = 0; u < kRows; ++u) {
+            n[u] = r0 + u * teams < rows ? (tokens(r0 + u * teams) + kPage - 1) / kPage : 0;
+            longest = max(longest, n[u]);
+          }
+          for (int p0 = lane; p0 < longest; p0 += kPieces * lanes) {
+            int id[kRows][kPieces];
 #pragma unroll
-        for (int u = 0; u < kAtOnce; ++u) {
-          const int p = p0 + u * kThreads;
-          // (entries past a row's pages are -1 by convention: only pieces with an id outside the pool are looked at)
-          if (p < n / 4 && max(max((unsigned)ids[u][0], (unsigned)ids[u][1]), max((unsigned)ids[u][2], (unsigned)ids[u][3])) >= (unsigned)a.num_pages) {
-            int row = 4 * p / pages, page = 4 * p - row * pages;
+            for (int u = 0; u < kRows; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              look(row, page, ids[u][e]);
-              if (++page == pages) { page = 0; ++row; }
-            }
+              for (int k = 0; k < kPieces; ++k)   // (in the row whatever its length)
+                id[u][k] = table[(size_t)min(r0 + u * teams, rows - 1) * pages + max(min(p0 + k * lanes, n[u] - 1), 0)];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u)
+#pragma unroll
+              for (int k = 0; k < kPieces; ++k)
+                if ((unsigned)id[u][k] >= (unsigned)a.num_pages && n[u] > 0) flags |= MARL_FLAG_BAD_PAGE;   // (past the end: the last one again)
           }
         }
-      }
-      if (tid < (n & 3)) {
-        const int e = (n & ~3) + tid, row = e / pages;
-        look(row, e - row * pages, table[e]);
-      }
+      };
+      if (rows <= teams) look(std::integral_constant<int, 1>{});
+      else look(std::integral_constant<int, 4>{});
     };
     check(a.suffix_table, a.NS, a.max_sp, [&](int s) { return suffix_len[s]; });
     check(a.prefix_table, a.NG, a.max_pp, [&](int g) { return cnt[g] ? prefix_len[g] : 0; });

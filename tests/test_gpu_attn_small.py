@@ -110,3 +110,44 @@ def test_work_list_and_flags_are_left_as_the_header_says():
     assert B.marl_attn_read_flags(call.workspace) == B.FLAG_BAD_PAGE
     others = [s for s in range(len(gos)) if s != 3]
     assert torch.equal(call.out[others], good[others]) and torch.isfinite(call.out[3]).all()
+
+
+# (sequences, longest own row in pages, capacity of a row in pages): one row and a row or more for every eight lanes of the
+# plan's workgroup, rows of less than one request and of several
+@pytest.mark.parametrize("seqs,longest,capacity", [(1, 3, 40), (1, 2060, 4000), (3, 65, 65), (32, 70, 90), (33, 17, 100), (130, 9, 200), (512, 3, 160)])
+def test_bad_page_ids_in_tables_of_a_fixed_capacity(seqs, longest, capacity):
+    """Entries outside the pool count up to a row's last addressed one, and not behind it (where there is nothing but them)."""
+    print("case: small call, tables of a fixed capacity", seqs, longest, capacity, flush=True)
+    rng = np.random.default_rng(seqs + longest)
+    slens = rng.integers(1, 16 * longest + 1, seqs)
+    slens[0] = 16 * longest
+    groups = max(1, seqs // 5)
+    inp = custom_inputs(rng.integers(0, 200, groups), slens, np.arange(seqs) % groups, 2, 1, seed=seqs, poison=False)
+    want = oracle_attn(inp)
+    inp = inp.to("cuda")
+    def widen(table, pages):
+        wide = torch.randint(0, 2, (table.shape[0], pages), dtype=torch.int32, device="cuda") * (2 ** 31 - 1) - (2 ** 30)
+        wide[:, :table.shape[1]] = torch.where(table < 0, wide[:, :table.shape[1]], table)
+        return wide
+    inp.suffix_block_table, inp.prefix_block_table = widen(inp.suffix_block_table, capacity), widen(inp.prefix_block_table, 20)
+    call = B.prepare_attn(inp, B.MARL_OUT_F32)
+    used = used_kernels(inp, call)
+    assert "plan" not in used
+    assert B.marl_attn_read_flags(call.workspace) == 0
+    good = call.out.clone()
+    assert np.abs(good.cpu().numpy() - want).max() <= ATTN_TOL + 2.0 ** -9 * np.abs(want).max()
+    lens = inp.suffix_lens.tolist()
+    for s in sorted({0, seqs // 2, seqs - 1}):
+        last = (lens[s] - 1) // 16
+        for page in sorted({0, last // 2, last}):
+            kept = int(inp.suffix_block_table[s, page])
+            inp.suffix_block_table[s, page] = inp.num_pages + int(rng.integers(0, 3))
+            B.run_attn(inp, call)
+            assert B.marl_attn_read_flags(call.workspace) == B.FLAG_BAD_PAGE, (s, page)
+            inp.suffix_block_table[s, page] = kept
+    g = int(inp.group_of_seq[seqs - 1])
+    last = (int(inp.prefix_lens[g]) - 1) // 16
+    if last >= 0:
+        inp.prefix_block_table[g, last] = -1
+        B.run_attn(inp, call)
+        assert B.marl_attn_read_flags(call.workspace) == B.FLAG_BAD_PAGE
