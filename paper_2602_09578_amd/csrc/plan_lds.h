@@ -279,16 +279,18 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       if (tid + k * kThreads < a.NS) suffix_len[tid + k * kThreads] = S_keep[k];
     __syncthreads();
     // Entries of addressed tokens only: tables of a fixed capacity are mostly padding, and looking through all of it took one
-    // workgroup longer than the attention (one sequence of 40 tokens in a row for 2^20: 29.7 us, now 8.4, general kernels 14.6; 512
-    // of up to 40 in rows for 2048: 33.8, now 13.1, 23.4).  A power of two lanes share a row, as many as there are for each; with a row or less
-    // for each eight pieces of it are requested together, else two pieces of four rows.
+    // workgroup longer than the attention (one sequence of 40 tokens in a row for 2^20: 29.7 us, now 8.4, general kernels 14.6;
+    // 512 of up to 40 in rows for 2048: 33.8, now 13.2, 23.4).  A power of two lanes share a row, as many as there are for each.
+    // With at most a row for each team of lanes a lane requests sixteen of its entries together, else two of four rows (eight
+    // instead of sixteen: 16 rows of 1024 entries 29.7 us, now 28.4; 16 bytes at a time, or four of four rows, or one of eight:
+    // 512 rows of 3 entries 10.1 to 10.6 us, now 10.0).
     auto check = [&](const int32_t* table, const int rows, const int pages, auto&& tokens) {
       if (rows == 0 || pages == 0) return;   // workgroup-uniform, as all of the loops' bounds but the lengths
       int lanes = 8;
       while (2 * lanes * rows <= kThreads) lanes *= 2;
       const int teams = kThreads / lanes, team = tid / lanes, lane = tid & (lanes - 1);
-      auto look = [&](auto rows_tag) {
-        constexpr int kRows = decltype(rows_tag)::value, kPieces = 8 / kRows;
+      auto look = [&](auto rows_tag, auto entries_tag) {
+        constexpr int kRows = decltype(rows_tag)::value, kPieces = decltype(entries_tag)::value;
         for (int r0 = team; r0 < rows; r0 += kRows * teams) {
           int n[kRows], longest = 0;
 #pragma unroll
@@ -311,8 +313,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
           }
         }
       };
-      if (rows <= teams) look(std::integral_constant<int, 1>{});
-      else look(std::integral_constant<int, 4>{});
+      if (rows <= teams) look(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
+      else look(std::integral_constant<int, 4>{}, std::integral_constant<int, 2>{});
     };
     check(a.suffix_table, a.NS, a.max_sp, [&](int s) { return suffix_len[s]; });
     check(a.prefix_table, a.NG, a.max_pp, [&](int g) { return cnt[g] ? prefix_len[g] : 0; });

@@ -114,7 +114,7 @@ def test_work_list_and_flags_are_left_as_the_header_says():
 
 # (sequences, longest own row in pages, capacity of a row in pages): one row and a row or more for every eight lanes of the
 # plan's workgroup, rows of less than one request and of several
-@pytest.mark.parametrize("seqs,longest,capacity", [(1, 3, 40), (1, 2060, 4000), (3, 65, 65), (32, 70, 90), (33, 17, 100), (130, 9, 200), (512, 3, 160)])
+@pytest.mark.parametrize("seqs,longest,capacity", [(1, 3, 40), (1, 2060, 4000), (2, 3, 3), (70, 2, 2), (40, 4, 4), (3, 65, 65), (32, 70, 90), (33, 17, 100), (130, 9, 200), (512, 3, 160)])
 def test_bad_page_ids_in_tables_of_a_fixed_capacity(seqs, longest, capacity):
     """Entries outside the pool count up to a row's last addressed one, and not behind it (where there is nothing but them)."""
     print("case: small call, tables of a fixed capacity", seqs, longest, capacity, flush=True)
