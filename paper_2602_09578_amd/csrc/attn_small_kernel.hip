@@ -209,18 +209,36 @@ __device__ __forceinline__ void small_item(const AttnArgs& a, const int s, const
 
 // Workgroups are dealt to the eight XCDs in turn.  The workgroups of eight neighbouring sequences (usually samples of
 // one prompt) for one KV head and part follow each other on one XCD, so that the prefix they share is read out
-// of its L2: 64 groups of 4 samples, 16 / 2 heads, 2304 tokens: 67 -> 41 us against a plain order.
+// of its L2: 64 groups of 4 samples, 16 / 2 heads, 2304 tokens: 67 -> 41 us against a plain order.  The last block of sequences
+// comes after the others and is as wide as there are sequences left: with empty workgroups for those that are not there, the
+// others met on a few CUs of the XCD (one sequence, 8 KV heads, 131072 tokens: 282 us, now 112; 4 KV heads, 16384: 25.7, now 16.9).
+struct SmallGrid {
+  int units;        // (KV head, part) pairs of a block of sequences
+  int left;         // sequences of the last, narrower block
+  int full_slots;   // of an XCD: workgroups for blocks of kSeqBlock sequences (the last eight units may be past the end)
+  __host__ __device__ SmallGrid(const AttnArgs& a)
+      : units(a.Hkv * a.splits), left(a.NS % kSeqBlock), full_slots((a.NS / kSeqBlock * units + 7) / 8 * kSeqBlock) {}
+  __host__ __device__ int workgroups() const { return 8 * (full_slots + (units + 7) / 8 * left); }
+};
+
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3)))
 void decode_small_kernel(AttnArgs a) {
   if (blockIdx.x == 0) {
     plan_in_lds<kAttnThreads, kSmallAttnSeqs, kSmallAttnSeqs, int, true>(a);
     return;
   }
-  const int b = blockIdx.x - 1, in_xcd = b >> 3;
-  const int unit = in_xcd / kSeqBlock * 8 + (b & 7);
+  const SmallGrid g(a);
+  const int xcd = (blockIdx.x - 1) & 7, slot = (blockIdx.x - 1) >> 3;
+  int unit = slot / kSeqBlock * 8 + xcd, first = 0, at = slot % kSeqBlock, end = a.NS - g.left;
+  if (slot >= g.full_slots) {   // workgroup-uniform
+    unit = (slot - g.full_slots) / g.left * 8 + xcd;
+    at = (slot - g.full_slots) % g.left;
+    first = end;
+    end = a.NS;
+  }
   const int part = unit % a.splits, pair = unit / a.splits;
-  const int s = pair / a.Hkv * kSeqBlock + in_xcd % kSeqBlock;
-  if (s < a.NS) small_item(a, s, pair % a.Hkv, part);   // (the last units may be past the end)
+  const int s = first + pair / a.Hkv * kSeqBlock + at;
+  if (s < end) small_item(a, s, pair % a.Hkv, part);   // (the last units may be past the end)
 }
 
 // Parts of a row added in their order (half a wave per row): the formula of the general merge kernel.
@@ -271,7 +289,10 @@ __global__ __launch_bounds__(kAttnThreads) void merge_parts_kernel(AttnArgs a) {
 // were timed with both.  Up to 1.5 M of them, of which 1 M may be prefix, 6 of 2788 batches lose more than 3 % and the mean
 // gain is 2.1 times; at 2 M and 1.3 M 16 of 3055 lose, the worst 0.72 times.
 // Parts: none below 1024 tokens (the second launch costs 3 us: 8 against 11 us), else of 384 tokens, as long as
-// at most 1536 workgroups come of it (768 run at a time; 768 or 512 in all lose 2-4 %, as lengths differ).
+// at most 1536 workgroups come of it (768 run at a time; 768 or 512 in all lose 2-4 %, as lengths differ), and at most 16 of a
+// row: what the second launch adds up grows with them, and is paid by what a table can hold (8 sequences of 40 tokens in rows for
+// 131072, one KV head: 8.6 us, 10.5 with 32 parts, 14.3 with 64; 10 pairs of 16384: 19.1, 23.5, 23.1), while one
+// to four pairs of long rows would gain (one of 16384: 15.5, 12.9, 13.5; of 131072: 79, 45, 33).
 int small_attn_splits(const AttnArgs& a) {
   const long items = (long)a.NS * a.Hkv, prefix = (long)a.max_pp * kPage, own = (long)a.max_sp * kPage;
   if (a.NS > kSmallAttnSeqs || a.NG > kSmallAttnSeqs || items > 1l << 16) return 0;
@@ -282,8 +303,7 @@ int small_attn_splits(const AttnArgs& a) {
 }
 
 hipError_t launch_small_attn(const AttnArgs& a, hipStream_t st) {
-  const int units = (a.NS + kSeqBlock - 1) / kSeqBlock * a.Hkv * a.splits;   // (at most 3 << 15 workgroups of work: see above)
-  const int grid = (units + 7) / 8 * 8 * kSeqBlock + 1;
+  const int grid = SmallGrid(a).workgroups() + 1;   // (at most 65536 pairs and 1536 parts: see above)
   hipLaunchKernelGGL(decode_small_kernel, dim3(grid), dim3(kAttnThreads), 0, st, a);
   return hipGetLastError();
 }

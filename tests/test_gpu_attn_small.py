@@ -37,6 +37,10 @@ CASES = [
     ("parts without a step", [0, 6000], [1, 0, 40, 129], [0, 0, 1, 1], 12, 4, PARTS),
     ("512 sequences", [30] * 64, [3 + s % 30 for s in range(512)], [(s * 7) % 64 for s in range(512)], 2, 1, SMALL),
     ("513 sequences", [30] * 64, [3 + s % 30 for s in range(512)] + [200], [(s * 7) % 64 for s in range(513)], 2, 1, GENERAL),
+    ("one sequence, parts of eight heads", [100], [2300], [0], 16, 8, PARTS),
+    ("seven sequences, parts", [17, 900], [1000, 1, 700, 33, 0, 1200, 64], [0, 1, 0, 1, 1, 0, 0], 8, 4, PARTS),
+    ("seventeen sequences, three heads", [50, 70], [3 * s for s in range(17)], [s % 2 for s in range(17)], 6, 3, SMALL),
+    ("nine sequences, five heads, parts", [600], [500 - s for s in range(9)], [0] * 9, 5, 5, PARTS),
     ("last rows of tokens", [16] * 2, [3 * 2 ** 19 // 64 - 16] + [9 + s for s in range(63)], [s % 2 for s in range(64)], 1, 1, PARTS),
     ("beyond them", [32] * 2, [3 * 2 ** 19 // 64 - 16] + [9 + s for s in range(63)], [s % 2 for s in range(64)], 1, 1, GENERAL),
 ]
