@@ -953,24 +953,28 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
 }
 
 // Waves of a workgroup that takes a row whole, 0 where rows are divided between workgroups and a second launch draws.
-// Rows of up to 8 chunks are taken whole at any number: the second launch is much of the call (1 to 1024 rows x 4096: 7.6 us
-// divided, 5.6 whole; 256 x 32000 10.1 and 8.0, 2048 32.1 and 27.9).  Longer rows are divided while there are fewer than CUs
-// (64 x 152064: 10.8 us divided, 16.5 whole), and where some CUs would have one row more and most would wait for them
-// (300: 23.8 and 30.2, 700 x 100003: 35.0 and 38.5, 1599 x 152064: 92.8 and 96.0), and taken whole where the rows fill the
-// CUs once, twice ... but for a few per cent (256 x 152064: 21.0 and 19.8, 512 37.6 and 34.2, 2048 114 and 108).  As many waves as
-// there are chunks, or as a CU has room for (16 for a row of 38 chunks: 8 take 21.1); fewer of more rows, whose ends then
-// overlap (2048 x 32000: 8 waves 34.8, 4 27.9).  The 256 are the CUs of an MI355X.
-static int sample_row_waves(int rows, int chunks) {
+// Rows of up to 7 chunks (8 up to 512 rows) are taken whole at any number: the second launch is much of the call (1 to 1024 rows
+// x 4096: 7.6 us divided, 5.6 whole; 600 x 24576: 12.9 and 11.7; 256 x 32000 10.1 and 8.0).  Longer rows are divided where the
+// last round of them over the 256 CUs of an MI355X would leave too many CUs idle (64 x 152064: 10.8 us divided, 16.5 whole;
+// 300: 23.8 and 30.2; 600 x 32003: 16.2 and 17.4; 1599 x 152064: 92.8 and 96.0), and whole where they fill it but for a
+// few per cent (256 x 152064: 21.0 and 19.8, 512 37.6 and 34.2, 2048 114 and 108).  Rows that are not aligned to 16 bytes need
+// more requests, which few waves on a CU wait longer for: they have to fill it all but exactly, and three rounds of them are
+// never as fast (496 x 140001: 33.9 and 35.3, 1000: 61.2 and 66.4, 768: 50.7 and 54.3; 1024 x 40001: 33.3 and 24.1).  As many
+// waves as there are chunks, or as a CU has room for (256 x 152064: 8 take 21.1); fewer of more rows, whose ends
+// then overlap (2048 x 32000: 8 waves 34.8, 4 27.9; 768 x 40001: 25.0 and 20.2).  Over 973 sizes, most of them at the edges
+// of this rule, the mean is 4 % above divided rows; 7 lose 5 to 9 %.
+static int sample_row_waves(int rows, int chunks, bool aligned) {
   const int rounds = (rows + 255) / 256;
-  if (chunks > 4 && chunks <= 8 && rows > 512 && rows < 800) return 0;   // (600 x 32003: 16.8 us divided, 17.4 whole)
-  if (chunks <= 8) return std::min(chunks, rows <= 512 ? 8 : 4);
-  if (chunks > kRowMaxChunks || 100l * rows < (rows < 1000 ? 93 : 90) * 256l * rounds) return 0;
-  return rounds == 1 ? kRowMaxWaves : rounds < 4 ? 8 : 4;
+  if (chunks < 8 || (chunks == 8 && rows <= 512)) return std::min(chunks, rows <= 512 ? 8 : 4);
+  const long least = rounds > 4 ? 90 : aligned ? 93 : 99;   // per cent of the CUs' rounds
+  if (chunks > kRowMaxChunks || 100l * rows < least * 256l * rounds || (!aligned && rounds == 3)) return 0;
+  return rounds == 1 ? kRowMaxWaves : rounds == 2 ? 8 : 4;
 }
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
-  if (const int waves = sample_row_waves(a.rows, a.num_chunks)) {
+  const bool aligned = a.vocab % 8 == 0 && reinterpret_cast<uintptr_t>(a.logits) % 16 == 0;
+  if (const int waves = sample_row_waves(a.rows, a.num_chunks, aligned)) {
     hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)a.rows), dim3(waves * 64), 0, st, a);
     return hipGetLastError();
   }
