@@ -7,6 +7,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 from dataclasses import dataclass
 from typing import Optional
 
@@ -72,17 +73,26 @@ _lib = None
 _fast = None   # the short way of the decode loop's calls (csrc/fast_calls.cpp); None: every call goes the long way
 
 
-def _load_fast_calls(lib):
-    """Binds the short way to the functions of `lib`, where it is built and torch can tell the current stream."""
-    if _raw_stream is None or not os.path.exists(FAST_PATH):
+def _load_fast_calls(lib, build: bool):
+    """Binds the short way to the functions of `lib`, where torch can tell the current stream.  It only saves host time: where it
+    cannot be built or loaded (no host compiler, another torch), that is said once and every call goes the long way."""
+    if _raw_stream is None or not (build or os.path.exists(FAST_PATH)):
         return None
-    loader = importlib.machinery.ExtensionFileLoader("fast_calls", FAST_PATH)
-    m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("fast_calls", FAST_PATH, loader=loader))
-    loader.exec_module(m)
-    m.bind(_raw_stream, *(ctypes.cast(f, VP).value for f in (
-        lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
-        lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)))
-    return m
+    try:
+        if not os.path.exists(FAST_PATH):
+            build_fast_calls()
+        loader = importlib.machinery.ExtensionFileLoader("fast_calls", FAST_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("fast_calls", FAST_PATH, loader=loader))
+        loader.exec_module(m)
+        if m.torch_version != torch.__version__.split("+")[0]:
+            raise ImportError(f"{FAST_PATH} was built for torch {m.torch_version}, not {torch.__version__}")
+        m.bind(_raw_stream, *(ctypes.cast(f, VP).value for f in (
+            lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
+            lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)))
+        return m
+    except (ImportError, OSError, RuntimeError) as e:
+        warnings.warn(f"calls take a few microseconds longer, without fast_calls: {e}", RuntimeWarning, stacklevel=3)
+        return None
 
 
 def load_library(build_if_missing: bool = True):
@@ -95,7 +105,6 @@ def load_library(build_if_missing: bool = True):
         if not build_if_missing or path != LIB_PATH:
             raise FileNotFoundError(path)
         build_library()
-        build_fast_calls()
     lib = ctypes.CDLL(path)
     PS, PL = ctypes.POINTER(AttnShape), ctypes.POINTER(PlanLayout)
     lib.marl_version.restype = ctypes.c_int
@@ -157,7 +166,7 @@ def load_library(build_if_missing: bool = True):
               "marl_attn_read_flags", "marl_logprobs_workspace_bytes", "marl_token_logprobs",
               "marl_profile_begin", "marl_profile_end"):
         getattr(lib, f).restype = ctypes.c_int
-    _fast = _load_fast_calls(lib)
+    _fast = _load_fast_calls(lib, build_if_missing and path == LIB_PATH)
     _lib = lib
     return lib
 

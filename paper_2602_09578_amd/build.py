@@ -58,13 +58,15 @@ def build_fast_calls(out_path: str = FAST_PATH) -> str:
     import torch
     from torch.utils.cpp_extension import include_paths, library_paths
     os.makedirs(LIB_DIR, exist_ok=True)
+    part = f"{out_path}.{os.getpid()}"   # (another process may be loading it, or building it too)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I" + os.path.join(_ROOT, "include"), "-I" + sysconfig.get_paths()["include"], *["-I" + p for p in include_paths()],
-           os.path.join(CSRC, "fast_calls.cpp"), "-o", out_path, *["-L" + p for p in library_paths()],
+           os.path.join(CSRC, "fast_calls.cpp"), "-o", part, *["-L" + p for p in library_paths()],
            "-ltorch_python", "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("g++ failed for fast_calls.cpp:\n" + r.stdout)
+    os.replace(part, out_path)
     return out_path
 
 

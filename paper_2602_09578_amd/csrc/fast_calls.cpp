@@ -6,6 +6,7 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <initializer_list>
 
@@ -256,4 +257,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "fast_calls", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_fast_calls(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit_fast_calls(void) {
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) != 0) Py_CLEAR(m);   // (tensors are read as this torch lays them out)
+  return m;
+}

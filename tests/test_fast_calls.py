@@ -6,6 +6,7 @@ import torch
 
 from paper_2602_09578_amd import binding as B
 from paper_2602_09578_amd import inputs as I
+from paper_2602_09578_amd.build import FAST_PATH
 
 ENTRIES = ("decode_attn", "token_logprobs", "sample_tokens", "kv_append", "prefill_attn")
 
@@ -23,6 +24,45 @@ def test_what_is_not_a_device_tensor_goes_the_long_way():
                 assert f(*([shape] + [filler] * (n - 1) if n else [])) is None
     with pytest.raises(ValueError, match="device tensors required"):
         B.marl_token_logprobs(torch.zeros(1, 8, dtype=torch.bfloat16), torch.zeros(1, dtype=torch.int32), 1.0, torch.zeros(1))
+
+
+def _reloaded(monkeypatch, fast_path, build):
+    """The module as a fresh process loads it, with another file and builder of the short way."""
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_fast", None)
+    monkeypatch.setattr(B, "FAST_PATH", str(fast_path))
+    monkeypatch.setattr(B, "build_fast_calls", build)
+    return B.load_library()
+
+
+def test_a_short_way_that_cannot_be_loaded_or_built_leaves_the_long_way(tmp_path, monkeypatch):
+    B.load_library()
+    if B._raw_stream is None:
+        pytest.skip("torch does not tell the current stream")
+    def no_compiler():
+        raise FileNotFoundError("g++")
+    def fails():
+        raise RuntimeError("g++ failed for fast_calls.cpp")
+    (tmp_path / "cut.so").write_bytes(b"\x7fELF cut short")
+    for path, build in ((tmp_path / "cut.so", fails), (B.LIB_PATH, fails), (tmp_path / "missing.so", no_compiler), (tmp_path / "missing.so", fails)):
+        with pytest.warns(RuntimeWarning, match="fast_calls"):
+            lib = _reloaded(monkeypatch, path, build)
+        assert lib.marl_version() == 1 and B._fast is None
+        assert B.marl_workspace_bytes(B.make_shape(2, 1, 4, 2, 3, 1, 1)) > 0
+    # another torch's: loads, but is not taken
+    with monkeypatch.context() as m, pytest.warns(RuntimeWarning, match="built for torch"):
+        m.setattr(torch, "__version__", "0.0.1")
+        _reloaded(m, FAST_PATH, fails)
+        assert B._fast is None
+
+
+def test_a_missing_short_way_is_built(tmp_path, monkeypatch):
+    B.load_library()
+    if B._raw_stream is None:
+        pytest.skip("torch does not tell the current stream")
+    built = tmp_path / "fast_calls.so"
+    _reloaded(monkeypatch, built, lambda: built.write_bytes(open(FAST_PATH, "rb").read()))
+    assert B._fast is not None
 
 
 def _calls():
