@@ -73,6 +73,10 @@ _lib = None
 _fast = None   # the short way of the decode loop's calls (csrc/fast_calls.cpp); None: every call goes the long way
 
 
+def _bind_fast_calls(m, *functions):
+    m.bind(_raw_stream, *(ctypes.cast(f, VP).value for f in functions))
+
+
 def _load_fast_calls(lib, build: bool):
     """Binds the short way to the functions of `lib`, where torch can tell the current stream.  It only saves host time: where it
     cannot be built or loaded (no host compiler, another torch), that is said once and every call goes the long way."""
@@ -86,9 +90,8 @@ def _load_fast_calls(lib, build: bool):
         loader.exec_module(m)
         if m.torch_version != torch.__version__.split("+")[0]:
             raise ImportError(f"{FAST_PATH} was built for torch {m.torch_version}, not {torch.__version__}")
-        m.bind(_raw_stream, *(ctypes.cast(f, VP).value for f in (
-            lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
-            lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)))
+        _bind_fast_calls(m, lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
+                         lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)
         return m
     except (ImportError, OSError, RuntimeError) as e:
         warnings.warn(f"calls take a few microseconds longer, without fast_calls: {e}", RuntimeWarning, stacklevel=3)

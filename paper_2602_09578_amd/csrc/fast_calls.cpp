@@ -8,6 +8,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/version.h>
 
+#include <exception>
 #include <initializer_list>
 
 #include "marl_decode.h"
@@ -99,13 +100,25 @@ PyObject* guarded(F&& f) {
     return not_here();
   }
 }
+struct WithoutGil {   // (given back also where the call ends by an exception)
+  PyThreadState* state = PyEval_SaveThread();
+  ~WithoutGil() { PyEval_RestoreThread(state); }
+};
+// An exception out of the library is the call's result: it may have enqueued work, so the call is not made again.
 template <class F>
 PyObject* finish(Call& c, F&& call) {
   if (!c.ok) return not_here();
   int rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = call();
-  Py_END_ALLOW_THREADS
+  try {
+    WithoutGil released;
+    rc = call();
+  } catch (const std::exception& e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+    return nullptr;
+  } catch (...) {
+    PyErr_SetString(PyExc_RuntimeError, "exception in the library");
+    return nullptr;
+  }
   return PyLong_FromLong(rc);
 }
 

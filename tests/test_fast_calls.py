@@ -1,5 +1,8 @@
 """The binding's short way (native checks and call in one step) against its long way: the same results, the same
 refusals, and nothing taken that is not plainly right."""
+import ctypes
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -141,3 +144,33 @@ def test_both_ways_give_the_same(which, monkeypatch):
             if isinstance(short, str) or isinstance(long, str):
                 assert short == long, (k, short, long)
     assert taken(*right[:1]) is None
+
+
+@pytest.mark.gpu
+def test_an_exception_in_the_library_is_raised_and_the_call_is_not_repeated(tmp_path):
+    """Functions that count their calls and throw, in the place of the library's."""
+    print("case: fast calls, exception", flush=True)
+    (tmp_path / "boom.cpp").write_text("#include <stdexcept>\n"
+                                       'extern "C" int calls = 0;\n'
+                                       'extern "C" int boom() { ++calls; throw std::runtime_error("out of paper"); }\n'
+                                       'extern "C" int number() { ++calls; throw 7; }\n')
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", str(tmp_path / "boom.so"), str(tmp_path / "boom.cpp")], check=True)
+    boom = ctypes.CDLL(str(tmp_path / "boom.so"))
+    calls = ctypes.c_int.in_dll(boom, "calls")
+    lib = B.load_library()
+    assert B._fast is not None
+    try:
+        for f, message in ((boom.boom, "out of paper"), (boom.number, "exception in the library")):
+            B._bind_fast_calls(B._fast, *[f] * 6)
+            for name, call, right, _ in _calls():
+                calls.value = 0
+                with pytest.raises(RuntimeError, match=message):
+                    call(*right)
+                assert calls.value == 1, name
+    finally:
+        B._bind_fast_calls(B._fast, lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
+                           lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)
+    name, call, right, outs = _calls()[1]
+    call(*right)
+    torch.cuda.synchronize()
+    assert torch.isfinite(right[outs[0]]).all()
