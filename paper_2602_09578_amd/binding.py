@@ -74,7 +74,7 @@ _fast = None   # the short way of the decode loop's calls (csrc/fast_calls.cpp);
 
 
 def _bind_fast_calls(m, *functions):
-    m.bind(_raw_stream, *(ctypes.cast(f, VP).value for f in functions))
+    m.bind(_raw_stream, AttnShape, PrefillShape, *(ctypes.cast(f, VP).value for f in functions))
 
 
 def _load_fast_calls(lib, build: bool):

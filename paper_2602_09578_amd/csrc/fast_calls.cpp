@@ -15,7 +15,9 @@
 
 namespace {
 
-PyObject* g_stream_of = nullptr;   // device index -> the current stream's handle
+PyObject* g_stream_of = nullptr;      // device index -> the current stream's handle
+PyObject* g_attn_shape = nullptr;     // the ctypes structures' types
+PyObject* g_prefill_shape = nullptr;
 decltype(&marl_decode_attn) f_decode_attn;
 decltype(&marl_token_logprobs) f_token_logprobs;
 decltype(&marl_kv_append) f_kv_append;
@@ -75,12 +77,13 @@ struct Call {
   const at::Tensor* fail() { ok = false; return nullptr; }
 };
 
-// The C structure behind a ctypes one.
+// The C structure behind a ctypes one of the given type (other objects may have as many bytes).
 template <class S>
 struct Struct {
   Py_buffer view{};
   bool ok;
-  explicit Struct(PyObject* o) : ok(PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) == 0) {
+  Struct(PyObject* o, PyObject* type)
+      : ok(type && PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(type)) && PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) == 0) {
     if (ok && view.len != (Py_ssize_t)sizeof(S)) { PyBuffer_Release(&view); ok = false; }
   }
   ~Struct() { if (ok) PyBuffer_Release(&view); }
@@ -130,7 +133,7 @@ at::ScalarType out_type(int32_t out_dtype) { return out_dtype == MARL_OUT_BF16 ?
 PyObject* decode_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
     if (n != 12 || !f_decode_attn) Py_RETURN_NONE;
-    Struct<marl_attn_shape> s(a[0]);
+    Struct<marl_attn_shape> s(a[0], g_attn_shape);
     if (!s.ok) return not_here();
     const marl_attn_shape& h = *s.get();
     if (a[1] == Py_None || a[11] == Py_None) return not_here();
@@ -203,7 +206,7 @@ PyObject* sample_tokens(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
     if (n != 8 || !f_kv_append) Py_RETURN_NONE;
-    Struct<marl_attn_shape> s(a[0]);
+    Struct<marl_attn_shape> s(a[0], g_attn_shape);
     if (!s.ok || a[3] == Py_None || a[7] != Py_None) return not_here();
     const marl_attn_shape& h = *s.get();
     Call c;
@@ -222,7 +225,7 @@ PyObject* kv_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
     if (n != 10 || !f_prefill_attn) Py_RETURN_NONE;
-    Struct<marl_prefill_shape> s(a[0]);
+    Struct<marl_prefill_shape> s(a[0], g_prefill_shape);
     if (!s.ok || a[1] == Py_None || a[2] == Py_None) return not_here();
     const marl_prefill_shape& h = *s.get();
     Call c;
@@ -241,19 +244,22 @@ PyObject* prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// bind(stream_of, addresses of the library's functions in the order of the declarations above)
+// bind(stream_of, types of the two shapes, addresses of the library's functions in the order of the declarations above)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 7) {
-    PyErr_SetString(PyExc_TypeError, "bind: seven arguments");
+  if (n != 9 || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
+    PyErr_SetString(PyExc_TypeError, "bind: a function, two types, six addresses");
     return nullptr;
   }
   void* f[6];
   for (int k = 0; k < 6; ++k) {
-    f[k] = PyLong_AsVoidPtr(a[k + 1]);
+    f[k] = PyLong_AsVoidPtr(a[k + 3]);
     if (PyErr_Occurred()) return nullptr;
   }
-  Py_INCREF(a[0]);
-  Py_XSETREF(g_stream_of, a[0]);
+  PyObject** const kept[3] = {&g_stream_of, &g_attn_shape, &g_prefill_shape};
+  for (int k = 0; k < 3; ++k) {
+    Py_INCREF(a[k]);
+    Py_XSETREF(*kept[k], a[k]);
+  }
   f_decode_attn = reinterpret_cast<decltype(f_decode_attn)>(f[0]);
   f_token_logprobs = reinterpret_cast<decltype(f_token_logprobs)>(f[1]);
   f_kv_append = reinterpret_cast<decltype(f_kv_append)>(f[2]);

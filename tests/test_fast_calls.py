@@ -69,7 +69,7 @@ def test_a_missing_short_way_is_built(tmp_path, monkeypatch):
 
 
 def _calls():
-    """(name, function, arguments) of one right call of each entry; outputs are cleared by the caller."""
+    """(name, function, arguments, outputs among them) of one right call of each entry."""
     dev = "cuda"
     gen = torch.Generator(device=dev).manual_seed(1)
     attn = I.build_attn_inputs(I.WORKLOADS["tiny"], device=dev)
@@ -94,7 +94,27 @@ def _calls():
                                                    pre.q_pos0, pre.scale, pout], [9])]
 
 
+def _native(name, args):
+    """What the native function itself says to the binding's arguments: a status, or None for the long way."""
+    f = getattr(B._fast, "sample_tokens" if name.startswith("sample") else name)
+    if name == "sample_tokens":
+        args = [*args[:3], None, *args[3:]]
+    elif name == "sample_tokens_top_p":
+        args = [*args, None]
+    elif name == "kv_append":
+        args = [*args, None]
+    return f(*args)
+
+
+def _spoil(args, outs):
+    """Outputs that hold what no call writes (a cache page: only the appended token's part is written)."""
+    for k in outs:
+        if args[k] is not None and torch.is_tensor(args[k]):
+            args[k].fill_(-77)
+
+
 def _outcome(f, args, outs):
+    _spoil(args, outs)
     try:
         f(*args)
     except Exception as e:      # noqa: BLE001 (what is compared is which)
@@ -105,25 +125,46 @@ def _outcome(f, args, outs):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("which", range(6))
+def test_right_calls_are_taken_by_the_short_way(which):
+    """The native function makes the call (status 0 and outputs written), and not for another structure of as many bytes."""
+    name, f, right, outs = _calls()[which]
+    print("case: fast calls, taken", name, flush=True)
+    _spoil(right, outs)
+    assert _native(name, right) == 0
+    torch.cuda.synchronize()
+    for k in outs:
+        assert (right[k] != -77).any(), k
+        if name != "kv_append":
+            assert (right[k] != -77).all(), k
+    if isinstance(right[0], ctypes.Structure):
+        other = (ctypes.c_byte * ctypes.sizeof(right[0])).from_buffer_copy(right[0])
+        assert _native(name, [other, *right[1:]]) is None
+        with pytest.raises(AttributeError):
+            f(other, *right[1:])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", range(6))
 def test_both_ways_give_the_same(which, monkeypatch):
     name, f, right, outs = _calls()[which]
     print("case: fast calls", name, flush=True)
     fast = B._fast
     assert fast is not None
-    taken = getattr(fast, "sample_tokens" if name == "sample_tokens_top_p" else name)
-
-    def both(args):
-        monkeypatch.setattr(B, "_fast", fast)
-        short = _outcome(f, args, outs)
-        monkeypatch.setattr(B, "_fast", None)
-        return short, _outcome(f, args, outs)
 
     def state():   # (appending changes the lengths: each way gets them as they were)
         return [a.clone() if torch.is_tensor(a) and k == 6 and name == "kv_append" else a for k, a in enumerate(right)]
-    short, long = both(state()) if name != "kv_append" else (_outcome(f, state(), outs), None)
-    if name == "kv_append":
-        monkeypatch.setattr(B, "_fast", None)
-        long = _outcome(f, state(), outs)
+
+    def both(changed=None, value=None):
+        results = []
+        for way in (fast, None):
+            monkeypatch.setattr(B, "_fast", way)
+            args = state()
+            if changed is not None:
+                args[changed] = value
+            results.append(_outcome(f, args, [k for k in outs if k != changed]))
+        monkeypatch.setattr(B, "_fast", fast)
+        return results
+    short, long = both()
     assert isinstance(short, list) and all(torch.equal(s.view(torch.uint8), g.view(torch.uint8)) for s, g in zip(short, long))
     # one argument wrong at a time: another type, another extent, a stride, host memory, nothing, a number that is none
     for k, a in enumerate(right):
@@ -138,12 +179,9 @@ def test_both_ways_give_the_same(which, monkeypatch):
         else:
             continue
         for w in wrong:
-            args = state()
-            args[k] = w
-            short, long = both(args)
+            short, long = both(k, w)
             if isinstance(short, str) or isinstance(long, str):
                 assert short == long, (k, short, long)
-    assert taken(*right[:1]) is None
 
 
 @pytest.mark.gpu
