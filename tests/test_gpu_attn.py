@@ -81,9 +81,9 @@ def test_head_layouts(Hq, Hkv):
 
 @pytest.mark.parametrize("sizes", [[21], [40], [60, 2], [17, 19, 1]])
 def test_big_groups_and_query_row_blocks(sizes):
-    """Groups whose G*R query rows fill one ragged block or several blocks of the prefix
-    kernel: 147 rows (8-wave kernel, one block), 280 rows (two blocks of 256), a large and a
-    tiny group together (8-wave kernel), groups just under and over 128 rows (4-wave kernel)."""
+    """Groups whose G*R query rows fill one ragged block or several blocks of prefix rows, once as a small call and once
+    with a chunk named (prefix and suffix items from one queue): 147 rows (blocks of 256, one of them), 280 rows (two of
+    256), a large and a tiny group together (blocks of 256), groups just under and over 128 rows (blocks of 128)."""
     print("case: big groups", sizes, flush=True)
     gos = np.repeat(np.arange(len(sizes)), sizes)
     rng = np.random.default_rng(sum(sizes))
@@ -149,8 +149,8 @@ def test_peaked_scores():
 
 
 def test_peaked_scores_in_a_big_group():
-    """The same with a group of 21 samples (147 query rows: the 8-wave prefix kernel, whose reference
-    maximum of a row moves only when a score exceeds it by more than 2^8: with scale 1 that happens
+    """The same with a group of 21 samples, as a small call and with a chunk named: then 147 query rows are a block of 256,
+    in which a row's reference maximum moves only when a score exceeds it by more than 2^8 (with scale 1 that happens
     in many steps, and in most of them for some rows of a wave only)."""
     print("case: peaked scores, big group", flush=True)
     rng = np.random.default_rng(77)
@@ -207,7 +207,7 @@ def test_bad_device_contents_are_clamped_and_flagged():
 
 @pytest.mark.parametrize("samples", [3, 21])
 def test_bad_prefix_page_ids_are_flagged(samples):
-    """A prefix block-table entry outside the pool (4-wave and 8-wave prefix kernels): the flag is
+    """A prefix block-table entry outside the pool (in small calls; other ways: test_gpu_attn_routes.py): the flag is
     raised, nothing outside the buffers is read, outputs stay finite, and a group whose table is
     intact is computed as if nothing had happened."""
     print("case: bad prefix page ids", samples, flush=True)
@@ -260,8 +260,8 @@ def test_full_size_every_row(name):
 
 def test_full_size_sixteen_samples_per_prompt():
     """The bench workload's shape with 16 samples per prompt instead of 8 (the paper runs a
-    parallelism of 4 x 16, Section 8.1): 112 query rows per group and KV head, which is the 4-wave
-    prefix kernel with two row tiles per wave at full size.  Every row is compared."""
+    parallelism of 4 x 16, Section 8.1): 112 query rows per group and KV head, which is the prefix kernel's block of
+    128 rows with two row tiles per wave at full size.  Every row is compared."""
     print("case: full size, 16 samples per prompt", flush=True)
     w = I.WORKLOADS["qwen7b"]
     agents = tuple(I.Agent(a.prompts // 2, 16, a.prompt_len, a.gen_len) for a in w.agents)
@@ -271,7 +271,8 @@ def test_full_size_sixteen_samples_per_prompt():
 @pytest.mark.parametrize("size", [128, 129, 136, 144, 145, 256, 257, 400])
 def test_halves_of_wide_row_blocks(size):
     """One query row per sequence: blocks of 8, 9, 16 and 17 row tiles, an odd tile count, a second block
-    of one row; chunks of one step with a few tokens (the first step is also the ragged last one)."""
+    of one row; chunks of one step with a few tokens (the first step is also the ragged last one).  With the chunk named
+    the halves are items of the one queue, without it this may be a small call."""
     print("case: wide halves", size, flush=True)
     rng = np.random.default_rng(size)
     gos = np.concatenate([np.zeros(size, int), np.ones(140, int)])   # average above 128 rows: the wide kernel
