@@ -476,7 +476,7 @@ struct LogprobSplit {
 };
 static int logprob_split(int32_t rows, int32_t vocab, LogprobSplit* s) {
   if (rows < 0 || vocab < 1) return MARL_INVALID_ARG;
-  long want = rows > 0 ? (1024 + rows - 1) / rows : 1;     // aim for >= 1024 workgroups (of 1024 threads)
+  long want = rows > 0 ? (1024 + rows - 1) / rows : 1;     // aim for >= 1024 workgroups (of 512 threads)
   long len = (vocab + want - 1) / want;
   if (len < 8192) len = 8192;                              // but keep slices worth a workgroup
   len = (len + 2047) / 2048 * 2048;

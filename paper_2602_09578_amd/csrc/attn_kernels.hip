@@ -3,7 +3,9 @@
 // sequence's own generated tokens) and the merge kernel.  The first two produce
 // flash-decoding style partials (running max, running sum, unnormalised output) per (query
 // row, chunk of tokens), which the merge kernel combines; a sequence whose own tokens are a
-// single work item is finished by whoever processes that item instead.  (Small calls: attn_small_kernel.hip.)
+// single work item is finished by whoever processes that item instead.  Calls of medium size have prefix and
+// suffix items in one kernel (the items kernel), where a long item behind a prefix is a partial too.  (Small calls:
+// attn_small_kernel.hip.)
 //
 // Context in the paper: rollout is memory-bound on KV caches (Section 4.1), every prompt is
 // expanded into several samples that share its prefix (Section 5.1) and lengths are skewed
@@ -392,7 +394,7 @@ __device__ __forceinline__ void process_item(const AttnArgs& a, const int32_t* _
 //                        the prefix partials are complete: its rows never pass through a partial.
 //                        The short items of sequences with several suffix chunks must be
 //                        partials before the merge kernel starts: they run as the first phase of
-//                        the PREFIX kernel's workgroups (as a phase of the suffix kernel they
+//                        the PREFIX (or items) kernel's workgroups (as a phase of the suffix kernel they
 //                        slowed the long items' hot loop down by a few percent through the
 //                        shared register allocation, and a kernel of their own cost one more
 //                        launch per call).
@@ -440,7 +442,7 @@ void suffix_kernel(AttnArgs a) {
 // (W = waves in the grid) with no LDS, no barrier and no atomic: the entries are sorted by
 // size, so a round-robin split is balanced, and a shared queue counter would serialise
 // thousands of waves on one address.  The next record is fetched while the current item runs.
-// kFinish = false (first phase of the prefix kernel): the items of sequences with several
+// kFinish = false (first phase of the prefix and items kernels): the items of sequences with several
 // suffix chunks, as partials.  kFinish = true (first phase of the merge kernel, after the
 // prefix partials are complete): the items of sequences whose own tokens are that one item,
 // finished to output rows, so that they never travel through a partial.

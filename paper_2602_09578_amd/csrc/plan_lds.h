@@ -24,7 +24,7 @@ __device__ __forceinline__ int clamp_len(int v, int hi, int& flags) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Same plan for shapes whose bookkeeping fits in LDS (NS <= 8192, NG <= 2048, chunks <= 8192
+// The plan of plan_kernel.hip for shapes whose bookkeeping fits in LDS (sizes below, chunks <= 8192
 // tokens): inputs are read once into registers, counts, offsets, member lists and histograms
 // live in LDS, and global memory only sees the final stores.  The general plan kernel pays
 // a chain of ~30 dependent global round trips; this one pays one.  What bounds it is the chain of
@@ -33,8 +33,9 @@ __device__ __forceinline__ int clamp_len(int v, int hi, int& flags) {
 // included; the former time had a block-wide scan with shuffles and three barriers for each of the three.  (One LDS atomic
 // for all lanes of a wave that count in the same word: 11.9 -> 16.5 us, 2048 sequences; 14.4 -> 23.6, 4096.)
 // ---------------------------------------------------------------------------------------
-// Two sizes: up to 8192 sequences in 2048 groups (56 KB of LDS), and up to 32768 sequences in
-// 8192 groups with 16-bit member ids (130 KB of the 160 KB).
+// Three sizes: up to 512 sequences and groups by 256 threads, beside a small call's attention (13 KB of LDS); up to 8192
+// sequences in 2048 groups (56 KB) and up to 32768 sequences in 8192 groups with 16-bit member ids (130 KB of the 160 KB), by
+// 1024 threads.
 constexpr int kSmallMaxClasses = 256;
 
 // kCheckPages: the plan's workgroup also looks for block-table entries outside the pool among those of addressed

@@ -310,13 +310,15 @@ __global__ __launch_bounds__(kRowMaxWaves * 64) void sample_rows_kernel(SampleAr
 //   3. per group the nucleus mass and the number of threshold-value tokens (from the list, else one
 //      more pass over the row); a scan over the group sums finds the group in which the scaled
 //      uniform is passed, a workgroup scan over the group's 2048 tokens finds the token.
-// What bounds it: the vector ALU.  An instruction on 64 lanes takes 4 cycles of a SIMD, v_exp_f32 16;
-// pass 1 is 7 of the 4-cycle units per logit, the list pass 3.5, and ten would fill the time in
-// which the row arrives from HBM.  The second read of the row comes out of the memory-side cache
-// (three rows per CU, 234 MB of 256 at a vocabulary of 152064).  Measured on 2048 x 152064, sigma 3,
-// top_p 0.9: 197 us (two workgroups per CU 212); with the row held in registers by one workgroup per CU, a count of all values in
+// What bounds it, 2048 x 152064, sigma 3, top_p 0.9 (197 us): both reads and the vector ALU, neither of them alone.  The rows are
+// fetched twice (1255 MB, 6.3 TB/s: three rows per CU are 234 MB, too many for the L2s), and the vector ALU issues in 76 %
+// of the CUs' time: 17.5 issue slots of 4 cycles per logit over all passes, of which the first has 7
+// and the copy into the list 3.5.  (Rows that the L2s hold take 148 us, and the fetches alone would take 180.)  Two workgroups
+// per CU 212; with the row held in registers by one workgroup per CU, a count of all values in
 // LDS (an LDS atomic on 64 lanes takes about 25 cycles) and a third pass over all tokens 508 us; the
 // same with the list but still in registers 316 us (nothing to overlap the short phases with).
+// A few rows (64 x 152064, top_p 0.95: 37 us): each has a CU of its own, whose vector ALU issues in 53 % of that time, two waves
+// per SIMD; in the rest it waits, for the two reads' latencies and at the barriers between the phases.
 // Three workgroups per CU leave 80 vector registers: two are spilled (12 bytes of scratch per lane), outside the passes,
 // and 46 scalar registers to lanes of vector registers, which the counts over windows read back.
 // ---------------------------------------------------------------------------------------
