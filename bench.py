@@ -91,6 +91,12 @@ def dominant_kernel_roofline(w, attn, call, stage_ms):
     Cs = call.layout.suffix_chunk_tokens
     tail = S % Cs
     long_tok = int(((S // Cs) * Cs * (Cs > 128) + tail * (tail > 128)).sum())
+    if stage_ms["plan"] == 0:   # one kernel for the whole call, prefix and own tokens and the plan: a chain of latencies
+        all_bytes = int(S.sum() + attn.prefix_lens.sum()) * bpt
+        gbps = all_bytes / (stage_ms["prefix"] * 1e-3) / 1e9
+        return {"kernel": "decode_small_kernel", "bound": "latency", "achieved": gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+                "frac": gbps / HBM_PEAK_GBPS, "traffic": None, "algorithmic_bytes_per_launch": all_bytes,
+                "avg_launch_ms": stage_ms["prefix"]}
     if stage_ms["prefix"] == 0:   # prefix items and long suffix items share a launch
         all_bytes = (long_tok + int(attn.prefix_lens.sum())) * bpt
         gbps = all_bytes / (stage_ms["suffix"] * 1e-3) / 1e9
@@ -109,8 +115,8 @@ def dominant_kernel_roofline(w, attn, call, stage_ms):
     flops = int(4 * 128 * w.Hq * (P * counts).sum())
     tf = flops / (stage_ms["prefix"] * 1e-3) / 1e12
     pbytes = int(P.sum()) * bpt
-    kernel = ("decode_small_kernel" if stage_ms["plan"] == 0 else   # one kernel for the whole call
-              "items_kernel" if w.num_seqs * w.Hkv <= 6144 else "prefix_kernel")
+    # (without a suffix stage the stages do not tell whether these items have a kernel of their own or share one queue with others)
+    kernel = "prefix_kernel" if stage_ms["suffix"] > 0 else "prefix items"
     return {"kernel": kernel, "bound": "mfma", "achieved": tf, "peak": 2500.0, "unit": "TFLOP/s",
             "frac": tf / 2500.0, "traffic": None, "algorithmic_flops_per_launch": flops,
             "avg_launch_ms": stage_ms["prefix"],
