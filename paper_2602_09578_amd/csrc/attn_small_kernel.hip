@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kAttnThreads) void merge_parts_kernel(AttnArgs a) {
 // Parts: none below 1024 tokens (the second launch costs 3 us: 8 against 11 us), else of 384 tokens, as long as
 // at most 1536 workgroups come of it (768 run at a time; 768 or 512 in all lose 2-4 %, as lengths differ), and at most 16 of a
 // row: what the second launch adds up grows with them, and is paid by what a table can hold (8 sequences of 40 tokens in rows for
-// 131072, one KV head: 8.6 us, 10.5 with 32 parts, 14.3 with 64; 10 pairs of 16384: 19.1, 23.5, 23.1), while one
+// 131072, one KV head: 8.9 us, 10.5 with 32 parts, 14.3 with 64; 10 pairs of 16384: 19.1, 23.5, 23.1), while one
 // to four pairs of long rows would gain (one of 16384: 15.5, 12.9, 13.5; of 131072: 79, 45, 33).
 int small_attn_splits(const AttnArgs& a) {
   const long items = (long)a.NS * a.Hkv, prefix = (long)a.max_pp * kPage, own = (long)a.max_sp * kPage;

@@ -280,7 +280,7 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       if (tid + k * kThreads < a.NS) suffix_len[tid + k * kThreads] = S_keep[k];
     __syncthreads();
     // Entries of addressed tokens only: tables of a fixed capacity are mostly padding, and looking through all of it took one
-    // workgroup longer than the attention (one sequence of 40 tokens in a row for 2^20: 29.7 us, now 8.4, general kernels 14.6;
+    // workgroup longer than the attention (one sequence of 40 tokens in a row for 2^20: 29.8 us, now 8.5, general kernels 14.7;
     // 512 of up to 40 in rows for 2048: 33.8, now 13.2, 23.4).  A power of two lanes share a row, as many as there are for each.
     // With at most a row for each team of lanes a lane requests sixteen of its entries together, else two of four rows (eight
     // instead of sixteen: 16 rows of 1024 entries 29.7 us, now 28.4; 16 bytes at a time, or four of four rows, or one of eight:
