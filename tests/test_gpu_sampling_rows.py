@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("rows,vocab", [(3, 4095), (3, 4096), (3, 4097), (5, 30001), (4, 32768), (4, 32769), (700, 9001), (600, 28672),
                                         (512, 28673), (513, 28673), (238, 41000), (239, 41000), (253, 41001), (254, 41001), (256, 41001),
                                         (257, 41001), (477, 33000), (714, 32768), (715, 32768), (768, 33001), (1000, 33001),
-                                        (1014, 33001), (1151, 33001), (1152, 33001)])
+                                        (1014, 33001), (1151, 33001), (1152, 33001),
+                                        (238, 41001), (239, 41001), (478, 33001), (513, 30001)])
 def test_whole_and_divided_rows(rows, vocab):
     """Some tokens and the whole tail masked; uniforms 0, just below 1 and in between.  A row's token and
     log-probability are the same bits in a batch that is divided and in one that is not."""
