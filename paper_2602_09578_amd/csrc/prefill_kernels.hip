@@ -39,13 +39,19 @@
 // scalar registers instead of 86; 2 to 3 % of such a list's time).
 // A workspace with room for the list alone is served with whole blocks.
 //
-// What bounds it: the issue of instructions.  A step of a wave is 48 matrix instructions (768 cycles
+// What bounds it: the issue of instructions at the clock that its power leaves (1.81 GHz on the 256 prompts below).  A step of a
+// wave is 48 matrix instructions (768 cycles
 // of the matrix core) and about 100 vector instructions, 24 of them exponentials (710 cycles of the
 // vector ALU), and the two waves of a SIMD overlap little of it: 1.58 us per step and workgroup at
-// two workgroups per CU with 141 vector and 105 scalar instructions, 1.50 with 120 and 50 (page
-// ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  256 prompts of
-// 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.58 ms (0.96 PFLOP/s; a large matrix product of this
-// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.  Memory is second: with an item
+// two workgroups per CU with 141 vector and 105 scalar instructions, 1.37 with 120 and 50 (page
+// ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  The same step on LDS data alone,
+// without loads, runs at 1.43 PFLOP/s, with loads that the caches hold at 1.28, with loads from memory at 0.97.  256 prompts of
+// 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.52 ms (0.98 PFLOP/s; a large matrix product of this
+// card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.  An item takes about 6 us beside its
+// steps (rows written 2.6, the next item read and queries requested 2.2, two steps on the causal edge 0.6), in which the
+// other workgroup of the CU has it alone; 7.5 with output rows through LDS, a first step taken twice
+// and maxima in every step on the edge (46 prompts of up to 1666, 28 / 4 heads: 604 -> 586 us; 33 of up to 2730, 4 / 4 heads: 148 -> 143).
+// Memory is second: with an item
 // bound ahead a prompt's blocks run further apart in time than one after the other did, and the 256 prompts fetch
 // 14.8 GB instead of 8.2; with all groups on the pages of one prompt, which stay in the caches, they take 4 % less.
 #include <algorithm>
@@ -76,7 +82,6 @@ constexpr int kPlanThreadsPf = 1024;
 constexpr int kPfStages = 4;
 struct PrefillLds {
   __attribute__((aligned(16))) char buf[kPfStages][kPfStepBytes];
-  __attribute__((aligned(16))) char out[kNW][16 * kD];   // half a tile's output rows (64 channels) on their way to memory, per wave
   int arrived;   // parts of the current block that were finished before this one
   int next;      // a drawn item
   int late;      // an item drawn when nothing was left to do
@@ -397,11 +402,17 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
   int tile_lo[kMT], tile_hi[kMT];
   auto opaque_lane = [&] { int l = lane; asm volatile("" : "+v"(l)); return l; };
   // this lane's row of a tile: its index in q and out (-1: none) and the number of keys it sees
+  auto row_at = [&](const PfItem& it, int r, int& tok) {
+    const int rho = it.rem0 + r;
+    tok = div_R(rho, a.inv_R);   // from the block's first token on
+    return (it.qrow0 + tok) * a.Hq + it.kvh * a.R + (rho - tok * a.R);
+  };
   auto row_of = [&](const PfItem& it, int qt, int row16, int& sees) {
     const int r = (qt * kNW + wave) * 16 + row16;
-    const int rho = it.rem0 + r, tok = div_R(rho, a.inv_R);   // from the block's first token on
+    int tok;
+    const int idx = row_at(it, r, tok);
     sees = r < it.rows ? it.pos0 + tok + 1 : 1;
-    return r < it.rows ? (it.qrow0 + tok) * a.Hq + it.kvh * a.R + (rho - tok * a.R) : -1;
+    return r < it.rows ? idx : -1;
   };
   u32x4 qreg[kMT][4];
   auto load_rows = [&](const PfItem& it) {
@@ -414,15 +425,24 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
         tile_lo[qt] = it.pos0 + div_R(it.rem0 + r0, a.inv_R) + 1;
         tile_hi[qt] = it.pos0 + div_R(it.rem0 + min(r0 + 15, it.rows - 1), a.inv_R) + 1;
       }
-      int sees;
-      const int idx = row_of(it, qt, l & 15, sees);
+      // (rows past the block's last are computed as that row and never written: loads without branches)
+      int tok;
+      const int idx = row_at(it, min(r0 + (l & 15), it.rows - 1), tok);
+      const u32x4* src = reinterpret_cast<const u32x4*>(a.q + (size_t)idx * kD + (l >> 4) * 8);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) qreg[qt][kk] = src[4 * kk];
+    }
+  };
+  // The queries are waited for here, once: with the loads still pending at the top of the loops the
+  // compiler would wait in every step, and for the steps in flight with them.
+  auto take_rows = [&] {
+#pragma unroll
+    for (int qt = 0; qt < kMT; ++qt)
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (idx >= 0) v = *reinterpret_cast<const u32x4*>(a.q + (size_t)idx * kD + (4 * kk + (l >> 4)) * 8);
-        qreg[qt][kk] = v;
+        qreg[qt][kk] ^= sign_flip;
+        asm volatile("" : "+v"(qreg[qt][kk]));
       }
-    }
   };
   f32x4 acc[kMT][8];
   float m_run[kMT], l_run[kMT];
@@ -508,87 +528,24 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
   // value unit 2 * (16 * ct + i) + (j & 1) with its lowest bit XOR-ed: one address for all ct
   const int v_rd = 2 * kBlockTok * kD + (j >> 1) * 4096 + (((2 * i + (j & 1)) ^ ((i >> 2) & 1)) << 4);
 
-  constexpr float kPfRescaleSlack = 8.0f, kPfMaxWeight = 256.0f;   // log2 units; the same as a weight
-  auto compute_edge = [&](int n, const char* buf, const int tok_end, const int (&limit)[kMT]) {
+  constexpr float kPfMaxWeight = 256.0f, kPfFirstLeast = 0x1p-16f;
+  // One step of 32 keys: all score products, then per tile the exponentials and that tile's output products.
+  //   The reference maximum of a row moves only when its weights grow past kPfMaxWeight.  With an
+  // exact running maximum one of a wave's 48 rows sets a new record in most steps of a long prompt; with
+  // the slack nearly no step after the first moves one, and then neither the rows' maxima nor new
+  // references nor rescaled accumulators are needed.  What is tested is the sum of a lane's eight
+  // weights, which is formed anyway (no weight exceeds a sum that passes; the eight scores'
+  // maximum cost six instructions per tile), and only a step that fails looks for maxima and takes
+  // its exponentials again.
+  //   kFirst: the item's first step, seen in full by every row.  The reference is 0 where that gives every lane weights between
+  // kPfFirstLeast and kPfMaxWeight (else the rows' maxima, as above), and the accumulators start with this step's
+  // products: 270 vector instructions per item and wave for a first pass that always failed, rescaled zeros, and the zeros.
+  //   kEdge: the causal edge of some row crosses the step, or a tile has no rows; a row that has seen no key keeps
+  // the reference -FLT_MAX, with weights exp2(-inf) = 0.
+  enum { kFull, kFirst, kEdge };
+  auto compute = [&](const char* buf, auto kind_tag, const int n, const int tok_end, const int (&limit)[kMT]) {
+    constexpr int kind = decltype(kind_tag)::value;
     const int t0 = n * kBlockTok;
-    const bool ragged = t0 + kBlockTok > tok_end;   // workgroup-uniform; only the last step
-    u32x4 pb[kMT];   // set and used only for the tiles this step touches
-    u32x4 kr[2][4];
-#pragma unroll
-    for (int T = 0; T < 2; ++T)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        kr[T][kk] = *reinterpret_cast<const u32x4*>(buf + k_rd + T * 4 * 256 + (((4 * kk + j) ^ i) << 4));
-    load_ids_after(kr[1][3][0]);
-#pragma unroll
-    for (int qt = 0; qt < kMT; ++qt) {
-      if (t0 < tile_hi[qt]) {   // wave-uniform: some row of the tile sees a token of this step
-        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          s0 = mfma_16x16x32(kr[0][kk], qreg[qt][kk], s0);
-          s1 = mfma_16x16x32(kr[1][kk], qreg[qt][kk], s1);
-        }
-        if (t0 + kBlockTok > tile_lo[qt]) {   // wave-uniform: the causal edge crosses this step
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (t0 + 8 * j + e >= limit[qt]) s0[e] = -INFINITY;
-            if (t0 + 8 * j + 4 + e >= limit[qt]) s1[e] = -INFINITY;
-          }
-        }
-        float mx = fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
-                         fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
-        mx = rows_allreduce_max(mx);
-        // the reference maximum is finite, so a fully masked row gives alpha = 1, p = 0; it moves only when the row's maximum
-        // exceeds it by more than 2^kPfRescaleSlack (as in the loop before the edge)
-        const float m_new = mx * sc > m_run[qt] + kPfRescaleSlack ? mx * sc : m_run[qt];
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
-        float p[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[e], sc, -m_new));
-          p[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[e], sc, -m_new));
-        }
-        const float psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-        if (__builtin_amdgcn_ballot_w64(m_new > m_run[qt]) != 0) {   // wave-uniform
-#pragma unroll
-          for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
-        }
-        l_run[qt] = l_run[qt] * alpha + psum;
-        m_run[qt] = m_new;
-        pb[qt] = u32x4{pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
-      }
-    }
-    u32x4 vr[8];
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) {
-      vr[ct] = *reinterpret_cast<const u32x4*>(buf + v_rd + ct * (16 * kPage * 2));
-    }
-    if (ragged) {
-      // value slots past the block's last key may hold anything (NaN included): zero them
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const int tok = t0 + 8 * j + 2 * d;
-        const uint32_t mask = (tok < tok_end ? 0x0000ffffu : 0u) | (tok + 1 < tok_end ? 0xffff0000u : 0u);
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct) vr[ct][d] &= mask;
-      }
-    }
-#pragma unroll
-    for (int qt = 0; qt < kMT; ++qt)
-      if (t0 < tile_hi[qt]) {
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = mfma_16x16x32(vr[ct], pb[qt], acc[qt][ct]);
-      }
-  };
-
-
-  // A step that every row of the wave's tiles sees in full (no causal edge, not ragged): the
-  // same arithmetic as compute_edge without masks, tile tests and per-tile branches: all score
-  // products, the row maxima, ONE test whether any row's reference maximum has to move (rare after
-  // the first steps; the accumulators are rescaled in that branch only), then per tile the exponentials
-  // and that tile's output products.  About 150 vector-ALU instructions per step instead of 250.
-  auto compute_full = [&](const char* buf) {
     u32x4 kr[2][4];
 #pragma unroll
     for (int T = 0; T < 2; ++T)
@@ -601,26 +558,40 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
     for (int qt = 0; qt < kMT; ++qt) {
       s0[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
       s1[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (kind == kEdge && t0 >= tile_hi[qt]) continue;   // wave-uniform: no row of the tile sees a token of this step
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         s0[qt] = mfma_16x16x32(kr[0][kk], qreg[qt][kk], s0[qt]);
         s1[qt] = mfma_16x16x32(kr[1][kk], qreg[qt][kk], s1[qt]);
       }
+      if (kind == kEdge && t0 + kBlockTok > tile_lo[qt]) {   // wave-uniform: the causal edge crosses this step
+        const int sees = limit[qt] - (t0 + 8 * j);           // of this lane's eight keys
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (e >= sees) s0[qt][e] = -INFINITY;
+          if (4 + e >= sees) s1[qt][e] = -INFINITY;
+        }
+      }
     }
-    // The reference maximum of a row moves only when its weights grow past 2^kPfRescaleSlack.  With an
-    // exact running maximum one of a wave's 48 rows sets a new record in most steps of a long prompt; with
-    // the slack nearly no step after the first moves one, and then neither the rows' maxima nor new
-    // references nor rescaled accumulators are needed.  What is tested is the sum of a lane's eight
-    // weights, which is formed anyway (no weight exceeds a sum that passes; the eight scores'
-    // maximum cost six instructions per tile), and only a step that fails looks for maxima and takes
-    // its exponentials again.
     u32x4 vr[8];
 #pragma unroll
     for (int ct = 0; ct < 8; ++ct) {
       vr[ct] = *reinterpret_cast<const u32x4*>(buf + v_rd + ct * (16 * kPage * 2));
     }
+    if (kind == kEdge && t0 + kBlockTok > tok_end) {   // workgroup-uniform; only the last step
+      // value slots past the block's last key may hold anything (NaN included): zero them
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const int tok = t0 + 8 * j + 2 * d;
+        const uint32_t mask = (tok < tok_end ? 0x0000ffffu : 0u) | (tok + 1 < tok_end ? 0xffff0000u : 0u);
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) vr[ct][d] &= mask;
+      }
+    }
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
+      if (kind == kEdge && t0 >= tile_hi[qt]) continue;
+      if (kind == kFirst) m_run[qt] = 0.f;
       float p[8], psum;
       auto weights = [&] {
 #pragma unroll
@@ -631,21 +602,24 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
         psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
       };
       weights();
-      if (__builtin_amdgcn_ballot_w64(psum > kPfMaxWeight) != 0) {   // wave-uniform; always so in the first step
+      if (__builtin_amdgcn_ballot_w64(psum > kPfMaxWeight || (kind == kFirst && psum < kPfFirstLeast)) != 0) {   // wave-uniform
         const float mx = fmaxf(fmaxf(fmaxf(s0[qt][0], s0[qt][1]), fmaxf(s0[qt][2], s0[qt][3])),
                                fmaxf(fmaxf(s1[qt][0], s1[qt][1]), fmaxf(s1[qt][2], s1[qt][3]))) * sc;   // this lane's 8 tokens
-        const float m_new = fmaxf(m_run[qt], rows_allreduce_max(mx));
-        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);   // 1 where the row did not move
-        l_run[qt] *= alpha;
-        m_run[qt] = m_new;
+        const float row_mx = rows_allreduce_max(mx), m_new = fmaxf(kind == kFirst ? -3.402823466e38f : m_run[qt], row_mx);
+        if (kind != kFirst) {
+          const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);   // 1 where the row did not move
+          l_run[qt] *= alpha;
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
+          for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
+        }
+        m_run[qt] = m_new;
         weights();
       }
-      l_run[qt] += psum;
+      l_run[qt] = kind == kFirst ? psum : l_run[qt] + psum;
       const u32x4 pb = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = mfma_16x16x32(vr[ct], pb, acc[qt][ct]);
+      for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = mfma_16x16x32(vr[ct], pb, kind == kFirst ? zero : acc[qt][ct]);
     }
   };
 
@@ -670,34 +644,19 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
   }
   load_ids();
   load_rows(cur);
+  take_rows();
   for (bool drawn_next = false;; drawn_next = true) {
-    // the queries are waited for here, once: with the loads still pending at the top of the loops the
-    // compiler would wait in every step, and for the steps in flight with them
-#pragma unroll
-    for (int qt = 0; qt < kMT; ++qt)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        qreg[qt][kk] ^= sign_flip;
-        asm volatile("" : "+v"(qreg[qt][kk]));
-      }
     if (drawn_next) {
-      // the next item (the draw was requested before the queries, so it has arrived)
-      if (tid == 0) lds.next = drawn;
+      // the next item (the draw was requested before the queries, so it has arrived; as an ordinary store the compiler
+      // would put it behind a wait for every load into LDS and every output row that is in flight)
+      if (tid == 0) asm volatile("ds_write_b32 %0, %1" :: "v"((uint32_t)reinterpret_cast<uintptr_t>(&lds.next)), "v"(drawn) : "memory");
       __builtin_amdgcn_s_waitcnt(pf_lgkmcnt0);
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      const int next = __builtin_amdgcn_readfirstlane(lds.next);
+      const int next = 2 * (int)gridDim.x + __builtin_amdgcn_readfirstlane(lds.next);
       more = next < n_ahead;
       if (more) nxt = read_item<kSplit>(a, next);
-    }
-#pragma unroll
-    for (int qt = 0; qt < kMT; ++qt) {
-      // (finite: a row that sees no key of a part keeps it, with weights exp2(-inf) = 0)
-      m_run[qt] = -3.402823466e38f;
-      l_run[qt] = 0.f;
-#pragma unroll
-      for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     auto ring_step = [&](auto&& comp) {
       __builtin_amdgcn_s_waitcnt(pf_vmcnt_imm((kPfStages - 2) * kLoads));
@@ -718,25 +677,35 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
     for (int qt = 0; qt < kMT; ++qt) all_tiles = all_tiles && (qt * kNW + wave) * 16 < cur.rows;
     const int n_full = all_tiles ? min(tile_lo[0] / kBlockTok, cur.nsteps) : 0;
     int n = cur.step0;
-    for (; n < n_full; ++n) ring_step(compute_full);
+    int limit[kMT] = {};
+    if (n < n_full) {
+      ring_step([&](const char* buf) { compute(buf, std::integral_constant<int, kFirst>{}, n, 0, limit); });
+      for (++n; n < n_full; ++n) ring_step([&](const char* buf) { compute(buf, std::integral_constant<int, kFull>{}, n, 0, limit); });
+    } else {
+#pragma unroll
+      for (int qt = 0; qt < kMT; ++qt) {
+        m_run[qt] = -3.402823466e38f;   // (finite: a row that sees no key of a part keeps it)
+        l_run[qt] = 0.f;
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
     if (n < cur.nsteps) {
-      int limit[kMT];
       const int l = opaque_lane();
 #pragma unroll
       for (int qt = 0; qt < kMT; ++qt) row_of(cur, qt, l & 15, limit[qt]);
-      for (; n < cur.nsteps; ++n) ring_step([&](const char* buf) { compute_edge(n, buf, cur.tok_end, limit); });
+      for (; n < cur.nsteps; ++n) ring_step([&](const char* buf) { compute(buf, std::integral_constant<int, kEdge>{}, n, cur.tok_end, limit); });
     }
     if (more)   // (without a next item nobody waits for the slots that are left)
       for (; n < cur.slots; ++n) ring_step([&](const char*) { load_ids(); });
     // the next item's queries are requested before this item's rows are written
     if (more) {
-      if (tid == 0) drawn = 2 * (int)gridDim.x + atomicAdd(&a.counters[kPfCursor], 1);
+      // (the pointer is one per lane to the compiler: it would wait at once for the result of an addition that it takes for the wave's)
+      int zero = 0;
+      asm volatile("" : "+v"(zero));
+      if (tid == 0) drawn = atomicAdd(&a.counters[kPfCursor + zero], 1);
       load_rows(nxt);
     }
-    // Lane (i, j) holds channels 16*ct + 4*j .. +3 of q-row i.  Written as they are held, an instruction
-    // stores 16 pieces of 32 bytes (8 per lane); through 2 KB of LDS half a bf16 tile leaves as 128-byte
-    // lines, 16 bytes per lane.  16-byte units of a row are XOR-ed with the row against bank conflicts;
-    // the lanes of a row then read its units in that order.  (256 prompts: 2 % of the whole.)
     const int l2 = opaque_lane();
     // A part of a block's keys: its sums go to memory in the layout of the registers; the workgroup that
     // finds all parts there adds them in their order and writes the rows (nobody waits for another).
@@ -789,41 +758,42 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
         }
       }
     }
-    if (write_rows)
-#pragma unroll
-    for (int qt = 0; qt < kMT; ++qt) {
+    // Lane (i, j) holds channels 16*ct + 4*j .. +3 of q-row i.  bf16 rows: the rows of lanes exchange halves of two
+    // 16-channel pieces, after which a lane has eight channels in a row and an instruction stores 64 bytes of each of 16 rows.
+    // (Through LDS, 128 bytes: the compiler puts a wait for every load into LDS, query and store in flight before a store
+    // to LDS, three times 1.4 us per item.)
+    auto store_tile = [&](int qt, int out_row) {
       const float inv = 1.0f / rows_allreduce_sum(l_run[qt]);   // a row's sum >= 1: its own maximum contributes exp2(0)
-      const int i = l2 & 15, j = l2 >> 4, lane = l2;
-      int sees;
-      const int out_row = row_of(cur, qt, i, sees);
+      const int j = l2 >> 4;
       if (a.out_dtype == MARL_OUT_F32) {
-        if (out_row >= 0) {
-          float* dst = reinterpret_cast<float*>(a.out) + (size_t)out_row * kD + 4 * j;
+        float* dst = reinterpret_cast<float*>(a.out) + (size_t)out_row * kD + 4 * j;
+        if (out_row >= 0)
 #pragma unroll
           for (int ct = 0; ct < 8; ++ct) *reinterpret_cast<f32x4*>(dst + 16 * ct) = acc[qt][ct] * inv;
-        }
       } else {
-        char* mine = lds.out[wave];
+        uint16_t* dst = reinterpret_cast<uint16_t*>(a.out) + (size_t)out_row * kD + 16 * (j & 1) + 8 * (j >> 1);
+        u32x4 v[4];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const f32x4 r = acc[qt][4 * h + c] * inv;
-            *reinterpret_cast<uint2*>(mine + i * 128 + (((2 * c + (j >> 1)) ^ (i & 7)) << 4) + (j & 1) * 8) =
-                make_uint2(pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]));
-          }
-          // (one wave's LDS operations are executed in order: no barrier)
-#pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            const int row = 8 * k + (lane >> 3);
-            const u32x4 v = *reinterpret_cast<const u32x4*>(mine + row * 128 + ((lane & 7) << 4));
-            const int at = __shfl(out_row, row);          // (lane `row` of the first 16 holds that row's index)
-            if (at >= 0)
-              *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(a.out) + (size_t)at * kD + 64 * h + (((lane & 7) ^ (row & 7)) << 3)) = v;
-          }
+        for (int c = 0; c < 4; ++c) {
+          const f32x4 x = acc[qt][2 * c] * inv, y = acc[qt][2 * c + 1] * inv;
+          const auto lo = __builtin_amdgcn_permlane16_swap(pack_bf16(x[0], x[1]), pack_bf16(y[0], y[1]), false, false);
+          const auto hi = __builtin_amdgcn_permlane16_swap(pack_bf16(x[2], x[3]), pack_bf16(y[2], y[3]), false, false);
+          const uint32_t lo0 = lo[0], lo1 = lo[1], hi0 = hi[0], hi1 = hi[1];
+          v[c] = u32x4{lo0, hi0, lo1, hi1};
         }
+        if (out_row >= 0)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) *reinterpret_cast<u32x4*>(dst + 32 * c) = v[c];
+      }
+    };
+    if (write_rows) {
+#pragma unroll
+      for (int qt = 0; qt < kMT; ++qt) {
+        int sees;
+        store_tile(qt, row_of(cur, qt, l2 & 15, sees));
       }
     }
+    take_rows();
     if (!more) break;
     cur = nxt;
   }

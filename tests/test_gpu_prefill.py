@@ -88,6 +88,21 @@ def test_peaked_flat_and_sign_flipped_scores(scale):
     check(replace(inp, scale=scale), B.MARL_OUT_BF16)
 
 
+@pytest.mark.parametrize("first,later", [(-3.0, -3.0), (-3.0, 3.0), (3.0, -3.0), (-0.8, -0.8)])
+@pytest.mark.parametrize("chunks,context", [([3, 20, 200], [0, 31, 0]), ([40, 1], [300, 64])])
+def test_scores_far_from_the_first_reference(first, later, chunks, context):
+    """A row's first reference maximum is 0 where that gives weights within bounds: keys that put every score at about -200
+    (weights of exactly 0) or -50 in base 2, or the first page at -200 and the others at +200, and the other way round; items that begin
+    with a whole step and items that begin on the causal edge."""
+    print("case: prefill scores far from 0", first, later, chunks, context, flush=True)
+    inp = I.build_prefill_inputs(28, 4, chunks, context, seed=31)
+    inp.q += 4
+    inp.k_pages += later
+    inp.k_pages[inp.prefix_block_table[:, 0].long()] += first - later
+    check(inp)
+    check(inp, B.MARL_OUT_BF16)
+
+
 def test_many_small_groups_and_more_than_one_plan_round():
     rng = np.random.default_rng(0)
     lens = rng.integers(0, 12, size=1500).tolist()      # plan scans 1024 groups per round
