@@ -88,3 +88,17 @@ def test_short_items_are_not_drawn(seqs, Hkv, drawn):
     prefix = groups * Hkv
     assert counter(call, CTR_DRAWN) <= drawn * (prefix + 3 * Hkv)
     check(inp, dict(suffix_chunk_tokens=32, prefix_chunk_tokens=32))
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(6, 6), (14, 2)])
+def test_partials_behind_the_first_ones(Hq, Hkv):
+    """Rows and short items whose number of partials stands at and beside the numbers that are requested together (four
+    partials of a row, eight maxima behind the first four, or behind a short item's first one); one head per KV head, where
+    the merge kernel has more waves of short items than of rows."""
+    print("case: many partials", Hq, Hkv, flush=True)
+    plens = [0, 32, 96, 128, 160, 256, 288, 320, 384, 416, 544]   # up to 17 prefix partials
+    own = [0, 5, 128, 129, 300, 512]                              # 0 to 4 partials of their own, or one short item
+    gos = np.repeat(np.arange(len(plens)), len(own))
+    inp = custom_inputs(plens, own * len(plens), gos, Hq, Hkv, seed=Hq)
+    check(inp, dict(suffix_chunk_tokens=128, prefix_chunk_tokens=32))
+    check(inp, dict(suffix_chunk_tokens=32, prefix_chunk_tokens=512))
