@@ -19,6 +19,7 @@
 // the per-row mask, and a tile skips steps that lie entirely beyond its rows.  A block that is
 // taken whole sees all of its keys, so its output is normalised and written directly.
 //
+// Small calls are one launch (prefill_small_kernel): a workgroup per item, which it finds in the groups by itself.  The others:
 // Work distribution: a one-workgroup plan kernel lists the row blocks group after group, inside a
 // group last-first (most keys first), so that blocks of a group run at the same time and its keys come
 // out of the caches; a list of at most kPfSorted blocks, but more items than workgroups, is put into falling order of cost instead
@@ -352,13 +353,60 @@ struct PfItem {
 // x / R for 0 <= x < 65536 / 16 with inv_R = ceil(65536 / R): exact, since x (inv_R R - 65536) < 65536
 __device__ __forceinline__ int div_R(int x, int inv_R) { return (x * inv_R) >> 16; }
 
+// A small call has no plan kernel: every workgroup goes over the groups, one per thread, until it has found its block in the
+// plan's list (the groups' blocks in their order, last block of a group first), and the one that sets the flags over all of them.
+//   visit(group, tokens, blocks, blocks up to this group's last): for every group that the plan would list (wave-uniform calls
+//   are not promised); false ends the walk after a round of kPfThreads groups once `before` blocks have gone by.
+struct FindLds {
+  int wave_blocks[kNW];
+  int group, packed, flags;
+};
+template <class Visit>
+__device__ __forceinline__ void walk_groups(const PrefillArgs& a, const int until, int& flag, FindLds& lds, Visit&& visit) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int before = 0;                      // blocks of the groups so far
+  for (int g0 = 0; g0 < a.NG && before <= until; g0 += kPfThreads) {   // workgroup-uniform
+    const int g = g0 + tid;
+    int n = 0, nb = 0;
+    if (g < a.NG) {
+      n = group_tokens(a, g, flag);
+      nb = blocks_of(n * a.R);
+      if (nb > a.max_blocks) { nb = 0; flag |= MARL_FLAG_BAD_GROUP; }   // (dropped, as in the plan)
+    }
+    const int inc = wave_inclusive_scan(nb);
+    __syncthreads();                   // (the waves' numbers of the round before have been read)
+    if (lane == 63) lds.wave_blocks[wave] = inc;
+    __syncthreads();
+    int end = before + inc;
+#pragma unroll
+    for (int w = 0; w < kNW; ++w) {
+      if (w < wave) end += lds.wave_blocks[w];
+      before += lds.wave_blocks[w];
+    }
+    if (g < a.NG && end > a.max_blocks) flag |= MARL_FLAG_BAD_GROUP;   // (past the room for blocks: dropped, too)
+    else if (nb > 0) visit(g, n, nb, end);
+  }
+}
+__device__ __forceinline__ bool find_block(const PrefillArgs& a, const int block, int& g, int& packed, FindLds& lds) {
+  if (threadIdx.x == 0) lds.group = -1;
+  int flag = 0;
+  walk_groups(a, block, flag, lds, [&](int group, int n, int nb, int end) {
+    if (end > block && end - nb <= block) {
+      const int qb = block_rows(n * a.R, nb);
+      lds.group = group;
+      lds.packed = pack_item(group, (end - 1 - block) * qb, qb).y;
+    }
+  });
+  __syncthreads();
+  g = __builtin_amdgcn_readfirstlane(lds.group);
+  packed = __builtin_amdgcn_readfirstlane(lds.packed);
+  return g >= 0;
+}
+
 template <bool kSplit>
-__device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
+__device__ __forceinline__ PfItem item_of(const PrefillArgs& a, const int block, const int kvh, const int g_rec, const int packed) {
   PfItem it;
-  const int block = qi / a.Hkv;
-  it.kvh = qi - block * a.Hkv;
-  const int32_t* rec = reinterpret_cast<const int32_t*>(a.items + block);
-  const int g_rec = ld_uniform(rec), packed = ld_uniform(rec + 1);
+  it.kvh = kvh;
   const int g = kSplit ? g_rec & ~kPfSplitBit : g_rec;
   const int b = ld_uniform(a.q_start + g), e = ld_uniform(a.q_start + g + 1);
   const int pos0 = ld_uniform(a.q_pos0 + g);
@@ -385,9 +433,18 @@ __device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
   return it;
 }
 
-// Items of one workgroup, one after the other: `first`, `second` and the drawn ones, as far as they are less than n_ahead.
 template <bool kSplit>
-__device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int first, const int second, const int n_ahead,
+__device__ __forceinline__ PfItem read_item(const PrefillArgs& a, int qi) {
+  const int block = qi / a.Hkv;
+  const int32_t* rec = reinterpret_cast<const int32_t*>(a.items + block);
+  const int g_rec = ld_uniform(rec), packed = ld_uniform(rec + 1);
+  return item_of<kSplit>(a, block, qi - block * a.Hkv, g_rec, packed);
+}
+
+// Items of one workgroup, one after the other: first(), `second` and the drawn ones, as far as they are less than n_ahead
+// (kAlone: only first()).
+template <bool kSplit, bool kAlone, class First>
+__device__ __forceinline__ void prefill_items(const PrefillArgs& a, First&& first, const int second, const int n_ahead,
                                               PrefillLds& lds, int& bad_page) {
   constexpr int kLoads = 1024 / (kNW * 64);     // 16-byte loads per thread and step (16 KB per step)
   const int tid = threadIdx.x;
@@ -629,8 +686,8 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, const int fi
   // landed and everybody has finished reading the slot before; a fence would wait for every
   // outstanding load), then the loads of the slot kPfStages-1 ahead, which may be the next item's.
   // An item takes at least kPfStages slots, so what is ahead is never further than the next item.
-  PfItem cur = read_item<kSplit>(a, first);
-  bool more = second < n_ahead;                               // workgroup-uniform: there is a next item
+  PfItem cur = first();
+  bool more = !kAlone && second < n_ahead;                    // workgroup-uniform: there is a next item
   PfItem nxt = more ? read_item<kSplit>(a, second) : cur;             // (without one its slots are never used)
   int drawn = 0;                                              // (thread 0 only) the item after the next one
   uint32_t ring = 0;                   // byte offset of the current slot's buffer
@@ -828,8 +885,8 @@ void prefill_kernel(PrefillArgs a) {   // kSplit: the list may hold parts of blo
     auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(kernarg));
     const PrefillArgs run = *(const PrefillArgs*)kernarg;
-    if (kSplit && run.counters[kPfDivided] != 0) prefill_items<true>(run, first, second, n_ahead, lds, bad_page);
-    else prefill_items<false>(run, first, second, n_ahead, lds, bad_page);
+    if (kSplit && run.counters[kPfDivided] != 0) prefill_items<true, false>(run, [&] { return read_item<true>(run, first); }, second, n_ahead, lds, bad_page);
+    else prefill_items<false, false>(run, [&] { return read_item<false>(run, first); }, second, n_ahead, lds, bad_page);
     if (!in_group_order) break;
     if (threadIdx.x == 0) lds.late = n_ahead + atomicAdd(&a.counters[kPfLate], 1);
     __syncthreads();   // (the loads of slots past the end have landed: prefill_items ends with their wait)
@@ -837,6 +894,43 @@ void prefill_kernel(PrefillArgs a) {   // kSplit: the list may hold parts of blo
     second = n_work;
   }
   if (bad_page) atomicOr(&a.counters[kPfFlags], MARL_FLAG_BAD_PAGE);
+}
+
+// Small calls in one launch: no order, no parts, an item per workgroup, which finds its block in the groups by itself.  What bounds
+// it is the chain of dependent loads at its start (groups, page ids, keys): 4 us of the 7 of the smallest call; the plan, a launch
+// of its own before the items, took as long again.
+// The first workgroup sets the flags, by the groups and the page ids that they address: nobody
+// else writes that word, which no earlier kernel has cleared.
+__global__ __launch_bounds__(kPfThreads)
+__attribute__((amdgpu_waves_per_eu(MARL_PREFILL_WAVES_PER_EU, MARL_PREFILL_WAVES_PER_EU)))
+void prefill_small_kernel(PrefillArgs a) {
+  __shared__ PrefillLds lds;
+  __shared__ FindLds find;
+  if (blockIdx.x == 0) {
+    int flag = 0;
+    if (threadIdx.x == 0) find.flags = 0;
+    walk_groups(a, a.max_blocks, flag, find, [&](int g, int n, int, int) {
+      const int32_t* row = a.prefix_table + (size_t)g * a.max_pp;
+      const int last = (a.q_pos0[g] + n - 1) / kPage;
+      constexpr int kIds = 8;          // of a group, requested together
+      for (int p = 0; p <= last; p += kIds) {
+        int id[kIds];
+#pragma unroll
+        for (int u = 0; u < kIds; ++u) id[u] = row[min(p + u, last)];
+#pragma unroll
+        for (int u = 0; u < kIds; ++u) flag |= (unsigned)id[u] >= (unsigned)a.num_pages ? MARL_FLAG_BAD_PAGE : 0;
+      }
+    });
+    __syncthreads();
+    if (flag) atomicOr(&find.flags, flag);
+    __syncthreads();
+    if (threadIdx.x == 0) a.counters[kPfFlags] = find.flags;
+    return;
+  }
+  const int item = (int)blockIdx.x - 1, block = item / a.Hkv;
+  int g, packed, bad_page = 0;
+  if (find_block(a, block, g, packed, find))   // workgroup-uniform
+    prefill_items<false, true>(a, [&] { return item_of<false>(a, block, item - block * a.Hkv, g, packed); }, 0, 0, lds, bad_page);
 }
 
 // Scatter of a prompt chunk's keys and values into the group's pages.  One workgroup of 128
@@ -919,7 +1013,24 @@ int prefill_blocks_per_cu() {
   return n;
 }
 
+// Whether a call is taken by one launch without a plan.  Not where the plan would weigh parts; what can be known here are the bounds
+// of the number of items and of their keys.  Up to as many items as run at the same time it is always faster (planned / here, us: one
+// prompt of 45 tokens, 28 / 4 heads, 11.4 and 7.0; 12 of up to 362, 31.1 and 25.7; 19 of up to 151, 32 / 8, 21.0 and 14.8).  Beyond that the
+// order of the items, and each one's start while another runs, are worth more as items get longer and more of them share a
+// workgroup: with at most 448 keys and six items per workgroup none of 60 random calls was slower (19.1 and 11.3; 42.8 and
+// 35.6 for 1400 items of up to 67 keys; 93 and 88 for 3700 of up to 200), behind it some (10 prompts of up to 731, 28 / 4 heads, 39.6 and
+// 42.3; 40 of up to 503, 8 / 2, 30.8 and 32.7; 5000 items of up to 162 keys 109 and 116, 11000 of up to 70 183 and 215).
+constexpr long kPfSmallRounds = 6, kPfSmallKeys = 448;
+static bool is_small_prefill(const PrefillArgs& a) {
+  const long items = (long)a.max_blocks * a.Hkv, keys = (long)a.max_pp * kPage;
+  return keys <= kPfLongKeys && (items < a.slots || (items <= kPfSmallRounds * a.slots && keys <= kPfSmallKeys));
+}
+
 hipError_t launch_prefill(const PrefillArgs& a, int grid, hipStream_t st) {
+  if (is_small_prefill(a)) {
+    hipLaunchKernelGGL(prefill_small_kernel, dim3((unsigned)(a.max_blocks * a.Hkv + 1)), dim3(kPfThreads), 0, st, a);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(prefill_plan_kernel, dim3(1), dim3(kPlanThreadsPf), 0, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

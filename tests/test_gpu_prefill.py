@@ -366,3 +366,48 @@ def test_groups_of_many_blocks_are_listed_whole(blocks, before):
     print("case: prefill group of", blocks, "blocks behind", before, "groups", flush=True)
     inp = I.build_prefill_inputs(16, 1, [1] * before + [12 * blocks, 5, 12 * blocks - 11], [9] * before + [0, 40, 7], seed=blocks)
     check(inp)
+
+
+def _general(inp):
+    """The same call with a table too wide for the one launch of small calls."""
+    from dataclasses import replace
+    tab = inp.prefix_block_table
+    wide = torch.full((tab.shape[0], 61), -1, dtype=torch.int32)
+    wide[:, :tab.shape[1]] = tab
+    return replace(inp, prefix_block_table=wide)
+
+
+@pytest.mark.parametrize("Hq,Hkv,chunks,context", [
+    (28, 4, [45], [0]), (1, 1, [1], [959]), (16, 1, [960], [0]), (16, 16, [31], [0]), (16, 16, [1] * 20 + [11], [0] * 21),
+    (8, 8, [1] * 30 + [100, 0, 400], [5] * 33), (12, 4, [0, 3, 0, 0, 64, 65, 129], [0, 0, 8, 950, 17, 600, 1]), (4, 4, [1] * 64 + [200] * 3 + [1] * 60, [7] * 127),
+    (2, 1, [1] * 255 + [97], [3] * 256), (2, 1, [1] * 600 + [200], [3] * 601), (64, 8, [100] * 12, [860] * 12),
+    (16, 8, [2] * 60 + [40], [446] * 60 + [1]), (16, 8, [2] * 60 + [40], [447] * 60 + [1]), (4, 4, [5] * 766, [11] * 766), (4, 4, [5] * 767, [11] * 767)])
+def test_small_calls_in_one_launch_equal_the_planned_ones(Hq, Hkv, chunks, context):
+    """Bit for bit, at the edges of the rule (960 keys in a table row, one item fewer than there are workgroups at once; 448 keys, six
+    items per workgroup), with empty groups, groups in the second and third round of 256, and blocks of one and several per group."""
+    print("case: small prefill", Hq, Hkv, len(chunks), chunks[:3], context[:3], flush=True)
+    inp = I.build_prefill_inputs(Hq, Hkv, chunks, context, seed=len(chunks))
+    assert inp.prefix_block_table.shape[1] <= 60
+    for out_dtype in (B.MARL_OUT_F32, B.MARL_OUT_BF16):
+        np.testing.assert_array_equal(run_gpu(inp, out_dtype), run_gpu(_general(inp), out_dtype))
+    check(inp)
+
+
+@pytest.mark.parametrize("what", ["page", "page past the tokens", "long", "rows", "order", "overlap"])
+def test_small_calls_flag_what_planned_ones_flag(what):
+    from dataclasses import replace
+    a = I.build_prefill_inputs(28, 4, [100, 40, 0, 77], [0, 16, 3, 5], seed=5, poison=False, extra_cols=13)
+    tab, qs, pos0 = a.prefix_block_table.clamp(min=0), a.q_start.clone(), a.q_pos0.clone()   # (320 positions a row)
+    if what == "page": tab[3, 5] = a.num_pages
+    if what == "page past the tokens": tab[1, 4] = -7           # (56 tokens: four pages)
+    if what == "long": pos0[0] = 290
+    if what == "rows": qs[4] = 250
+    if what == "order": qs[1] = 150
+    if what == "overlap": qs = torch.tensor([0, 217, 0, 217, 0], dtype=torch.int32)
+    flag = {"page": B.FLAG_BAD_PAGE, "page past the tokens": 0, "long": B.FLAG_LEN_CLAMPED}.get(what, B.FLAG_BAD_GROUP)
+    bad = replace(a, prefix_block_table=tab, q_start=qs, q_pos0=pos0)
+    got = run_gpu(bad, B.MARL_OUT_F32, flag)
+    if what == "long":                                          # (a wider table would hold the tokens)
+        assert np.isfinite(got[:30]).all() and np.isnan(got[30:100]).all()
+    else:
+        np.testing.assert_array_equal(got, run_gpu(_general(bad), B.MARL_OUT_F32, flag))
