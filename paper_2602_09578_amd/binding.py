@@ -91,7 +91,7 @@ def _load_fast_calls(lib, build: bool):
         if m.torch_version != torch.__version__.split("+")[0]:
             raise ImportError(f"{FAST_PATH} was built for torch {m.torch_version}, not {torch.__version__}")
         _bind_fast_calls(m, lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
-                         lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)
+                         lib.marl_sample_tokens_top_p, lib.marl_prefill_attn, lib.marl_kv_write_prompt)
         return m
     except (ImportError, OSError, RuntimeError) as e:
         warnings.warn(f"calls take a few microseconds longer, without fast_calls: {e}", RuntimeWarning, stacklevel=3)
@@ -485,6 +485,10 @@ def marl_prefill_attn(shape: PrefillShape, workspace, q, k_pages, v_pages, prefi
 
 def marl_kv_write_prompt(shape: PrefillShape, k_new, v_new, k_pages, v_pages, prefix_block_table, q_start, q_pos0,
                          flags=None):
+    if _fast is not None:
+        rc = _fast.kv_write_prompt(shape, k_new, v_new, k_pages, v_pages, prefix_block_table, q_start, q_pos0, flags)
+        if rc is not None:
+            return _check(rc, "marl_kv_write_prompt")
     _require_cuda(k_new, v_new, k_pages, v_pages, prefix_block_table, q_start, q_pos0, flags)
     NT, NG, Hkv = shape.num_tokens, shape.num_groups, shape.num_kv_heads
     _require(k_new, "k_new", torch.bfloat16, (NT, Hkv, 128))

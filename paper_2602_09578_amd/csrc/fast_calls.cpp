@@ -2,7 +2,7 @@
 // extents, device and contiguity as in binding.py, made on the tensors themselves, and the call, in one step.
 // A call whose arguments are not plainly right is not made here: None is returned and the binding goes its long
 // way, which reports what is wrong.  (Host time of a call, long way and short: attention of 16 sequences 7.9 and 3.5 us,
-// log-probabilities 5.8 and 3.0; most of what is left is the launch.)
+// log-probabilities 5.8 and 3.0, prompt scatter 7.4 and 3.5; most of what is left is the launch.)
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -24,6 +24,7 @@ decltype(&marl_kv_append) f_kv_append;
 decltype(&marl_sample_tokens) f_sample_tokens;
 decltype(&marl_sample_tokens_top_p) f_sample_tokens_top_p;
 decltype(&marl_prefill_attn) f_prefill_attn;
+decltype(&marl_kv_write_prompt) f_kv_write_prompt;
 
 struct Call {
   bool ok = true;
@@ -244,14 +245,35 @@ PyObject* prefill_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// bind(stream_of, types of the two shapes, addresses of the library's functions in the order of the declarations above)
+// shape, k_new, v_new, k_pages, v_pages, prefix_block_table, q_start, q_pos0, flags
+PyObject* kv_write_prompt(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  return guarded([&]() -> PyObject* {
+    if (n != 9 || !f_kv_write_prompt) Py_RETURN_NONE;
+    Struct<marl_prefill_shape> s(a[0], g_prefill_shape);
+    if (!s.ok || a[1] == Py_None || a[8] != Py_None) return not_here();
+    const marl_prefill_shape& h = *s.get();
+    Call c;
+    const void* kn = c.data(a[1], kBf16, {h.num_tokens, h.num_kv_heads, 128});   // (first: the call's device)
+    const void* vn = c.data(a[2], kBf16, {h.num_tokens, h.num_kv_heads, 128});
+    void* k = c.data(a[3], kBf16, {h.num_pages, h.num_kv_heads, 16, 128});
+    void* v = c.data(a[4], kBf16, {h.num_pages, h.num_kv_heads, 128, 16});
+    const int32_t* pt = c.data<int32_t>(a[5], kI32, {h.num_groups, h.max_prefix_pages});
+    const int32_t* qs = c.data<int32_t>(a[6], kI32, {(int64_t)h.num_groups + 1});
+    const int32_t* qp = c.data<int32_t>(a[7], kI32, {h.num_groups});
+    void* stream = c.stream();
+    return finish(c, [&] { return f_kv_write_prompt(&h, kn, vn, k, v, pt, qs, qp, nullptr, stream); });
+  });
+}
+
+// bind(stream_of, types of the two shapes, addresses of the library's functions in the order of the declarations above; what is
+// not given is not called)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n != 9 || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
-    PyErr_SetString(PyExc_TypeError, "bind: a function, two types, six addresses");
+  if (n < 9 || n > 10 || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
+    PyErr_SetString(PyExc_TypeError, "bind: a function, two types, six or seven addresses");
     return nullptr;
   }
-  void* f[6];
-  for (int k = 0; k < 6; ++k) {
+  void* f[7] = {};
+  for (int k = 0; k + 3 < n; ++k) {
     f[k] = PyLong_AsVoidPtr(a[k + 3]);
     if (PyErr_Occurred()) return nullptr;
   }
@@ -266,12 +288,13 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   f_sample_tokens = reinterpret_cast<decltype(f_sample_tokens)>(f[3]);
   f_sample_tokens_top_p = reinterpret_cast<decltype(f_sample_tokens_top_p)>(f[4]);
   f_prefill_attn = reinterpret_cast<decltype(f_prefill_attn)>(f[5]);
+  f_kv_write_prompt = reinterpret_cast<decltype(f_kv_write_prompt)>(f[6]);
   Py_RETURN_NONE;
 }
 
 #define MARL_FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {MARL_FAST(bind), MARL_FAST(decode_attn), MARL_FAST(token_logprobs), MARL_FAST(sample_tokens),
-                         MARL_FAST(kv_append), MARL_FAST(prefill_attn), {nullptr, nullptr, 0, nullptr}};
+                         MARL_FAST(kv_append), MARL_FAST(prefill_attn), MARL_FAST(kv_write_prompt), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "fast_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

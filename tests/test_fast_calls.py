@@ -212,3 +212,42 @@ def test_an_exception_in_the_library_is_raised_and_the_call_is_not_repeated(tmp_
     call(*right)
     torch.cuda.synchronize()
     assert torch.isfinite(right[outs[0]]).all()
+
+
+@pytest.mark.gpu
+def test_prompt_scatter_by_the_short_way(monkeypatch):
+    """The native function makes the plain call, leaves everything else to the long way, and both write the same bytes."""
+    print("case: fast calls, prompt scatter", flush=True)
+    lib = B.load_library()
+    B._bind_fast_calls(B._fast, lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
+                       lib.marl_sample_tokens_top_p, lib.marl_prefill_attn, lib.marl_kv_write_prompt)
+    pre = I.build_prefill_inputs(8, 2, np.array([20, 33]), np.array([0, 16]), device="cuda", seed=1, poison=False)
+    shape, _, _ = B.prepare_prefill(pre, B.MARL_OUT_BF16)
+    args = lambda: [shape, pre.k_new, pre.v_new, pre.k_pages.clone(), pre.v_pages.clone(), pre.prefix_block_table, pre.q_start, pre.q_pos0]
+    short, long = args(), args()
+    assert B._fast.kv_write_prompt(*short, None) == 0
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    assert B._fast.kv_write_prompt(*long, flags) is None            # (with flags: the long way)
+    B.marl_kv_write_prompt(*long, flags)
+    torch.cuda.synchronize()
+    assert int(flags) == 0 and not torch.equal(short[3], pre.k_pages)
+    assert torch.equal(short[3], long[3]) and torch.equal(short[4], long[4])
+    for k, a in enumerate(args()):
+        if not torch.is_tensor(a):
+            continue
+        for wrong in (a.to(torch.float64), a[:-1], a.cpu(), a.unsqueeze(0), None, 5):
+            bad = args()
+            bad[k] = wrong
+            if wrong is None and k > 1:                             # (no address: what the library itself refuses)
+                assert B._fast.kv_write_prompt(*bad, None) != 0
+            else:
+                assert B._fast.kv_write_prompt(*bad, None) is None, k
+            said = []
+            for way in (B._fast, None):
+                with monkeypatch.context() as m, pytest.raises(Exception) as e:
+                    m.setattr(B, "_fast", way)
+                    B.marl_kv_write_prompt(*bad)
+                said.append((e.type, str(e.value)))
+            assert said[0] == said[1]
+    other = (ctypes.c_byte * ctypes.sizeof(shape)).from_buffer_copy(shape)
+    assert B._fast.kv_write_prompt(other, *args()[1:], None) is None
