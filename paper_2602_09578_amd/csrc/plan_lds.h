@@ -31,10 +31,14 @@ __device__ __forceinline__ int clamp_len(int v, int hi, int& flags) {
 // barriers and LDS round trips of its one workgroup: the three scans (groups, suffix and prefix classes)
 // share one pass and stay in the vector ALU.  16 sequences 9.9 -> 7.2 us, 2048 sequences 12.0 -> 9.9 us, launch
 // included; the former time had a block-wide scan with shuffles and three barriers for each of the three.  (One LDS atomic
-// for all lanes of a wave that count in the same word: 11.9 -> 16.5 us, 2048 sequences; 14.4 -> 23.6, 4096.)
+// for all lanes of a wave that count in the same word: 11.9 -> 16.5 us, 2048 sequences; 14.4 -> 23.6, 4096.  But whole chunks, which
+// are all of one class, take their places by one atomic per wave: lanes that add to the same word one after the other, and
+// wait for what they get, took 4 us of the plan of 256 sequences of several chunks, 10.7 -> 6.5 us as a replayed graph, 1 us for
+// 64 sequences, 6.7 -> 5.6, both with the code for two sequences per thread.  With eight or 32 per thread, whose scans run
+// whether there are whole chunks or not, 14.4 -> 15.2 us for 8000 sequences, 42 -> 52 for 20000: an atomic each there.)
 // ---------------------------------------------------------------------------------------
-// Three sizes: up to 512 sequences and groups by 256 threads, beside a small call's attention (13 KB of LDS); up to 8192
-// sequences in 2048 groups (56 KB) and up to 32768 sequences in 8192 groups with 16-bit member ids (130 KB of the 160 KB), by
+// Four sizes: up to 512 sequences and groups by 256 threads, beside a small call's attention (13 KB of LDS); up to 2048
+// sequences in 1024 groups (22 KB), up to 8192 in 2048 (56 KB) and up to 32768 sequences in 8192 groups with 16-bit member ids (130 KB of the 160 KB), by
 // 1024 threads.
 constexpr int kSmallMaxClasses = 256;
 
@@ -181,9 +185,25 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
   }
   __syncthreads();
 
+  constexpr bool kTogether = kSeqsPerThread <= 2;   // whole chunks' places by one atomic per wave
+  auto take = [&](int* word, int n) {               // (for all lanes of the wave)
+    const int inc = wave_inclusive_scan(n);
+    int base = 0;
+    if (lane_id() == 63) base = atomicAdd(word, inc);
+    return __builtin_amdgcn_readlane(base, 63) + inc - n;
+  };
+  auto put_suffix = [&](int pos, int s, int nfull) {
+    for (int i = 0; i < nfull; ++i) a.suffix_items[pos + i] = make_int4(s, i * Cs, (i + 1) * Cs, 0);
+  };
+  auto put_prefix = [&](int pos, int g, int nfull, int nqb) {
+    for (int i = 0; i < nfull; ++i)
+      for (int b = 0; b < nqb; ++b)
+        a.prefix_items[pos + i * nqb + b] = make_int4(g, i * Cp, (i + 1) * Cp, b * QB);
+  };
 #pragma unroll
   for (int k = 0; k < kSeqsPerThread; ++k) {
     const int s = tid + k * kThreads;
+    int nfull_of = 0;
     if (s < a.NS) {
       const int g = G(k);
       if (rank_of[k] >= 0) members[start[g] + rank_of[k]] = (MemberId)s;
@@ -196,20 +216,21 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       }
       a.seq_chunks[s] = ((P + Cp - 1) / Cp) | (((S + Cs - 1) / Cs) << 16);
       const int nfull = S / Cs, tail = S % Cs;
-      if (nfull) {
-        const int pos = atomicAdd(&hist_s[0], nfull);
-        for (int i = 0; i < nfull; ++i) a.suffix_items[pos + i] = make_int4(s, i * Cs, (i + 1) * Cs, 0);
-      }
+      if constexpr (kTogether) nfull_of = nfull;
+      else if (nfull) put_suffix(atomicAdd(&hist_s[0], nfull), s, nfull);
       if (tail) {
         const int pos = atomicAdd(&hist_s[(Cs - tail) / 32], 1);
         a.suffix_items[pos] = make_int4(s, nfull * Cs, S, 0);
       }
     }
+    if constexpr (kTogether)
+      if (__builtin_amdgcn_ballot_w64(nfull_of > 0) != 0) put_suffix(take(&hist_s[0], nfull_of), s, nfull_of);   // wave-uniform
   }
   bool ranked = false;   // a group that has an order
 #pragma unroll
   for (int k = 0; k < kGroupsPerThread; ++k) {
     const int g = tid + k * kThreads;
+    int nfull_of = 0, nqb_of = 0;
     if (g < a.NG) {
       a.group_count[g] = cnt[g];
       ranked |= cnt[g] >= 2 && cnt[g] <= 64;
@@ -218,12 +239,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       const int nqb = (cnt[g] * R + QB - 1) / QB;
       const int nfull = P / Cp, tail = P % Cp;
       if (nqb) {
-        if (nfull) {
-          const int pos = atomicAdd(&hist_p[0], nfull * nqb);
-          for (int i = 0; i < nfull; ++i)
-            for (int b = 0; b < nqb; ++b)
-              a.prefix_items[pos + i * nqb + b] = make_int4(g, i * Cp, (i + 1) * Cp, b * QB);
-        }
+        if constexpr (kTogether) nfull_of = nfull, nqb_of = nqb;
+        else if (nfull) put_prefix(atomicAdd(&hist_p[0], nfull * nqb), g, nfull, nqb);
         if (tail) {
           const int pos = atomicAdd(&hist_p[(Cp - tail) / 32], nqb);
           for (int b = 0; b < nqb; ++b)
@@ -231,6 +248,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
         }
       }
     }
+    if constexpr (kTogether)
+      if (__builtin_amdgcn_ballot_w64(nfull_of > 0) != 0) put_prefix(take(&hist_p[0], nfull_of * nqb_of), g, nfull_of, nqb_of);
   }
   if (tid == 0) a.group_start[a.NG] = nseq_grouped;
   if (ranked) any_ranked = 1;

@@ -117,6 +117,21 @@ def big_case(NG, lo, hi, seed):
     return shape, pl, sl, gos
 
 
+@pytest.mark.parametrize("NS,NG", [(2048, 1024), (2049, 1024), (2048, 1025), (1, 1), (65, 1024), (1500, 300)])
+@pytest.mark.parametrize("lo,hi", [(0, 300), (700, 2600)])
+def test_plan_at_the_sizes_of_its_variants(NS, NG, lo, hi):
+    """Both sides of the limits of the variant that places a wave's whole chunks together; sequences and groups of none, one and
+    many whole chunks side by side in a wave, and waves without any."""
+    print("case: plan variants", NS, NG, lo, flush=True)
+    rng = np.random.default_rng(NS + NG)
+    gos = rng.integers(0, NG, NS).astype(np.int32)
+    sl, pl = rng.integers(lo, hi, NS).astype(np.int32), rng.integers(lo, hi, NG).astype(np.int32)
+    sl[rng.random(NS) < 0.3] = 0
+    sl[: NS // 3] %= 64
+    shape = B.make_shape(NS, NG, 8, 2, 10, 163, 163, suffix_chunk_tokens=64, prefix_chunk_tokens=128)
+    compare(shape, pl, sl, gos, 8, 2)
+
+
 def test_plan_larger_lds_variant():
     """8193 .. 32768 sequences in up to 8192 groups: the LDS-resident plan with 16-bit member ids."""
     print("case: plan medium", flush=True)
