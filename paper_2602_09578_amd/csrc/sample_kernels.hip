@@ -317,8 +317,10 @@ __global__ __launch_bounds__(kRowMaxWaves * 64) void sample_rows_kernel(SampleAr
 // per CU 212; with the row held in registers by one workgroup per CU, a count of all values in
 // LDS (an LDS atomic on 64 lanes takes about 25 cycles) and a third pass over all tokens 508 us; the
 // same with the list but still in registers 316 us (nothing to overlap the short phases with).
-// A few rows (64 x 152064, top_p 0.95: 37 us): each has a CU of its own, whose vector ALU issues in 53 % of that time, two waves
-// per SIMD; in the rest it waits, for the two reads' latencies and at the barriers between the phases.
+// A few rows (64 x 152064, top_p 0.95: 34 us): each has a CU of its own, whose vector ALU issues in half of that time, two waves
+// per SIMD: pass 1 for 9 us (issue), the copy into the list 10 us (an exec mask and a store per token: a chain), in the rest it waits,
+// at the barriers between the phases.  (16 waves a row: 3 % faster up to 128 rows, half as fast from 512 on.  Two stores per four
+// tokens, selected and placed by lane counts, instead of four: 40 us.)
 // Three workgroups per CU leave 80 vector registers: two are spilled (12 bytes of scratch per lane), outside the passes,
 // and 46 scalar registers to lanes of vector registers, which the counts over windows read back.
 // ---------------------------------------------------------------------------------------
@@ -775,13 +777,17 @@ void sample_top_p_kernel(TopPArgs a) {
   if (from_list) {
     part_m = sh.group_mass;
     part_n = sh.group_ties;
-    // Four lanes per group where a wave has more than four of them, 16 groups at a time (a group after the
-    // other, reduced over the wave, took five times as long: a chain of LDS reads and reductions per group);
-    // in shorter rows, where four lanes would walk through hundreds of entries, 16 or all (1 row x 4096,
-    // sigma 2, top_p 0.95, half of the row listed: 28.3 us with four lanes, 14.5 with all; 32003 logits 32.6 and 21.6).
-    const int per = most_groups > 4 ? 4 : most_groups > 1 ? 16 : 64, at_once = 64 / per, mine = lane & (per - 1);
+    // A power of two lanes per group, 4 to 64, so that most of the wave has a share of a group: 16, 8, 4, 2 groups at once or one,
+    // whichever leaves the fewest idle and takes the fewest rounds (10 groups: 8 and 2).  One group after the other, reduced over the
+    // wave, took five times as long (a chain of LDS reads and reductions per group); four lanes each wherever there are more
+    // than four groups walk through hundreds of entries (64 x 152064, top_p 0.95: 36.3 us, now 34.3; 256 x 32003, sigma 2:
+    // 25.3, now 23.2; 2048 x 152064 208 and 204).
+    int at_once;
     for (int k0 = 0; k0 < my_groups; k0 += at_once) {   // wave-uniform
-      const int slot = k0 + lane / per, k = min(slot, my_groups - 1);
+      const int left = my_groups - k0, log = left > 10 ? 4 : left > 5 ? 3 : left > 2 ? 2 : left - 1;
+      at_once = 1 << log;
+      const int per = 64 >> log, mine = lane & (per - 1);
+      const int slot = k0 + (lane >> (6 - log)), k = min(slot, my_groups - 1);
       const int begin = k + 1 < my_groups ? sh.seg_end[wave][k + 1] : 0, end = sh.seg_end[wave][k];   // (listed backwards)
       double mg = 0.0;
       int n = 0;
@@ -806,12 +812,16 @@ void sample_top_p_kernel(TopPArgs a) {
       if (per > 4) {
         mg += dpp_or_zero<0x114, 0xf>(mg);   // row_shr:4
         n += dpp_or_zero<0x114, 0xf>(n);
+      }
+      if (per > 8) {
         mg += dpp_or_zero<0x118, 0xf>(mg);   // row_shr:8
         n += dpp_or_zero<0x118, 0xf>(n);
       }
       if (per > 16) {
         mg += dpp_or_zero<0x142, 0xa>(mg);   // row_bcast:15 into rows 1 and 3
         n += dpp_or_zero<0x142, 0xa>(n);
+      }
+      if (per > 32) {
         mg += dpp_or_zero<0x143, 0xc>(mg);   // row_bcast:31 into rows 2 and 3
         n += dpp_or_zero<0x143, 0xc>(n);
       }

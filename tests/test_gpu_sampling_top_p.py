@@ -202,3 +202,12 @@ def test_wide_nuclei_at_every_row_length(V, sigma, T, top_p):
     print("case: top-p row lengths", V, sigma, T, top_p, flush=True)
     lp = I.build_logprob_inputs(4, V, sigma, V, temperature=T)
     check(lp.logits, np.array([0.0, 0.37, 0.71, 0.999999]), T, top_p)
+
+
+@pytest.mark.parametrize("groups", [2, 3, 5, 6, 7, 10, 11, 12, 13, 17, 20])
+def test_lists_of_every_number_of_groups(groups):
+    """Groups per wave on both sides of the numbers at which other numbers of lanes share one, the last wave with a group less."""
+    V = groups * 16384 - 2048 - 700
+    print("case: top-p groups", groups, V, flush=True)
+    lp = I.build_logprob_inputs(5, V, 3.0, groups, temperature=0.8)
+    check(lp.logits, np.array([0.0, 0.2, 0.5, 0.8, 0.999999]), 0.8, 0.9)
