@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kRowMaxWaves * 64) void sample_rows_kernel(SampleAr
 // tokens at the threshold value": the kernel finds the threshold with exact counts per value
 // instead of sorting 150 k tokens.
 //
-// One workgroup of 512 threads owns a row, three of them share a CU.  The row is cut into groups of
+// One workgroup of 512 threads owns a row, three of them share a CU (long rows of small batches have one for themselves).  The row is cut into groups of
 // 2048 tokens, group k * 8 + w belongs to wave w.  Passes over the row:
 //   1. maximum value and Z = sum 2^(y - M)  (running (max, sum) per thread, fixed-order merge);
 //   2. short list: the mass of the unlikely tokens is estimated from a sample of the row (it is made
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kRowMaxWaves * 64) void sample_rows_kernel(SampleAr
 //      below the maximum, the counts are taken of the whole row instead, over windows of 8192 values: first
 //      the one that starts at the cut, if the threshold is likely to lie in it, with the mass of what is
 //      above it, then from the maximum down.  (Nuclei of half of a long row or more, rows of negative
-//      logits.  64 x 152064, sigma 3, top_p 0.95: 37 us at T 1, with the list, and 52 at T 1.3, without;
+//      logits.  64 x 152064, sigma 2, top_p 0.95: 48 us at T 1, with the list, and 60 at T 1.3, without;
 //      2048 x 152064, top_p 0.9: 200 us, and 304 with 40 subtracted from every logit, which changes nothing else.)
 //   3. per group the nucleus mass and the number of threshold-value tokens (from the list, else one
 //      more pass over the row); a scan over the group sums finds the group in which the scaled
@@ -331,7 +331,6 @@ constexpr int kTpGroup = 2048;               // tokens of a group: 4 x 512, one 
 constexpr int kLowestKey = 0x0080;           // key of the most negative finite bf16; below: -inf, NaN
 constexpr int kScanStep = 4;                 // scan positions per thread and round of the threshold search
 constexpr int kListGroups = 20;              // groups per wave that the list covers (vocab <= 327680)
-constexpr int kListCap = 2624;               // list entries per wave
 constexpr int kListWin = 2048;               // values the list may span
 constexpr int kBins = 256;                   // bins of the tail estimate, an eighth of a power of two each
 constexpr int kSampleWords = 10;             // words per thread that the estimate looks at
@@ -345,6 +344,7 @@ __device__ __forceinline__ float value_of_key(int key) {
   return __uint_as_float(bits << 16);
 }
 
+template <int kListCap>   // list entries per wave
 struct TpShared {
   union {
     uint32_t hist[kWin];                       // counts of pass 2 without the list; group sums of pass 3
@@ -370,10 +370,13 @@ struct TpShared {
   float want_in_group;          // nucleus mass still to pass inside the chosen group
   int out_tok;
 };
-static_assert(sizeof(TpShared) <= 42 * 1280, "three workgroups share a CU's 160 KB");
+constexpr int kListCapShared = 2624, kListCapAlone = 9216;
+static_assert(sizeof(TpShared<kListCapShared>) <= 42 * 1280, "three workgroups share a CU's 160 KB");
+static_assert(sizeof(TpShared<kListCapAlone>) <= 160 * 1024, "a workgroup has a CU's LDS");
 
 // exclusive scans over the workgroup in thread order (fixed order: bit-identical reruns)
-__device__ __forceinline__ double block_excl_scan_d(double v, double& total, TpShared& sh) {
+template <class Shared>
+__device__ __forceinline__ double block_excl_scan_d(double v, double& total, Shared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double inc = wave_inclusive_scan(v);
   __syncthreads();
@@ -388,7 +391,8 @@ __device__ __forceinline__ double block_excl_scan_d(double v, double& total, TpS
   total = all;
   return before + inc - v;
 }
-__device__ __forceinline__ float block_excl_scan_f(float v, TpShared& sh) {
+template <class Shared>
+__device__ __forceinline__ float block_excl_scan_f(float v, Shared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float inc = wave_inclusive_scan(v);
   __syncthreads();
@@ -400,7 +404,8 @@ __device__ __forceinline__ float block_excl_scan_f(float v, TpShared& sh) {
     if (w < wave) before += sh.wave_f[w];
   return before + inc - v;
 }
-__device__ __forceinline__ int block_excl_scan_i(int v, TpShared& sh) {
+template <class Shared>
+__device__ __forceinline__ int block_excl_scan_i(int v, Shared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int inc = wave_inclusive_scan(v);
   __syncthreads();
@@ -428,9 +433,9 @@ __device__ __forceinline__ int uniform_i(int v) { return __builtin_amdgcn_readfi
 // that is the first round, a few hundred values below the maximum.  Returns whether it was
 // reached (workgroup-uniform; then sh.thr_* are set, visible after the barrier this ends with),
 // adds the scanned mass to `above`.
-template <class Weight>
+template <class Weight, class Shared>
 __device__ __forceinline__ bool find_threshold(const uint32_t* hist, int hi, int lo, int npos, double tau,
-                                               double& above, Weight&& weight, TpShared& sh) {
+                                               double& above, Weight&& weight, Shared& sh) {
   const int tid = threadIdx.x;
   auto mass_at = [&](int pos) {
     const int key = hi - pos;
@@ -499,9 +504,9 @@ __device__ __forceinline__ void append_words(uint32_t& at, u32x4 v, int cut, flo
 #undef MARL_APPEND_WORD
 }
 
-__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
-void sample_top_p_kernel(TopPArgs a) {
-  __shared__ TpShared sh;
+template <int kListCap>
+__device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
+  __shared__ TpShared<kListCap> sh;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row = blockIdx.x;
@@ -952,15 +957,27 @@ void sample_top_p_kernel(TopPArgs a) {
   }
 }
 
+__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
+void sample_top_p_kernel(TopPArgs a) { sample_top_p<kListCapShared>(a); }
+__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void sample_top_p_alone_kernel(TopPArgs a) { sample_top_p<kListCapAlone>(a); }
+
 }  // namespace
 
 int sample_num_chunks(int vocab) { return (vocab + kChunk - 1) / kChunk; }
 
 int top_p_max_vocab() { return 1 << 23; }   // its 4096 groups' sums fit the LDS buffer
 
+constexpr int kTpAloneVocab = 49152;
+
 hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(sample_top_p_kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
+  // Where every row has a CU of an MI355X for itself, its list may take all of the LDS: half of a row of 152064 fits, not a seventh, and
+  // wider nuclei are found without counting whole rows (256 x 152064, top_p 0.95: sigma 3 at T 1.3 56.2 -> 46.0 us, sigma 2 56.5 ->
+  // 50.8; 1 row 49.6 -> 40.7).  In shorter rows the smaller list takes as much as is ever worth it, and three rows a
+  // CU are no slower alone (32003: 19.4 and 19.7 us).
+  if (a.rows <= 256 && a.vocab > kTpAloneVocab) hipLaunchKernelGGL(sample_top_p_alone_kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
+  else hipLaunchKernelGGL(sample_top_p_kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -211,3 +211,13 @@ def test_lists_of_every_number_of_groups(groups):
     print("case: top-p groups", groups, V, flush=True)
     lp = I.build_logprob_inputs(5, V, 3.0, groups, temperature=0.8)
     check(lp.logits, np.array([0.0, 0.2, 0.5, 0.8, 0.999999]), 0.8, 0.9)
+
+
+@pytest.mark.parametrize("rows,V", [(256, 49153), (257, 49153), (256, 49152), (3, 152064), (3, 157697)])
+@pytest.mark.parametrize("sigma,T,top_p", [(2.0, 1.0, 0.95), (3.0, 1.3, 0.95), (2.0, 1.3, 0.9), (2.0, 1.3, 0.95)])
+def test_long_lists_of_rows_alone_on_a_cu(rows, V, sigma, T, top_p):
+    """Both sides of the rule for rows that have a CU's LDS for their list; nuclei of a tenth of the row to most of it, which fit
+    the longer list, or neither."""
+    print("case: top-p alone", rows, V, sigma, T, top_p, flush=True)
+    lp = I.build_logprob_inputs(rows, V, sigma, V + rows, temperature=T)
+    check(lp.logits, np.random.default_rng(rows).random(rows), T, top_p)
