@@ -339,6 +339,7 @@ constexpr int kTpWaves = kTpThreads / 64;
 constexpr int kWin = 8192;                   // values per window of the count without the list
 constexpr int kTpGroup = 2048;               // tokens of a group: 4 x 512, one wave
 constexpr int kLowestKey = 0x0080;           // key of the most negative finite bf16; below: -inf, NaN
+constexpr int kTpMaxVocab = 1 << 23;         // its 4096 groups' sums fit the LDS buffer
 constexpr int kScanStep = 4;                 // scan positions per thread and round of the threshold search
 constexpr int kListGroups = 20;              // groups per wave that the list covers (vocab <= 327680)
 constexpr int kListWin = 2048;               // values the list may span
@@ -514,15 +515,19 @@ __device__ __forceinline__ void append_words(uint32_t& at, u32x4 v, int cut, flo
 #undef MARL_APPEND_WORD
 }
 
-template <int kListCap>
+template <int kListCap, bool kSkewed>
 __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
   __shared__ TpShared<kListCap> sh;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row = blockIdx.x;
-  const uint16_t* x = a.logits + (size_t)row * a.vocab;
+  // kSkewed: positions count from the 16-byte boundary at or before the row (rows of an odd vocabulary start anywhere), so that
+  // loads are aligned: position p is token p - skew, those before `skew` and from V on are no tokens.
+  const uint16_t* const row_begin = a.logits + (size_t)row * a.vocab;
+  const int skew = kSkewed ? (int)(reinterpret_cast<uintptr_t>(row_begin) & 15) / 2 : 0;
+  const uint16_t* x = row_begin - skew;   // (never read before row_begin)
   const float c = a.inv_temp_log2e;
-  const long V = a.vocab;
+  const long V = (long)a.vocab + skew;
   const int ngroups = (int)((V + kTpGroup - 1) / kTpGroup);
   const float u = a.uniforms[row];   // (requested early: used after the passes)
   const int my_groups = wave < ngroups ? (ngroups - wave + kTpWaves - 1) / kTpWaves : 0;   // of this wave
@@ -532,12 +537,24 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     constexpr bool kBack = decltype(backwards_tag)::value;
     auto fetch = [&](int g, u32x4 (&v)[4]) {
       const long base = (long)g * kTpGroup;
-      if (base + kTpGroup <= V) {   // wave-uniform
+      if (base + kTpGroup <= V && (!kSkewed || g > 0)) {   // wave-uniform
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const u32x4_any*>(x + base + j * 512 + lane * 8);
       } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = load8_words(x, base + j * 512 + lane * 8, V);
+        for (int j = 0; j < 4; ++j) {
+          const long pos = base + j * 512 + lane * 8;
+          if (!kSkewed || pos >= skew) {
+            v[j] = load8_words(x, pos, V);
+          } else {   // the row's first lane
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+              const uint32_t lo = 2 * d >= skew && 2 * d < V ? x[2 * d] : 0xff80u;
+              const uint32_t hi = 2 * d + 1 >= skew && 2 * d + 1 < V ? x[2 * d + 1] : 0xff80u;
+              v[j][d] = lo | (hi << 16);
+            }
+          }
+        }
       }
     };
     u32x4 cur[4], nxt[4];
@@ -914,9 +931,9 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     float r[4];
     uint32_t raw[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) raw[e] = x[min(pos + e, V - 1)];
+    for (int e = 0; e < 4; ++e) raw[e] = x[kSkewed ? max(min(pos + e, V - 1), (long)skew) : min(pos + e, V - 1)];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = pos + e < V ? __uint_as_float(raw[e] << 16) : -INFINITY;
+    for (int e = 0; e < 4; ++e) r[e] = (!kSkewed || pos + e >= skew) && pos + e < V ? __uint_as_float(raw[e] << 16) : -INFINITY;
     int n4 = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) n4 += r[e] == thr_x;
@@ -961,24 +978,28 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
       float r_pick = r[0];
 #pragma unroll
       for (int e = 1; e < 4; ++e) if (e == e_pick) r_pick = r[e];
-      a.out_tokens[row] = (int)(pos + e_pick);
+      a.out_tokens[row] = (int)(pos + e_pick) - skew;
       a.out_logprobs[row] = logprob_of(r_pick, c, M, Z);
     }
   }
 }
 
 __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
-void sample_top_p_kernel(TopPArgs a) { sample_top_p<kListCapShared>(a); }
+void sample_top_p_kernel(TopPArgs a) { sample_top_p<kListCapShared, false>(a); }
+__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
+void sample_top_p_skewed_kernel(TopPArgs a) { sample_top_p<kListCapShared, true>(a); }
 __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void sample_top_p_alone_kernel(TopPArgs a) { sample_top_p<kListCapAlone>(a); }
+void sample_top_p_alone_kernel(TopPArgs a) { sample_top_p<kListCapAlone, false>(a); }
+__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void sample_top_p_alone_skewed_kernel(TopPArgs a) { sample_top_p<kListCapAlone, true>(a); }
 
 }  // namespace
 
 int sample_num_chunks(int vocab) { return (vocab + kChunk - 1) / kChunk; }
 
-int top_p_max_vocab() { return 1 << 23; }   // its 4096 groups' sums fit the LDS buffer
+int top_p_max_vocab() { return kTpMaxVocab; }
 
-constexpr int kTpAloneVocab = 49152;
+constexpr int kTpAloneVocab = 49152, kTpSkewedVocab = 28672;
 
 hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
@@ -986,8 +1007,16 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   // wider nuclei are found without counting whole rows (256 x 152064, top_p 0.95: sigma 3 at T 1.3 56.2 -> 46.0 us, sigma 2 56.5 ->
   // 50.8; 1 row 49.6 -> 40.7).  In shorter rows the smaller list takes as much as is ever worth it, and three rows a
   // CU are no slower alone (32003: 19.4 and 19.7 us).
-  if (a.rows <= 256 && a.vocab > kTpAloneVocab) hipLaunchKernelGGL(sample_top_p_alone_kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
-  else hipLaunchKernelGGL(sample_top_p_kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
+  // Rows that start off 16-byte boundaries: their loads take up to twice the requests, unless positions are counted from the
+  // boundary before, which costs the row's first group a slower load and some address arithmetic (2000 rows, unskewed / skewed:
+  // 128001 208 and 176 us, 100003 168 and 148, 32003 68.1 and 66.0, 20481 54.0 and 58.2; 64 rows 31.4 and 30.1, 27.7 and 26.3,
+  // 17.4 and 15.9; one row 27.7 and 28.2; aligned rows 2 % slower).
+  const bool alone = a.rows <= 256 && a.vocab > kTpAloneVocab;
+  const bool aligned = a.vocab % 8 == 0 && reinterpret_cast<uintptr_t>(a.logits) % 16 == 0;
+  const bool skewed = !aligned && a.rows >= 8 && a.vocab >= kTpSkewedVocab && a.vocab <= kTpMaxVocab - 8;   // (no more groups than there is room for)
+  const auto kernel = alone ? skewed ? sample_top_p_alone_skewed_kernel : sample_top_p_alone_kernel
+                            : skewed ? sample_top_p_skewed_kernel : sample_top_p_kernel;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
   return hipGetLastError();
 }
 

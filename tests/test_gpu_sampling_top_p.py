@@ -139,6 +139,14 @@ def test_full_size_rows_rerun_identical_and_sampled_check():
     check(sub, u[sample], 1.0, 0.9)
 
 
+def run_rows(logits, u, T, top_p):
+    rows = logits.shape[0]
+    tok, lp = torch.empty(rows, dtype=torch.int32, device="cuda"), torch.empty(rows, dtype=torch.float32, device="cuda")
+    B.marl_sample_tokens_top_p(logits, torch.from_numpy(u.astype(np.float32)).cuda(), T, top_p, tok, lp)
+    torch.cuda.synchronize()
+    return tok.cpu().numpy(), lp.cpu().numpy()
+
+
 def _route_rows(kind, V, rng):
     """Rows that send the threshold search down one of its routes."""
     x = (rng.standard_normal((3, V)) * 3).astype(np.float32)
@@ -221,3 +229,29 @@ def test_long_lists_of_rows_alone_on_a_cu(rows, V, sigma, T, top_p):
     print("case: top-p alone", rows, V, sigma, T, top_p, flush=True)
     lp = I.build_logprob_inputs(rows, V, sigma, V + rows, temperature=T)
     check(lp.logits, np.random.default_rng(rows).random(rows), T, top_p)
+
+
+@pytest.mark.parametrize("V", [28671, 28673, 28675, 32767, 49155, 100003])
+@pytest.mark.parametrize("first", [0, 1, 7])
+def test_rows_that_start_anywhere(V, first):
+    """Rows at every distance from a 16-byte boundary, the first one in the middle of a buffer whose other elements must not be
+    drawn or counted: the token before a row and the one behind it are the largest values there are.  Tokens at
+    both ends of a row are drawn too."""
+    print("case: top-p skewed rows", V, first, flush=True)
+    rows = 9
+    lp = I.build_logprob_inputs(rows, V, 2.5, V + first, temperature=0.9)
+    x = lp.logits.clone()
+    x[0, 0] = x[1, V - 1] = x[2, 1] = x[3, V - 2] = 30.0
+    buf = torch.full((first + rows * V + 8,), 3.0e38, dtype=torch.bfloat16)
+    buf[first:first + rows * V] = x.flatten()
+    on_gpu = buf.cuda()[first:first + rows * V].view(rows, V)
+    assert on_gpu.data_ptr() % 16 == 2 * first
+    u = np.linspace(0.0, 0.999999, rows)
+    check(x, u, 0.9, 0.9)                       # (the same rows in a buffer of their own)
+    want_tok, want_lp = run_rows(x.cuda(), u, 0.9, 0.9)
+    tok, got = run_rows(on_gpu, u, 0.9, 0.9)
+    assert tok[:4].tolist() == [0, V - 1, 1, V - 2]
+    few = [run_rows(on_gpu[k:k + 1], u[k:k + 1], 0.9, 0.9) for k in range(rows)]   # (short batches: not skewed)
+    for other in ((want_tok, want_lp), tuple(np.concatenate(v) for v in zip(*few))):
+        assert (other[0] != tok).sum() <= 1     # (a uniform number at an interval's edge)
+        assert np.abs(other[1] - got)[other[0] == tok].max() <= 1e-5
