@@ -342,6 +342,7 @@ constexpr int kLowestKey = 0x0080;           // key of the most negative finite 
 constexpr int kTpMaxVocab = 1 << 23;         // its 4096 groups' sums fit the LDS buffer
 constexpr int kScanStep = 4;                 // scan positions per thread and round of the threshold search
 constexpr int kListGroups = 20;              // groups per wave that the list covers (vocab <= 327680)
+constexpr int kListAtLeast = 128, kSeveralRows = 16;   // tokens it has at least in batches of so many rows
 constexpr int kListWin = 2048;               // values the list may span
 constexpr int kBins = 256;                   // bins of the tail estimate, an eighth of a power of two each
 constexpr int kSampleWords = 10;             // words per thread that the estimate looks at
@@ -657,7 +658,8 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
       mass[e] = (float)count[e] * w;
       square[e] = mass[e] * w;
     }
-    const int sampled = from_lane(wave_inclusive_scan((count[0] + count[1]) + (count[2] + count[3])), 63);
+    const int counted_to = wave_inclusive_scan((count[0] + count[1]) + (count[2] + count[3]));
+    const int sampled = from_lane(counted_to, 63);
     const float mine_m = (mass[0] + mass[1]) + (mass[2] + mass[3]), mine_s = (square[0] + square[1]) + (square[2] + square[3]);
     float tail = wave_inclusive_scan(mine_m) - mine_m, var = fmaxf(wave_inclusive_scan(mine_s) - mine_s, 0.f);
     const float allowed = (float)((1.0 - (double)a.top_p) * Z * (double)sampled / ((double)ngroups * kTpGroup));
@@ -672,7 +674,14 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     auto key_below = [&](int bins) {   // the largest key that lies below so many bins from the maximum on
       return uniform_i(min(kmax, max(kLowestKey, key_of(__float_as_uint(xmax - 0.125f * (float)max(1, bins) / c) >> 16))));
     };
-    cut_key = key_below(kBins - skip);
+    // Where few tokens hold the mass, the sample may miss the very ones that decide, and knows nothing of it; a cut that is too
+    // high costs the row its counts over windows and its batch the wait (at sigma 3, T 0.7, top_p 0.8 one row in twenty).  In a batch
+    // of kSeveralRows the cut lies below the bins that should have kListAtLeast tokens together, in fours: 30 x 152064 57 -> 29 us, 250 x
+    // 65536 32.5 -> 19.0, 1500 x 20481 52 -> 41.  The longer list costs a batch that would have been lucky up to a tenth (30 x
+    // 65536 17.2 -> 18.8), which is why the few rows that mostly are have none of it.
+    const int few = a.rows >= kSeveralRows ? (int)((float)kListAtLeast * (float)sampled / (float)(ngroups * kTpGroup)) : -1;
+    const int enough = 4 * (int)__popcll(__builtin_amdgcn_ballot_w64(sampled - counted_to <= few));
+    cut_key = key_below(max(kBins - skip, enough));
     likely_key = key_below(kBins - unlikely);
     // The list starts at the cut, or where its counts still span it if the threshold is likely to lie above that
     // (short rows give a vague estimate, whose cut may be zero or negative), and is not begun if the
@@ -684,7 +693,11 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) listed += (float)(kBins - 4 * lane - e) <= bins_listed ? count[e] : 0;   // (whole bins)
     listed = from_lane(wave_inclusive_scan(listed), 63);
-    const bool fits = (float)listed * (float)(most_groups * kTpGroup) <= (float)kListCap * (float)sampled;
+    // (An overflow costs a row alone on a CU its whole list pass, and its batch with it: such a list keeps room for what
+    // the waves and the sample deviate, or 68 x 156368 at sigma 2, T 1.3, top_p 0.9 takes 69 us, not 57.  Among rows that share a CU
+    // it is hidden, and counting instead costs more: 700 x 152064 at sigma 3, T 1.3, top_p 0.84 122 us, 86 with some in vain.)
+    constexpr float kListRoom = kListCap > kListCapShared ? 0.95f * kListCap : kListCap;
+    const bool fits = (float)listed * (float)(most_groups * kTpGroup) <= kListRoom * (float)sampled;
     if (lkey >= 0x8080 && likely_key >= lkey && fits) {   // workgroup-uniform: a positive, normal cut
       const int cut = lkey - 0x8000;           // its bits
       const float cut_f = uniform_f(value_of_key(lkey));

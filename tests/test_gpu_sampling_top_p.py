@@ -255,3 +255,14 @@ def test_rows_that_start_anywhere(V, first):
     for other in ((want_tok, want_lp), tuple(np.concatenate(v) for v in zip(*few))):
         assert (other[0] != tok).sum() <= 1     # (a uniform number at an interval's edge)
         assert np.abs(other[1] - got)[other[0] == tok].max() <= 1e-5
+
+
+@pytest.mark.parametrize("rows,V,sigma,T,top_p", [
+    (15, 20481, 3.0, 0.7, 0.8), (16, 20481, 3.0, 0.7, 0.8), (40, 65536, 3.0, 0.7, 0.8), (40, 2048, 4.0, 0.6, 0.8),
+    (16, 152064, 6.0, 0.5, 0.5), (300, 4096, 3.0, 0.7, 0.8), (17, 152064, 2.0, 1.3, 0.9), (17, 152064, 2.0, 1.3, 0.92)])
+def test_rows_whose_estimate_may_fail(rows, V, sigma, T, top_p):
+    """Rows whose mass a handful of tokens hold, which a sample easily misses (from 16 rows on the cut is lowered for it), and rows
+    whose list may just overflow."""
+    print("case: top-p estimate", rows, V, sigma, T, top_p, flush=True)
+    lp = I.build_logprob_inputs(rows, V, sigma, V + rows, temperature=T)
+    check(lp.logits, np.random.default_rng(rows).random(rows), T, top_p)
