@@ -332,7 +332,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // at the barriers between the phases.  (16 waves a row: 3 % faster up to 128 rows, half as fast from 512 on.  Two stores per four
 // tokens, selected and placed by lane counts, instead of four: 40 us.)
 // Three workgroups per CU leave 80 vector registers: two are spilled (12 bytes of scratch per lane), outside the passes,
-// and 46 scalar registers to lanes of vector registers, which the counts over windows read back.
+// and 48 scalar registers (68 where positions are skewed) to lanes of vector registers, which the counts over windows read back.
 // ---------------------------------------------------------------------------------------
 constexpr int kTpThreads = 512;
 constexpr int kTpWaves = kTpThreads / 64;

@@ -191,6 +191,26 @@ def test_prompt_scatter_is_bit_exact_and_feeds_attention():
     assert excess.max() <= 0
 
 
+@pytest.mark.parametrize("heads,chunk,ctx", [
+    ((16, 1), [1], [0]), ((8, 2), [1, 2000, 3, 0, 17], [4000, 5, 15, 100, 31]), ((4, 4), [16, 16, 15, 17], [0, 8, 1, 15]),
+    ((8, 2), [3000] + [1] * 40, [7] + [63] * 40), ((8, 2), [0, 0, 33], [16, 0, 8000])])
+def test_scatter_of_uneven_chunks(heads, chunk, ctx):
+    """Chunks much longer than the mean (a workgroup takes several columns), and such as touch few columns of a wide table,
+    whole and in part."""
+    print("case: scatter", heads, chunk[:5], ctx[:5], flush=True)
+    inp = I.build_prefill_inputs(*heads, chunk, ctx, seed=3)
+    dev = inp.to("cuda")
+    shape, _, _ = B.prepare_prefill(dev, B.MARL_OUT_F32)
+    flags = torch.zeros(1, dtype=torch.int32, device="cuda")
+    B.marl_kv_write_prompt(shape, dev.k_new, dev.v_new, dev.k_pages, dev.v_pages, dev.prefix_block_table, dev.q_start, dev.q_pos0, flags)
+    torch.cuda.synchronize()
+    assert int(flags.item()) == 0
+    kp, vp = R.kv_write_prompt(I.bf16_bits(inp.k_pages), I.bf16_bits(inp.v_pages), inp.prefix_block_table.numpy(),
+                               inp.q_start.numpy(), inp.q_pos0.numpy(), I.bf16_bits(inp.k_new), I.bf16_bits(inp.v_new))
+    np.testing.assert_array_equal(I.bf16_bits(dev.k_pages.cpu()), kp)
+    np.testing.assert_array_equal(I.bf16_bits(dev.v_pages.cpu()), vp)
+
+
 def test_scatter_flags_tokens_it_cannot_place():
     from dataclasses import replace
     inp = I.build_prefill_inputs(8, 2, [20, 30], [0, 0], seed=10, poison=False)
