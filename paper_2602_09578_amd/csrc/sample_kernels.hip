@@ -48,6 +48,26 @@ __device__ __forceinline__ u32x4 load8_words(const uint16_t* x, long pos, long e
   return v;
 }
 
+// Where a row ends, in two steps, so that loads stay in flight together: the 8 logits at x[pos .. pos+8) or, if the row ends before,
+// its last 8 (end >= 8), and when they are used the shift that puts them in their places and -inf behind them.  (Element by element,
+// in branches, the loads of a last chunk wait for each other, and most rows have one: 13 x 4099 6.74 -> 5.84 us, 250 x 32000 7.96 -> 6.98, 13 x
+// 152064 9.3 -> 7.7, 2410 x 20481 33.5 -> 30.7.  The top-p kernel has no registers left for it: 2 to 7 % slower with it where it counts
+// whole rows.)
+__device__ __forceinline__ u32x4 load8_clamped(const uint16_t* x, long pos, long end) {
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(x + min(pos, end - 8)));
+}
+__device__ __forceinline__ u32x4 end_in_place(u32x4 v, long pos, long end) {
+  const int s = (int)min(max(pos - (end - 8), 0l), 8l);   // logits of v that belong to the lanes before
+  constexpr unsigned long long kNone = 0xff80ff80ff80ff80ull;
+  unsigned long long lo = v[0] | (unsigned long long)v[1] << 32, hi = v[2] | (unsigned long long)v[3] << 32;
+  if (s & 4) { lo = hi; hi = kNone; }
+  const int r = (s & 3) * 16;
+  lo = lo >> r | hi << (63 - r) << 1;
+  hi = hi >> r | kNone << (63 - r) << 1;
+  if (s == 8) lo = hi = kNone;
+  return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
 template <class T>
 __device__ __forceinline__ T wave_allreduce_sum(T v) { return wave_allreduce(v, [](T x, T y) { return x + y; }); }
 __device__ __forceinline__ float wave_max(float v) { return wave_allreduce(v, [](float x, float y) { return fmaxf(x, y); }); }
@@ -64,10 +84,24 @@ __device__ __forceinline__ double from_lane(double v, int l) {
   return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
 }
 
-// The logits of a chunk, as a wave holds them.
+// The logits of a chunk, as a wave holds them; requested, and as they are used.
 __device__ __forceinline__ void fetch_chunk(const uint16_t* x, long base, int lane, long vocab, u32x4 (&w)[kIters]) {
+  if (base + kChunk <= vocab) {   // wave-uniform
 #pragma unroll
-  for (int it = 0; it < kIters; ++it) w[it] = load8_words(x, base + it * 512 + lane * 8, vocab);
+    for (int it = 0; it < kIters; ++it) w[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(x + base + it * 512 + lane * 8));
+  } else if (vocab >= 8) {
+#pragma unroll
+    for (int it = 0; it < kIters; ++it) w[it] = load8_clamped(x, base + it * 512 + lane * 8, vocab);
+  } else {
+#pragma unroll
+    for (int it = 0; it < kIters; ++it) w[it] = load8_words(x, base + it * 512 + lane * 8, vocab);
+  }
+}
+__device__ __forceinline__ void end_chunk(long base, int lane, long vocab, u32x4 (&w)[kIters]) {
+  if (base + kChunk <= vocab || vocab < 8) return;   // wave-uniform
+#pragma unroll
+  for (int it = 0; it < kIters; ++it)
+    if (base + (it + 1) * 512 > vocab) w[it] = end_in_place(w[it], base + it * 512 + lane * 8, vocab);
 }
 // (max, sum of 2^(y - max)) of a chunk.  Per lane a running (largest raw logit, sum relative to it), 16 logits at
 // a time as they arrive: with the wave's maximum first, all of a batch's waves waited for whole chunks and then
@@ -113,6 +147,7 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
     if (chunk >= a.num_chunks) break;
     const bool more = k + 1 < a.chunks_per_wave && chunk + 4 < a.num_chunks;   // wave-uniform
     if (more) fetch_chunk(x, (long)(chunk + 4) * kChunk, lane, a.vocab, nxt);
+    end_chunk((long)chunk * kChunk, lane, a.vocab, cur);
     const float2 v = chunk_sum(cur, a.inv_temp_log2e);
     if (lane == 0) a.partials[(size_t)row * a.num_chunks + chunk] = v;
     if (more) {
@@ -178,8 +213,8 @@ __device__ __forceinline__ void pick_token(const SampleArgs& a, const float2* pa
   const float want = take_last ? INFINITY : (float)(target - before);
   const long cbase = (long)chunk * kChunk + lane * 8;
   u32x4 words[kIters];
-#pragma unroll
-  for (int it = 0; it < kIters; ++it) words[it] = load8_words(x, cbase + it * 512, a.vocab);
+  fetch_chunk(x, (long)chunk * kChunk, lane, a.vocab, words);
+  end_chunk((long)chunk * kChunk, lane, a.vocab, words);
   // the weights 2^(y - M) of 8 logits, the same each time they are formed
   const float ms = M == -INFINITY ? 0.f : M;
   auto weights = [&](u32x4 v, float (&w)[8]) {
@@ -277,6 +312,7 @@ __device__ __forceinline__ void sample_rows(const SampleArgs& a) {
     } else {
       fetch_chunk(x, (long)chunk * kChunk, lane, a.vocab, cur);
     }
+    end_chunk((long)chunk * kChunk, lane, a.vocab, cur);
     const float2 v = chunk_sum(cur, a.inv_temp_log2e);
     if (lane == 0) part[chunk] = v;
     if constexpr (kAhead) {

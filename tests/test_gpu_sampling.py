@@ -123,3 +123,25 @@ def test_only_possible_tokens_are_drawn(vocab):
         p, cdf = ref.softmax_cdf(bits[r], 1.0)
         u[r] = min(float(np.float32(rng.choice(cdf[p > 0]))), 1.0 - 2.0 ** -24)
     check(I.LogprobInputs(logits, torch.zeros(rows, dtype=torch.int32), 1.0), u)
+
+
+@pytest.mark.parametrize("vocab", [7, 8, 9, 11, 14, 509, 513, 4090, 4095, 4097, 4103, 7680, 8197, 20482, 36871])
+@pytest.mark.parametrize("rows", [3, 600])
+def test_row_ends_anywhere_in_a_chunk(vocab, rows):
+    """A row gives what it gives with -inf behind it up to whole chunks, bit for bit: what stands in memory behind (and before) it is
+    not drawn or counted.  Uniform numbers near 1 draw from the last tokens."""
+    print("case: row end", rows, vocab, flush=True)
+    lp = I.build_logprob_inputs(rows, vocab, 3.0, vocab, temperature=1.0)
+    buf = torch.full((rows * vocab + 16,), 3.0e38, dtype=torch.bfloat16)
+    buf[8:8 + rows * vocab] = lp.logits.flatten()
+    x = buf.cuda()[8:8 + rows * vocab].view(rows, vocab)
+    whole = torch.full((rows, (vocab + 4095) // 4096 * 4096), -torch.inf, dtype=torch.bfloat16)
+    whole[:, :vocab] = lp.logits
+    u = 1.0 - np.random.default_rng(vocab).random(rows) ** 8
+    u[0] = np.nextafter(np.float32(1.0), np.float32(0.0))
+    got = run(I.LogprobInputs(x, torch.zeros(rows, dtype=torch.int32).cuda(), 1.0), u)
+    want = run(I.LogprobInputs(whole.cuda(), torch.zeros(rows, dtype=torch.int32).cuda(), 1.0), u)
+    assert (got[0] < vocab).all()
+    np.testing.assert_array_equal(got[0], want[0])
+    np.testing.assert_array_equal(got[1], want[1])
+    check(I.LogprobInputs(lp.logits[:3], torch.zeros(3, dtype=torch.int32), 1.0), u[:3])
