@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64) void sample_pick_kernel(SampleArgs a) {
 // Whole rows: a workgroup of up to 16 waves sums a row's chunks into LDS and its first wave draws the token, so
 // there is one launch, and the chunk sums do not go through memory.  Chunks and sums are those of divided rows, bit for
 // bit: which token is drawn does not depend on the size of the batch.  What bounds it: the vector ALU of the row's CU (7 issue
-// slots of 4 cycles per logit) and the read together (256 x 152064: 78 MB in 19.8 us), and at a row's end 3 us of dependent
+// slots of 4 cycles per logit) and the read together (256 x 152064: 78 MB in 18.9 us), and at a row's end 3 us of dependent
 // steps.  (Chunks of 2048 take 17.1 us, but draw another token now and then, where the uniform number falls into an
 // interval of the size of the sums' rounding.)
 constexpr int kRowMaxWaves = 16;
@@ -351,14 +351,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 //      below the maximum, the counts are taken of the whole row instead, over windows of 8192 values: first
 //      the one that starts at the cut, if the threshold is likely to lie in it, with the mass of what is
 //      above it, then from the maximum down.  (Nuclei of half of a long row or more, rows of negative
-//      logits.  64 x 152064, sigma 2, top_p 0.95: 48 us at T 1, with the list, and 60 at T 1.3, without;
+//      logits.  64 x 152064, sigma 2, top_p 0.95: 47 us at T 1, with the list, and 60 at T 1.3, without;
 //      2048 x 152064, top_p 0.9: 200 us, and 304 with 40 subtracted from every logit, which changes nothing else.)
 //   3. per group the nucleus mass and the number of threshold-value tokens (from the list, else one
 //      more pass over the row); a scan over the group sums finds the group in which the scaled
 //      uniform is passed, a workgroup scan over the group's 2048 tokens finds the token.
-// What bounds it, 2048 x 152064, sigma 3, top_p 0.9 (197 us): both reads and the vector ALU, neither of them alone.  The rows are
-// fetched twice (1255 MB, 6.3 TB/s: three rows per CU are 234 MB, too many for the L2s), and the vector ALU issues in 76 %
-// of the CUs' time: 17.5 issue slots of 4 cycles per logit over all passes, of which the first has 7
+// What bounds it, 2048 x 152064, sigma 3, top_p 0.9 (196 us): both reads and the vector ALU, neither of them alone.  The rows are
+// fetched twice (1255 MB, 6.4 TB/s: three rows per CU are 234 MB, too many for the L2s), and the vector ALU issues in 76 %
+// of the CUs' time: 17.1 issue slots of 4 cycles per logit over all passes, of which the first has 7
 // and the copy into the list 3.5.  (Rows that the L2s hold take 148 us, and the fetches alone would take 180.)  Two workgroups
 // per CU 212; with the row held in registers by one workgroup per CU, a count of all values in
 // LDS (an LDS atomic on 64 lanes takes about 25 cycles) and a third pass over all tokens 508 us; the
@@ -1070,22 +1070,22 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
 }
 
 // Waves of a workgroup that takes a row whole, 0 where rows are divided between workgroups and a second launch draws.
-// Rows of up to 7 chunks (8 up to 512 rows) are taken whole at any number: the second launch is much of the call (1 to 1024 rows
-// x 4096: 7.6 us divided, 5.6 whole; 600 x 24576: 12.9 and 11.7; 256 x 32000 10.1 and 8.0).  Longer rows are divided where the
-// last round of them over the 256 CUs of an MI355X would leave too many CUs idle (64 x 152064: 10.8 us divided, 16.5 whole;
-// 300: 23.8 and 30.2; 600 x 32003: 16.2 and 17.4; 1599 x 152064: 92.8 and 96.0), and whole where they fill it but for a
-// few per cent (256 x 152064: 21.0 and 19.8, 512 37.6 and 34.2, 2048 114 and 108).  Rows that are not aligned to 16 bytes need
+// Rows of up to 7 chunks (8 up to 512 rows) are taken whole at any number: the second launch is much of the call (30 rows x
+// 20481: 7.5 us divided, 6.8 whole; 64 x 32000 7.4 and 6.5; 300 x 32000 10.1 and 9.1).  Longer rows are divided where the
+// last round of them over the 256 CUs of an MI355X would leave too many CUs idle (64 x 152064: 10.8 us divided, 16.5 whole, 300: 24.0 and
+// 27.3; 100 x 65536 8.2 and 8.3), and whole where they fill it but for a few per cent (256 x 152064: 21.2 and 18.9, 512
+// 35.5 and 30.3, 2048 112.5 and 107.1).  Rows that are not aligned to 16 bytes need
 // more requests, which few waves on a CU wait longer for: they have to fill it all but exactly, and three rounds of them are
-// never as fast (496 x 140001: 33.9 and 35.3, 1000: 61.2 and 66.4, 768: 50.7 and 54.3; 1024 x 40001: 33.3 and 24.1).  As many
-// waves as there are chunks, or as a CU has room for (256 x 152064: 8 take 21.1); fewer of more rows, whose ends
-// then overlap (2048 x 32000: 8 waves 34.8, 4 27.9; 768 x 40001: 25.0 and 20.2).  Over 973 sizes, most of them at the edges
-// of this rule, the mean is 4 % above divided rows; 7 lose 5 to 9 %.
+// never as fast (496 x 140001: 33.2 and 35.7, 1000: 61.1 and 64.9, 768: 49.4 and 52.2; 1024 x 40001: 33.5 and 23.4).  As many
+// waves as there are chunks, or as a CU has room for (256 x 152064: 8 take 19.1, 4 22.1); fewer of more rows, whose ends
+// then overlap (512 x 152064: 8 waves 32.0, 4 30.3, 512 x 100000 24.3 and 21.9; 2048 x 32000 31.8 and 27.2; 768 x 40001 25.4 and 19.4).
+// Over 973 sizes, most of them at the edges of this rule, the mean was 4 % above divided rows; 7 lost 5 to 9 %.
 static int sample_row_waves(int rows, int chunks, bool aligned) {
   const int rounds = (rows + 255) / 256;
   if (chunks < 8 || (chunks == 8 && rows <= 512)) return std::min(chunks, rows <= 512 ? 8 : 4);
   const long least = rounds > 4 ? 90 : aligned ? 93 : 99;   // per cent of the CUs' rounds
   if (chunks > kRowMaxChunks || 100l * rows < least * 256l * rounds || (!aligned && rounds == 3)) return 0;
-  return rounds == 1 ? kRowMaxWaves : rounds == 2 ? 8 : 4;
+  return rounds == 1 ? kRowMaxWaves : 4;
 }
 
 hipError_t launch_sample(const SampleArgs& a, hipStream_t st) {
