@@ -585,7 +585,8 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, First&& firs
   // value unit 2 * (16 * ct + i) + (j & 1) with its lowest bit XOR-ed: one address for all ct
   const int v_rd = 2 * kBlockTok * kD + (j >> 1) * 4096 + (((2 * i + (j & 1)) ^ ((i >> 2) & 1)) << 4);
 
-  constexpr float kPfMaxWeight = 256.0f, kPfFirstLeast = 0x1p-16f;
+  constexpr float kPfRescaleSlack = 8.0f, kPfMaxWeight = 256.0f;   // log2 units; the same as a weight
+  constexpr float kLowest = -3.402823466e38f;   // the reference of a row that has seen no key (finite: its weights are exp2(-inf) = 0)
   // One step of 32 keys: all score products, then per tile the exponentials and that tile's output products.
   //   The reference maximum of a row moves only when its weights grow past kPfMaxWeight.  With an
   // exact running maximum one of a wave's 48 rows sets a new record in most steps of a long prompt; with
@@ -594,11 +595,13 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, First&& firs
   // weights, which is formed anyway (no weight exceeds a sum that passes; the eight scores'
   // maximum cost six instructions per tile), and only a step that fails looks for maxima and takes
   // its exponentials again.
-  //   kFirst: the item's first step, seen in full by every row.  The reference is 0 where that gives every lane weights between
-  // kPfFirstLeast and kPfMaxWeight (else the rows' maxima, as above), and the accumulators start with this step's
-  // products: 270 vector instructions per item and wave for a first pass that always failed, rescaled zeros, and the zeros.
-  //   kEdge: the causal edge of some row crosses the step, or a tile has no rows; a row that has seen no key keeps
-  // the reference -FLT_MAX, with weights exp2(-inf) = 0.
+  //   kFirst: the item's first step, seen in full by every row.  The rows' maxima come before the only pass, and the
+  // accumulators start with this step's products.  The reference has to be the exact maximum here: the weights are rounded to
+  // bf16 for the products while their sum is not, and a key that holds much of a row's mass mostly lies in the first step (an
+  // attention sink); as the maximum its weight is 1, without rounding.  (With reference 0 where no weight grows too large, half a
+  // row's mass on such a key: 1.6e-3 from 64 bits instead of 1.5e-4, 200 to 500 keys.)
+  //   kEdge: the causal edge of some row crosses the step, or a tile has no rows; only rows whose maximum exceeds their
+  // reference by more than the slack move it.
   enum { kFull, kFirst, kEdge };
   auto compute = [&](const char* buf, auto kind_tag, const int n, const int tok_end, const int (&limit)[kMT]) {
     constexpr int kind = decltype(kind_tag)::value;
@@ -648,8 +651,12 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, First&& firs
 #pragma unroll
     for (int qt = 0; qt < kMT; ++qt) {
       if (kind == kEdge && t0 >= tile_hi[qt]) continue;
-      if (kind == kFirst) m_run[qt] = 0.f;
       float p[8], psum;
+      auto row_max = [&] {
+        const float mx = fmaxf(fmaxf(fmaxf(s0[qt][0], s0[qt][1]), fmaxf(s0[qt][2], s0[qt][3])),
+                               fmaxf(fmaxf(s1[qt][0], s1[qt][1]), fmaxf(s1[qt][2], s1[qt][3])));   // this lane's 8 tokens
+        return rows_allreduce_max(mx * sc);
+      };
       auto weights = [&] {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -658,18 +665,15 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, First&& firs
         }
         psum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
       };
+      if (kind == kFirst) m_run[qt] = fmaxf(kLowest, row_max());
       weights();
-      if (__builtin_amdgcn_ballot_w64(psum > kPfMaxWeight || (kind == kFirst && psum < kPfFirstLeast)) != 0) {   // wave-uniform
-        const float mx = fmaxf(fmaxf(fmaxf(s0[qt][0], s0[qt][1]), fmaxf(s0[qt][2], s0[qt][3])),
-                               fmaxf(fmaxf(s1[qt][0], s1[qt][1]), fmaxf(s1[qt][2], s1[qt][3]))) * sc;   // this lane's 8 tokens
-        const float row_mx = rows_allreduce_max(mx), m_new = fmaxf(kind == kFirst ? -3.402823466e38f : m_run[qt], row_mx);
-        if (kind != kFirst) {
-          const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);   // 1 where the row did not move
-          l_run[qt] *= alpha;
+      if (kind != kFirst && __builtin_amdgcn_ballot_w64(psum > kPfMaxWeight) != 0) {   // wave-uniform
+        const float mx = row_max(), m_old = m_run[qt];
+        m_run[qt] = kind == kEdge ? (mx > m_old + kPfRescaleSlack ? mx : m_old) : fmaxf(m_old, mx);
+        const float alpha = __builtin_amdgcn_exp2f(m_old - m_run[qt]);   // 1 where the row did not move
+        l_run[qt] *= alpha;
 #pragma unroll
-          for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
-        }
-        m_run[qt] = m_new;
+        for (int ct = 0; ct < 8; ++ct) acc[qt][ct] *= alpha;
         weights();
       }
       l_run[qt] = kind == kFirst ? psum : l_run[qt] + psum;
@@ -741,7 +745,7 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, First&& firs
     } else {
 #pragma unroll
       for (int qt = 0; qt < kMT; ++qt) {
-        m_run[qt] = -3.402823466e38f;   // (finite: a row that sees no key of a part keeps it)
+        m_run[qt] = kLowest;
         l_run[qt] = 0.f;
 #pragma unroll
         for (int ct = 0; ct < 8; ++ct) acc[qt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};

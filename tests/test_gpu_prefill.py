@@ -91,9 +91,8 @@ def test_peaked_flat_and_sign_flipped_scores(scale):
 @pytest.mark.parametrize("first,later", [(-3.0, -3.0), (-3.0, 3.0), (3.0, -3.0), (-0.8, -0.8)])
 @pytest.mark.parametrize("chunks,context", [([3, 20, 200], [0, 31, 0]), ([40, 1], [300, 64])])
 def test_scores_far_from_the_first_reference(first, later, chunks, context):
-    """A row's first reference maximum is 0 where that gives weights within bounds: keys that put every score at about -200
-    (weights of exactly 0) or -50 in base 2, or the first page at -200 and the others at +200, and the other way round; items that begin
-    with a whole step and items that begin on the causal edge."""
+    """Keys that put every score at about -200 or -50 in base 2, or the first page at -200 and the others at +200, and the
+    other way round; items that begin with a whole step and items that begin on the causal edge."""
     print("case: prefill scores far from 0", first, later, chunks, context, flush=True)
     inp = I.build_prefill_inputs(28, 4, chunks, context, seed=31)
     inp.q += 4
@@ -101,6 +100,33 @@ def test_scores_far_from_the_first_reference(first, later, chunks, context):
     inp.k_pages[inp.prefix_block_table[:, 0].long()] += first - later
     check(inp)
     check(inp, B.MARL_OUT_BF16)
+
+
+@pytest.mark.parametrize("share", [0.5, 0.8])
+@pytest.mark.parametrize("Hq,Hkv,chunks,context", [(28, 4, [200, 330], [0, 300]), (4, 4, [700], [0]), (16, 1, [40], [900])])
+def test_a_key_that_holds_much_of_a_row_costs_no_rounding(share, Hq, Hkv, chunks, context):
+    """An attention sink: about `share` of every row's mass sits on the prompt's first key.  As the reference maximum its weight
+    is exactly 1 in bf16; the other n keys hold 1 - share between them, their weights each rounded by at most 2^-8 of
+    itself (2^-8 / sqrt(3) in the root mean square): together (1 - share) / sqrt(n) of that, times sqrt(e) for the spread of
+    their weights, whose scores are N(0, 1).  Relative to a row that is share of one value, over rows of at least n = 64 keys:
+    2^-8 / sqrt(3) * (1 - share) / share * sqrt(e / 64) = 4.6e-4 for half; a rounded weight of the sink itself would add about
+    1.2e-3 whatever n is.  Scores lie about 1 for the sink, where neither their size nor their sign makes the rows move."""
+    print("case: prefill sink", share, Hq, Hkv, chunks, context, flush=True)
+    inp = I.build_prefill_inputs(Hq, Hkv, chunks, context, seed=17)
+    inp.q.mul_(0.25).add_(1.0)                                  # |q|^2 = 136: scores against N(0, 1) keys are N(0, 1.06)
+    sums = inp.q.float().sum(-1).mean().item() * inp.scale      # of a key of ones
+    keys = np.array(chunks) + np.array(context) / 2
+    for g, pages in enumerate(inp.prefix_block_table):
+        used = pages[pages >= 0].long()
+        inp.k_pages[used] += float((0.5 - np.log(keys[g] * share / (1 - share))) / sums)
+        inp.k_pages[int(pages[0]), :, 0, :] = 1.0 / sums
+    want, _ = reference(inp)
+    got = run_gpu(inp, B.MARL_OUT_F32)
+    pos = np.concatenate([np.arange(n) + p0 for n, p0 in zip(chunks, context)])
+    rows = pos >= 64
+    rel = np.sqrt(((got - want)[rows] ** 2).sum() / (want[rows] ** 2).sum())
+    print("relative error", rel, flush=True)
+    assert rel <= 2.0 ** -8 / 3 ** 0.5 * (1 - share) / share * np.sqrt(np.e / 64)
 
 
 def test_many_small_groups_and_more_than_one_plan_round():
