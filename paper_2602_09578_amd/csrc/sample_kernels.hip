@@ -368,14 +368,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // at the barriers between the phases.  (16 waves a row: 3 % faster up to 128 rows, half as fast from 512 on.  Two stores per four
 // tokens, selected and placed by lane counts, instead of four: 40 us.)
 // Three workgroups per CU leave 80 vector registers: two are spilled (12 bytes of scratch per lane), outside the passes,
-// and 48 scalar registers (68 where positions are skewed) to lanes of vector registers, which the counts over windows read back.
+// and 48 scalar registers (60 where odd rows are shifted) to lanes of vector registers, which the counts over windows read back.
 // ---------------------------------------------------------------------------------------
 constexpr int kTpThreads = 512;
 constexpr int kTpWaves = kTpThreads / 64;
 constexpr int kWin = 8192;                   // values per window of the count without the list
 constexpr int kTpGroup = 2048;               // tokens of a group: 4 x 512, one wave
 constexpr int kLowestKey = 0x0080;           // key of the most negative finite bf16; below: -inf, NaN
-constexpr int kTpMaxVocab = 1 << 23;         // its 4096 groups' sums fit the LDS buffer
 constexpr int kScanStep = 4;                 // scan positions per thread and round of the threshold search
 constexpr int kListGroups = 20;              // groups per wave that the list covers (vocab <= 327680)
 constexpr int kListAtLeast = 128, kSeveralRows = 16;   // tokens it has at least in batches of so many rows
@@ -552,56 +551,62 @@ __device__ __forceinline__ void append_words(uint32_t& at, u32x4 v, int cut, flo
 #undef MARL_APPEND_WORD
 }
 
-template <int kListCap, bool kSkewed>
+// The 32 tokens of a thread where the group was read from the element before it, which starts a dword: every token moves down by half
+// a dword, and a lane's last one comes from the lane behind it, the last lane's from `next` (the dword of the group's last token).
+__device__ __forceinline__ void shift_down(u32x4 (&v)[4], uint32_t next) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t behind = j < 3 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)v[j + 1][0]) : next;
+    const uint32_t above = (uint32_t)__builtin_amdgcn_update_dpp((int)behind, (int)v[j][0], 0x130, 0xf, 0xf, false);   // wave_shl:1
+#pragma unroll
+    for (int d = 0; d < 4; ++d) v[j][d] = __builtin_amdgcn_alignbit(d < 3 ? v[j][d + 1] : above, v[j][d], 16);
+  }
+}
+
+template <int kListCap, bool kOdd>
 __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
   __shared__ TpShared<kListCap> sh;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row = blockIdx.x;
-  // kSkewed: positions count from the 16-byte boundary at or before the row (rows of an odd vocabulary start anywhere), so that
-  // loads are aligned: position p is token p - skew, those before `skew` and from V on are no tokens.
-  const uint16_t* const row_begin = a.logits + (size_t)row * a.vocab;
-  const int skew = kSkewed ? (int)(reinterpret_cast<uintptr_t>(row_begin) & 15) / 2 : 0;
-  const uint16_t* x = row_begin - skew;   // (never read before row_begin)
+  const uint16_t* x = a.logits + (size_t)row * a.vocab;
   const float c = a.inv_temp_log2e;
-  const long V = (long)a.vocab + skew;
+  const long V = a.vocab;
   const int ngroups = (int)((V + kTpGroup - 1) / kTpGroup);
   const float u = a.uniforms[row];   // (requested early: used after the passes)
   const int my_groups = wave < ngroups ? (ngroups - wave + kTpWaves - 1) / kTpWaves : 0;   // of this wave
+  // kOdd: rows that start in the middle of a dword.  Their 16-byte loads would take up to twice the requests (from dwords on, all
+  // are alike): whole groups are read from the element before them and shifted into place.  Which thread has which token does not
+  // depend on where a row starts: what it draws is a function of the row.
+  const bool odd_row = kOdd && (reinterpret_cast<uintptr_t>(x) & 2) != 0;
+  auto shifted = [&](int g) { return kOdd && odd_row && g > 0 && (long)(g + 1) * kTpGroup < V; };   // (never read outside the row)
   // One pass over this wave's groups in order, the next group's loads in flight:
   // fn(group, this thread's 4 x 8 tokens of it); positions past the end of the row read as -inf.
   auto sweep = [&](auto&& fn, auto backwards_tag) {
     constexpr bool kBack = decltype(backwards_tag)::value;
-    auto fetch = [&](int g, u32x4 (&v)[4]) {
+    uint32_t cur_next = 0, nxt_next = 0;
+    auto fetch = [&](int g, u32x4 (&v)[4], uint32_t& next) {
       const long base = (long)g * kTpGroup;
-      if (base + kTpGroup <= V && (!kSkewed || g > 0)) {   // wave-uniform
+      if (base + kTpGroup <= V) {   // wave-uniform
+        const uint16_t* from = x + base - (shifted(g) ? 1 : 0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const u32x4_any*>(x + base + j * 512 + lane * 8);
+        for (int j = 0; j < 4; ++j) v[j] = *reinterpret_cast<const u32x4_any*>(from + j * 512 + lane * 8);
+        if (shifted(g)) next = (uint32_t)ld_uniform(reinterpret_cast<const int32_t*>(from + kTpGroup));
       } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const long pos = base + j * 512 + lane * 8;
-          if (!kSkewed || pos >= skew) {
-            v[j] = load8_words(x, pos, V);
-          } else {   // the row's first lane
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              const uint32_t lo = 2 * d >= skew && 2 * d < V ? x[2 * d] : 0xff80u;
-              const uint32_t hi = 2 * d + 1 >= skew && 2 * d + 1 < V ? x[2 * d + 1] : 0xff80u;
-              v[j][d] = lo | (hi << 16);
-            }
-          }
-        }
+        for (int j = 0; j < 4; ++j) v[j] = load8_words(x, base + j * 512 + lane * 8, V);
       }
     };
     u32x4 cur[4], nxt[4];
     auto group_at = [&](int k) { return wave + kTpWaves * (kBack ? my_groups - 1 - k : k); };
-    if (my_groups > 0) fetch(group_at(0), cur);
+    if (my_groups > 0) fetch(group_at(0), cur, cur_next);
     for (int k = 0; k < my_groups; ++k) {
-      if (k + 1 < my_groups) fetch(group_at(k + 1), nxt);
+      if (k + 1 < my_groups) fetch(group_at(k + 1), nxt, nxt_next);
+      if (shifted(group_at(k))) shift_down(cur, cur_next);
       fn(group_at(k), cur);
 #pragma unroll
       for (int j = 0; j < 4; ++j) cur[j] = nxt[j];
+      cur_next = nxt_next;
     }
   };
   const std::false_type forwards{};
@@ -980,9 +985,9 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     float r[4];
     uint32_t raw[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) raw[e] = x[kSkewed ? max(min(pos + e, V - 1), (long)skew) : min(pos + e, V - 1)];
+    for (int e = 0; e < 4; ++e) raw[e] = x[min(pos + e, V - 1)];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = (!kSkewed || pos + e >= skew) && pos + e < V ? __uint_as_float(raw[e] << 16) : -INFINITY;
+    for (int e = 0; e < 4; ++e) r[e] = pos + e < V ? __uint_as_float(raw[e] << 16) : -INFINITY;
     int n4 = 0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) n4 += r[e] == thr_x;
@@ -1027,7 +1032,7 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
       float r_pick = r[0];
 #pragma unroll
       for (int e = 1; e < 4; ++e) if (e == e_pick) r_pick = r[e];
-      a.out_tokens[row] = (int)(pos + e_pick) - skew;
+      a.out_tokens[row] = (int)(pos + e_pick);
       a.out_logprobs[row] = logprob_of(r_pick, c, M, Z);
     }
   }
@@ -1036,19 +1041,17 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
 __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
 void sample_top_p_kernel(TopPArgs a) { sample_top_p<kListCapShared, false>(a); }
 __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
-void sample_top_p_skewed_kernel(TopPArgs a) { sample_top_p<kListCapShared, true>(a); }
+void sample_top_p_odd_kernel(TopPArgs a) { sample_top_p<kListCapShared, true>(a); }
 __global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void sample_top_p_alone_kernel(TopPArgs a) { sample_top_p<kListCapAlone, false>(a); }
-__global__ __launch_bounds__(kTpThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void sample_top_p_alone_skewed_kernel(TopPArgs a) { sample_top_p<kListCapAlone, true>(a); }
 
 }  // namespace
 
 int sample_num_chunks(int vocab) { return (vocab + kChunk - 1) / kChunk; }
 
-int top_p_max_vocab() { return kTpMaxVocab; }
+int top_p_max_vocab() { return 1 << 23; }   // its 4096 groups' sums fit the LDS buffer
 
-constexpr int kTpAloneVocab = 49152, kTpSkewedVocab = 28672;
+constexpr int kTpAloneVocab = 49152;
 
 hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
@@ -1056,15 +1059,12 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   // wider nuclei are found without counting whole rows (256 x 152064, top_p 0.95: sigma 3 at T 1.3 56.2 -> 46.0 us, sigma 2 56.5 ->
   // 50.8; 1 row 49.6 -> 40.7).  In shorter rows the smaller list takes as much as is ever worth it, and three rows a
   // CU are no slower alone (32003: 19.4 and 19.7 us).
-  // Rows that start off 16-byte boundaries: their loads take up to twice the requests, unless positions are counted from the
-  // boundary before, which costs the row's first group a slower load and some address arithmetic (2000 rows, unskewed / skewed:
-  // 128001 208 and 176 us, 100003 168 and 148, 32003 68.1 and 66.0, 20481 54.0 and 58.2; 64 rows 31.4 and 30.1, 27.7 and 26.3,
-  // 17.4 and 15.9; one row 27.7 and 28.2; aligned rows 2 % slower).
+  // Odd rows (of an odd vocabulary every second one): shifted into place from dwords, or loaded where they start, us: 2000 rows of
+  // 152067 201 and 247, 128001 171 and 207, 100003 141 and 168, 32003 64.3 and 67.7; 64 of 32003 16.1 and 17.3.  Rows
+  // alone on a CU wait for their vector ALU, which the shift adds to: 64 of 128001 32.4 and 31.4, 152067 35.3 and 35.2.
   const bool alone = a.rows <= 256 && a.vocab > kTpAloneVocab;
-  const bool aligned = a.vocab % 8 == 0 && reinterpret_cast<uintptr_t>(a.logits) % 16 == 0;
-  const bool skewed = !aligned && a.rows >= 8 && a.vocab >= kTpSkewedVocab && a.vocab <= kTpMaxVocab - 8;   // (no more groups than there is room for)
-  const auto kernel = alone ? skewed ? sample_top_p_alone_skewed_kernel : sample_top_p_alone_kernel
-                            : skewed ? sample_top_p_skewed_kernel : sample_top_p_kernel;
+  const bool odd = a.vocab % 2 != 0 || reinterpret_cast<uintptr_t>(a.logits) % 4 != 0;
+  const auto kernel = alone ? sample_top_p_alone_kernel : odd ? sample_top_p_odd_kernel : sample_top_p_kernel;
   hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
   return hipGetLastError();
 }

@@ -237,7 +237,7 @@ def test_rows_that_start_anywhere(V, first):
     """Rows at every distance from a 16-byte boundary, the first one in the middle of a buffer whose other elements must not be
     drawn or counted: the token before a row and the one behind it are the largest values there are.  Tokens at
     both ends of a row are drawn too."""
-    print("case: top-p skewed rows", V, first, flush=True)
+    print("case: top-p row starts", V, first, flush=True)
     rows = 9
     lp = I.build_logprob_inputs(rows, V, 2.5, V + first, temperature=0.9)
     x = lp.logits.clone()
@@ -251,10 +251,55 @@ def test_rows_that_start_anywhere(V, first):
     want_tok, want_lp = run_rows(x.cuda(), u, 0.9, 0.9)
     tok, got = run_rows(on_gpu, u, 0.9, 0.9)
     assert tok[:4].tolist() == [0, V - 1, 1, V - 2]
-    few = [run_rows(on_gpu[k:k + 1], u[k:k + 1], 0.9, 0.9) for k in range(rows)]   # (short batches: not skewed)
-    for other in ((want_tok, want_lp), tuple(np.concatenate(v) for v in zip(*few))):
-        assert (other[0] != tok).sum() <= 1     # (a uniform number at an interval's edge)
-        assert np.abs(other[1] - got)[other[0] == tok].max() <= 1e-5
+    for k in range(rows):                       # every row at a start of its own
+        alone = x[k:k + 1].cuda()
+        one_tok, one_lp = run_rows(alone, u[k:k + 1], 0.9, 0.9)
+        assert one_tok[0] == tok[k] and one_lp[0] == got[k]
+    np.testing.assert_array_equal(tok, want_tok)
+    np.testing.assert_array_equal(got, want_lp)
+
+
+def edge_uniforms(bits, T, top_p, n, rng):
+    """Uniform numbers at the float32 next to n edges of the row's CDF inside its nucleus, where the last bits of the sums decide."""
+    p, _ = ref.softmax_cdf(bits, T)
+    keep = ref.nucleus(p, float(np.float32(top_p)))
+    cdf = np.cumsum(np.where(keep, p, 0.0))
+    return np.clip(cdf[rng.choice(np.nonzero(keep)[0], n)] / cdf[-1], 0.0, 1.0 - 2.0 ** -24)
+
+
+def same_in_every_batch(V, sigma, T, top_p, rows, sizes):
+    """One row `rows` times, with uniform numbers at its CDF's edges: token and log-probability of each are the same bits in
+    batches of the given sizes, whatever the copy's alignment."""
+    lp = I.build_logprob_inputs(1, V, sigma, V + 1, temperature=T)
+    u = edge_uniforms(I.bf16_bits(lp.logits)[0], T, top_p, rows, np.random.default_rng(V))
+    x = lp.logits.cuda().expand(rows, V).contiguous()
+    want = run_rows(x, u, T, top_p)
+    for n in sizes:
+        for a in (0, rows - n):
+            got = run_rows(x[a:a + n], u[a:a + n], T, top_p)
+            np.testing.assert_array_equal(got[0], want[0][a:a + n])
+            np.testing.assert_array_equal(got[1], want[1][a:a + n])
+    by_token = {}
+    for t, l in zip(*want):
+        assert by_token.setdefault(int(t), l) == l
+
+
+@pytest.mark.parametrize("V,sigma,T,top_p", [(32003, 2.0, 1.0, 0.95), (28673, 3.0, 1.0, 0.9), (4099, 2.0, 1.0, 0.95), (34816, 2.0, 1.0, 0.9)])
+def test_a_row_is_the_same_at_every_alignment(V, sigma, T, top_p):
+    """Copies of a row in a batch start at every distance from a 16-byte boundary, or all at an odd element."""
+    print("case: top-p alignments", V, flush=True)
+    if V % 2:
+        same_in_every_batch(V, sigma, T, top_p, 40, [1, 7, 8, 33])
+    lp = I.build_logprob_inputs(1, V, sigma, V, temperature=T)
+    u = edge_uniforms(I.bf16_bits(lp.logits)[0], T, top_p, 100, np.random.default_rng(V))
+    want = None
+    for first in range(8):
+        buf = torch.full((first + 100 * V + 8,), 3.0e38, dtype=torch.bfloat16, device="cuda")
+        buf[first:first + 100 * V].view(100, V).copy_(lp.logits.cuda().expand(100, V))
+        got = run_rows(buf[first:first + 100 * V].view(100, V), u, T, top_p)
+        want = want or got
+        np.testing.assert_array_equal(got[0], want[0])
+        np.testing.assert_array_equal(got[1], want[1])
 
 
 @pytest.mark.parametrize("rows,V,sigma,T,top_p", [
