@@ -377,7 +377,6 @@ constexpr int kTpGroup = 2048;               // tokens of a group: 4 x 512, one 
 constexpr int kLowestKey = 0x0080;           // key of the most negative finite bf16; below: -inf, NaN
 constexpr int kScanStep = 4;                 // scan positions per thread and round of the threshold search
 constexpr int kListGroups = 20;              // groups per wave that the list covers (vocab <= 327680)
-constexpr int kListAtLeast = 128, kSeveralRows = 16;   // tokens it has at least in batches of so many rows
 constexpr int kListWin = 2048;               // values the list may span
 constexpr int kBins = 256;                   // bins of the tail estimate, an eighth of a power of two each
 constexpr int kSampleWords = 10;             // words per thread that the estimate looks at
@@ -687,8 +686,13 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
   const double tau = (double)a.top_p * Z;
   if (a.top_p < 1.f && ngroups <= kListGroups * kTpWaves) {
     // the cut: the largest bin boundary below which the sample promises at most 1 - top_p: its sum (every
-    // token at the upper edge of its bin) plus three standard deviations of it
+    // token at the upper edge of its bin) plus three standard deviations of it.  Where few tokens hold the mass, the sample may
+    // have missed the very ones that decide, and its variance knows nothing of them: kUnseen tokens at the boundary are added to
+    // that.  (Without them, sigma 3, T 0.7, top_p 0.8, two to four rows in a hundred have too high a cut, sigma 4 at T 0.6 one in
+    // four, and their counts over windows keep the whole batch: 30 x 152064 57.6 us, with them 28.9, 250 x 65536 32.6 and 18.1, 1500 x 20481 51.6
+    // and 39.9.  In 16000 simulated rows of 4096 to 152064 tokens none; the list is 0 to 3 % longer where it has more than 500 tokens.)
     // (every wave computes it for itself; the bins were complete before the scan's barriers)
+    constexpr float kUnseen = 3.f;
     int count[4];        // lane 0: the lightest bins, from kBins - 1 down
     float mass[4], square[4];
 #pragma unroll
@@ -699,8 +703,7 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
       mass[e] = (float)count[e] * w;
       square[e] = mass[e] * w;
     }
-    const int counted_to = wave_inclusive_scan((count[0] + count[1]) + (count[2] + count[3]));
-    const int sampled = from_lane(counted_to, 63);
+    const int sampled = from_lane(wave_inclusive_scan((count[0] + count[1]) + (count[2] + count[3])), 63);
     const float mine_m = (mass[0] + mass[1]) + (mass[2] + mass[3]), mine_s = (square[0] + square[1]) + (square[2] + square[3]);
     float tail = wave_inclusive_scan(mine_m) - mine_m, var = fmaxf(wave_inclusive_scan(mine_s) - mine_s, 0.f);
     const float allowed = (float)((1.0 - (double)a.top_p) * Z * (double)sampled / ((double)ngroups * kTpGroup));
@@ -709,20 +712,14 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     for (int e = 0; e < 4; ++e) {
       tail += mass[e];
       var += square[e];
-      skip += (int)__popcll(__builtin_amdgcn_ballot_w64(tail + 3.f * __builtin_sqrtf(var) <= allowed));
+      const float w = ex2(-0.125f * (float)(kBins - 1 - 4 * lane - e));
+      skip += (int)__popcll(__builtin_amdgcn_ballot_w64(tail + 3.f * __builtin_sqrtf(__builtin_fmaf(kUnseen * w, w, var)) <= allowed));
       unlikely += (int)__popcll(__builtin_amdgcn_ballot_w64(tail <= allowed));
     }
     auto key_below = [&](int bins) {   // the largest key that lies below so many bins from the maximum on
       return uniform_i(min(kmax, max(kLowestKey, key_of(__float_as_uint(xmax - 0.125f * (float)max(1, bins) / c) >> 16))));
     };
-    // Where few tokens hold the mass, the sample may miss the very ones that decide, and knows nothing of it; a cut that is too
-    // high costs the row its counts over windows and its batch the wait (at sigma 3, T 0.7, top_p 0.8 one row in twenty).  In a batch
-    // of kSeveralRows the cut lies below the bins that should have kListAtLeast tokens together, in fours: 30 x 152064 57 -> 29 us, 250 x
-    // 65536 32.5 -> 19.0, 1500 x 20481 52 -> 41.  The longer list costs a batch that would have been lucky up to a tenth (30 x
-    // 65536 17.2 -> 18.8), which is why the few rows that mostly are have none of it.
-    const int few = a.rows >= kSeveralRows ? (int)((float)kListAtLeast * (float)sampled / (float)(ngroups * kTpGroup)) : -1;
-    const int enough = 4 * (int)__popcll(__builtin_amdgcn_ballot_w64(sampled - counted_to <= few));
-    cut_key = key_below(max(kBins - skip, enough));
+    cut_key = key_below(kBins - skip);
     likely_key = key_below(kBins - unlikely);
     // The list starts at the cut, or where its counts still span it if the threshold is likely to lie above that
     // (short rows give a vague estimate, whose cut may be zero or negative), and is not begun if the

@@ -306,8 +306,15 @@ def test_a_row_is_the_same_at_every_alignment(V, sigma, T, top_p):
     (15, 20481, 3.0, 0.7, 0.8), (16, 20481, 3.0, 0.7, 0.8), (40, 65536, 3.0, 0.7, 0.8), (40, 2048, 4.0, 0.6, 0.8),
     (16, 152064, 6.0, 0.5, 0.5), (300, 4096, 3.0, 0.7, 0.8), (17, 152064, 2.0, 1.3, 0.9), (17, 152064, 2.0, 1.3, 0.92)])
 def test_rows_whose_estimate_may_fail(rows, V, sigma, T, top_p):
-    """Rows whose mass a handful of tokens hold, which a sample easily misses (from 16 rows on the cut is lowered for it), and rows
-    whose list may just overflow."""
+    """Rows whose mass a handful of tokens hold, which a sample easily misses, and rows whose list may just overflow."""
     print("case: top-p estimate", rows, V, sigma, T, top_p, flush=True)
     lp = I.build_logprob_inputs(rows, V, sigma, V + rows, temperature=T)
     check(lp.logits, np.random.default_rng(rows).random(rows), T, top_p)
+
+
+@pytest.mark.parametrize("V,sigma,T,top_p", [
+    (20481, 3.0, 0.7, 0.8), (4096, 3.0, 0.7, 0.8), (32000, 2.0, 1.0, 0.95), (65536, 3.0, 0.7, 0.8), (20480, 4.0, 0.6, 0.8)])
+def test_a_row_is_the_same_in_few_rows_and_in_many(V, sigma, T, top_p):
+    """The cut, and with it what the list holds, follows from the row."""
+    print("case: top-p batches", V, sigma, T, top_p, flush=True)
+    same_in_every_batch(V, sigma, T, top_p, 60, [1, 7, 8, 15, 16, 17])
