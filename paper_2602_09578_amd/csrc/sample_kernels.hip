@@ -351,10 +351,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 //      below the maximum, the counts are taken of the whole row instead, over windows of 8192 values: first
 //      the one that starts at the cut, if the threshold is likely to lie in it, with the mass of what is
 //      above it, then from the maximum down.  (Nuclei of half of a long row or more, rows of negative
-//      logits.  64 x 152064, sigma 2, top_p 0.95: 47 us at T 1, with the list, and 60 at T 1.3, without;
+//      logits.  64 x 152064, sigma 2, top_p 0.95: 49 us at T 1, with the list, and 60 at T 1.3, without;
 //      2048 x 152064, top_p 0.9: 200 us, and 304 with 40 subtracted from every logit, which changes nothing else.)
-//   3. per group the nucleus mass and the number of threshold-value tokens (from the list, else one
-//      more pass over the row); a scan over the group sums finds the group in which the scaled
+//   3. per group the nucleus mass and the number of threshold-value tokens (from the list, if a third of a CU has room
+//      for it, else one more pass over the row); a scan over the group sums finds the group in which the scaled
 //      uniform is passed, a workgroup scan over the group's 2048 tokens finds the token.
 // What bounds it, 2048 x 152064, sigma 3, top_p 0.9 (196 us): both reads and the vector ALU, neither of them alone.  The rows are
 // fetched twice (1255 MB, 6.4 TB/s: three rows per CU are 234 MB, too many for the L2s), and the vector ALU issues in 76 %
@@ -390,7 +390,9 @@ __device__ __forceinline__ float value_of_key(int key) {
   return __uint_as_float(bits << 16);
 }
 
-template <int kListCap>   // list entries per wave
+constexpr int kListCapShared = 2624, kListCapAlone = 9216;   // list entries per wave: three rows on a CU, and one
+static_assert((kListWin & (kScanStep - 1)) == 0, "the list spans whole threads of the threshold search");
+template <int kListCap>
 struct TpShared {
   union {
     uint32_t hist[kWin];                       // counts of pass 2 without the list; group sums of pass 3
@@ -408,7 +410,7 @@ struct TpShared {
   float wave_f[kTpWaves];
   float wave_m[kTpWaves];
   int wave_i[kTpWaves];
-  int list_full;
+  int list_full, list_long;     // a wave's list has no room; had none in kListCapShared
   int found_at;                 // smallest scan position / thread index that meets a condition
   int thr_key, thr_cnt;         // threshold value (key) and how many tokens have it
   double thr_above;             // mass strictly above the threshold value
@@ -416,7 +418,6 @@ struct TpShared {
   float want_in_group;          // nucleus mass still to pass inside the chosen group
   int out_tok;
 };
-constexpr int kListCapShared = 2624, kListCapAlone = 9216;
 static_assert(sizeof(TpShared<kListCapShared>) <= 42 * 1280, "three workgroups share a CU's 160 KB");
 static_assert(sizeof(TpShared<kListCapAlone>) <= 160 * 1024, "a workgroup has a CU's LDS");
 
@@ -652,7 +653,7 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
   float xmax = wave_max(xrun);
   if (lane == 0) sh.wave_m[wave] = xmax;
   if (tid < kBins) sh.bins[tid] = 0;
-  if (tid == 0) { sh.thr_key = -1; sh.thr_cnt = 0; sh.thr_above = 0.0; sh.found_at = kWin; sh.list_full = 0; }
+  if (tid == 0) { sh.thr_key = -1; sh.thr_cnt = 0; sh.thr_above = 0.0; sh.found_at = kWin; sh.list_full = sh.list_long = 0; }
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kTpWaves; ++w) xmax = fmaxf(xmax, sh.wave_m[w]);
@@ -681,7 +682,11 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
 
   // ---- pass 2: the threshold value --------------------------------------------------------
   // thr_key = -1: every token with a finite logit is in the nucleus
-  bool from_list = false;
+  // What is drawn is a function of the row, whatever the list has room for.  From the list or from a window that starts at the
+  // maximum, the threshold is found by the same sums, so a row whose list would begin never tries another window before that
+  // one.  The groups' masses are rounded otherwise in a list than in the row: they are taken from lists that
+  // kListCapShared has room for, in every instance (`short_list`).
+  bool from_list = false, short_list = true;
   int cut_key = 0, likely_key = 0;   // where the estimate puts the threshold at the lowest, and where it puts it
   const double tau = (double)a.top_p * Z;
   if (a.top_p < 1.f && ngroups <= kListGroups * kTpWaves) {
@@ -724,7 +729,8 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     // The list starts at the cut, or where its counts still span it if the threshold is likely to lie above that
     // (short rows give a vague estimate, whose cut may be zero or negative), and is not begun if the
     // sample has more tokens above than a wave's list takes.
-    const int lkey = max(cut_key, kmax - (kListWin - 1));
+    // (Whole threads of the threshold search: the last one's sum has the values that it has in a window.)
+    const int lkey = kmax - ((kmax - max(cut_key, kmax - (kListWin - 1))) | (kScanStep - 1));
     const int span = kmax - lkey + 1;
     const float bins_listed = 8.f * c * (xmax - value_of_key(lkey));
     int listed = 0;
@@ -737,6 +743,7 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     constexpr float kListRoom = kListCap > kListCapShared ? 0.95f * kListCap : kListCap;
     const bool fits = (float)listed * (float)(most_groups * kTpGroup) <= kListRoom * (float)sampled;
     if (lkey >= 0x8080 && likely_key >= lkey && fits) {   // workgroup-uniform: a positive, normal cut
+      if (kListCap > kListCapShared) short_list = (float)listed * (float)(most_groups * kTpGroup) <= (float)kListCapShared * (float)sampled;
       const int cut = lkey - 0x8000;           // its bits
       const float cut_f = uniform_f(value_of_key(lkey));
       // (the list takes the sample's place: it was read before the barriers of the sum)
@@ -772,7 +779,9 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
       }, backwards);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the stores of append_words
       if (full && lane == 0) sh.list_full = 1;
+      if (kListCap > kListCapShared && n > kListCapShared && lane == 0) sh.list_long = 1;
       __syncthreads();
+      if (kListCap > kListCapShared) short_list = short_list && !sh.list_long;
       if (!sh.list_full) {   // workgroup-uniform
         constexpr int kAtOnce = 8;
         for (int p = lane; p < n; p += 64 * kAtOnce) {
@@ -819,7 +828,8 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
       __syncthreads();
     };
     bool found = false;
-    if (cut_key > kLowestKey && cut_key + kWin <= kmax && likely_key < cut_key + kWin) {
+    const int list_from = kmax - (kListWin - 1);   // where the list of such a wide span would begin
+    if (cut_key > kLowestKey && cut_key + kWin <= kmax && likely_key < cut_key + kWin && (list_from < 0x8080 || likely_key < list_from)) {
       const int hi = cut_key + kWin - 1;
       double mine = 0.0, above;
       count_window(hi, cut_key, value_of_key(hi + 1), mine);
@@ -857,7 +867,7 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
   // per group: mass of the tokens above the threshold, number of tokens at it
   float* part_m = reinterpret_cast<float*>(sh.hist);             // [ngroups]
   int* part_n = reinterpret_cast<int*>(sh.hist) + kWin / 2;      // [ngroups]
-  if (from_list) {
+  if (from_list && short_list) {
     part_m = sh.group_mass;
     part_n = sh.group_ties;
     // A power of two lanes per group, 4 to 64, so that most of the wave has a share of a group: 16, 8, 4, 2 groups at once or one,
@@ -1053,8 +1063,9 @@ constexpr int kTpAloneVocab = 49152;
 hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
   // Where every row has a CU of an MI355X for itself, its list may take all of the LDS: half of a row of 152064 fits, not a seventh, and
-  // wider nuclei are found without counting whole rows (256 x 152064, top_p 0.95: sigma 3 at T 1.3 56.2 -> 46.0 us, sigma 2 56.5 ->
-  // 50.8; 1 row 49.6 -> 40.7).  In shorter rows the smaller list takes as much as is ever worth it, and three rows a
+  // wider nuclei are found without counting whole rows (256 x 152064, top_p 0.95: sigma 3 at T 1.3 56.5 -> 50.9 us, sigma 2 56.8 ->
+  // 53.0; 1 row 49.9 -> 44.8; 46.1, 50.9 and 40.5 if their groups' masses, too, came from such lists, but then what they draw
+  // at the edge of an interval would depend on the number of rows).  In shorter rows the smaller list takes as much as is ever worth it, and three rows a
   // CU are no slower alone (32003: 19.4 and 19.7 us).
   // Odd rows (of an odd vocabulary every second one): shifted into place from dwords, or loaded where they start, us: 2000 rows of
   // 152067 201 and 247, 128001 171 and 207, 100003 141 and 168, 32003 64.3 and 67.7; 64 of 32003 16.1 and 17.3.  Rows

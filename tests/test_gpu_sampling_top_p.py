@@ -318,3 +318,12 @@ def test_a_row_is_the_same_in_few_rows_and_in_many(V, sigma, T, top_p):
     """The cut, and with it what the list holds, follows from the row."""
     print("case: top-p batches", V, sigma, T, top_p, flush=True)
     same_in_every_batch(V, sigma, T, top_p, 60, [1, 7, 8, 15, 16, 17])
+
+
+@pytest.mark.parametrize("V,sigma,T,top_p", [
+    (49160, 2.0, 1.0, 0.95), (65536, 3.0, 1.3, 0.95), (152064, 3.0, 1.0, 0.95), (152064, 3.0, 1.3, 0.95), (152064, 2.0, 1.0, 0.9),
+    (100003, 2.0, 1.0, 0.95), (156368, 2.0, 1.3, 0.9), (152064, 2.0, 1.3, 0.95), (65536, 1.0, 1.0, 0.99)])
+def test_a_row_is_the_same_alone_on_a_cu_and_beside_others(V, sigma, T, top_p):
+    """Lists that a third of a CU's LDS has room for, lists that only all of it has room for, and none of them."""
+    print("case: top-p alone or not", V, sigma, T, top_p, flush=True)
+    same_in_every_batch(V, sigma, T, top_p, 300, [1, 64, 256, 257])
