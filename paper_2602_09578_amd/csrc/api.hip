@@ -734,7 +734,7 @@ int marl_kv_write_prompt(const marl_prefill_shape* shape, const void* k_new, con
   if (!k_new || !v_new || !k_pages || !v_pages || !prefix_block_table || !q_start || !q_pos0)
     return MARL_INVALID_ARG;
   if (shape->max_prefix_pages < 1) return MARL_INVALID_ARG;
-  // one workgroup per (group, KV head, table column)
+  // at most one workgroup per (group, KV head, table column)
   if ((long)shape->num_groups * shape->num_kv_heads * shape->max_prefix_pages >= (1L << 31)) return MARL_UNSUPPORTED;
   // keys are copied, and whole value pages stored, as 16-byte vectors
   if (!aligned16(k_new) || !aligned16(k_pages) || !aligned16(v_pages)) return MARL_INVALID_ARG;

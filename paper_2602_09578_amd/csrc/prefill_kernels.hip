@@ -937,67 +937,130 @@ void prefill_small_kernel(PrefillArgs a) {
     prefill_items<false, true>(a, [&] { return item_of<false>(a, block, item - block * a.Hkv, g, packed); }, 0, 0, lds, bad_page);
 }
 
-// Scatter of a prompt chunk's keys and values into the group's pages.  `cols` workgroups of 128 threads per (group, KV
-// head) take every so many-th of the columns of the group's table row that its chunk touches.  The key rows of a page are contiguous
+// Scatter of a prompt chunk's keys and values into the group's pages: column `col` of group g's table row, whose chunk brings n
+// tokens from q row b on to position pos0, for one KV head and 128 threads.  The key rows of a page are contiguous
 // (4 KB): 16-byte copies.  Values are stored channel-major, so thread c collects channel c of the page's 16 tokens and writes
 // its 32 bytes with two stores when the chunk covers the whole page, else slot by slot.
 // What bounds it: memory (256 prompts, 1.36 GB read and written: 274 us, 5 TB/s), a short call its launch and three dependent reads.
-__global__ __launch_bounds__(kD) void kv_write_prompt_kernel(PrefillArgs a, int cols) {
-  const int first = blockIdx.x % cols;
-  const int gk = blockIdx.x / cols;
-  const int g = gk / a.Hkv, kvh = gk % a.Hkv;
+__device__ __forceinline__ void write_prompt_page(const PrefillArgs& a, const int g, const int b, const int n, const int pos0,
+                                                  const int kvh, const int col) {
   const int c = threadIdx.x;
-  int flag = 0;
-  const int n = group_tokens(a, g, flag);
-  const int pos0 = a.q_pos0[g];
-  if (first == 0 && kvh == 0 && c == 0 && flag && a.flags) atomicOr(a.flags, flag);
-  if (flag & MARL_FLAG_BAD_GROUP) return;
-  if (n == 0) return;
-  const int last = (int)((unsigned)(pos0 + n - 1) / kPage);
-#pragma unroll 1
-  for (int col = (int)((unsigned)pos0 / kPage) + first; col <= last; col += cols) {
-    const int lo = max(pos0, col * kPage), hi = min(pos0 + n, (col + 1) * kPage);   // positions to write
-    const int page = a.prefix_table[(size_t)g * a.max_pp + col];
-    if ((unsigned)page >= (unsigned)a.num_pages) {
-      if (kvh == 0 && c == 0 && a.flags) atomicOr(a.flags, MARL_FLAG_BAD_PAGE);
-      continue;
-    }
-    const size_t blk = ((size_t)page * a.Hkv + kvh) * (kPage * kD);                 // elements
-    const size_t tok0 = (size_t)a.q_start[g] + (col * kPage - pos0);                // token of slot 0 (may be "negative")
-    const size_t row_stride = (size_t)a.Hkv * kD;
-    // keys: 16 slots x 16 chunks of 16 bytes, two per thread
+  const int lo = max(pos0, col * kPage), hi = min(pos0 + n, (col + 1) * kPage);   // positions to write
+  const int page = a.prefix_table[(size_t)g * a.max_pp + col];
+  if ((unsigned)page >= (unsigned)a.num_pages) {
+    if (kvh == 0 && c == 0 && a.flags) atomicOr(a.flags, MARL_FLAG_BAD_PAGE);
+    return;
+  }
+  const size_t blk = ((size_t)page * a.Hkv + kvh) * (kPage * kD);                 // elements
+  const size_t tok0 = (size_t)b + (col * kPage - pos0);                           // token of slot 0 (may be "negative")
+  const size_t row_stride = (size_t)a.Hkv * kD;
+  // keys: 16 slots x 16 chunks of 16 bytes, two per thread
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int v = c + k * kD;
-      const int slot = v >> 4, chunk = v & 15;
-      const int pos = col * kPage + slot;
-      if (pos >= lo && pos < hi)
-        *reinterpret_cast<u32x4*>(a.k_pages_w + blk + (size_t)slot * kD + chunk * 8) =
-            *reinterpret_cast<const u32x4*>(a.k_new + (tok0 + slot) * row_stride + (size_t)kvh * kD + chunk * 8);
+  for (int k = 0; k < 2; ++k) {
+    const int v = c + k * kD;
+    const int slot = v >> 4, chunk = v & 15;
+    const int pos = col * kPage + slot;
+    if (pos >= lo && pos < hi)
+      *reinterpret_cast<u32x4*>(a.k_pages_w + blk + (size_t)slot * kD + chunk * 8) =
+          *reinterpret_cast<const u32x4*>(a.k_new + (tok0 + slot) * row_stride + (size_t)kvh * kD + chunk * 8);
+  }
+  // values: channel c of every slot
+  uint16_t vals[kPage];
+#pragma unroll
+  for (int slot = 0; slot < kPage; ++slot) {
+    const int pos = col * kPage + slot;
+    vals[slot] = (pos >= lo && pos < hi) ? a.v_new[(tok0 + slot) * row_stride + (size_t)kvh * kD + c] : (uint16_t)0;
+  }
+  uint16_t* vdst = a.v_pages_w + blk + (size_t)c * kPage;
+  if (hi - lo == kPage) {
+    u32x4 w0, w1;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      w0[d] = (uint32_t)vals[2 * d] | ((uint32_t)vals[2 * d + 1] << 16);
+      w1[d] = (uint32_t)vals[8 + 2 * d] | ((uint32_t)vals[8 + 2 * d + 1] << 16);
     }
-    // values: channel c of every slot
-    uint16_t vals[kPage];
+    *reinterpret_cast<u32x4*>(vdst) = w0;
+    *reinterpret_cast<u32x4*>(vdst + 8) = w1;
+  } else {
 #pragma unroll
     for (int slot = 0; slot < kPage; ++slot) {
       const int pos = col * kPage + slot;
-      vals[slot] = (pos >= lo && pos < hi) ? a.v_new[(tok0 + slot) * row_stride + (size_t)kvh * kD + c] : (uint16_t)0;
+      if (pos >= lo && pos < hi) vdst[slot] = vals[slot];
     }
-    uint16_t* vdst = a.v_pages_w + blk + (size_t)c * kPage;
-    if (hi - lo == kPage) {
-      u32x4 w0, w1;
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        w0[d] = (uint32_t)vals[2 * d] | ((uint32_t)vals[2 * d + 1] << 16);
-        w1[d] = (uint32_t)vals[8 + 2 * d] | ((uint32_t)vals[8 + 2 * d + 1] << 16);
-      }
-      *reinterpret_cast<u32x4*>(vdst) = w0;
-      *reinterpret_cast<u32x4*>(vdst + 8) = w1;
-    } else {
-#pragma unroll
-      for (int slot = 0; slot < kPage; ++slot) {
-        const int pos = col * kPage + slot;
-        if (pos >= lo && pos < hi) vdst[slot] = vals[slot];
-      }
+  }
+}
+
+// `cols` workgroups per (group, KV head): one for every column of the tables, or else for every so many-th of those that the chunk
+// touches, from the first on.
+template <bool kAll>
+__global__ __launch_bounds__(kD) void kv_write_prompt_kernel(PrefillArgs a, int cols) {
+  const int at = blockIdx.x % cols;
+  const int gk = blockIdx.x / cols;
+  const int g = gk / a.Hkv, kvh = gk % a.Hkv;
+  int flag = 0;
+  const int n = group_tokens(a, g, flag);
+  const int pos0 = a.q_pos0[g];
+  if (at == 0 && kvh == 0 && threadIdx.x == 0 && flag && a.flags) atomicOr(a.flags, flag);
+  if (n == 0) return;
+  const int first = (int)((unsigned)pos0 / kPage), last = (int)((unsigned)(pos0 + n - 1) / kPage);
+  if (kAll) {
+    if (at >= first && at <= last) write_prompt_page(a, g, a.q_start[g], n, pos0, kvh, at);
+  } else {
+#pragma unroll 1
+    for (int col = first + at; col <= last; col += cols) write_prompt_page(a, g, a.q_start[g], n, pos0, kvh, col);
+  }
+}
+
+// Where the chunks touch few of the columns: a workgroup for every page that they may touch together, and KV head.  A group whose
+// tokens begin at row b has the places from b / 16 + 2 g on: n tokens touch at most n / 16 + 2 pages, so that groups that share
+// no rows share no place, and the last place lies before NT / 16 + 2 NG, which the host knows.  Which group a place belongs to
+// the workgroup finds by itself: it looks at all of them (0.1 us for 64, 0.4 for 500), and so writes every group's pages
+// whatever the order of q_start.
+constexpr int kScatterGroups = 1024;
+__global__ __launch_bounds__(kD) void kv_write_prompt_pages_kernel(PrefillArgs a) {
+  extern __shared__ int4 chunk_of[];                     // [NG] first row, tokens, position, first column less its place
+  __shared__ unsigned long long here[kScatterGroups / 64];
+  const int place = blockIdx.x / a.Hkv, kvh = blockIdx.x % a.Hkv;
+  const int c = threadIdx.x, lane = c & 63;
+  int flag = 0;
+  // the group's first row, tokens, position and first column less its place; whether this workgroup's place is one of its pages
+  auto chunk = [&](int g, int4& h) {
+    h = make_int4(0, 0, 0, 0);
+    if (g >= a.NG) return false;
+    const int n = group_tokens(a, g, flag), b = a.q_start[g], pos0 = a.q_pos0[g];
+    const int first = (int)((unsigned)pos0 / kPage), shift = first - (int)((unsigned)b / kPage + 2u * (unsigned)g);
+    h = make_int4(b, n, pos0, shift);
+    return n > 0 && place + shift >= first && place + shift <= (int)((unsigned)(pos0 + n - 1) / kPage);
+  };
+  if (a.NG <= 64) {                                      // a wave sees them all: no LDS, no barrier
+    int4 h;
+    const bool mine = chunk(lane, h);
+    if (blockIdx.x == 0 && c < 64 && flag && a.flags) atomicOr(a.flags, flag);
+    for (unsigned long long m = __builtin_amdgcn_ballot_w64(mine); m != 0; m &= m - 1) {   // (one group, unless groups share rows)
+      const int g = __builtin_ctzll(m);
+      write_prompt_page(a, g, __builtin_amdgcn_readlane(h.x, g), __builtin_amdgcn_readlane(h.y, g),
+                        __builtin_amdgcn_readlane(h.z, g), kvh, place + __builtin_amdgcn_readlane(h.w, g));
+    }
+    return;
+  }
+  for (int g0 = 0; g0 < a.NG; g0 += kD) {                // workgroup-uniform
+    const int g = g0 + c;
+    int4 h;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(chunk(g, h));
+    if (g < a.NG) chunk_of[g] = h;
+    if (lane == 0) here[g >> 6] = m;
+  }
+  if (blockIdx.x == 0 && flag && a.flags) atomicOr(a.flags, flag);
+  __syncthreads();
+  for (int w = 0; w < (a.NG + 63) / 64; ++w) {           // workgroup-uniform
+    unsigned long long m = here[w];
+    m = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(m >> 32)) << 32 |
+        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)m);
+    for (; m != 0; m &= m - 1) {
+      const int g = 64 * w + __builtin_ctzll(m);
+      const int4 h = chunk_of[g];
+      write_prompt_page(a, g, __builtin_amdgcn_readfirstlane(h.x), __builtin_amdgcn_readfirstlane(h.y),
+                        __builtin_amdgcn_readfirstlane(h.z), kvh, place + __builtin_amdgcn_readfirstlane(h.w));
     }
   }
 }
@@ -1049,14 +1112,25 @@ hipError_t launch_prefill(const PrefillArgs& a, int grid, hipStream_t st) {
 
 hipError_t launch_kv_write_prompt(const PrefillArgs& a, hipStream_t st) {
   if (a.NT == 0 || a.NG == 0) return hipSuccess;
-  // How long a chunk is the host does not know, only what there is together and how wide the tables are: twice the mean of the
-  // chunks' pages, a longer one's workgroups go round.  (A workgroup for every column of the tables, most of them empty where
-  // chunks are short and their context long, against this: six chunks of up to 512 tokens behind up to 8192, 64 / 8 heads, 13.7 and 7.1
-  // us; 41 of up to 152 behind up to 7528, 28 / 4, 28.3 and 9.7; 200 single tokens behind up to 4000, 8 / 2, 33.3 and 4.6; 64 of
-  // very different length, 16 / 1, 11.2 and 10.3; without context within 0.5 %, with little of it within 2.)
-  const long pages = (a.NT + (long)a.NG * kPage - 1) / ((long)a.NG * kPage);   // of a chunk in the mean
-  const int cols = (int)std::min<long>(a.max_pp, 2 * pages + 2);
-  hipLaunchKernelGGL(kv_write_prompt_kernel, dim3((unsigned)a.NG * a.Hkv * cols), dim3(kD), 0, st, a, cols);
+  // How long a chunk is the host does not know, only what there is together and how wide the tables are.
+  //   1. Every column that a chunk may touch has a workgroup where that leaves few without work (0.3 us a thousand), or where
+  // memory hides them: 256 chunks of up to 1500, 64 / 8 heads, 364 us, by places 400; 900 of up to 600 behind up to 300 556 and 931.
+  //   2. Twice the mean of the chunks' columns, and a longer chunk's workgroups go round (1.1 us each time), where the longest that there
+  // can be takes less than an eighth of what the call needs for its bytes: 400 of up to 1000 behind up to 3000, 64 / 8, 402 us by
+  // columns, 397 by rounds, 426 by places.
+  //   3. Else the places: one chunk of 8192 tokens and 31 of one, 16 / 1 heads, 8.9 us by columns, 23 by rounds, 4.2 by places,
+  // 64 / 8 54, 38 and 12; one of 300 and 40 of one, 28 / 4, 4.9, 10.2 and 4.9; 200 single tokens behind up to 4000, 64 / 8, 126, 10 and 6.8; six of up to 512 behind up to 8192,
+  // 64 / 8, 14.7, 8.2 and 7.3.  (Groups without end would cost each workgroup more than the rounds do.)
+  const long all = std::min<long>(a.max_pp, a.NT / kPage + 2);       // columns that a chunk may touch
+  const long places = a.NT / kPage + 2l * a.NG;
+  const long mean = (a.NT + (long)a.NG * kPage - 1) / ((long)a.NG * kPage);
+  const bool few_empty = a.NG * all * a.Hkv <= 2048 || a.NG * all <= (places * a.Hkv >= 8192 ? 4 : 2) * places;
+  long cols = few_empty ? all : std::min(all, 2 * mean + 2);
+  const bool short_rounds = (all + cols - 1) / cols * (8 * 1100) <= places * a.Hkv * 3;   // ns; 16 KB at 5 TB/s a place and head
+  if (few_empty || short_rounds || a.NG > kScatterGroups)
+    hipLaunchKernelGGL(cols == a.max_pp ? kv_write_prompt_kernel<true> : kv_write_prompt_kernel<false>, dim3((unsigned)(a.NG * a.Hkv * cols)), dim3(kD), 0, st, a, (int)cols);
+  else
+    hipLaunchKernelGGL(kv_write_prompt_pages_kernel, dim3((unsigned)(places * a.Hkv)), dim3(kD), a.NG <= 64 ? 0 : sizeof(int4) * a.NG, st, a);
   return hipGetLastError();
 }
 

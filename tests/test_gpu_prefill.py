@@ -217,24 +217,43 @@ def test_prompt_scatter_is_bit_exact_and_feeds_attention():
     assert excess.max() <= 0
 
 
-@pytest.mark.parametrize("heads,chunk,ctx", [
-    ((16, 1), [1], [0]), ((8, 2), [1, 2000, 3, 0, 17], [4000, 5, 15, 100, 31]), ((4, 4), [16, 16, 15, 17], [0, 8, 1, 15]),
-    ((8, 2), [3000] + [1] * 40, [7] + [63] * 40), ((8, 2), [0, 0, 33], [16, 0, 8000])])
-def test_scatter_of_uneven_chunks(heads, chunk, ctx):
-    """Chunks much longer than the mean (a workgroup takes several columns), and such as touch few columns of a wide table,
-    whole and in part."""
-    print("case: scatter", heads, chunk[:5], ctx[:5], flush=True)
-    inp = I.build_prefill_inputs(*heads, chunk, ctx, seed=3)
+def scatter_equals_reference(inp, flag=0):
     dev = inp.to("cuda")
     shape, _, _ = B.prepare_prefill(dev, B.MARL_OUT_F32)
     flags = torch.zeros(1, dtype=torch.int32, device="cuda")
     B.marl_kv_write_prompt(shape, dev.k_new, dev.v_new, dev.k_pages, dev.v_pages, dev.prefix_block_table, dev.q_start, dev.q_pos0, flags)
     torch.cuda.synchronize()
-    assert int(flags.item()) == 0
+    assert int(flags.item()) == flag
     kp, vp = R.kv_write_prompt(I.bf16_bits(inp.k_pages), I.bf16_bits(inp.v_pages), inp.prefix_block_table.numpy(),
                                inp.q_start.numpy(), inp.q_pos0.numpy(), I.bf16_bits(inp.k_new), I.bf16_bits(inp.v_new))
     np.testing.assert_array_equal(I.bf16_bits(dev.k_pages.cpu()), kp)
     np.testing.assert_array_equal(I.bf16_bits(dev.v_pages.cpu()), vp)
+
+
+@pytest.mark.parametrize("heads,chunk,ctx", [
+    ((16, 1), [1], [0]), ((8, 2), [1, 2000, 3, 0, 17], [4000, 5, 15, 100, 31]), ((4, 4), [16, 16, 15, 17], [0, 8, 1, 15]),
+    ((8, 2), [3000] + [1] * 40, [7] + [63] * 40), ((8, 2), [0, 0, 33], [16, 0, 8000]),
+    # by places, up to and beyond what a wave sees at once, and the most groups that it is done for; and by rounds beyond
+    ((16, 4), [2000] + [1] * 63, [3] + [900] * 63), ((16, 4), [1] * 64 + [2000], [900] * 64 + [15]),
+    ((2, 2), [1] * 500 + [1500] + [2, 17, 0] * 174 + [18], [95] * 1024), ((2, 2), [1] * 500 + [1500] + [2, 17, 0] * 174 + [18] * 2, [95] * 1025),
+    ((8, 8), [18, 2, 34, 1, 14, 3, 16], [15, 15, 31, 4000, 2, 14, 16]),
+    # every column, and twice the mean of the chunks'
+    ((4, 4), [700] * 30 + [1500], [300] * 31), ((4, 4), [200] * 60 + [1000], [900] * 60 + [0])])
+def test_scatter_of_uneven_chunks(heads, chunk, ctx):
+    """Chunks much longer than the mean, and such as touch few columns of a wide table, whole and in part, on each way a call can take."""
+    print("case: scatter", heads, chunk[:5], ctx[:5], flush=True)
+    scatter_equals_reference(I.build_prefill_inputs(*heads, chunk, ctx, seed=3))
+
+
+@pytest.mark.parametrize("groups", [4, 40, 80])
+def test_scatter_of_groups_that_share_rows(groups):
+    """Entries of q_start in no order: every group that is consistent in itself has its pages written, the others are flagged."""
+    from dataclasses import replace
+    print("case: scatter, shared rows", groups, flush=True)
+    inp = I.build_prefill_inputs(8, 1, [21] * groups, [979] * groups, seed=5, poison=False)
+    ends = torch.zeros(groups + 1, dtype=torch.int32)
+    ends[1:groups:2] = 21                                        # 0..21, back to 0, again: shared rows and reversed ones
+    scatter_equals_reference(replace(inp, q_start=ends), B.FLAG_BAD_GROUP)
 
 
 def test_scatter_flags_tokens_it_cannot_place():
