@@ -356,7 +356,7 @@ __device__ __forceinline__ int div_R(int x, int inv_R) { return (x * inv_R) >> 1
 // A small call has no plan kernel: every workgroup goes over the groups, one per thread, until it has found its block in the
 // plan's list (the groups' blocks in their order, last block of a group first), and the one that sets the flags over all of them.
 //   visit(group, tokens, blocks, blocks up to this group's last): for every group that the plan would list (wave-uniform calls
-//   are not promised); false ends the walk after a round of kPfThreads groups once `before` blocks have gone by.
+//   are not promised), in rounds of kPfThreads groups, up to the one in which block `until` has gone by.
 struct FindLds {
   int wave_blocks[kNW];
   int group, packed, flags;
@@ -913,7 +913,7 @@ void prefill_small_kernel(PrefillArgs a) {
   if (blockIdx.x == 0) {
     int flag = 0;
     if (threadIdx.x == 0) find.flags = 0;
-    walk_groups(a, a.max_blocks, flag, find, [&](int g, int n, int, int) {
+    walk_groups(a, 0x7fffffff, flag, find, [&](int g, int n, int, int) {   // (all groups: those past the room for blocks are flagged, too)
       const int32_t* row = a.prefix_table + (size_t)g * a.max_pp;
       const int last = (a.q_pos0[g] + n - 1) / kPage;
       constexpr int kIds = 8;          // of a group, requested together

@@ -476,3 +476,21 @@ def test_small_calls_flag_what_planned_ones_flag(what):
         assert np.isfinite(got[:30]).all() and np.isnan(got[30:100]).all()
     else:
         np.testing.assert_array_equal(got, run_gpu(_general(bad), B.MARL_OUT_F32, flag))
+
+
+def test_small_calls_flag_groups_past_the_room_for_blocks():
+    """Groups that all claim all rows: the room for blocks is used up by the first ones, and a group of a later round of 256 whose
+    tokens do not fit its table row is flagged for that as well."""
+    from dataclasses import replace
+    print("case: small prefill, flags of late groups", flush=True)
+    NG = 400
+    a = I.build_prefill_inputs(8, 1, [1] * NG, [7] * NG, seed=2, poison=False)
+    qs = torch.zeros(NG + 1, dtype=torch.int32)
+    qs[1::2] = NG                                               # 0..400, 400..0 (flagged), 0..400 ...
+    pos0 = a.q_pos0.clone().zero_()
+    tab = torch.zeros(NG, 38, dtype=torch.int32)                # (608 positions, all of them on page 0)
+    bad = replace(a, q_start=qs, q_pos0=pos0, prefix_block_table=tab)
+    late = replace(bad, q_pos0=pos0.clone().index_fill_(0, torch.tensor([398]), 1000))
+    for inp, flags in ((bad, B.FLAG_BAD_GROUP), (late, B.FLAG_BAD_GROUP | B.FLAG_LEN_CLAMPED)):
+        run_gpu(inp, B.MARL_OUT_F32, flags)
+        run_gpu(_general(inp), B.MARL_OUT_F32, flags)
