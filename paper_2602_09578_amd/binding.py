@@ -14,7 +14,7 @@ from typing import Optional
 import numpy as np
 import torch
 
-from .build import FAST_PATH, LIB_PATH, build_fast_calls, build_library
+from .build import FAST_PATH, LIB_PATH, build_fast_calls, build_library, fast_calls_sources
 
 I32 = ctypes.c_int32
 SZ = ctypes.c_size_t
@@ -79,7 +79,7 @@ def _bind_fast_calls(m, *functions):
 
 def _load_fast_calls(lib, build: bool):
     """Binds the short way to the functions of `lib`, where torch can tell the current stream.  It only saves host time: where it
-    cannot be built or loaded (no host compiler, another torch), that is said once and every call goes the long way."""
+    cannot be built or loaded (no host compiler, another torch, built from other sources), that is said once and every call goes the long way."""
     if _raw_stream is None or not (build or os.path.exists(FAST_PATH)):
         return None
     try:
@@ -90,10 +90,12 @@ def _load_fast_calls(lib, build: bool):
         loader.exec_module(m)
         if m.torch_version != torch.__version__.split("+")[0]:
             raise ImportError(f"{FAST_PATH} was built for torch {m.torch_version}, not {torch.__version__}")
+        if getattr(m, "sources", None) != fast_calls_sources():
+            raise ImportError(f"{FAST_PATH} was built from other sources")
         _bind_fast_calls(m, lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
                          lib.marl_sample_tokens_top_p, lib.marl_prefill_attn, lib.marl_kv_write_prompt)
         return m
-    except (ImportError, OSError, RuntimeError) as e:
+    except (ImportError, OSError, RuntimeError, TypeError, AttributeError) as e:
         warnings.warn(f"calls take a few microseconds longer, without fast_calls: {e}", RuntimeWarning, stacklevel=3)
         return None
 

@@ -1,6 +1,7 @@
 """Builds libmarl_decode.so for gfx950 with hipcc, in-tree (paper_2602_09578_amd/lib/)."""
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
 import sys
@@ -52,6 +53,15 @@ def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PAT
     return out_path
 
 
+def fast_calls_sources() -> str:
+    """What the binding's host code is built from: a module of other sources may call the library with other arguments."""
+    h = hashlib.sha256()
+    for path in (os.path.join(CSRC, "fast_calls.cpp"), os.path.join(_ROOT, "include", "marl_decode.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
 def build_fast_calls(out_path: str = FAST_PATH) -> str:
     """Compiles the binding's host code against torch's headers (always)."""
     import sysconfig
@@ -60,6 +70,7 @@ def build_fast_calls(out_path: str = FAST_PATH) -> str:
     os.makedirs(LIB_DIR, exist_ok=True)
     part = f"{out_path}.{os.getpid()}"   # (another process may be loading it, or building it too)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DMARL_FAST_CALLS_SOURCES="{fast_calls_sources()}"',
            "-I" + os.path.join(_ROOT, "include"), "-I" + sysconfig.get_paths()["include"], *["-I" + p for p in include_paths()],
            os.path.join(CSRC, "fast_calls.cpp"), "-o", part, *["-L" + p for p in library_paths()],
            "-ltorch_python", "-ltorch_cpu", "-lc10"]

@@ -302,5 +302,6 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "fast_calls", nullptr, -1, methods,
 PyMODINIT_FUNC PyInit_fast_calls(void) {
   PyObject* m = PyModule_Create(&module);
   if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) != 0) Py_CLEAR(m);   // (tensors are read as this torch lays them out)
+  if (m && PyModule_AddStringConstant(m, "sources", MARL_FAST_CALLS_SOURCES) != 0) Py_CLEAR(m);
   return m;
 }

@@ -1,6 +1,8 @@
 """The binding's short way (native checks and call in one step) against its long way: the same results, the same
 refusals, and nothing taken that is not plainly right."""
 import ctypes
+import importlib.machinery
+import importlib.util
 import subprocess
 
 import numpy as np
@@ -9,7 +11,7 @@ import torch
 
 from paper_2602_09578_amd import binding as B
 from paper_2602_09578_amd import inputs as I
-from paper_2602_09578_amd.build import FAST_PATH
+from paper_2602_09578_amd.build import FAST_PATH, fast_calls_sources
 
 ENTRIES = ("decode_attn", "token_logprobs", "sample_tokens", "kv_append", "prefill_attn")
 
@@ -57,6 +59,26 @@ def test_a_short_way_that_cannot_be_loaded_or_built_leaves_the_long_way(tmp_path
         m.setattr(torch, "__version__", "0.0.1")
         _reloaded(m, FAST_PATH, fails)
         assert B._fast is None
+
+
+@pytest.mark.parametrize("sources", [None, "other", "these"])
+def test_a_short_way_of_other_sources_leaves_the_long_way(sources, monkeypatch):
+    """A module built before its functions changed: it says nothing of its sources, or names others, or cannot be bound."""
+    B.load_library()
+    if B._raw_stream is None:
+        pytest.skip("torch does not tell the current stream")
+
+    class Old:
+        torch_version = torch.__version__.split("+")[0]
+        def bind(self, *args):
+            raise TypeError("bind: a function, two types, six addresses")
+    if sources is not None:
+        Old.sources = fast_calls_sources() if sources == "these" else sources
+    with monkeypatch.context() as m, pytest.warns(RuntimeWarning, match="six addresses" if sources == "these" else "other sources"):
+        m.setattr(importlib.util, "module_from_spec", lambda spec: Old())
+        m.setattr(importlib.machinery.ExtensionFileLoader, "exec_module", lambda self, module: None)
+        lib = _reloaded(m, FAST_PATH, lambda: pytest.fail("built"))
+        assert lib.marl_version() == 1 and B._fast is None
 
 
 def test_a_missing_short_way_is_built(tmp_path, monkeypatch):
