@@ -265,8 +265,8 @@ PyObject* kv_write_prompt(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// bind(stream_of, types of the two shapes, addresses of the library's functions in the order of the declarations above; what is
-// not given is not called)
+// bind(stream_of, types of the two shapes, addresses of the library's functions in the order of the declarations above; the
+// scatter's may be left out and then stays what it is)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (n < 9 || n > 10 || !PyType_Check(a[1]) || !PyType_Check(a[2])) {
     PyErr_SetString(PyExc_TypeError, "bind: a function, two types, six or seven addresses");
@@ -288,7 +288,7 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   f_sample_tokens = reinterpret_cast<decltype(f_sample_tokens)>(f[3]);
   f_sample_tokens_top_p = reinterpret_cast<decltype(f_sample_tokens_top_p)>(f[4]);
   f_prefill_attn = reinterpret_cast<decltype(f_prefill_attn)>(f[5]);
-  f_kv_write_prompt = reinterpret_cast<decltype(f_kv_write_prompt)>(f[6]);
+  if (n == 10) f_kv_write_prompt = reinterpret_cast<decltype(f_kv_write_prompt)>(f[6]);
   Py_RETURN_NONE;
 }
 

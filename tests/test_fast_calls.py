@@ -237,6 +237,19 @@ def test_an_exception_in_the_library_is_raised_and_the_call_is_not_repeated(tmp_
 
 
 @pytest.mark.gpu
+def test_the_scatter_stays_bound_where_the_other_functions_are_bound_anew():
+    print("case: fast calls, six functions bound", flush=True)
+    lib = B.load_library()
+    B._bind_fast_calls(B._fast, lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
+                       lib.marl_sample_tokens_top_p, lib.marl_prefill_attn)
+    pre = I.build_prefill_inputs(8, 2, np.array([20]), np.array([5]), device="cuda", seed=1, poison=False)
+    shape, _, _ = B.prepare_prefill(pre, B.MARL_OUT_BF16)
+    assert B._fast.kv_write_prompt(shape, pre.k_new, pre.v_new, pre.k_pages, pre.v_pages, pre.prefix_block_table, pre.q_start,
+                                   pre.q_pos0, None) == 0
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
 def test_prompt_scatter_by_the_short_way(monkeypatch):
     """The native function makes the plain call, leaves everything else to the long way, and both write the same bytes."""
     print("case: fast calls, prompt scatter", flush=True)
