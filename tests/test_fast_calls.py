@@ -274,7 +274,7 @@ def test_prompt_scatter_by_the_short_way(monkeypatch):
             bad = args()
             bad[k] = wrong
             if wrong is None and k > 1:                             # (no address: what the library itself refuses)
-                assert B._fast.kv_write_prompt(*bad, None) != 0
+                assert B._fast.kv_write_prompt(*bad, None) == -1    # MARL_INVALID_ARG
             else:
                 assert B._fast.kv_write_prompt(*bad, None) is None, k
             said = []
