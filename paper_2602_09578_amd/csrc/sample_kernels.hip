@@ -84,12 +84,13 @@ __device__ __forceinline__ double from_lane(double v, int l) {
   return __builtin_bit_cast(double, (unsigned long long)lo | ((unsigned long long)hi << 32));
 }
 
-// The logits of a chunk, as a wave holds them; requested, and as they are used.
+// The logits of a chunk, as a wave holds them; requested, and as they are used.  (kAnyLength: also of a row of fewer than 8.)
+template <bool kAnyLength = true>
 __device__ __forceinline__ void fetch_chunk(const uint16_t* x, long base, int lane, long vocab, u32x4 (&w)[kIters]) {
   if (base + kChunk <= vocab) {   // wave-uniform
 #pragma unroll
     for (int it = 0; it < kIters; ++it) w[it] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(x + base + it * 512 + lane * 8));
-  } else if (vocab >= 8) {
+  } else if (!kAnyLength || vocab >= 8) {
 #pragma unroll
     for (int it = 0; it < kIters; ++it) w[it] = load8_clamped(x, base + it * 512 + lane * 8, vocab);
   } else {
@@ -140,13 +141,15 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(SampleArgs a) {
   const int first = (blockIdx.x % a.groups_per_row) * 4 * a.chunks_per_wave;
   const uint16_t* x = a.logits + (size_t)row * a.vocab;
   // the words of the wave's next chunk are requested before the current chunk is reduced
+  // (rows of fewer than 8 chunks are not divided; with the loads of the shortest ones four registers more: 300 x 65537 14.7 us, now 14.3,
+  // 600 x 28673 15.6 and 15.1)
   u32x4 cur[kIters], nxt[kIters];
-  if (first + wave < a.num_chunks) fetch_chunk(x, (long)(first + wave) * kChunk, lane, a.vocab, cur);
+  if (first + wave < a.num_chunks) fetch_chunk<false>(x, (long)(first + wave) * kChunk, lane, a.vocab, cur);
   for (int k = 0; k < a.chunks_per_wave; ++k) {
     const int chunk = first + wave + 4 * k;
     if (chunk >= a.num_chunks) break;
     const bool more = k + 1 < a.chunks_per_wave && chunk + 4 < a.num_chunks;   // wave-uniform
-    if (more) fetch_chunk(x, (long)(chunk + 4) * kChunk, lane, a.vocab, nxt);
+    if (more) fetch_chunk<false>(x, (long)(chunk + 4) * kChunk, lane, a.vocab, nxt);
     end_chunk((long)chunk * kChunk, lane, a.vocab, cur);
     const float2 v = chunk_sum(cur, a.inv_temp_log2e);
     if (lane == 0) a.partials[(size_t)row * a.num_chunks + chunk] = v;
