@@ -78,6 +78,16 @@ def test_scales_and_output_types(scale):
         assert np.all(np.abs(bf16 - f32) <= np.abs(f32) * 2.0 ** -8 + 1e-30)   # one rounding apart
 
 
+def work_list(call, NG, NS):
+    """The plan that a call has left in its workspace; items in order of their contents."""
+    L, host = call.layout, call.workspace.cpu().numpy()
+    i32 = lambda off, n: host[off:off + 4 * n].view(np.int32).copy()
+    ctr = i32(L.counters_off, 64)
+    return (ctr, i32(L.group_count_off, NG), i32(L.group_start_off, NG + 1), i32(L.group_seqs_off, NS), i32(L.seq_chunks_off, NS),
+            sorted(map(tuple, i32(L.suffix_items_off, 4 * ctr[0]).reshape(-1, 4).tolist())),
+            sorted(map(tuple, i32(L.prefix_items_off, 4 * ctr[1]).reshape(-1, 4).tolist())))
+
+
 def test_work_list_and_flags_are_left_as_the_header_says():
     """The workspace of a small call holds the plan that marl_attn_plan builds, and the flags of bad contents."""
     print("case: small call, workspace", flush=True)
@@ -85,15 +95,9 @@ def test_work_list_and_flags_are_left_as_the_header_says():
     gos = rng.permutation(np.repeat(np.arange(6), [1, 2, 3, 8, 0, 5]))
     inp = custom_inputs(rng.integers(0, 300, 6), rng.integers(0, 300, len(gos)), gos, 8, 2, seed=2, poison=False).to("cuda")
     call = B.prepare_attn(inp, B.MARL_OUT_F32)
-    L, shape = call.layout, call.shape
+    shape = call.shape
     compare(shape, inp.prefix_lens.cpu(), inp.suffix_lens.cpu(), gos.astype(np.int32), 8, 2)   # marl_attn_plan against its reference
-    def lists():
-        host = call.workspace.cpu().numpy()
-        i32 = lambda off, n: host[off:off + 4 * n].view(np.int32).copy()
-        ctr = i32(L.counters_off, 64)
-        return (ctr, i32(L.group_count_off, 6), i32(L.group_start_off, 7), i32(L.group_seqs_off, len(gos)), i32(L.seq_chunks_off, len(gos)),
-                sorted(map(tuple, i32(L.suffix_items_off, 4 * ctr[0]).reshape(-1, 4).tolist())),
-                sorted(map(tuple, i32(L.prefix_items_off, 4 * ctr[1]).reshape(-1, 4).tolist())))
+    lists = lambda: work_list(call, 6, len(gos))
     call.workspace.fill_(0xAB)
     B.marl_attn_plan(shape, call.workspace, inp.prefix_lens, inp.suffix_lens, inp.group_of_seq)
     want = lists()
@@ -114,6 +118,32 @@ def test_work_list_and_flags_are_left_as_the_header_says():
     assert B.marl_attn_read_flags(call.workspace) == B.FLAG_BAD_PAGE
     others = [s for s in range(len(gos)) if s != 3]
     assert torch.equal(call.out[others], good[others]) and torch.isfinite(call.out[3]).all()
+
+
+@pytest.mark.parametrize("NS,NG", [(1, 1), (64, 65), (300, 257), (512, 512), (512, 40)])   # (members are in order in groups of at most 64)
+@pytest.mark.parametrize("longest", [255, 512, 1100])
+def test_work_list_of_whole_chunks(NS, NG, longest):
+    """Sequences and groups of none, one and several whole chunks side by side in a wave, and waves without any; one or two of each
+    per thread of the plan's workgroup."""
+    print("case: small call, whole chunks", NS, NG, longest, flush=True)
+    rng = np.random.default_rng(NS + longest)
+    own, prefix = rng.integers(0, longest + 1, NS), rng.integers(0, longest + 1, NG)
+    own[NS // 3: NS // 2] %= 256      # (chunks of 256 tokens and more)
+    prefix[NG // 2:] %= 256
+    gos = rng.integers(0, NG, NS)
+    inp = custom_inputs(prefix, own, gos, 4, 1, seed=2, poison=False).to("cuda")
+    call = B.prepare_attn(inp, B.MARL_OUT_F32)
+    assert used_kernels(inp, call) in (SMALL, PARTS)
+    compare(call.shape, prefix, own, gos.astype(np.int32), 4, 1)   # marl_attn_plan against its reference
+    call.workspace.fill_(0xAB)
+    B.marl_attn_plan(call.shape, call.workspace, inp.prefix_lens, inp.suffix_lens, inp.group_of_seq)
+    want = work_list(call, NG, NS)
+    call.workspace.fill_(0xAB)
+    B.run_attn(inp, call)
+    torch.cuda.synchronize()
+    n = int(want[2][-1])
+    for k, (w, g) in enumerate(zip(want, work_list(call, NG, NS))):
+        assert np.array_equal(w[:n], g[:n]) if k == 3 else np.array_equal(w, g)
 
 
 # (sequences, longest own row in pages, capacity of a row in pages): one row and a row or more for every eight lanes of the
