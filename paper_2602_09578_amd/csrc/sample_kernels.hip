@@ -394,7 +394,6 @@ __device__ __forceinline__ float value_of_key(int key) {
 }
 
 constexpr int kListCapShared = 2624, kListCapAlone = 9216;   // list entries per wave: three rows on a CU, and one
-static_assert((kListWin & (kScanStep - 1)) == 0, "the list spans whole threads of the threshold search");
 template <int kListCap>
 struct TpShared {
   union {
@@ -425,7 +424,8 @@ static_assert(sizeof(TpShared<kListCapShared>) <= 42 * 1280, "three workgroups s
 static_assert(sizeof(TpShared<kListCapAlone>) <= 160 * 1024, "a workgroup has a CU's LDS");
 
 // exclusive scans over the workgroup in thread order (fixed order: bit-identical reruns)
-template <class Shared>
+// kBefore: what comes before a thread is summed without the thread's own value, not taken as the difference (which rounds with it)
+template <bool kBefore = false, class Shared>
 __device__ __forceinline__ double block_excl_scan_d(double v, double& total, Shared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double inc = wave_inclusive_scan(v);
@@ -439,6 +439,7 @@ __device__ __forceinline__ double block_excl_scan_d(double v, double& total, Sha
     all += sh.wave_d[w];
   }
   total = all;
+  if constexpr (kBefore) return before + dpp_or_zero<0x138, 0xf>(inc);   // wave_shr:1
   return before + inc - v;
 }
 template <class Shared>
@@ -500,7 +501,7 @@ __device__ __forceinline__ bool find_threshold(const uint32_t* hist, int hi, int
 #pragma unroll
     for (int q = 0; q < kScanStep; ++q) mine += mass_at(p0 + q);
     double round_total;
-    const double before = above + scanned + block_excl_scan_d(mine, round_total, sh);
+    const double before = above + scanned + block_excl_scan_d<true>(mine, round_total, sh);
     // first scan position at which the cumulative mass reaches tau: every thread at or past
     // the crossing proposes its first such position, the smallest wins (robust against the
     // last-bit differences between neighbouring threads' scan values)
@@ -686,8 +687,8 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
   // ---- pass 2: the threshold value --------------------------------------------------------
   // thr_key = -1: every token with a finite logit is in the nucleus
   // What is drawn is a function of the row, whatever the list has room for.  From the list or from a window that starts at the
-  // maximum, the threshold is found by the same sums, so a row whose list would begin never tries another window before that
-  // one.  The groups' masses are rounded otherwise in a list than in the row: they are taken from lists that
+  // maximum, the threshold is found by the same sums (what comes before a thread of the search does not depend on how many of
+  // the thread's own values the list has), so a row whose list would begin never tries another window before that one.  The groups' masses are rounded otherwise in a list than in the row: they are taken from lists that
   // kListCapShared has room for, in every instance (`short_list`).
   bool from_list = false, short_list = true;
   int cut_key = 0, likely_key = 0;   // where the estimate puts the threshold at the lowest, and where it puts it
@@ -732,8 +733,7 @@ __device__ __forceinline__ void sample_top_p(const TopPArgs& a) {
     // The list starts at the cut, or where its counts still span it if the threshold is likely to lie above that
     // (short rows give a vague estimate, whose cut may be zero or negative), and is not begun if the
     // sample has more tokens above than a wave's list takes.
-    // (Whole threads of the threshold search: the last one's sum has the values that it has in a window.)
-    const int lkey = kmax - ((kmax - max(cut_key, kmax - (kListWin - 1))) | (kScanStep - 1));
+    const int lkey = max(cut_key, kmax - (kListWin - 1));
     const int span = kmax - lkey + 1;
     const float bins_listed = 8.f * c * (xmax - value_of_key(lkey));
     int listed = 0;
