@@ -1072,9 +1072,13 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
   // CU are no slower alone (32003: 19.4 and 19.7 us).
   // Odd rows (of an odd vocabulary every second one): shifted into place from dwords, or loaded where they start, us: 2000 rows of
   // 152067 201 and 247, 128001 171 and 207, 100003 141 and 168, 32003 64.3 and 67.7; 64 of 32003 16.1 and 17.3.  Rows
-  // alone on a CU wait for their vector ALU, which the shift adds to: 64 of 128001 32.4 and 31.4, 152067 35.3 and 35.2.
+  // alone on a CU wait for their vector ALU, which the shift adds to: 64 of 128001 32.4 and 31.4, 152067 35.3 and 35.2.  A row
+  // alone that starts on a dword has nothing to shift, and few groups of few rows are not worth the longer code: one of 32003 16.5 and
+  // 16.0, 64 of 8193 15.0 and 14.7, of 12291 15.3 and 15.3, of 16385 16.0 and 16.2; 300 of 2051 16.8 and 16.6, of 4099 16.9 and
+  // 16.9, of 10243 18.0 and 18.3.
   const bool alone = a.rows <= 256 && a.vocab > kTpAloneVocab;
-  const bool odd = a.vocab % 2 != 0 || reinterpret_cast<uintptr_t>(a.logits) % 4 != 0;
+  const bool odd = ((a.rows > 1 && a.vocab % 2 != 0) || reinterpret_cast<uintptr_t>(a.logits) % 4 != 0) &&
+                   a.vocab > (a.rows > 256 ? 4096 : 12288);
   const auto kernel = alone ? sample_top_p_alone_kernel : odd ? sample_top_p_odd_kernel : sample_top_p_kernel;
   hipLaunchKernelGGL(kernel, dim3((unsigned)a.rows), dim3(kTpThreads), 0, st, a);
   return hipGetLastError();

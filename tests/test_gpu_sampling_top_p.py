@@ -322,8 +322,10 @@ def test_a_row_is_the_same_in_few_rows_and_in_many(V, sigma, T, top_p):
 
 @pytest.mark.parametrize("V,sigma,T,top_p", [
     (49160, 2.0, 1.0, 0.95), (65536, 3.0, 1.3, 0.95), (152064, 3.0, 1.0, 0.95), (152064, 3.0, 1.3, 0.95), (152064, 2.0, 1.0, 0.9),
-    (100003, 2.0, 1.0, 0.95), (156368, 2.0, 1.3, 0.9), (152064, 2.0, 1.3, 0.95), (65536, 1.0, 1.0, 0.99)])
+    (100003, 2.0, 1.0, 0.95), (156368, 2.0, 1.3, 0.9), (152064, 2.0, 1.3, 0.95), (65536, 1.0, 1.0, 0.99),
+    (4095, 3.0, 1.0, 0.95), (4097, 3.0, 1.0, 0.95), (12287, 3.0, 1.0, 0.95), (12289, 3.0, 1.0, 0.95)])
 def test_a_row_is_the_same_alone_on_a_cu_and_beside_others(V, sigma, T, top_p):
-    """Lists that a third of a CU's LDS has room for, lists that only all of it has room for, and none of them."""
+    """Lists that a third of a CU's LDS has room for, lists that only all of it has room for, and none of them; odd rows on both
+    sides of the sizes from which they are shifted into place."""
     print("case: top-p alone or not", V, sigma, T, top_p, flush=True)
     same_in_every_batch(V, sigma, T, top_p, 300, [1, 64, 256, 257])
