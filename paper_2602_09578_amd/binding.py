@@ -90,7 +90,8 @@ def _load_fast_calls(lib, build: bool):
         loader.exec_module(m)
         if m.torch_version != torch.__version__.split("+")[0]:
             raise ImportError(f"{FAST_PATH} was built for torch {m.torch_version}, not {torch.__version__}")
-        if getattr(m, "sources", None) != fast_calls_sources():
+        sources = fast_calls_sources()
+        if sources is not None and getattr(m, "sources", None) != sources:
             raise ImportError(f"{FAST_PATH} was built from other sources")
         _bind_fast_calls(m, lib.marl_decode_attn, lib.marl_token_logprobs, lib.marl_kv_append, lib.marl_sample_tokens,
                          lib.marl_sample_tokens_top_p, lib.marl_prefill_attn, lib.marl_kv_write_prompt)

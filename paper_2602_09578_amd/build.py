@@ -53,10 +53,13 @@ def build_library(verbose: bool = False, extra_flags=(), out_path: str = LIB_PAT
     return out_path
 
 
-def fast_calls_sources() -> str:
-    """What the binding's host code is built from: a module of other sources may call the library with other arguments."""
+def fast_calls_sources():
+    """What the binding's host code is built from: a module of other sources may call the library with other arguments.  None
+    where the sources are not there (the built package alone)."""
     h = hashlib.sha256()
     for path in (os.path.join(CSRC, "fast_calls.cpp"), os.path.join(_ROOT, "include", "marl_decode.h")):
+        if not os.path.exists(path):
+            return None
         with open(path, "rb") as f:
             h.update(f.read())
     return h.hexdigest()

@@ -81,6 +81,17 @@ def test_a_short_way_of_other_sources_leaves_the_long_way(sources, monkeypatch):
         assert lib.marl_version() == 1 and B._fast is None
 
 
+def test_a_short_way_without_its_sources_is_taken(tmp_path, monkeypatch):
+    """The built package alone: there is nothing to compare."""
+    B.load_library()
+    if B._raw_stream is None:
+        pytest.skip("torch does not tell the current stream")
+    with monkeypatch.context() as m:
+        m.setattr("paper_2602_09578_amd.build.CSRC", str(tmp_path))
+        _reloaded(m, FAST_PATH, lambda: pytest.fail("built"))
+        assert B._fast is not None
+
+
 def test_a_missing_short_way_is_built(tmp_path, monkeypatch):
     B.load_library()
     if B._raw_stream is None:
