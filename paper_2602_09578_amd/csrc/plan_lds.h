@@ -185,10 +185,10 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
   }
   __syncthreads();
 
-  // Whole chunks' places by one atomic per wave, for all of a wave's sequences and groups behind one test: most small calls
-  // have none (a test in each round was 0.07 us of a call of 5).
+  // Whole chunks' places by one atomic per wave.  Whether a wave has any is known from the sums above: most small calls have
+  // none, and a test in each round was 0.07 us of a call of 5.
   constexpr bool kTogether = kSeqsPerThread <= 2;
-  int whole_s[kTogether ? kSeqsPerThread : 1] = {}, whole_p[kTogether ? kGroupsPerThread : 1] = {}, blocks_p[kTogether ? kGroupsPerThread : 1] = {};
+  const bool whole_s = __builtin_amdgcn_readfirstlane(nfull_mine) > 0, whole_p = __builtin_amdgcn_readfirstlane(longest) == Cp;
   auto take = [&](int* word, int n) {               // (for all lanes of the wave)
     const int inc = wave_inclusive_scan(n);
     int base = 0;
@@ -206,6 +206,7 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
 #pragma unroll
   for (int k = 0; k < kSeqsPerThread; ++k) {
     const int s = tid + k * kThreads;
+    int nfull_of = 0;
     if (s < a.NS) {
       const int g = G(k);
       if (rank_of[k] >= 0) members[start[g] + rank_of[k]] = (MemberId)s;
@@ -218,18 +219,21 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       }
       a.seq_chunks[s] = ((P + Cp - 1) / Cp) | (((S + Cs - 1) / Cs) << 16);
       const int nfull = S / Cs, tail = S % Cs;
-      if constexpr (kTogether) whole_s[k] = nfull;
+      if constexpr (kTogether) nfull_of = nfull;
       else if (nfull) put_suffix(atomicAdd(&hist_s[0], nfull), s, nfull);
       if (tail) {
         const int pos = atomicAdd(&hist_s[(Cs - tail) / 32], 1);
         a.suffix_items[pos] = make_int4(s, nfull * Cs, S, 0);
       }
     }
+    if constexpr (kTogether)
+      if (whole_s && __builtin_amdgcn_ballot_w64(nfull_of > 0) != 0) put_suffix(take(&hist_s[0], nfull_of), s, nfull_of);   // wave-uniform
   }
   bool ranked = false;   // a group that has an order
 #pragma unroll
   for (int k = 0; k < kGroupsPerThread; ++k) {
     const int g = tid + k * kThreads;
+    int nfull_of = 0, nqb_of = 0;
     if (g < a.NG) {
       a.group_count[g] = cnt[g];
       ranked |= cnt[g] >= 2 && cnt[g] <= 64;
@@ -238,7 +242,7 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
       const int nqb = (cnt[g] * R + QB - 1) / QB;
       const int nfull = P / Cp, tail = P % Cp;
       if (nqb) {
-        if constexpr (kTogether) whole_p[k] = nfull, blocks_p[k] = nqb;
+        if constexpr (kTogether) nfull_of = nfull, nqb_of = nqb;
         else if (nfull) put_prefix(atomicAdd(&hist_p[0], nfull * nqb), g, nfull, nqb);
         if (tail) {
           const int pos = atomicAdd(&hist_p[(Cp - tail) / 32], nqb);
@@ -247,20 +251,8 @@ __device__ __forceinline__ void plan_in_lds(const AttnArgs& a) {
         }
       }
     }
-  }
-  if constexpr (kTogether) {
-    int any = 0;
-#pragma unroll
-    for (int k = 0; k < kSeqsPerThread; ++k) any |= whole_s[k];
-#pragma unroll
-    for (int k = 0; k < kGroupsPerThread; ++k) any |= whole_p[k];
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(any != 0) != 0, 0)) {   // wave-uniform
-#pragma unroll
-      for (int k = 0; k < kSeqsPerThread; ++k) put_suffix(take(&hist_s[0], whole_s[k]), tid + k * kThreads, whole_s[k]);
-#pragma unroll
-      for (int k = 0; k < kGroupsPerThread; ++k)
-        put_prefix(take(&hist_p[0], whole_p[k] * blocks_p[k]), tid + k * kThreads, whole_p[k], blocks_p[k]);
-    }
+    if constexpr (kTogether)
+      if (whole_p && __builtin_amdgcn_ballot_w64(nfull_of > 0) != 0) put_prefix(take(&hist_p[0], nfull_of * nqb_of), g, nfull_of, nqb_of);
   }
   if (tid == 0) a.group_start[a.NG] = nseq_grouped;
   if (ranked) any_ranked = 1;
