@@ -31,8 +31,8 @@ HBM_PEAK_GBPS = 8000.0
 # factors that the one-launch copy of the weight_pack leg, a copy kernel of known size in the same
 # run, gives).  Valid only for the kernel source and flags it was taken
 # with: reported as null when either has changed since.
-SUFFIX_TRAFFIC = {"workload": "qwen7b", "bytes": 5556.7e6 + 14.1e6,
-                  "kernel_sources_sha256": "037a5be7dc9d7f42acf1bacb596f65eda6992a7de6c15b3a86c58abac3678af3"}
+SUFFIX_TRAFFIC = {"workload": "qwen7b", "bytes": 5556.9e6 + 14.1e6,
+                  "kernel_sources_sha256": "327bc93f65d0d9314d07bdb511d371c902673af5015ef308690db917d22bc749"}
 SUFFIX_SOURCES = ("attn_kernels.hip", "wave_ops.h")
 
 

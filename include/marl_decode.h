@@ -257,6 +257,8 @@ int marl_token_logprobs(const void* logits, const int32_t* tokens, float tempera
  * random numbers).  If rounding leaves no such t, the last token with non-zero probability is
  * returned.  The sums run in float32, so for a uniform within ~1e-6 of a CDF step the
  * neighbouring token may be returned.  A row without any finite logit gives token -1 and NaN.
+ * What a row draws depends on its logits, its uniform number and T alone, bit for bit: not on the
+ * other rows, on their number or on the address at which the row starts.
  * out_tokens int32 [rows], out_logprobs float32 [rows]; workspace of
  * marl_sample_workspace_bytes() bytes, 8-byte aligned.  Other arguments as marl_token_logprobs.
  */
@@ -276,8 +278,8 @@ int marl_sample_tokens(const void* logits, const float* uniforms, float temperat
  * with an exact count per value instead of a sort; float32 sums decide which value is the
  * threshold and which token passes u, so within ~1e-6 (relative) of such a boundary the
  * neighbouring choice may be returned.  A row without a finite logit, or with +inf / NaN,
- * gives token -1 and NaN.  No workspace.  vocab <= 8388608.  Other arguments as
- * marl_sample_tokens.
+ * gives token -1 and NaN.  No workspace.  vocab <= 8388608.  Other arguments, and what a row's
+ * result depends on, as marl_sample_tokens.
  */
 int marl_sample_tokens_top_p(const void* logits, const float* uniforms, float temperature,
                              float top_p, int32_t* out_tokens, float* out_logprobs, int32_t rows,

@@ -45,16 +45,17 @@
 // of the matrix core) and about 100 vector instructions, 24 of them exponentials (710 cycles of the
 // vector ALU), and the two waves of a SIMD overlap little of it: 1.58 us per step and workgroup at
 // two workgroups per CU with 141 vector and 105 scalar instructions, 1.37 with 120 and 50 (page
-// ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  The same step on LDS data alone,
-// without loads, runs at 1.43 PFLOP/s, with loads that the caches hold at 1.28, with loads from memory at 0.97.  256 prompts of
+// ids and addresses of the loads, LDS addresses, no test of the eight scores' maximum).  The same step alone, over and over on LDS data
+// and without items, runs at 1.43 PFLOP/s, with loads that the caches hold at 1.28.  256 prompts of
 // 512 to 2048 tokens, 28 / 4 heads: 3.99 -> 3.52 ms (0.98 PFLOP/s; a large matrix product of this
 // card: 1.19); six chunks behind up to 8192 tokens, 64 / 8 heads: 0.43 -> 0.37 ms.  An item takes about 6 us beside its
 // steps (rows written 2.6, the next item read and queries requested 2.2, two steps on the causal edge 0.6), in which the
 // other workgroup of the CU has it alone; 7.5 with output rows through LDS, a first step taken twice
 // and maxima in every step on the edge (46 prompts of up to 1666, 28 / 4 heads: 604 -> 586 us; 33 of up to 2730, 4 / 4 heads: 148 -> 143).
-// Memory is second: with an item
+// Memory costs clock, not cycles: with an item
 // bound ahead a prompt's blocks run further apart in time than one after the other did, and the 256 prompts fetch
-// 14.8 GB instead of 8.2; with all groups on the pages of one prompt, which stay in the caches, they take 4 % less.
+// 15 GB instead of 8.2; with all groups on the pages of one prompt, which the caches hold, they fetch 5.5 GB, take as many cycles
+// (6.59 M) and 5 % less time (3.63 and 3.44 ms on one card): what the traffic takes is power, and with it 0.1 GHz.
 #include <algorithm>
 
 #include "marl_internal.h"
@@ -824,7 +825,7 @@ __device__ __forceinline__ void prefill_items(const PrefillArgs& a, First&& firs
     // (Through LDS, 128 bytes: the compiler puts a wait for every load into LDS, query and store in flight before a store
     // to LDS, three times 1.4 us per item.)
     auto store_tile = [&](int qt, int out_row) {
-      const float inv = 1.0f / rows_allreduce_sum(l_run[qt]);   // a row's sum >= 1: its own maximum contributes exp2(0)
+      const float inv = 1.0f / rows_allreduce_sum(l_run[qt]);   // a row's sum >= 1: the key that set its reference contributes exp2(0)
       const int j = l2 >> 4;
       if (a.out_dtype == MARL_OUT_F32) {
         float* dst = reinterpret_cast<float*>(a.out) + (size_t)out_row * kD + 4 * j;
@@ -1014,7 +1015,7 @@ __global__ __launch_bounds__(kD) void kv_write_prompt_kernel(PrefillArgs a, int 
 // Where the chunks touch few of the columns: a workgroup for every page that they may touch together, and KV head.  A group whose
 // tokens begin at row b has the places from b / 16 + 2 g on: n tokens touch at most n / 16 + 2 pages, so that groups that share
 // no rows share no place, and the last place lies before NT / 16 + 2 NG, which the host knows.  Which group a place belongs to
-// the workgroup finds by itself: it looks at all of them (0.1 us for 64, 0.4 for 500), and so writes every group's pages
+// the workgroup finds by itself: it looks at all of them (0.2 us of the call for 70, 0.7 for 210, 1.9 for 500), and so writes every group's pages
 // whatever the order of q_start.
 constexpr int kScatterGroups = 1024;
 __global__ __launch_bounds__(kD) void kv_write_prompt_pages_kernel(PrefillArgs a) {
@@ -1091,6 +1092,8 @@ int prefill_blocks_per_cu() {
 // workgroup: with at most 448 keys and six items per workgroup none of 60 random calls was slower (19.1 and 11.3; 42.8 and
 // 35.6 for 1400 items of up to 67 keys; 93 and 88 for 3700 of up to 200), behind it some (10 prompts of up to 731, 28 / 4 heads, 39.6 and
 // 42.3; 40 of up to 503, 8 / 2, 30.8 and 32.7; 5000 items of up to 162 keys 109 and 116, 11000 of up to 70 183 and 215).
+// The keys are those that a table row can hold: rows of a fixed capacity above 960 tokens keep their calls on the plan, however short
+// the prompts are.
 constexpr long kPfSmallRounds = 6, kPfSmallKeys = 448;
 static bool is_small_prefill(const PrefillArgs& a) {
   const long items = (long)a.max_blocks * a.Hkv, keys = (long)a.max_pp * kPage;

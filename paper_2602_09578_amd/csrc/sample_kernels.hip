@@ -1094,7 +1094,8 @@ hipError_t launch_sample_top_p(const TopPArgs& a, hipStream_t st) {
 // never as fast (496 x 140001: 33.2 and 35.7, 1000: 61.1 and 64.9, 768: 49.4 and 52.2; 1024 x 40001: 33.5 and 23.4).  As many
 // waves as there are chunks, or as a CU has room for (256 x 152064: 8 take 19.1, 4 22.1); fewer of more rows, whose ends
 // then overlap (512 x 152064: 8 waves 32.0, 4 30.3, 512 x 100000 24.3 and 21.9; 2048 x 32000 31.8 and 27.2; 768 x 40001 25.4 and 19.4).
-// Over 973 sizes, most of them at the edges of this rule, the mean was 4 % above divided rows; 7 lost 5 to 9 %.
+// Over 400 sizes of more than 8 chunks that it takes whole, most of them at its edges, calls are 1.105 times as fast as divided; 11 lose
+// more than 2 %, the worst of them 4.4 (1845 x 256000: 161 us, divided 154) and 13 (254 x 140001: 22.0, 19.1).
 static int sample_row_waves(int rows, int chunks, bool aligned) {
   const int rounds = (rows + 255) / 256;
   if (chunks < 8 || (chunks == 8 && rows <= 512)) return std::min(chunks, rows <= 512 ? 8 : 4);
